@@ -1,0 +1,227 @@
+"""Workloads by which the speed of the framework is judged: Euler characteristic curves of images and volumes.
+
+A case names one call (or one training step) of the public interface and the data it meets:
+
+  call   "curve"  one ecc_hard call: the integer curve of every item of a batch
+         "sets"   one ecc_hard_dir call: the curves of an item along a set of directions
+         "step"   a training step through SoftECCLayer: chi, then the gradients with respect to the input, the
+                  thresholds and the angle(s)
+         "pair"   ecc_soft_fwd and ecc_soft_bwd on the same input: chi and its three derivatives
+         "score"  SoftECCLayer without gradients (inference)
+  d, h, w, batch  extents of one item (d = 0: an image) and the number of items
+  dtype  element type;  field "smooth" (white noise under a Gaussian of width sigma) or "noise" (independent levels)
+
+`listed` holds the workloads the benchmark and the tests are built around and a few generic ones; `draw` spreads
+over the same calls, sizes, types and options.
+"""
+import math
+
+import torch
+
+from paper_2510_20271_amd import api
+from paper_2510_20271_amd.layer import SoftECCLayer
+
+DTYPES = {"u8": (torch.uint8, 1), "u16": (torch.uint16, 2), "i16": (torch.int16, 2), "f16": (torch.float16, 2),
+          "bf16": (torch.bfloat16, 2), "f32": (torch.float32, 4)}
+ALPHA = 0.01   # weight of the tilt per pixel in the soft curves
+SHARP = 20.0   # sharpness of their sigmoids
+
+
+def _curve(name, d, h, w, batch, dtype, field, sigma, bins, known, top=False, superlevel=False):
+    return dict(name=name, call="curve", d=d, h=h, w=w, batch=batch, dtype=dtype, field=field, sigma=sigma, bins=bins,
+                known=known, top=top, superlevel=superlevel)
+
+
+def _soft(name, call, d, h, w, batch, sigma, T, tilted=False):
+    return dict(name=name, call=call, d=d, h=h, w=w, batch=batch, dtype="f32", field="smooth", sigma=sigma, T=T, tilted=tilted)
+
+
+def listed():
+    return [
+        # the smallest calls, bound by launches and host work: one tile of an 8-bit image, one bin per level; one
+        # small float image with the range found on the device
+        _curve("levels_256x256_u8", 0, 256, 256, 1, "u8", "noise", 0.0, 256, True),
+        _curve("image_128x128", 0, 128, 128, 1, "f32", "smooth", 4.0, 1024, False),
+        # a batch of thumbnails, as a topological feature extractor sees a data set
+        _curve("thumbs_1024x28x28", 0, 28, 28, 1024, "f32", "smooth", 2.0, 256, False),
+        # one 8-bit page scan (odd in both extents), pixels as squares: long flat runs of equal levels
+        _curve("page_4677x3307_u8", 0, 4677, 3307, 1, "u8", "smooth", 3.0, 256, True, top=True),
+        # a batch of large float fields: the benchmark's headline
+        _curve("fields_16x4096x4096", 0, 4096, 4096, 16, "f32", "smooth", 4.0, 1024, False),
+        # a volume of independent 12-bit levels: the worst case, most vertices are critical
+        _curve("levels_256cube_u16", 256, 256, 256, 1, "u16", "noise", 0.0, 4096, True),
+        # a large float volume, and a scanner's volume of 16-bit values read over a known window as superlevel sets
+        _curve("volume_512cube", 512, 512, 512, 1, "f32", "smooth", 3.0, 1024, False),
+        _curve("scan_193x229x193_i16", 193, 229, 193, 1, "i16", "smooth", 2.0, 1024, True, superlevel=True),
+        # a directional transform of one image
+        dict(name="sets_64dir_256x256", call="sets", d=0, h=256, w=256, batch=1, dtype="f32", field="smooth", sigma=2.0,
+             bins=256, ndir=64),
+        # a training step of the layer on a batch of images; forward and backward on a volume; a step with more
+        # thresholds than a wave's registers hold, on images whose rows are not a multiple of anything
+        _soft("step_32x512x512", "step", 0, 512, 512, 32, 4.0, 128),
+        _soft("pair_256cube", "pair", 256, 256, 256, 1, 3.0, 64),
+        _soft("step_16x217x181_fine", "step", 0, 217, 181, 16, 2.0, 512),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _size(rng, three, most, least_side):
+    """(d, h, w, batch) with at most `most` vertices in all, the total spread over its logarithm."""
+    nd = 3 if three else 2
+    total = math.exp(rng.uniform(math.log(float(least_side) ** nd), math.log(float(most))))
+    batch = 1 if rng.random() < 0.5 else _log(rng, 1, min(1024, max(1, total / float(least_side) ** nd)))
+    side = (total / batch) ** (1.0 / nd)
+    sides = [max(least_side, int(round(side * math.exp(rng.uniform(-0.4, 0.4))))) for _ in range(nd)]
+    if rng.random() < 0.4:  # the sizes that data sets are cut to
+        sides = [max(8, s // 16 * 16) for s in sides]
+    while batch > 1 and math.prod(sides) * batch > most:
+        batch -= max(1, batch // 8)
+    while math.prod(sides) * batch > most:
+        sides[0] = max(least_side, sides[0] * 7 // 8)
+        sides[-1] = max(least_side, sides[-1] * 7 // 8)
+    return (sides[0] if three else 0, sides[-2], sides[-1], batch)
+
+
+def draw(rng):
+    call = rng.choice(["curve", "curve", "curve", "curve", "sets", "step", "step", "pair", "score"])
+    three = rng.random() < (0.4 if call != "sets" else 0.2)
+    sigma = round(rng.uniform(1.5, 5.0), 2)
+    if call == "curve":
+        dtype = rng.choice(["u8", "u16", "i16", "f16", "bf16", "f32", "f32", "f32"])
+        field = "noise" if dtype in ("u8", "u16") and rng.random() < 0.3 else "smooth"
+        most = 2 ** 24 if field == "noise" else 2 ** 27 if three else 2 ** 28
+        d, h, w, batch = _size(rng, three, most, 24)
+        known = dtype in ("u8", "u16") or rng.random() < 0.3
+        bins = (256 if dtype == "u8" else 4096) if dtype in ("u8", "u16") else rng.choice([64, 100, 256, 512, 1000, 1024])
+        return dict(call=call, d=d, h=h, w=w, batch=batch, dtype=dtype, field=field, sigma=sigma, bins=bins, known=known,
+                    top=rng.random() < 0.25, superlevel=rng.random() < 0.2)
+    if call == "sets":
+        ndir = _log(rng, 8, 128)
+        d, h, w, batch = _size(rng, three, min(2 ** 24, 2 ** 27 // ndir), 32)
+        return dict(call=call, d=d, h=h, w=w, batch=min(batch, 16), dtype="f32", field="smooth", sigma=sigma,
+                    bins=rng.choice([64, 100, 256, 512]), ndir=ndir)
+    T = _log(rng, 16, 512)
+    d, h, w, batch = _size(rng, three, 2 ** 24 if T <= 128 else 2 ** 22, 28)
+    return dict(call=call, d=d, h=h, w=w, batch=batch, dtype="f32", field="smooth", sigma=max(sigma, 2.0), T=T,
+                tilted=rng.random() < 0.25)
+
+
+def _shape(case):
+    return (case["batch"],) + ((case["d"],) if case["d"] else ()) + (case["h"], case["w"])
+
+
+def _smooth(x, sigma, axes):
+    """Gaussian of width sigma along each of the axes, with wrap-around."""
+    r = int(4.0 * sigma + 0.5)
+    taps = [math.exp(-0.5 * (k / sigma) ** 2) for k in range(-r, r + 1)]
+    for axis in axes:
+        out = torch.zeros_like(x)
+        for k, t in zip(range(-r, r + 1), taps):
+            out.add_(torch.roll(x, k, axis), alpha=t / sum(taps))
+        x = out
+    return x
+
+
+def _grid(case, gen):
+    shape, dtype = _shape(case), DTYPES[case["dtype"]][0]
+    if case["field"] == "noise":
+        x = torch.randint(0, case["bins"], shape, generator=gen, device="cuda", dtype=torch.int16)
+        return x.view(torch.uint16) if dtype == torch.uint16 else x.to(dtype)
+    x = torch.empty(shape, device="cuda").normal_(generator=gen)
+    if x[0].numel() <= 2 ** 20:
+        x = _smooth(x, case["sigma"], range(1, x.dim()))
+    else:
+        for item in x:  # large items one at a time: little memory beside the batch
+            item.copy_(_smooth(item, case["sigma"], range(item.dim())))
+    if dtype == torch.float32:
+        return x
+    if dtype in (torch.float16, torch.bfloat16):
+        return x.to(dtype)
+    x = x / x.std()
+    if dtype == torch.int16:  # a scanner's values: about -1000 .. 3000
+        return (x * 600 + 600).round_().clamp_(-1024, 3071).to(dtype)
+    levels = case["bins"]
+    x = (x * (levels / 6) + levels / 2).round_().clamp_(0, levels - 1)
+    return x.to(torch.int16).view(torch.uint16) if dtype == torch.uint16 else x.to(dtype)
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    ndim = 3 if case["d"] else 2
+    state = dict(case=case, ndim=ndim, grid=_grid(case, gen))
+    if case["call"] == "curve":
+        state["range"] = None
+        if case["known"] and case["dtype"] == "i16":
+            state["range"] = (-1024.0, 3071.0)
+        elif case["known"] and case["dtype"] not in ("u8", "u16"):  # about three standard deviations of the field
+            s = 3.0 * (2.0 * math.sqrt(math.pi) * case["sigma"]) ** (-ndim / 2)
+            state["range"] = (-s, s)
+        return state
+    if case["call"] == "sets":
+        u = torch.randn((case["ndir"], ndim), generator=gen, device="cuda")
+        state["u"] = u / u.norm(dim=1, keepdim=True)
+        return state
+    lo, hi = float(state["grid"].min()), float(state["grid"].max())
+    angles = [0.3] if ndim == 2 else [0.3, 1.1]
+    state["g"] = torch.randn((case["batch"], case["T"]), generator=gen, device="cuda")
+    layer = SoftECCLayer(ndim, case["T"], lo, hi, alpha=ALPHA, lam=SHARP, theta=angles, tilted_c=case["tilted"]).cuda()
+    state["layer"] = layer
+    if case["call"] == "step":
+        state["grid"].requires_grad_()
+    if case["call"] == "pair":
+        state["u"], state["tau"] = layer.direction().detach(), layer.tau.detach()
+    return state
+
+
+def run(state):
+    case, grid, ndim = state["case"], state["grid"], state["ndim"]
+    call = case["call"]
+    if call == "curve":
+        return api.ecc_hard(grid, ndim, case["bins"], range=state["range"], top=case["top"], superlevel=case["superlevel"])
+    if call == "sets":
+        return api.ecc_hard_dir(grid, ndim, state["u"], ALPHA / 10, case["bins"])
+    if call == "pair":
+        args = (grid, ndim, state["u"], ALPHA, state["tau"], SHARP)
+        chi = api.ecc_soft_fwd(*args, tilted_c=case["tilted"])
+        return (chi,) + tuple(api.ecc_soft_bwd(*args, grad_chi=state["g"], tilted_c=case["tilted"]))
+    layer = state["layer"]
+    if call == "score":
+        with torch.no_grad():
+            return layer(grid)
+    chi = layer(grid)
+    return (chi.detach(),) + torch.autograd.grad(chi, [grid, layer.tau, layer.theta], state["g"])
+
+
+def work(case):
+    """Bytes: the input once, every output once.  Operations: the comparisons that order a vertex and its later
+    neighbours (4 in an image, 13 in a volume), the tilt of a direction, and for the soft curves the sigmoids of the
+    critical vertices (a share of about 0.22 / sigma^2 in an image and 0.16 / sigma^3 in a volume; saturated ones
+    included) with 8 operations for chi and 8 more for each derivative's sum."""
+    n = math.prod(_shape(case))
+    nd = 3 if case["d"] else 2
+    stencil = 4 if nd == 2 else 13
+    size = DTYPES[case["dtype"]][1]
+    if case["call"] == "curve":
+        return {"bytes": n * size + 8 * case["batch"] * case["bins"], "flops": n * stencil}
+    if case["call"] == "sets":
+        k = case["ndir"]
+        return {"bytes": n * size + 8 * k * (case["batch"] * case["bins"] + nd / 2), "flops": n * k * (stencil + 2)}
+    share = 0.22 / case["sigma"] ** 2 if nd == 2 else 0.16 / case["sigma"] ** 3
+    out, sums = case["batch"] * case["T"], 1
+    if case["call"] != "score":
+        out, sums = out * 2 + n, 2 + nd
+        if case["call"] == "pair":
+            out += case["batch"] * case["T"] * (1 + nd)
+    return {"bytes": 4 * (n + out), "flops": n * stencil + n * share * case["T"] * 8 * sums}
+
+
+def tolerance(case):
+    """Curves are integers.  The soft outputs against the same sums in float64 (both listed steps, the pair and eleven
+    others, two inputs each): 2-norm within 1e-6 of chi and of the derivatives with respect to X, tau and u, within
+    5e-6 of the angles' (one or two numbers, sums that cancel); single elements within 2.1e-5.  Four times that."""
+    if case["call"] in ("curve", "sets"):
+        return "exact"
+    return {"rel": 2e-5, "max": 1e-4}
