@@ -14,6 +14,7 @@ A case names one call (or one training step) of the public interface and the dat
 `listed` holds the workloads the benchmark and the tests are built around and a few generic ones; `draw` spreads
 over the same calls, sizes, types and options.
 """
+import itertools
 import math
 
 import torch
@@ -225,3 +226,76 @@ def tolerance(case):
     if case["call"] in ("curve", "sets"):
         return "exact"
     return {"rel": 2e-5, "max": 1e-4}
+
+
+def _coefficient(x):
+    """c(p) of every vertex of one item (bool sums): each cell counts with its last vertex, equal values by index."""
+    nd = x.dim()
+    padded = torch.full([n + 2 for n in x.shape], math.inf, dtype=x.dtype, device=x.device)
+    padded[(slice(1, -1),) * nd] = x
+    before = {}
+    for off in itertools.product((-1, 0, 1), repeat=nd):
+        if any(off):
+            q = padded[tuple(slice(1 + o, 1 + o + n) for o, n in zip(off, x.shape))]
+            before[off] = q < x if off > (0,) * nd else q <= x
+    c = torch.ones(x.shape, dtype=torch.int8, device=x.device)
+    for corner in before:  # the cell between p and p + corner, and its other vertices
+        rest = set(itertools.product(*[(0, o) for o in corner])) - {(0,) * nd}
+        charged = torch.stack([before[o] for o in rest]).all(0) if len(rest) > 1 else before[corner]
+        c += charged.to(torch.int8) * (-1) ** sum(map(abs, corner))
+    return c
+
+
+def exact(case, seed):
+    """The soft outputs by their definition, in float64 over the vertices with c(p) != 0.  alpha, lambda and the
+    angles are the float32 numbers that the entry points take.  The curves are whole numbers: None."""
+    if case["call"] in ("curve", "sets"):
+        return None
+    state = prepare(case, seed)
+    grid, nd = state["grid"].detach(), state["ndim"]
+    layer = state["layer"]
+    tau, g = layer.tau.detach().double(), state["g"].double()
+    alpha = float(torch.tensor(ALPHA, dtype=torch.float32))
+
+    def direction(t):
+        if nd == 2:
+            return torch.stack([torch.cos(t[0]), torch.sin(t[0])])
+        return torch.stack([torch.sin(t[1]) * torch.cos(t[0]), torch.sin(t[1]) * torch.sin(t[0]), torch.cos(t[1])])
+
+    u32 = direction(layer.theta.detach())
+    theta = layer.theta.detach().double().requires_grad_()
+    u = direction(theta) if case["call"] != "pair" else u32.double()
+    ud = u.detach()
+    chi, dtau, du, grad_x = [], [], [], []
+    for item, gi in zip(grid, g):
+        field = item
+        if case["tilted"]:  # the tilted field's order is that of its float32 values, formed term by term
+            a = (torch.tensor(ALPHA, dtype=torch.float32, device=u32.device) * u32)
+            axes = [torch.arange(n, device=item.device, dtype=torch.float32) for n in item.shape]
+            x, y = a[0] * axes[-1], a[1] * axes[-2]
+            t = x[None, :] + y[:, None]
+            if nd == 3:
+                t = t[None] + (a[2] * axes[0])[:, None, None]
+            field = item + t
+        c = _coefficient(field)
+        where = c.nonzero()
+        cp = c[tuple(where.T)].double()
+        p = where.flip(1).double()  # x is the fastest axis
+        s = torch.sigmoid(SHARP * (tau - (item[tuple(where.T)].double() + alpha * (p @ ud))[:, None]))
+        chi.append(cp @ s)
+        if case["call"] == "score":
+            continue
+        s = s * (1 - s) * SHARP * cp[:, None]
+        dtau.append(s.sum(0))
+        du.append(-alpha * (s.T @ p))
+        gx = torch.zeros(item.shape, dtype=torch.float64, device=item.device)
+        gx[tuple(where.T)] = -(s @ gi)
+        grad_x.append(gx)
+    chi = torch.stack(chi)
+    if case["call"] == "score":
+        return chi
+    dtau, du, grad_x = torch.stack(dtau), torch.stack(du), torch.stack(grad_x)
+    if case["call"] == "pair":
+        return chi, grad_x, dtau, du
+    (grad_theta,) = torch.autograd.grad(u, theta, (g[:, :, None] * du).sum((0, 1)))
+    return chi, grad_x, (g * dtau).sum(0), grad_theta
