@@ -238,6 +238,24 @@ int ecc_soft_bwd_saved(const float* grid, int ndim, const int64_t* dims, int64_t
                        size_t workspace_bytes, void* hip_stream);
 
 /*
+ * The two ends of a training step with learnable thresholds and direction.
+ *   ecc_soft_direction  u (device out float32 [ndim]) from theta (device float32 [ndim - 1]):
+ *                       2D u = (cos t, sin t); 3D, theta = (t, p): u = (sin p cos t, sin p sin t, cos p)
+ *   ecc_soft_contract   with the derivatives that ecc_soft_fwd_save / ecc_soft_bwd return:
+ *                         grad_tau[j] = sum_i grad_chi[i][j] dchi_dtau[i][j]
+ *                         grad_u[k]   = sum_i sum_j grad_chi[i][j] dchi_du[i][j][k]
+ *                       theta NULL: grad_dir = grad_u [ndim]; otherwise grad_dir [ndim - 1] is the gradient
+ *                       with respect to the angles.  dchi_dtau / grad_tau and dchi_du / grad_dir may be NULL in
+ *                       pairs (not both pairs).  Summed in float64 in a fixed order.
+ *                       workspace: ecc_soft_contract_bytes() bytes, 256-byte aligned.
+ */
+int ecc_soft_direction(const float* theta, int ndim, float* u, void* hip_stream);
+size_t ecc_soft_contract_bytes(int64_t batch, int T);
+int ecc_soft_contract(const float* grad_chi, const float* dchi_dtau, const float* dchi_du, const float* theta,
+                      int64_t batch, int T, int ndim, float* grad_tau, float* grad_dir, void* workspace,
+                      size_t workspace_bytes, void* hip_stream);
+
+/*
  * Soft ECC with the coefficient of the TILTED field: Eq. 6 and Eq. 8-10 exactly
  * as in ecc_soft_fwd / ecc_soft_bwd, except that c(p) is the coefficient (Eq. 3)
  * of Y(p) = X(p) + alpha <u,p> instead of the coefficient of X.  Y is formed in

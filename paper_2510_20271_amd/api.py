@@ -282,6 +282,37 @@ def ecc_soft_bwd_saved(grid, ndim, u, alpha, tau, lam, state, grad_chi=None, gra
     return grad_X
 
 
+def ecc_soft_direction(theta, u=None):
+    """Unit direction [ndim] from its angle(s) theta [ndim - 1] (float32, on the device)."""
+    _need_device(theta, u)
+    if theta.dtype != torch.float32 or theta.numel() not in (1, 2):
+        raise ValueError("theta must hold one or two float32 angles")
+    ndim = theta.numel() + 1
+    if u is None:
+        u = torch.empty(ndim, dtype=torch.float32, device=theta.device)
+    _check(_lib.load().ecc_soft_direction(_ptr(theta), ndim, _ptr(u), _stream()))
+    return u
+
+
+def ecc_soft_contract(grad_chi, dchi_dtau=None, dchi_du=None, theta=None, ndim=2):
+    """(grad_tau [T], gradient of the direction [ndim], or of its angles when theta is given) from the derivatives
+    and the upstream gradient; None where the derivative is None."""
+    _need_device(grad_chi, dchi_dtau, dchi_du, theta)
+    batch, T = grad_chi.shape
+    for t, n in ((grad_chi, batch * T), (dchi_dtau, batch * T), (dchi_du, batch * T * ndim), (theta, ndim - 1)):
+        if t is not None and (t.dtype != torch.float32 or t.numel() != n):
+            raise ValueError("grad_chi, dchi_dtau [batch, T], dchi_du [batch, T, ndim] and theta must be float32")
+    dev = grad_chi.device
+    grad_tau = None if dchi_dtau is None else torch.empty(T, dtype=torch.float32, device=dev)
+    grad_dir = None
+    if dchi_du is not None:
+        grad_dir = torch.empty(ndim if theta is None else ndim - 1, dtype=torch.float32, device=dev)
+    ws = _cached_workspace(int(_lib.load().ecc_soft_contract_bytes(batch, T)), dev)
+    _check(_lib.load().ecc_soft_contract(_ptr(grad_chi), _ptr(dchi_dtau), _ptr(dchi_du), _ptr(theta), batch, T, ndim,
+                                         _ptr(grad_tau), _ptr(grad_dir), _ptr(ws), ws.numel(), _stream()))
+    return grad_tau, grad_dir
+
+
 def ecc_count_nonfinite(grid: torch.Tensor, count=None):
     """Number of NaN / Inf elements of a device tensor, as a device int64 scalar tensor (no sync)."""
     _need_device(grid, count)

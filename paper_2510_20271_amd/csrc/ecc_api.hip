@@ -443,6 +443,45 @@ int ecc_soft_bwd_tilted(const float* grid, int ndim, const int64_t* dims, int64_
                          grad_chi, grad_X, dchi_dtau, dchi_du, workspace, workspace_bytes, hip_stream);
 }
 
+int ecc_soft_direction(const float* theta, int ndim, float* u, void* hip_stream) {
+  if (ndim != 2 && ndim != 3) return fail(ECC_ERR_INVALID_ARG, "ndim must be 2 or 3, got %d", ndim);
+  if (!theta || !u) return fail(ECC_ERR_INVALID_ARG, "theta or u is NULL");
+  int rc;
+  if ((rc = check_f32_out(theta, "theta")) != ECC_OK || (rc = check_f32_out(u, "u")) != ECC_OK) return rc;
+  ecc::launch_direction(theta, ndim, u, static_cast<hipStream_t>(hip_stream));
+  return device_status(hipGetLastError(), "ecc_soft_direction");
+}
+
+static int check_contract_sizes(int64_t batch, int T) {
+  if (batch < 1 || batch > kMaxBatch)
+    return fail(ECC_ERR_INVALID_ARG, "batch must be in 1 .. %lld, got %lld", (long long)kMaxBatch, (long long)batch);
+  if (T < 1 || T > ECC_MAX_THRESHOLDS)
+    return fail(ECC_ERR_INVALID_ARG, "T must be in 1 .. %d, got %d", ECC_MAX_THRESHOLDS, T);
+  return ECC_OK;
+}
+
+size_t ecc_soft_contract_bytes(int64_t batch, int T) {
+  return check_contract_sizes(batch, T) == ECC_OK ? ecc::contract_workspace_bytes(batch, T) : 0;
+}
+
+int ecc_soft_contract(const float* grad_chi, const float* dchi_dtau, const float* dchi_du, const float* theta,
+                      int64_t batch, int T, int ndim, float* grad_tau, float* grad_dir, void* workspace,
+                      size_t workspace_bytes, void* hip_stream) {
+  if (ndim != 2 && ndim != 3) return fail(ECC_ERR_INVALID_ARG, "ndim must be 2 or 3, got %d", ndim);
+  int rc = check_contract_sizes(batch, T);
+  if (rc != ECC_OK) return rc;
+  if (!grad_chi) return fail(ECC_ERR_INVALID_ARG, "grad_chi is NULL");
+  if (!dchi_dtau != !grad_tau || !dchi_du != !grad_dir || (!dchi_dtau && !dchi_du))
+    return fail(ECC_ERR_INVALID_ARG, "derivatives and gradients come in pairs, one pair at least");
+  const float* const all[] = {grad_chi, dchi_dtau, dchi_du, theta, grad_tau, grad_dir};
+  for (const float* p : all)
+    if ((rc = check_f32_out(p, "an array argument")) != ECC_OK) return rc;
+  if ((rc = check_workspace(workspace, workspace_bytes, ecc::contract_workspace_bytes(batch, T))) != ECC_OK) return rc;
+  return device_status(ecc::launch_contract(grad_chi, dchi_dtau, dchi_du, theta, batch, T, ndim, grad_tau, grad_dir,
+                                            workspace, static_cast<hipStream_t>(hip_stream)),
+                       "ecc_soft_contract");
+}
+
 int ecc_count_nonfinite(const void* grid, int64_t n, ecc_dtype dtype, unsigned long long* count,
                         void* hip_stream) {
   if (!converted_dtype(dtype) && check_dtype(dtype) != ECC_OK) return ECC_ERR_INVALID_ARG;

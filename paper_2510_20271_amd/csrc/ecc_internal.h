@@ -117,6 +117,13 @@ hipError_t launch_soft_bwd(const float* grid, const Shape& s, const float* u, fl
                            const float* tau, int T, float lambda, const float* g, float* grad_X,
                            float* dtau, float* du, void* ws, hipStream_t st, bool tiltc = false);
 
+// the ends of a training step (ecc_layer.hip): direction from its angle(s); gradients of thresholds and direction
+// (theta not null: of the angles) from the derivatives and the upstream gradient
+void launch_direction(const float* theta, int ndim, float* u, hipStream_t st);
+size_t contract_workspace_bytes(int64_t batch, int T);
+hipError_t launch_contract(const float* g, const float* dtau, const float* du, const float* theta, int64_t batch, int T,
+                           int ndim, float* grad_tau, float* grad_dir, void* ws, hipStream_t st);
+
 void launch_clear_f32(float* p, int64_t n, hipStream_t st);  // p[0..n) = 0 (fill kernel)
 
 // ---- soft path with state saved for the backward pass --------------------------------

@@ -4,8 +4,8 @@
 sums of Eq. 9-10, which share its sigmoids, and the saved list of critical vertices), backward is
 ``ecc_soft_bwd_saved`` (Eq. 8 over that list; appendix on analytical derivatives).  The kernels
 return d chi / d tau and d chi / d u uncontracted ([batch, T] and [batch, T, ndim]); the two
-small contractions with the upstream gradient that autograd needs are the only arithmetic
-done here.  ``SoftECCLayer`` holds the learnable thresholds and a direction kept on the unit
+small contractions with the upstream gradient that autograd needs are ``ecc_soft_contract`` (tensor
+operations only where a graph of the backward pass is asked for).  ``SoftECCLayer`` holds the learnable thresholds and a direction kept on the unit
 sphere by reparametrisation (an angle in 2D, two angles in 3D), as the main text suggests.
 
 Inputs must live on the GPU; there is no CPU path.
@@ -19,41 +19,84 @@ import torch
 from . import api
 
 
+def _forward(ctx, grid, u, tau, alpha, lam, tilted_c, theta=None):
+    """Forward of both functions below; theta: the angles u comes from, when they are what is learned."""
+    ndim = grid.dim() - 1
+    grid_c = grid.detach().contiguous().float()
+    tau_c = tau.detach().contiguous().float()
+    ctx.alpha, ctx.lam, ctx.ndim, ctx.tilted_c = float(alpha), float(lam), ndim, bool(tilted_c)
+    need_x, need_u, need_tau = ctx.needs_input_grad[:3]
+    if not (need_x or need_u or need_tau):
+        return api.ecc_soft_fwd(grid_c, ndim, u, alpha, tau_c, lam, tilted_c=ctx.tilted_c)
+    # The forward kernel shares its sigmoids with the sums of Eq. 9 / Eq. 10 and finds the vertices
+    # with c != 0 that Eq. 8 needs: it returns the former and saves the latter, so backward() neither
+    # sweeps the grid again nor, with fixed inputs and learnable thresholds (the usual case), runs more
+    # than the small contraction.
+    want = [n for n, need in (("dchi_du", need_u), ("dchi_dtau", need_tau)) if need]
+    chi, dtau, du, state = api.ecc_soft_fwd_save(grid_c, ndim, u, alpha, tau_c, lam, tilted_c=ctx.tilted_c, want=want)
+    ctx.save_for_backward(grid_c, u, tau_c, state if need_x else None, dtau, du, theta)
+    return chi
+
+
+def _backward(ctx, grad_chi):
+    """Gradients with respect to the grid, the direction (or the angles) and the thresholds."""
+    grid, u, tau, state, dtau, du, theta = ctx.saved_tensors
+    g = grad_chi.contiguous().float()
+    need_x, need_u, need_tau = ctx.needs_input_grad[:3]
+    grad_X = None
+    if need_x:
+        grad_X = api.ecc_soft_bwd_saved(grid, ctx.ndim, u, ctx.alpha, tau, ctx.lam, state, grad_chi=g,
+                                        tilted_c=ctx.tilted_c)
+    if not (need_u or need_tau):
+        return grad_X, None, None
+    if not torch.is_grad_enabled() and _has_memory(g):
+        grad_tau, grad_dir = api.ecc_soft_contract(g, dtau, du, theta, ctx.ndim)
+        return grad_X, grad_dir, grad_tau
+    # a graph of the backward pass is wanted, or it runs over a batch of upstream gradients (thresholds alone)
+    grad_dir = torch.einsum("bj,bjd->d", g, du) if need_u else None
+    if need_u and theta is not None:
+        st, ct = torch.sin(theta[0]), torch.cos(theta[0])
+        if ctx.ndim == 2:
+            grad_dir = torch.stack([ct * grad_dir[1] - st * grad_dir[0]])
+        else:
+            sp, cp = torch.sin(theta[1]), torch.cos(theta[1])
+            grad_dir = torch.stack([sp * (ct * grad_dir[1] - st * grad_dir[0]),
+                                    cp * (ct * grad_dir[0] + st * grad_dir[1]) - sp * grad_dir[2]])
+    grad_tau = (g * dtau).sum(0) if need_tau else None
+    return grad_X, grad_dir, grad_tau
+
+
+def _has_memory(t) -> bool:
+    """False for the wrappers that function transforms pass around."""
+    try:
+        t.data_ptr()
+    except RuntimeError:
+        return False
+    return True
+
+
 class SoftECCFunction(torch.autograd.Function):
     """chi[b, j] = sum_p c(p) sigmoid(lambda (tau_j - X_b(p) - alpha <u, p>)), p = (x, y[, z])."""
 
     @staticmethod
     def forward(ctx, grid, u, tau, alpha: float, lam: float, tilted_c: bool = False):
-        ndim = grid.dim() - 1
-        grid_c = grid.detach().contiguous().float()
-        u_c = u.detach().contiguous().float()
-        tau_c = tau.detach().contiguous().float()
-        ctx.alpha, ctx.lam, ctx.ndim, ctx.tilted_c = float(alpha), float(lam), ndim, bool(tilted_c)
-        need_x, need_u, need_tau = ctx.needs_input_grad[:3]
-        if not (need_x or need_u or need_tau):
-            return api.ecc_soft_fwd(grid_c, ndim, u_c, alpha, tau_c, lam, tilted_c=ctx.tilted_c)
-        # The forward kernel shares its sigmoids with the sums of Eq. 9 / Eq. 10 and finds the vertices
-        # with c != 0 that Eq. 8 needs: it returns the former and saves the latter, so backward() neither
-        # sweeps the grid again nor, with fixed inputs and learnable thresholds (the usual case), runs a
-        # kernel at all.
-        want = [n for n, need in (("dchi_du", need_u), ("dchi_dtau", need_tau)) if need]
-        chi, dtau, du, state = api.ecc_soft_fwd_save(grid_c, ndim, u_c, alpha, tau_c, lam, tilted_c=ctx.tilted_c,
-                                                     want=want)
-        ctx.save_for_backward(grid_c, u_c, tau_c, state if need_x else None, dtau, du)
-        return chi
+        return _forward(ctx, grid, u.detach().contiguous().float(), tau, alpha, lam, tilted_c)
 
     @staticmethod
     def backward(ctx, grad_chi):
-        grid, u, tau, state, dtau, du = ctx.saved_tensors
-        g = grad_chi.contiguous().float()
-        need_x, need_u, need_tau = ctx.needs_input_grad[:3]
-        grad_X = None
-        if need_x:
-            grad_X = api.ecc_soft_bwd_saved(grid, ctx.ndim, u, ctx.alpha, tau, ctx.lam, state, grad_chi=g,
-                                            tilted_c=ctx.tilted_c)
-        grad_u = torch.einsum("bj,bjd->d", g, du) if need_u else None
-        grad_tau = (g * dtau).sum(0) if need_tau else None
-        return grad_X, grad_u, grad_tau, None, None, None
+        return *_backward(ctx, grad_chi), None, None, None
+
+
+class _SoftECCAngles(torch.autograd.Function):
+    """The same with the direction given by its angle(s): the gradient comes back for the angles."""
+
+    @staticmethod
+    def forward(ctx, grid, theta, tau, alpha: float, lam: float, tilted_c: bool):
+        return _forward(ctx, grid, api.ecc_soft_direction(theta.detach()), tau, alpha, lam, tilted_c, theta=theta)
+
+    @staticmethod
+    def backward(ctx, grad_chi):
+        return *_backward(ctx, grad_chi), None, None, None
 
 
 def soft_ecc(grid, u, tau, alpha: float, lam: float, tilted_c: bool = False):
@@ -95,4 +138,11 @@ class SoftECCLayer(torch.nn.Module):
                             torch.cos(t[1])])
 
     def forward(self, grid: torch.Tensor) -> torch.Tensor:
+        # The direction inside the autograd function: two launches instead of some fifteen small tensor operations,
+        # which took most of a step's time on the host.  Only for the layer's own direction() and plain angles.
+        theta = self.theta
+        own = type(self).direction is SoftECCLayer.direction and "direction" not in self.__dict__
+        if (own and type(theta) in (torch.nn.Parameter, torch.Tensor) and theta.is_cuda and theta.is_contiguous()
+                and theta.dtype == torch.float32 and theta.numel() == self.ndim - 1):
+            return _SoftECCAngles.apply(grid, theta, self.tau, self.alpha, self.lam, self.tilted_c)
         return soft_ecc(grid, self.direction(), self.tau, self.alpha, self.lam, self.tilted_c)

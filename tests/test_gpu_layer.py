@@ -94,3 +94,63 @@ def test_layer_learns_its_thresholds_back():
         first = first if first is not None else float(loss.detach())
     assert float(loss.detach()) < 0.1 * first
     assert float((model.tau - target.tau).abs().mean().detach()) < 0.015
+
+
+@pytest.mark.parametrize("nd,B,T", [(2, 1, 1), (2, 3, 63), (3, 7, 65), (2, 32, 128), (3, 16, 512), (2, 2, 1500),
+                                    (2, 33, 1025), (3, 600, 130), (2, 512, 64)])
+def test_contraction_with_the_upstream_gradient(nd, B, T):
+    gen = torch.Generator(device="cuda").manual_seed(B * T)
+    g, dtau = (torch.randn(B, T, generator=gen, device="cuda") for _ in range(2))
+    du = torch.randn(B, T, nd, generator=gen, device="cuda")
+    theta = torch.tensor([0.7, 1.9][:nd - 1], device="cuda")
+    grad_tau, grad_u = layer.api.ecc_soft_contract(g, dtau, du, None, nd)
+    _, grad_theta = layer.api.ecc_soft_contract(g, None, du, theta, nd)
+    gd, t = g.double(), theta.double().requires_grad_()
+    want_u = torch.einsum("bj,bjd->d", gd, du.double())
+    u = [torch.cos(t[0]), torch.sin(t[0])]
+    if nd == 3:
+        u = [torch.sin(t[1]) * u[0], torch.sin(t[1]) * u[1], torch.cos(t[1])]
+    (want_theta,) = torch.autograd.grad(torch.stack(u), t, want_u)
+    # float64 sums rounded once to float32: half an ulp of the value, and nothing for the sums' own rounding
+    for got, want in ((grad_tau, (gd * dtau.double()).sum(0)), (grad_u, want_u), (grad_theta, want_theta)):
+        torch.testing.assert_close(got.double(), want, rtol=2.0 ** -24, atol=1e-12 * B * T)
+
+
+class _Overridden(layer.SoftECCLayer):
+    def direction(self):
+        return super().direction()
+
+
+@pytest.mark.parametrize("shape", [(20, 33), (9, 12, 17)])
+@pytest.mark.parametrize("tilted", [False, True])
+def test_layer_equals_its_parts_as_tensor_operations(shape, tilted):
+    """The direction and the contraction inside the layer against those of the general path."""
+    nd = len(shape)
+    X = dev(np.stack([synth.grf(shape, 2.0, 190 + i) for i in range(3)]))
+    g = torch.randn(3, 40, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    out = []
+    for cls in (layer.SoftECCLayer, _Overridden):
+        m = cls(nd, 40, float(X.min()), float(X.max()) + 0.4, alpha=0.02, theta=[0.3, 1.1][:nd - 1],
+                tilted_c=tilted).cuda()
+        x = X.clone().requires_grad_()
+        chi = m(x)
+        out.append((chi,) + torch.autograd.grad(chi, [x, m.tau, m.theta], g, retain_graph=True))
+        # the graph of the backward pass, and a batch of upstream gradients at once
+        gg = g.clone().requires_grad_()
+        d_tau, d_theta = torch.autograd.grad(chi, [m.tau, m.theta], gg, create_graph=True, retain_graph=True)
+        out[-1] += (d_tau, d_theta) + torch.autograd.grad(d_tau.sum() + d_theta.sum(), [gg])
+        m.theta.requires_grad_(False)
+        out[-1] += torch.autograd.grad(m(X), [m.tau], torch.stack([g, 2 * g]), is_grads_batched=True)
+    for a, b in zip(*out):  # chi and grad_X: the same kernels; the others: float32 sums of some 100 terms
+        torch.testing.assert_close(a, b, rtol=1e-4, atol=1e-4 * float(b.detach().abs().max()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+def test_direction_is_that_of_the_tensor_operations():
+    theta = torch.linspace(-7.0, 7.0, 400, device="cuda")
+    for nd in (2, 3):
+        m = layer.SoftECCLayer(nd, 2, 0.0, 1.0).cuda()
+        for i in range(0, 400, 7):
+            with torch.no_grad():
+                m.theta.copy_(theta[[i, 399 - i]][:nd - 1])
+            assert torch.equal(layer.api.ecc_soft_direction(m.theta.detach()), m.direction().detach())
