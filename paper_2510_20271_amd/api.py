@@ -6,6 +6,7 @@ current stream, every step of the computation runs inside libecc_hip.so.
 from __future__ import annotations
 
 import ctypes
+import functools
 
 import torch
 
@@ -32,17 +33,24 @@ def _check(status: int):
         raise EccError(status, ecc_last_error())
 
 
+# The host's share of a small call is as long as its kernels (a 128^2 image: 18 us a call with a stream object made
+# twice, sizes and extents marshalled anew each time; 14 us of kernels), so the marshalling is kept lean.
+@functools.lru_cache(maxsize=1024)
+def _kept_dims(shape: tuple):
+    return (ctypes.c_int64 * len(shape))(*shape)  # (the library only reads it)
+
+
 def _dims(shape):
-    arr = (ctypes.c_int64 * len(shape))(*shape)
-    return arr
+    return _kept_dims(tuple(shape))
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    """The current stream's handle."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _need_device(*tensors):
@@ -59,6 +67,12 @@ def ecc_workspace_bytes_dtype(item_shape, batch: int, dtype: int, bins: int) -> 
     return int(_lib.load().ecc_workspace_bytes_dtype(len(item_shape), _dims(item_shape), batch, dtype, bins))
 
 
+@functools.lru_cache(maxsize=4096)
+def _kept_bytes(query, *numbers) -> int:
+    """A size query of this module (its result depends on the numbers alone)."""
+    return query(*numbers)
+
+
 # Workspaces handed out when the caller passes none: one per (device, stream), grown on demand
 # and kept, so that repeated calls allocate nothing.  Calls on one stream run in order and may
 # share it; calls on different streams get different ones.
@@ -66,7 +80,7 @@ _WS_CACHE = {}
 
 
 def _cached_workspace(need: int, device) -> torch.Tensor:
-    key = (torch.device(device).index, torch.cuda.current_stream().cuda_stream)
+    key = (device.index, _stream())
     ws = _WS_CACHE.get(key)
     if ws is None or ws.numel() < need:
         ws = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
@@ -76,7 +90,7 @@ def _cached_workspace(need: int, device) -> torch.Tensor:
 
 def _workspace(item_shape, batch, n, device, workspace, dtype=ECC_F32):
     if workspace is None:
-        workspace = _cached_workspace(ecc_workspace_bytes_dtype(item_shape, batch, dtype, n), device)
+        workspace = _cached_workspace(_kept_bytes(ecc_workspace_bytes_dtype, item_shape, batch, dtype, n), device)
     return workspace
 
 
@@ -174,7 +188,7 @@ def ecc_hard_dir(grid: torch.Tensor, ndim: int, u: torch.Tensor, alpha: float, b
     if curve is None:
         curve = torch.empty((ndir, batch, bins), dtype=torch.int64, device=grid.device)
     if workspace is None:
-        workspace = _cached_workspace(ecc_workspace_bytes_dir(item, batch, ndir, bins), grid.device)
+        workspace = _cached_workspace(_kept_bytes(ecc_workspace_bytes_dir, item, batch, ndir, bins), grid.device)
     rng = None
     if range is not None:
         rng = (ctypes.c_double * 2)(float(range[0]), float(range[1]))
@@ -256,7 +270,7 @@ def ecc_soft_fwd_save(grid, ndim, u, alpha, tau, lam, chi=None, dchi_dtau=None, 
     if dchi_du is None and "dchi_du" in want:
         dchi_du = torch.empty((batch, T, ndim), dtype=torch.float32, device=dev)
     if state is None:
-        state = torch.empty(max(ecc_soft_state_bytes(item, batch), 256), dtype=torch.uint8, device=dev)
+        state = torch.empty(max(_kept_bytes(ecc_soft_state_bytes, item, batch), 256), dtype=torch.uint8, device=dev)
     workspace = _workspace(item, batch, max(T, 1), dev, workspace)
     _check(_lib.load().ecc_soft_fwd_save(_ptr(grid), ndim, _dims(item), batch, _ptr(u), float(alpha), _ptr(tau), T,
                                          float(lam), int(bool(tilted_c)), _ptr(chi), _ptr(dchi_dtau), _ptr(dchi_du),
@@ -294,6 +308,10 @@ def ecc_soft_direction(theta, u=None):
     return u
 
 
+def ecc_soft_contract_bytes(batch: int, T: int) -> int:
+    return int(_lib.load().ecc_soft_contract_bytes(batch, T))
+
+
 def ecc_soft_contract(grad_chi, dchi_dtau=None, dchi_du=None, theta=None, ndim=2):
     """(grad_tau [T], gradient of the direction [ndim], or of its angles when theta is given) from the derivatives
     and the upstream gradient; None where the derivative is None."""
@@ -307,7 +325,7 @@ def ecc_soft_contract(grad_chi, dchi_dtau=None, dchi_du=None, theta=None, ndim=2
     grad_dir = None
     if dchi_du is not None:
         grad_dir = torch.empty(ndim if theta is None else ndim - 1, dtype=torch.float32, device=dev)
-    ws = _cached_workspace(int(_lib.load().ecc_soft_contract_bytes(batch, T)), dev)
+    ws = _cached_workspace(_kept_bytes(ecc_soft_contract_bytes, batch, T), dev)
     _check(_lib.load().ecc_soft_contract(_ptr(grad_chi), _ptr(dchi_dtau), _ptr(dchi_du), _ptr(theta), batch, T, ndim,
                                          _ptr(grad_tau), _ptr(grad_dir), _ptr(ws), ws.numel(), _stream()))
     return grad_tau, grad_dir
