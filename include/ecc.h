@@ -223,7 +223,7 @@ int ecc_soft_bwd(const float* grid, int ndim, const int64_t* dims, int64_t batch
  *          (more than one in eight of some unit of rows / planes) that its list
  *          overflowed, are noticed on the device: those items are evaluated from
  *          the grid again, so the result is right either way.
- * Shapes outside the fused kernels (T > 256, grids narrower than 8, volumes of
+ * Shapes outside the fused kernels (grids narrower than 8, volumes of
  * 2^31 vertices or more) keep no state: the two calls then run ecc_soft_fwd +
  * ecc_soft_bwd's kernels.  workspace as ecc_soft_fwd.
  */

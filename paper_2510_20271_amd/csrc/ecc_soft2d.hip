@@ -6,16 +6,17 @@
 // bit-sliced stencil and hands them to this file's sinks 64 at a time, straight
 // from the wave's LDS queue.  A sink evaluates the sigmoid on entries x
 // thresholds pairs only:
-//   - threshold-major: lane l owns thresholds tau_l, tau_{l+64}, ... (up to 4,
-//     so T <= 256) and runs over the queue entries (LDS broadcast reads): the
-//     sums over p of Eq. 6 / Eq. 9 / Eq. 10 need no cross-lane reduction;
+//   - threshold-major: lane l owns thresholds tau_l, tau_{l+64}, ... and runs over
+//     the entries (LDS broadcast reads): the sums over p of Eq. 6 / Eq. 9 / Eq. 10
+//     need no cross-lane reduction;
 //   - backward: the same pass also forms, per entry, the contraction of Eq. 8 with
-//     the upstream gradient as a fixed-order sum over the lanes (grad_X).
+//     the upstream gradient as a fixed-order sum over the lanes (grad_X);
+// see ecc_soft_eval.h.
 // grad_X is zero away from critical vertices; the sweep writes those zeros row
 // by row for the vertices it owns, before any entry of those rows is drained
 // (measured a little quicker than a fill kernel in front of the sweep).
-// Each wave writes its partial sums to the workspace; a second kernel adds them
-// in a fixed order in float64, so results are run-to-run identical.
+// Each wave keeps its partial sums in a row of the workspace; a second kernel adds the
+// rows in a fixed order in float64, so results are run-to-run identical.
 //
 // y = X(p) + alpha <u,p> is formed in float64 and carried as two floats (yh + yl), so that
 // z = (tau_j - yh) - yl is the float64 difference to within an ulp of z; exp2 and the
@@ -23,125 +24,50 @@
 // [min tau, max tau] that every sigmoid is 0 or 1 to 2^-64 is not evaluated at all: it adds
 // c to every threshold (sigma = 1) or nothing, and nothing to the derivatives.
 #include "ecc_sweep2d.h"
+#include "ecc_soft_eval.h"
 #include "ecc_soft_saved.h"
 #include "ecc_soft_reduce.h"
 
 namespace ecc {
 
-constexpr int kSoftTL = 4;  // thresholds per lane
-
+// What the queue holds per critical vertex: the value and its place, eight bytes, so that rings, queues and the
+// stages below take 40 KB a block and four blocks fit a CU (44 KB and three with y formed as a vertex is queued).
 struct SoftEntry {
-  float yh, yl;  // X(p) + alpha <u,p> = yh + yl
-  float c;
-  int col, row;
-  int pad;
+  float v;       // value the sweep ran on
+  unsigned rel;  // row - row0 << 12 | column - col0 << 4 | c & 15
+};
+struct SoftStaged {
+  float yh, yl, c;  // X(p) + alpha <u,p> = yh + yl
+  unsigned rel;
 };
 
-struct SoftCommon {
+// CHI / DERIV / GRADX: what is formed (see ecc_soft_eval.h); SAVE: every entry is also appended to the unit's list
+// in the state buffer.  ZERO: the sweep clears grad_X row by row.
+template <bool CHI, bool DERIV, bool GRADX, bool SAVE, int STRIDE>
+struct SoftSink {
   typedef SoftEntry Entry;
   static constexpr bool kTrackRange = false;
+  static constexpr bool kZeroFill = GRADX;
   double ux, uy, alpha;
-  float tj[kSoftTL];  // this lane's thresholds
-  int T;
-  int nt;  // threshold slots in use: ceil(T / 64)
-  float kneg;
   float sat_lo, sat_hi;  // y <= sat_lo: every sigma is 1;  y >= sat_hi: every sigma is 0 (to 2^-64)
   // The sweep ran on the tilted field (c of the tilted field): the value it hands over
   // is the tilted one in float32; X is read again so that y is formed as always.
   const float* xsrc;  // this item's grid, or null when the sweep ran on X itself
-  int xW;
+  int W;
+  int col0, row0;     // origin of the wave's unit: coordinates are summed relative to it
+  SoftStaged* stage;  // wave-private LDS, 64 entries
+  SoftEval<2, CHI, DERIV, GRADX, STRIDE> eval;
+  float* gx;          // GRADX: grad_X of this item or null
+  float lambda;
+  SavedEntry* list;     // SAVE: this unit's list
+  unsigned cap, saved;  // saved: entries seen so far (wave-uniform; may pass cap)
+
   __device__ __forceinline__ Entry make(float v, int c, int col, int row) const {
     Entry e;
-    if (xsrc) v = xsrc[(int64_t)row * xW + col];  // wave-uniform condition
-    const double y = (double)v + alpha * (ux * (double)col + uy * (double)row);
-    e.yh = (float)y;
-    e.yl = (float)(y - (double)e.yh);
-    e.c = (float)c;
-    e.col = col;
-    e.row = row;
-    e.pad = 0;
+    e.v = v;
+    e.rel = ((unsigned)(row - row0) << 12) | ((unsigned)(col - col0) << 4) | ((unsigned)c & 15u);
     return e;
   }
-  __device__ __forceinline__ void init(const float* u, float alpha_, const float* tau, int T_, float kneg_) {
-    ux = (double)u[0];
-    uy = (double)u[1];
-    alpha = (double)alpha_;
-    T = T_;
-    nt = (T_ + kWave - 1) / kWave;
-    kneg = kneg_;
-    xsrc = nullptr;
-    xW = 0;
-    const int lane = threadIdx.x & (kWave - 1);
-    float lo = INFINITY, hi = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < kSoftTL; ++t) {
-      const int j = lane + kWave * t;
-      tj[t] = j < T ? tau[j] : 0.0f;
-      if (j < T) {
-        lo = fminf(lo, tj[t]);
-        hi = fmaxf(hi, tj[t]);
-      }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      lo = fminf(lo, __shfl_xor(lo, o));
-      hi = fmaxf(hi, __shfl_xor(hi, o));
-    }
-    soft_sat_bounds(lo, hi, kneg_, sat_lo, sat_hi);
-  }
-  // Packs the entries of buf[0..n) that have to be evaluated to the front of buf (a wave's LDS
-  // reads and writes execute in order: every lane has read its entry before any lane overwrites
-  // one) and returns how many there are; *csat receives the sum of c over the dropped entries whose
-  // sigmoids are all 1 (dropped entries whose sigmoids are all 0 add nothing).
-  __device__ __forceinline__ int drop_saturated(Entry* buf, int n, float* csat) const {
-    const int lane = threadIdx.x & (kWave - 1);
-    Entry e = buf[lane < n ? lane : 0];
-    const bool in = lane < n;
-    const bool keep = in && e.yh > sat_lo && e.yh < sat_hi;
-    const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
-    const int kept = __builtin_popcountll(m);
-    if (kept == n) return n;  // wave-uniform: nothing to drop
-    if (csat) {
-      const float ones = wave_sum_lane63((in && e.yh <= sat_lo) ? e.c : 0.0f);
-      *csat += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ones), kWave - 1));
-    }
-    const int pos = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-    if (keep) buf[pos] = e;
-    return kept;
-  }
-  __device__ __forceinline__ float zarg(int t, float yh, float yl) const { return (tj[t] - yh) - yl; }
-};
-
-struct SoftFwdSink : SoftCommon {
-  static constexpr bool kZeroFill = false;
-  float acc[kSoftTL];
-  float csat;  // sum of c over the entries whose sigmoids are all 1 (wave-uniform)
-  __device__ __forceinline__ void consume(Entry* buf, int n) {
-    n = drop_saturated(buf, n, &csat);
-    for (int e = 0; e < n; ++e) {
-      const float yh = buf[e].yh, yl = buf[e].yl;
-      const float c = buf[e].c;
-#pragma unroll
-      for (int t = 0; t < kSoftTL; ++t) {
-        if (t < nt) {  // wave-uniform
-          const float ex = soft_exp_neg(zarg(t, yh, yl), kneg);
-          acc[t] += c * __builtin_amdgcn_rcpf(1.0f + ex);
-        }
-      }
-    }
-  }
-  __device__ __forceinline__ float total(int t) const { return acc[t] + csat; }
-};
-
-struct SoftBwdSink : SoftCommon {
-  static constexpr bool kZeroFill = true;
-  float a0[kSoftTL], ax[kSoftTL], ay[kSoftTL];
-  float gj[kSoftTL];  // upstream gradient at this lane's thresholds (0 beyond T)
-  float* gx;          // grad_X of this item or null
-  int W;
-  int col0, row0;    // origin of the wave's unit: coordinates are summed relative to it
-  float lambda;
-
   template <bool EDGE>
   __device__ __forceinline__ void zero_row(int row, int col, const bool (&ok)[kNC], bool out_lane) const {
     if (!gx || !out_lane) return;
@@ -154,34 +80,49 @@ struct SoftBwdSink : SoftCommon {
         if (ok[e]) p[e] = 0.f;
     }
   }
-
-  // One pass over entries x thresholds serves all three derivatives: lane l holds
-  // sigma'(z) / lambda for its thresholds; the sums over p stay in the lane, the
-  // contraction with the upstream gradient (Eq. 8) is a fixed-order sum over the lanes.
-  __device__ __forceinline__ void consume(Entry* buf, int n) {
+  __device__ __forceinline__ void consume(const Entry* buf, int n) {
     const int lane = threadIdx.x & (kWave - 1);
-    n = drop_saturated(buf, n, nullptr);  // sigma' < 2^-64 lambda at every threshold; grad_X stays 0 there
-    for (int e = 0; e < n; ++e) {
-      const float yh = buf[e].yh, yl = buf[e].yl;
-      const float c = buf[e].c;
-      const float rx = (float)(buf[e].col - col0), ry = (float)(buf[e].row - row0);
-      float gd = 0.0f;
-#pragma unroll
-      for (int t = 0; t < kSoftTL; ++t) {
-        if (t < nt) {  // wave-uniform
-          const float ex = soft_exp_neg(zarg(t, yh, yl), kneg);
-          const float s = __builtin_amdgcn_rcpf(1.0f + ex);
-          const float d = ex * s * s;  // sigma (1 - sigma)
-          const float cd = c * d;
-          a0[t] += cd;
-          ax[t] += cd * rx;
-          ay[t] += cd * ry;
-          gd += gj[t] * d;
-        }
+    const bool in = lane < n;
+    const Entry q = buf[in ? lane : 0];
+    const int col = col0 + (int)((q.rel >> 4) & 255u), row = row0 + (int)(q.rel >> 12);
+    const int ci = (int)(q.rel << 28) >> 28;
+    float v = q.v;
+    if (xsrc) v = xsrc[(int64_t)row * W + col];  // wave-uniform condition
+    const double y = (double)v + alpha * (ux * (double)col + uy * (double)row);
+    SoftStaged e;
+    e.yh = (float)y;
+    e.yl = (float)(y - (double)e.yh);
+    e.c = (float)ci;
+    e.rel = q.rel;
+    if constexpr (SAVE) {
+      if (in && saved + (unsigned)lane < cap) {
+        SavedEntry o;
+        o.y = y;
+        o.idx = row * W + col;
+        o.c = ci;
+        list[saved + lane] = o;
       }
-      if (gx) {  // wave-uniform
-        gd = wave_sum_lane63(gd);
-        if (lane == kWave - 1) gx[(int64_t)buf[e].row * W + buf[e].col] = -lambda * c * gd;
+      saved += (unsigned)n;
+    }
+    float csat;
+    int pos;
+    n = pack_entries(in && e.yh > sat_lo && e.yh < sat_hi, in && e.yh <= sat_lo, e.c, n, csat, pos);
+    if (in && e.yh > sat_lo && e.yh < sat_hi) stage[pos] = e;
+    if (!CHI) csat = 0.0f;  // (sigma' < 2^-64 lambda at every threshold; grad_X stays 0 there)
+    if (n == 0 && csat == 0.0f) return;
+    const SoftStaged* st = stage;
+    const float g = eval.template run<2>(n, csat, [st](int i, StagedValue& o, float (&r)[2]) {
+      const SoftStaged s = st[i];
+      o.yh = s.yh;
+      o.yl = s.yl;
+      o.c = s.c;
+      r[0] = (float)((s.rel >> 4) & 255u);
+      r[1] = (float)(s.rel >> 12);
+    });
+    if constexpr (GRADX) {
+      if (gx && lane < n) {
+        const SoftStaged s = stage[lane];
+        gx[(int64_t)(row0 + (int)(s.rel >> 12)) * W + col0 + (int)((s.rel >> 4) & 255u)] = -lambda * s.c * g;
       }
     }
   }
@@ -198,211 +139,95 @@ size_t soft2d_state_bytes(const Shape& s) {
   return state_bytes(s.batch, (size_t)pl.nstrip * pl.nseg, state_cap(pl));
 }
 
-// LDS: [4 waves] value rings, then [4 waves] queues of SoftEntry
-__device__ __forceinline__ void soft_lds(int* smem, float*& ring, SoftEntry*& qbuf) {
+// LDS: [4 waves] value rings, then [4 waves] queues of SoftEntry, then [4 waves] stages
+constexpr size_t kSoftLds = ring_bytes2d<SoftEntry>() + (size_t)4 * kWave * sizeof(SoftStaged);
+
+// The sweep of a wave with sink `queue.sink`, whose own fields the kernels below have set; partial (may be null):
+// rows of STRIDE floats a threshold, one row a unit.  TILTC: the sweep runs on the tilted field, so c(p) is that
+// field's coefficient.
+template <bool TILTC, int STRIDE, typename Sink>
+__device__ __forceinline__ void soft2d_sweep(WaveQueue<Sink>& queue, const float* __restrict__ grid, int H, int W,
+                                             int64_t N, int nstrip, int nseg, int rows_per_seg, const float* u,
+                                             float alpha, const float* tau, int T, float kneg, const float* gup,
+                                             float* partial) {
+  extern __shared__ int smem[];
   const int wv = threadIdx.x >> 6;
-  ring = reinterpret_cast<float*>(smem) + wv * (kChunkRows * kWave * kNC);
-  qbuf = reinterpret_cast<SoftEntry*>(smem + 4 * kChunkRows * kWave * kNC) + wv * kQueueCap;
+  const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wv), units = nstrip * nseg;
+  float* ring = reinterpret_cast<float*>(smem) + wv * (kChunkRows * kWave * kNC);
+  SoftEntry* qbuf = reinterpret_cast<SoftEntry*>(smem + 4 * kChunkRows * kWave * kNC);
+  queue.buf = qbuf + wv * kQueueCap;
+  queue.count = 0;
+  Sink& s = queue.sink;
+  s.stage = reinterpret_cast<SoftStaged*>(qbuf + 4 * kQueueCap) + wv * kWave;
+  s.ux = (double)u[0];
+  s.uy = (double)u[1];
+  s.alpha = (double)alpha;
+  float lo, hi;
+  threshold_span(tau, T, lo, hi);
+  soft_sat_bounds(lo, hi, kneg, s.sat_lo, s.sat_hi);
+  s.W = W;
+  s.col0 = (unit % nstrip) * kStripOut - kNC;
+  s.row0 = (unit / nstrip) * rows_per_seg;
+  const bool on = unit < units;
+  s.eval.init(tau, T, kneg, gup ? gup + (int64_t)blockIdx.y * T : nullptr,
+              on && partial ? partial + ((int64_t)blockIdx.y * units + unit) * (int64_t)T * STRIDE : nullptr);
+  const float* g = grid + (int64_t)blockIdx.y * N;
+  s.xsrc = TILTC ? g : nullptr;
+  WaveRange range;
+  if constexpr (TILTC) {
+    const DirArgs da = {u, alpha, 1, 2};
+    sweep2d_wave<float>(g, H, W, N, nstrip, nseg, rows_per_seg, queue, ring, range, load_tilt(da, 0));
+  } else {
+    sweep2d_wave<float>(g, H, W, N, nstrip, nseg, rows_per_seg, queue, ring, range, NoTilt());
+  }
+  s.eval.finish();
 }
 
 // partial[(item * units + unit) * T + j]
-// TILTC: the sweep runs on the tilted field, so c(p) is that field's coefficient
 template <bool TILTC>
-__global__ __launch_bounds__(256) void soft2d_fwd_kernel(const float* __restrict__ grid, int H, int W,
+__global__ __launch_bounds__(256, 4) void soft2d_fwd_kernel(const float* __restrict__ grid, int H, int W,
                                                          int64_t N, int nstrip, int nseg, int rows_per_seg,
                                                          const float* __restrict__ u, float alpha,
                                                          const float* __restrict__ tau, int T, float kneg,
                                                          float* __restrict__ partial) {
-  extern __shared__ int smem[];
-  float* ring;
-  SoftEntry* qbuf;
-  soft_lds(smem, ring, qbuf);
-  WaveQueue<SoftFwdSink> queue;
-  queue.buf = qbuf;
-  queue.count = 0;
-  queue.sink.init(u, alpha, tau, T, kneg);
-#pragma unroll
-  for (int t = 0; t < kSoftTL; ++t) queue.sink.acc[t] = 0.f;
-  queue.sink.csat = 0.f;
-  WaveRange range;
-  if constexpr (TILTC) {
-    queue.sink.xsrc = grid + (int64_t)blockIdx.y * N;
-    queue.sink.xW = W;
-    const DirArgs da = {u, alpha, 1, 2};
-    sweep2d_wave<float>(grid + (int64_t)blockIdx.y * N, H, W, N, nstrip, nseg, rows_per_seg, queue, ring, range,
-                        load_tilt(da, 0));
-  } else {
-    sweep2d_wave<float>(grid + (int64_t)blockIdx.y * N, H, W, N, nstrip, nseg, rows_per_seg, queue, ring, range,
-                        NoTilt());
-  }
-  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6), units = nstrip * nseg;
-  if (unit < units) {
-    float* out = partial + ((int64_t)blockIdx.y * units + unit) * T;
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int t = 0; t < kSoftTL; ++t) {
-      const int j = lane + kWave * t;
-      if (j < T) out[j] = queue.sink.total(t);
-    }
-  }
+  WaveQueue<SoftSink<true, false, false, false, 1>> queue;
+  soft2d_sweep<TILTC, 1>(queue, grid, H, W, N, nstrip, nseg, rows_per_seg, u, alpha, tau, T, kneg, nullptr, partial);
 }
 
 // partial[((item * units + unit) * T + j) * 4 + {0: A0, 1: Ax, 2: Ay}]
 template <bool TILTC>
-__global__ __launch_bounds__(256) void soft2d_bwd_kernel(const float* __restrict__ grid, int H, int W,
+__global__ __launch_bounds__(256, 4) void soft2d_bwd_kernel(const float* __restrict__ grid, int H, int W,
                                                          int64_t N, int nstrip, int nseg, int rows_per_seg,
                                                          const float* __restrict__ u, float alpha,
                                                          const float* __restrict__ tau, int T, float kneg,
                                                          float lambda, const float* __restrict__ gup,
                                                          float* __restrict__ grad_X,
                                                          float* __restrict__ partial) {
-  extern __shared__ int smem[];
-  float* ring;
-  SoftEntry* qbuf;
-  soft_lds(smem, ring, qbuf);
-  WaveQueue<SoftBwdSink> queue;
-  queue.buf = qbuf;
-  queue.count = 0;
-  SoftBwdSink& s = queue.sink;
-  s.init(u, alpha, tau, T, kneg);
-#pragma unroll
-  for (int t = 0; t < kSoftTL; ++t) s.a0[t] = s.ax[t] = s.ay[t] = 0.f;
-  {
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int t = 0; t < kSoftTL; ++t) {
-      const int j = lane + kWave * t;
-      s.gj[t] = j < T ? (gup ? gup[(int64_t)blockIdx.y * T + j] : 1.0f) : 0.0f;
-    }
-  }
-  s.gx = grad_X ? grad_X + (int64_t)blockIdx.y * N : nullptr;
-  s.W = W;
-  s.lambda = lambda;
-  const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), units = nstrip * nseg;
-  s.col0 = (unit % nstrip) * kStripOut - kNC;
-  s.row0 = (unit / nstrip) * rows_per_seg;
-  WaveRange range;
-  if constexpr (TILTC) {
-    queue.sink.xsrc = grid + (int64_t)blockIdx.y * N;
-    queue.sink.xW = W;
-    const DirArgs da = {u, alpha, 1, 2};
-    sweep2d_wave<float>(grid + (int64_t)blockIdx.y * N, H, W, N, nstrip, nseg, rows_per_seg, queue, ring, range,
-                        load_tilt(da, 0));
-  } else {
-    sweep2d_wave<float>(grid + (int64_t)blockIdx.y * N, H, W, N, nstrip, nseg, rows_per_seg, queue, ring, range,
-                        NoTilt());
-  }
-  if (partial && unit < units) {
-    float* out = partial + ((int64_t)blockIdx.y * units + unit) * (int64_t)T * 4;
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int t = 0; t < kSoftTL; ++t) {
-      const int j = lane + kWave * t;
-      if (j < T) {
-        out[j * 4 + 0] = s.a0[t];
-        out[j * 4 + 1] = s.ax[t];
-        out[j * 4 + 2] = s.ay[t];
-      }
-    }
-  }
+  WaveQueue<SoftSink<false, true, true, false, 4>> queue;
+  queue.sink.gx = grad_X ? grad_X + (int64_t)blockIdx.y * N : nullptr;
+  queue.sink.lambda = lambda;
+  soft2d_sweep<TILTC, 4>(queue, grid, H, W, N, nstrip, nseg, rows_per_seg, u, alpha, tau, T, kneg, gup, partial);
 }
 
-
-// Forward pass that saves its critical vertices: chi as SoftFwdSink, optionally the sums of
-// Eq. 9 / Eq. 10 in the same pass (they share the sigmoid), and every entry appended to the
-// unit's own list in the state buffer.
-template <bool DERIV>
-struct SoftSaveSink : SoftCommon {
-  static constexpr bool kZeroFill = false;
-  float acc[kSoftTL], a0[kSoftTL], ax[kSoftTL], ay[kSoftTL];
-  float csat;
-  int W, col0, row0;
-  SavedEntry* list;     // this unit's list
-  unsigned cap, saved;  // saved: entries seen so far (wave-uniform; may pass cap)
-  __device__ __forceinline__ void consume(Entry* buf, int n) {
-    const int lane = threadIdx.x & (kWave - 1);
-    if (lane < n && saved + (unsigned)lane < cap) {
-      const Entry e = buf[lane];
-      SavedEntry o;
-      o.y = (double)e.yh + (double)e.yl;
-      o.idx = e.row * W + e.col;
-      o.c = (int)e.c;
-      list[saved + lane] = o;
-    }
-    saved += (unsigned)n;
-    n = drop_saturated(buf, n, &csat);
-    for (int e = 0; e < n; ++e) {
-      const float yh = buf[e].yh, yl = buf[e].yl;
-      const float c = buf[e].c;
-      const float rx = (float)(buf[e].col - col0), ry = (float)(buf[e].row - row0);
-#pragma unroll
-      for (int t = 0; t < kSoftTL; ++t) {
-        if (t < nt) {  // wave-uniform
-          const float ex = soft_exp_neg(zarg(t, yh, yl), kneg);
-          const float sg = __builtin_amdgcn_rcpf(1.0f + ex);
-          acc[t] += c * sg;
-          if (DERIV) {
-            const float cd = c * (ex * sg * sg);  // c sigma (1 - sigma)
-            a0[t] += cd;
-            ax[t] += cd * rx;
-            ay[t] += cd * ry;
-          }
-        }
-      }
-    }
-  }
-};
-
+// Forward pass that saves its critical vertices: chi as soft2d_fwd_kernel, with DERIV the sums of Eq. 9 / Eq. 10 in
+// the same pass (they share the sigmoid), and every entry appended to the unit's own list in the state buffer.
 // partial[((item * units + unit) * T + j) * 4 + {0: chi, 1: A0, 2: Ax, 3: Ay}]
 template <bool TILTC, bool DERIV>
-__global__ __launch_bounds__(256) void soft2d_fwd_save_kernel(const float* __restrict__ grid, int H, int W, int64_t N,
+__global__ __launch_bounds__(256, 4) void soft2d_fwd_save_kernel(const float* __restrict__ grid, int H, int W, int64_t N,
                                                               int nstrip, int nseg, int rows_per_seg,
                                                               const float* __restrict__ u, float alpha,
                                                               const float* __restrict__ tau, int T, float kneg,
                                                               float* __restrict__ partial, StateView sv, unsigned cap) {
-  extern __shared__ int smem[];
-  float* ring;
-  SoftEntry* qbuf;
-  soft_lds(smem, ring, qbuf);
-  WaveQueue<SoftSaveSink<DERIV>> queue;
-  queue.buf = qbuf;
-  queue.count = 0;
-  SoftSaveSink<DERIV>& s = queue.sink;
-  s.init(u, alpha, tau, T, kneg);
-#pragma unroll
-  for (int t = 0; t < kSoftTL; ++t) s.acc[t] = s.a0[t] = s.ax[t] = s.ay[t] = 0.f;
-  s.csat = 0.f;
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), units = nstrip * nseg;
-  s.W = W;
-  s.col0 = (unit % nstrip) * kStripOut - kNC;
-  s.row0 = (unit / nstrip) * rows_per_seg;
-  s.cap = cap;
-  s.saved = 0u;
-  s.list = sv.lists + ((size_t)blockIdx.y * units + (unit < units ? unit : 0)) * cap;
+  WaveQueue<SoftSink<true, DERIV, false, true, 4>> queue;
+  queue.sink.cap = cap;
+  queue.sink.saved = 0u;
+  queue.sink.list = sv.lists + ((size_t)blockIdx.y * units + (unit < units ? unit : 0)) * cap;
   const unsigned next_gen = *sv.gen + 1u;  // (the reduction kernel that follows stores it)
-  WaveRange range;
-  if constexpr (TILTC) {
-    s.xsrc = grid + (int64_t)blockIdx.y * N;
-    s.xW = W;
-    const DirArgs da = {u, alpha, 1, 2};
-    sweep2d_wave<float>(grid + (int64_t)blockIdx.y * N, H, W, N, nstrip, nseg, rows_per_seg, queue, ring, range,
-                        load_tilt(da, 0));
-  } else {
-    sweep2d_wave<float>(grid + (int64_t)blockIdx.y * N, H, W, N, nstrip, nseg, rows_per_seg, queue, ring, range,
-                        NoTilt());
-  }
-  if (unit < units) {
-    const int lane = threadIdx.x & (kWave - 1);
-    if (lane == 0) {
-      sv.counts[(size_t)blockIdx.y * units + unit] = s.saved;
-      if (s.saved > cap) sv.overflow[blockIdx.y] = next_gen;
-    }
-    float4* out = reinterpret_cast<float4*>(partial) + ((int64_t)blockIdx.y * units + unit) * (int64_t)T;
-#pragma unroll
-    for (int t = 0; t < kSoftTL; ++t) {
-      const int j = lane + kWave * t;
-      if (j < T) out[j] = make_float4(s.acc[t] + s.csat, s.a0[t], s.ax[t], s.ay[t]);
-    }
+  soft2d_sweep<TILTC, 4>(queue, grid, H, W, N, nstrip, nseg, rows_per_seg, u, alpha, tau, T, kneg, nullptr, partial);
+  if (unit < units && (threadIdx.x & (kWave - 1)) == 0) {
+    sv.counts[(size_t)blockIdx.y * units + unit] = queue.sink.saved;
+    if (queue.sink.saved > cap) sv.overflow[blockIdx.y] = next_gen;
   }
 }
 
@@ -436,8 +261,8 @@ __global__ __launch_bounds__(256) void soft2d_bwd_saved_kernel(const float* __re
                                                                SoftStateHeader expect) {
   const int item = blockIdx.y, unit = blockIdx.x, units = nstrip * nseg;
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
-  __shared__ float stau[kSoftTL * kWave];
-  __shared__ float sg[kSoftTL * kWave];
+  extern __shared__ float stau[];  // [T] thresholds, [T] upstream gradient
+  float* const sg = stau + T;
   __shared__ StagedEntry stage[256];
   __shared__ float sred[2][4];
   __shared__ int skept[4];
@@ -518,10 +343,9 @@ __global__ __launch_bounds__(256) void soft2d_bwd_saved_kernel(const float* __re
 }
 
 static float kneg2d(float lambda) { return (float)(-(double)lambda * 1.4426950408889634); }
-constexpr size_t kSoftLds = ring_bytes2d<SoftEntry>();
 
 bool soft2d_supported(const Shape& s, int T) {
-  return s.D == 1 && s.ndim == 2 && T <= kSoftTL * kWave && s.W >= 8 && s.W <= (1 << 22) &&
+  return s.D == 1 && s.ndim == 2 && T >= 1 && s.W >= 8 && s.W <= (1 << 22) &&
          s.H <= (1 << 30) && s.N < ((int64_t)1 << 31);
 }
 
@@ -537,7 +361,7 @@ static double* soft2d_mid(void* ws, const Shape& s, const Plan2d& pl, int T) {
 size_t soft2d_workspace_bytes(const Shape& s, int T) {
   if (!soft2d_supported(s, T)) return 0;
   const Plan2d pl = plan2d<float>(s, true);
-  return (size_t)256 + soft2d_partial_bytes(s, pl, T) + soft_reduce_mid_bytes(s.batch, T);
+  return (size_t)256 + soft2d_partial_bytes(s, pl, T) + soft_reduce_mid_bytes(pl.nstrip * pl.nseg, s.batch, T);
 }
 
 void launch_soft2d_fwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau,
@@ -623,12 +447,13 @@ void launch_soft2d_bwd_saved(const float* grid, const Shape& s, const float* u, 
   const StateView sv = state_view(const_cast<void*>(state), s.batch, (size_t)pl.nstrip * pl.nseg);
   const SoftStateHeader expect = state_header(s, pl, tiltc);
   const dim3 g((unsigned)(pl.nstrip * pl.nseg), (unsigned)s.batch);
+  const size_t lds = (size_t)T * 2 * sizeof(float);
   profile_mark(st, false);
   if (tiltc)
-    hipLaunchKernelGGL(soft2d_bwd_saved_kernel<true>, g, dim3(256), 0, st, grid, (int)s.H, (int)s.W, s.N, pl.nstrip,
+    hipLaunchKernelGGL(soft2d_bwd_saved_kernel<true>, g, dim3(256), lds, st, grid, (int)s.H, (int)s.W, s.N, pl.nstrip,
                        pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), lambda, gup, grad_X, sv, expect);
   else
-    hipLaunchKernelGGL(soft2d_bwd_saved_kernel<false>, g, dim3(256), 0, st, grid, (int)s.H, (int)s.W, s.N, pl.nstrip,
+    hipLaunchKernelGGL(soft2d_bwd_saved_kernel<false>, g, dim3(256), lds, st, grid, (int)s.H, (int)s.W, s.N, pl.nstrip,
                        pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), lambda, gup, grad_X, sv, expect);
   profile_mark(st, true);
 }

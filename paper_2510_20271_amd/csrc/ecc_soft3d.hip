@@ -8,13 +8,12 @@
 // parks the entry in a small LDS stage -- unless y lies so far outside [min tau, max tau]
 // that every sigmoid is 0 or 1 to 2^-64: such an entry adds c or nothing to every
 // threshold and is not evaluated.  Then every lane runs over the staged entries for the
-// thresholds it owns (tau_l, tau_{l+64}, ...; T <= 256): the sums over p of
-// Eq. 6 / Eq. 9 / Eq. 10 need no cross-lane reduction, the contraction of Eq. 8
-// with the upstream gradient is a fixed-order sum over the lanes.  grad_X is
+// thresholds it owns (tau_l, tau_{l+64}, ...; see ecc_soft_eval.h).  grad_X is
 // cleared by a fill kernel first and written at the critical vertices only.
-// Each wave leaves its partial sums in the workspace; a second kernel adds them
+// Each wave keeps its partial sums in a row of the workspace; a second kernel adds them
 // in a fixed order in float64, so results are run-to-run identical.
 #include "ecc_sweep3d.h"
+#include "ecc_soft_eval.h"
 #include "ecc_soft_saved.h"
 #include "ecc_soft_reduce.h"
 
@@ -22,183 +21,115 @@
 
 namespace ecc {
 
-constexpr int kSoft3TL = 4;  // thresholds per lane
+constexpr int kSoft3Slots = 1;  // slots of 64 thresholds taken together
+constexpr int kSoft3Waves = 4;  // waves on a SIMD that the registers are kept within
 
-struct Soft3Entry {
-  float yh, yl;  // X(p) + alpha <u,p> = yh + yl
-  float c;
-  int x, yy, z;
-  unsigned inpl;  // yy * W + x
-  int pad;
+struct Soft3Staged {
+  float yh, yl, c;  // X(p) + alpha <u,p> = yh + yl
+  unsigned inpl;    // element offset inside the plane
+  float rx, ry, rz; // coordinates relative to the unit's origin
+  unsigned zrel;    // plane of the segment
 };
 
-struct Soft3Common {
+// CHI / DERIV / GRADX: what is formed (see ecc_soft_eval.h); SAVE: every entry is also appended to the unit's list
+// in the state buffer (sweep order, no atomics: the same on every run).
+template <bool CHI, bool DERIV, bool GRADX, bool SAVE, int STRIDE>
+struct Soft3Sink {
   static constexpr bool kTrackRange = false;
   double ux, uy, uz, alpha;
-  float tj[kSoft3TL];  // this lane's thresholds
-  int nt;              // threshold slots in use: ceil(T / 64)
-  float kneg;
   float sat_lo, sat_hi;  // y <= sat_lo: every sigma is 1;  y >= sat_hi: every sigma is 0 (to 2^-64)
   int W;
-  int64_t plane;      // H * W
-  int oz;             // first plane of the wave's segment
-  Soft3Entry* stage;  // wave-private LDS, 64 entries
-  __device__ __forceinline__ void init(const float* u, float alpha_, const float* tau, int T, float kneg_, int H_, int W_,
-                                       Soft3Entry* stage_) {
-    ux = (double)u[0];
-    uy = (double)u[1];
-    uz = (double)u[2];
-    alpha = (double)alpha_;
-    nt = (T + kWave - 1) / kWave;
-    kneg = kneg_;
-    W = W_;
-    plane = (int64_t)H_ * W_;
-    stage = stage_;
-    const int lane = threadIdx.x & (kWave - 1);
-    float lo = INFINITY, hi = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < kSoft3TL; ++t) {
-      const int j = lane + kWave * t;
-      tj[t] = j < T ? tau[j] : 0.0f;
-      if (j < T) {
-        lo = fminf(lo, tj[t]);
-        hi = fmaxf(hi, tj[t]);
-      }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      lo = fminf(lo, __shfl_xor(lo, o));
-      hi = fmaxf(hi, __shfl_xor(hi, o));
-    }
-    soft_sat_bounds(lo, hi, kneg_, sat_lo, sat_hi);
-  }
-  // Lane i < n forms its entry; the entries that have to be evaluated are packed into the stage
-  // and counted (the return value).  A dropped entry whose sigmoids are all 1 adds its c to
-  // *csat, one whose sigmoids are all 0 adds nothing; neither has a derivative above 2^-64 lambda.
-  // save_to (may be null): room for the n entries, every one of them, as the backward pass wants them.
-  __device__ __forceinline__ int park(int n, float v, int c, unsigned inpl, unsigned zrel, float* csat,
-                                      SavedEntry* save_to = nullptr) const {
+  int64_t plane;       // H * W
+  int ox, oy, oz;      // origin of the wave's unit: coordinates are summed relative to it
+  Soft3Staged* stage;  // wave-private LDS, 64 entries
+  SoftEval<3, CHI, DERIV, GRADX, STRIDE> eval;
+  float* gx;           // GRADX: grad_X of this item or null
+  float lambda;
+  SavedEntry* list;     // SAVE: this unit's list
+  unsigned cap, saved;  // saved: entries seen so far (wave-uniform; may pass cap)
+
+  // lane i < n forms its entry; the entries that have to be evaluated are packed into the stage
+  __device__ __forceinline__ void take(int n, float v, int ci, unsigned inpl, unsigned zrel) {
     const int lane = threadIdx.x & (kWave - 1);
     const bool in = lane < n;
-    Soft3Entry e;
-    e.yy = (int)(inpl / (unsigned)W);
-    e.x = (int)(inpl - (unsigned)e.yy * (unsigned)W);
-    e.z = oz + (int)zrel;
-    const double y = (double)v + alpha * ((ux * (double)e.x + uy * (double)e.yy) + uz * (double)e.z);
+    const int yy = (int)(inpl / (unsigned)W), x = (int)(inpl - (unsigned)yy * (unsigned)W), z = oz + (int)zrel;
+    const double y = (double)v + alpha * ((ux * (double)x + uy * (double)yy) + uz * (double)z);
+    Soft3Staged e;
     e.yh = (float)y;
     e.yl = (float)(y - (double)e.yh);
-    e.c = (float)c;
+    e.c = (float)ci;
     e.inpl = inpl;
-    e.pad = 0;
-    if (save_to && in) {
-      SavedEntry o;
-      o.y = y;
-      o.idx = (int)((int64_t)e.z * plane + inpl);
-      o.c = c;
-      save_to[lane] = o;
-    }
-    const bool keep = in && e.yh > sat_lo && e.yh < sat_hi;
-    const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
-    const int kept = __builtin_popcountll(m);
-    if (kept != n && csat) {  // wave-uniform
-      const float ones = wave_sum_lane63((in && e.yh <= sat_lo) ? e.c : 0.0f);
-      *csat += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ones), kWave - 1));
-    }
-    const int pos = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-    if (keep) stage[pos] = e;
-    return kept;
-  }
-  __device__ __forceinline__ float zarg(int t, float yh, float yl) const { return (tj[t] - yh) - yl; }
-};
-
-struct Soft3FwdSink : Soft3Common {
-  float acc[kSoft3TL];
-  float csat;  // sum of c over the entries whose sigmoids are all 1 (wave-uniform)
-  __device__ __forceinline__ void take(int n, float v, int c, unsigned inpl, unsigned zrel) {
-    n = park(n, v, c, inpl, zrel, &csat);
-    for (int e = 0; e < n; ++e) {
-      const float yh = stage[e].yh, yl = stage[e].yl;
-      const float cf = stage[e].c;
-#pragma unroll
-      for (int t = 0; t < kSoft3TL; ++t) {
-        if (t < nt) {  // wave-uniform
-          const float ex = soft_exp_neg(zarg(t, yh, yl), kneg);
-          acc[t] += cf * __builtin_amdgcn_rcpf(1.0f + ex);
-        }
+    e.rx = (float)(x - ox);
+    e.ry = (float)(yy - oy);
+    e.rz = (float)(z - oz);
+    e.zrel = zrel;
+    if constexpr (SAVE) {
+      if (in && saved + (unsigned)n <= cap) {  // (a batch that does not fit is left out whole)
+        SavedEntry o;
+        o.y = y;
+        o.idx = (int)((int64_t)z * plane + inpl);
+        o.c = ci;
+        list[saved + lane] = o;
       }
+      saved += (unsigned)n;
     }
-  }
-  __device__ __forceinline__ float total(int t) const { return acc[t] + csat; }
-};
-
-struct Soft3BwdSink : Soft3Common {
-  float a0[kSoft3TL], ax[kSoft3TL], ay[kSoft3TL], az[kSoft3TL];
-  float gj[kSoft3TL];  // upstream gradient at this lane's thresholds (0 beyond T)
-  float* gx;           // grad_X of this item or null
-  int ox, oy;          // origin of the wave's unit (with oz): coordinates are summed relative to it
-  float lambda;
-  __device__ __forceinline__ void take(int n, float v, int c, unsigned inpl, unsigned zrel) {
-    n = park(n, v, c, inpl, zrel, nullptr);  // grad_X stays 0 at a saturated vertex
-    const int lane = threadIdx.x & (kWave - 1);
-    for (int e = 0; e < n; ++e) {
-      const Soft3Entry en = stage[e];
-      const float rx = (float)(en.x - ox), ry = (float)(en.yy - oy), rz = (float)(en.z - oz);
-      float gd = 0.0f;
-#pragma unroll
-      for (int t = 0; t < kSoft3TL; ++t) {
-        if (t < nt) {  // wave-uniform
-          const float ex = soft_exp_neg(zarg(t, en.yh, en.yl), kneg);
-          const float s = __builtin_amdgcn_rcpf(1.0f + ex);
-          const float d = ex * s * s;  // sigma (1 - sigma)
-          const float cd = en.c * d;
-          a0[t] += cd;
-          ax[t] += cd * rx;
-          ay[t] += cd * ry;
-          az[t] += cd * rz;
-          gd += gj[t] * d;
-        }
-      }
-      if (gx) {  // wave-uniform
-        gd = wave_sum_lane63(gd);
-        if (lane == kWave - 1) gx[(int64_t)en.z * plane + en.inpl] = -lambda * en.c * gd;
+    float csat;
+    int pos;
+    n = pack_entries(in && e.yh > sat_lo && e.yh < sat_hi, in && e.yh <= sat_lo, e.c, n, csat, pos);
+    if (in && e.yh > sat_lo && e.yh < sat_hi) stage[pos] = e;
+    if (!CHI) csat = 0.0f;  // (grad_X stays 0 at a saturated vertex)
+    if (n == 0 && csat == 0.0f) return;
+    const Soft3Staged* st = stage;
+    const float g = eval.template run<kSoft3Slots>(n, csat, [st](int i, StagedValue& o, float (&r)[3]) {
+      const Soft3Staged s = st[i];
+      o.yh = s.yh;
+      o.yl = s.yl;
+      o.c = s.c;
+      r[0] = s.rx;
+      r[1] = s.ry;
+      r[2] = s.rz;
+    });
+    if constexpr (GRADX) {
+      if (gx && lane < n) {
+        const Soft3Staged s = stage[lane];
+        gx[(int64_t)(oz + (int)s.zrel) * plane + s.inpl] = -lambda * s.c * g;
       }
     }
   }
 };
 
 // LDS of a block: exchange words, [4 waves] queue entries and tilts, [4 waves] stages
-constexpr size_t kSoft3Lds = kFixedLds3d + (size_t)4 * kWave * sizeof(Soft3Entry);
+constexpr size_t kSoft3Lds = kFixedLds3d + (size_t)4 * kWave * sizeof(Soft3Staged);
 
-template <typename Sink>
-__device__ __forceinline__ void soft3_lds(int* smem, unsigned*& xch, s3::TubeQueue<Sink>& queue, Soft3Entry*& stage) {
+// The sweep of a wave with sink `queue.sink`, whose own fields the kernels below have set; partial (may be null):
+// rows of STRIDE floats a threshold, one row a unit.  TILTC: the sweep runs on the tilted field, so c(p) is that
+// field's coefficient.
+template <bool TILTC, int STRIDE, typename Sink>
+__device__ __forceinline__ void soft3d_sweep(s3::TubeQueue<Sink>& queue, const float* __restrict__ grid, int D, int H,
+                                             int W, int64_t N, int nstrip, int ngroup, int nseg, int planes_per_seg,
+                                             const float* u, float alpha, const float* tau, int T, float kneg,
+                                             const float* gup, float* partial) {
+  extern __shared__ int smem[];
   const int wv = threadIdx.x >> 6;
-  xch = reinterpret_cast<unsigned*>(smem);
+  unsigned* xch = reinterpret_cast<unsigned*>(smem);
   queue.buf = reinterpret_cast<uint2*>(smem + kXchInts) + wv * kQueueCap;
   queue.tbuf = reinterpret_cast<float*>(smem + kXchInts + 4 * kQueueCap * 2) + wv * kQueueCap;
   queue.count = 0;
-  stage = reinterpret_cast<Soft3Entry*>(smem + kXchInts + 4 * kQueueCap * 3) + wv * kWave;
-}
-
-// partial[(item * units + unit) * T + j]
-// TILTC: the sweep runs on the tilted field, so c(p) is that field's coefficient
-template <bool TILTC>
-__global__ __launch_bounds__(256) void soft3d_fwd_kernel(const float* __restrict__ grid, int D, int H, int W,
-                                                         int64_t N, int nstrip, int ngroup, int nseg,
-                                                         int planes_per_seg, const float* __restrict__ u,
-                                                         float alpha, const float* __restrict__ tau, int T,
-                                                         float kneg, float* __restrict__ partial) {
-  extern __shared__ int smem[];
-  unsigned* xch;
-  Soft3Entry* stage;
-  s3::TubeQueue<Soft3FwdSink> queue;
-  soft3_lds(smem, xch, queue, stage);
-  queue.sink.init(u, alpha, tau, T, kneg, H, W, stage);
-#pragma unroll
-  for (int t = 0; t < kSoft3TL; ++t) queue.sink.acc[t] = 0.f;
-  queue.sink.csat = 0.f;
-  const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int ox, oy;
-  unit_origin3(unit, D, H, W, gridDim.y, planes_per_seg, kRows3d, ox, oy, queue.sink.oz);
+  Sink& s = queue.sink;
+  s.stage = reinterpret_cast<Soft3Staged*>(smem + kXchInts + 4 * kQueueCap * 3) + wv * kWave;
+  s.ux = (double)u[0];
+  s.uy = (double)u[1];
+  s.uz = (double)u[2];
+  s.alpha = (double)alpha;
+  float lo, hi;
+  threshold_span(tau, T, lo, hi);
+  soft_sat_bounds(lo, hi, kneg, s.sat_lo, s.sat_hi);
+  s.W = W;
+  s.plane = (int64_t)H * W;
+  const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wv), units = gridDim.x * 4;
+  unit_origin3(unit, D, H, W, gridDim.y, planes_per_seg, kRows3d, s.ox, s.oy, s.oz);
+  s.eval.init(tau, T, kneg, gup ? gup + (int64_t)blockIdx.y * T : nullptr,
+              partial ? partial + ((int64_t)blockIdx.y * units + unit) * (int64_t)T * STRIDE : nullptr);
   WaveRange range;
   const float* g = grid + (int64_t)blockIdx.y * N;
   if constexpr (TILTC) {
@@ -210,152 +141,55 @@ __global__ __launch_bounds__(256) void soft3d_fwd_kernel(const float* __restrict
   } else {
     sweep3d_wave<float, kRows3d>(g, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, queue, xch, range, NoTilt());
   }
-  const int units = gridDim.x * 4;
-  float* out = partial + ((int64_t)blockIdx.y * units + unit) * T;
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int t = 0; t < kSoft3TL; ++t) {
-    const int j = lane + kWave * t;
-    if (j < T) out[j] = queue.sink.total(t);
-  }
+  s.eval.finish();
+}
+
+// partial[(item * units + unit) * T + j]
+template <bool TILTC>
+__global__ __launch_bounds__(256, kSoft3Waves) void soft3d_fwd_kernel(const float* __restrict__ grid, int D, int H, int W,
+                                                            int64_t N, int nstrip, int ngroup, int nseg,
+                                                            int planes_per_seg, const float* __restrict__ u,
+                                                            float alpha, const float* __restrict__ tau, int T,
+                                                            float kneg, float* __restrict__ partial) {
+  s3::TubeQueue<Soft3Sink<true, false, false, false, 1>> queue;
+  soft3d_sweep<TILTC, 1>(queue, grid, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, u, alpha, tau, T, kneg, nullptr,
+                         partial);
 }
 
 // partial[((item * units + unit) * T + j) * 4 + {0: A0, 1: Ax, 2: Ay, 3: Az}]
 template <bool TILTC>
-__global__ __launch_bounds__(256) void soft3d_bwd_kernel(const float* __restrict__ grid, int D, int H, int W,
-                                                         int64_t N, int nstrip, int ngroup, int nseg,
-                                                         int planes_per_seg, const float* __restrict__ u,
-                                                         float alpha, const float* __restrict__ tau, int T,
-                                                         float kneg, float lambda, const float* __restrict__ gup,
-                                                         float* __restrict__ grad_X, float* __restrict__ partial) {
-  extern __shared__ int smem[];
-  unsigned* xch;
-  Soft3Entry* stage;
-  s3::TubeQueue<Soft3BwdSink> queue;
-  soft3_lds(smem, xch, queue, stage);
-  Soft3BwdSink& s = queue.sink;
-  s.init(u, alpha, tau, T, kneg, H, W, stage);
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int t = 0; t < kSoft3TL; ++t) {
-    s.a0[t] = s.ax[t] = s.ay[t] = s.az[t] = 0.f;
-    const int j = lane + kWave * t;
-    s.gj[t] = j < T ? (gup ? gup[(int64_t)blockIdx.y * T + j] : 1.0f) : 0.0f;
-  }
-  s.gx = grad_X ? grad_X + (int64_t)blockIdx.y * N : nullptr;
-  s.lambda = lambda;
-  const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  unit_origin3(unit, D, H, W, gridDim.y, planes_per_seg, kRows3d, s.ox, s.oy, s.oz);
-  WaveRange range;
-  const float* g = grid + (int64_t)blockIdx.y * N;
-  if constexpr (TILTC) {
-    const DirArgs da = {u, alpha, 1, 3};
-    const Tilt t = load_tilt(da, 0);
-    TiltRaw tr;
-    tr.ax = t.ax, tr.ay = t.ay, tr.az = t.az;
-    sweep3d_wave<float, kRows3d>(g, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, queue, xch, range, tr);
-  } else {
-    sweep3d_wave<float, kRows3d>(g, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, queue, xch, range, NoTilt());
-  }
-  if (partial) {
-    const int units = gridDim.x * 4;
-    float4* out = reinterpret_cast<float4*>(partial) + ((int64_t)blockIdx.y * units + unit) * (int64_t)T;
-#pragma unroll
-    for (int t = 0; t < kSoft3TL; ++t) {
-      const int j = lane + kWave * t;
-      if (j < T) out[j] = make_float4(s.a0[t], s.ax[t], s.ay[t], s.az[t]);
-    }
-  }
+__global__ __launch_bounds__(256, kSoft3Waves) void soft3d_bwd_kernel(const float* __restrict__ grid, int D, int H, int W,
+                                                            int64_t N, int nstrip, int ngroup, int nseg,
+                                                            int planes_per_seg, const float* __restrict__ u,
+                                                            float alpha, const float* __restrict__ tau, int T,
+                                                            float kneg, float lambda, const float* __restrict__ gup,
+                                                            float* __restrict__ grad_X, float* __restrict__ partial) {
+  s3::TubeQueue<Soft3Sink<false, true, true, false, 4>> queue;
+  queue.sink.gx = grad_X ? grad_X + (int64_t)blockIdx.y * N : nullptr;
+  queue.sink.lambda = lambda;
+  soft3d_sweep<TILTC, 4>(queue, grid, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, u, alpha, tau, T, kneg, gup,
+                         partial);
 }
 
-// Forward pass that saves its critical vertices: chi as Soft3FwdSink, optionally the sums of
-// Eq. 9 / Eq. 10 in the same pass (they share the sigmoid), and every entry appended to the
-// unit's own list in the state buffer (sweep order, no atomics: the same on every run).
-template <bool DERIV>
-struct Soft3SaveSink : Soft3Common {
-  float acc[kSoft3TL], a0[kSoft3TL], ax[kSoft3TL], ay[kSoft3TL], az[kSoft3TL];
-  float csat;
-  int ox, oy;
-  SavedEntry* list;     // this unit's list
-  unsigned cap, saved;  // saved: entries seen so far (wave-uniform; may pass cap)
-  __device__ __forceinline__ void take(int n, float v, int c, unsigned inpl, unsigned zrel) {
-    const bool room = saved + (unsigned)n <= cap;  // (a batch that does not fit is left out whole)
-    const unsigned at = saved;
-    saved += (unsigned)n;
-    n = park(n, v, c, inpl, zrel, &csat, room ? list + at : nullptr);
-    for (int e = 0; e < n; ++e) {
-      const Soft3Entry en = stage[e];
-      const float rx = (float)(en.x - ox), ry = (float)(en.yy - oy), rz = (float)(en.z - oz);
-#pragma unroll
-      for (int t = 0; t < kSoft3TL; ++t) {
-        if (t < nt) {  // wave-uniform
-          const float ex = soft_exp_neg(zarg(t, en.yh, en.yl), kneg);
-          const float sg = __builtin_amdgcn_rcpf(1.0f + ex);
-          acc[t] += en.c * sg;
-          if (DERIV) {
-            const float cd = en.c * (ex * sg * sg);  // c sigma (1 - sigma)
-            a0[t] += cd;
-            ax[t] += cd * rx;
-            ay[t] += cd * ry;
-            az[t] += cd * rz;
-          }
-        }
-      }
-    }
-  }
-};
-
+// Forward pass that saves its critical vertices: chi as soft3d_fwd_kernel, with DERIV the sums of Eq. 9 / Eq. 10 in
+// the same pass (they share the sigmoid), and the unit's list.
 // partial[((item * units + unit) * T + j) * 5 + {0: chi, 1: A0, 2: Ax, 3: Ay, 4: Az}]
 template <bool TILTC, bool DERIV>
-__global__ __launch_bounds__(256) void soft3d_fwd_save_kernel(const float* __restrict__ grid, int D, int H, int W,
-                                                              int64_t N, int nstrip, int ngroup, int nseg,
-                                                              int planes_per_seg, const float* __restrict__ u,
-                                                              float alpha, const float* __restrict__ tau, int T,
-                                                              float kneg, float* __restrict__ partial, StateView sv,
-                                                              unsigned cap) {
-  extern __shared__ int smem[];
-  unsigned* xch;
-  Soft3Entry* stage;
-  s3::TubeQueue<Soft3SaveSink<DERIV>> queue;
-  soft3_lds(smem, xch, queue, stage);
-  Soft3SaveSink<DERIV>& s = queue.sink;
-  s.init(u, alpha, tau, T, kneg, H, W, stage);
-#pragma unroll
-  for (int t = 0; t < kSoft3TL; ++t) s.acc[t] = s.a0[t] = s.ax[t] = s.ay[t] = s.az[t] = 0.f;
-  s.csat = 0.f;
+__global__ __launch_bounds__(256, kSoft3Waves) void soft3d_fwd_save_kernel(
+    const float* __restrict__ grid, int D, int H, int W, int64_t N, int nstrip, int ngroup, int nseg, int planes_per_seg,
+    const float* __restrict__ u, float alpha, const float* __restrict__ tau, int T, float kneg,
+    float* __restrict__ partial, StateView sv, unsigned cap) {
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), units = gridDim.x * 4;
-  unit_origin3(unit, D, H, W, gridDim.y, planes_per_seg, kRows3d, s.ox, s.oy, s.oz);
-  s.cap = cap;
-  s.saved = 0u;
-  s.list = sv.lists + ((size_t)blockIdx.y * units + unit) * cap;
+  s3::TubeQueue<Soft3Sink<true, DERIV, false, true, 5>> queue;
+  queue.sink.cap = cap;
+  queue.sink.saved = 0u;
+  queue.sink.list = sv.lists + ((size_t)blockIdx.y * units + unit) * cap;
   const unsigned next_gen = *sv.gen + 1u;  // (the reduction kernel that follows stores it)
-  WaveRange range;
-  const float* g = grid + (int64_t)blockIdx.y * N;
-  if constexpr (TILTC) {
-    const DirArgs da = {u, alpha, 1, 3};
-    const Tilt t = load_tilt(da, 0);
-    TiltRaw tr;
-    tr.ax = t.ax, tr.ay = t.ay, tr.az = t.az;
-    sweep3d_wave<float, kRows3d>(g, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, queue, xch, range, tr);
-  } else {
-    sweep3d_wave<float, kRows3d>(g, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, queue, xch, range, NoTilt());
-  }
-  const int lane = threadIdx.x & (kWave - 1);
-  if (lane == 0) {
-    sv.counts[(size_t)blockIdx.y * units + unit] = s.saved;
-    if (s.saved > cap) sv.overflow[blockIdx.y] = next_gen;
-  }
-  float* out = partial + ((int64_t)blockIdx.y * units + unit) * (int64_t)T * 5;
-#pragma unroll
-  for (int t = 0; t < kSoft3TL; ++t) {
-    const int j = lane + kWave * t;
-    if (j < T) {
-      out[j * 5 + 0] = s.acc[t] + s.csat;
-      out[j * 5 + 1] = s.a0[t];
-      out[j * 5 + 2] = s.ax[t];
-      out[j * 5 + 3] = s.ay[t];
-      out[j * 5 + 4] = s.az[t];
-    }
+  soft3d_sweep<TILTC, 5>(queue, grid, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, u, alpha, tau, T, kneg, nullptr,
+                         partial);
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    sv.counts[(size_t)blockIdx.y * units + unit] = queue.sink.saved;
+    if (queue.sink.saved > cap) sv.overflow[blockIdx.y] = next_gen;
   }
 }
 
@@ -372,8 +206,8 @@ __global__ __launch_bounds__(256) void soft3d_bwd_saved_kernel(const float* __re
                                                                SoftStateHeader expect) {
   const int item = blockIdx.y, unit = blockIdx.x, units = gridDim.x;
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
-  __shared__ float stau[kSoft3TL * kWave];
-  __shared__ float sg[kSoft3TL * kWave];
+  extern __shared__ float stau[];  // [T] thresholds, [T] upstream gradient
+  float* const sg = stau + T;
   __shared__ StagedEntry stage[256];
   __shared__ float sred[2][4];
   __shared__ int skept[4];
@@ -448,7 +282,7 @@ static Origin3 origin3(const Shape& s, const Plan3d& pl) {
 static float kneg3d(float lambda) { return (float)(-(double)lambda * 1.4426950408889634); }
 
 bool soft3d_supported(const Shape& s, int T) {
-  return s.ndim == 3 && T <= kSoft3TL * kWave && sweep3d_supported(s, 1);
+  return s.ndim == 3 && T >= 1 && sweep3d_supported(s, 1);
 }
 
 // per-unit partial sums (up to five floats per unit and threshold), a multiple of 256 bytes
@@ -460,7 +294,7 @@ static size_t soft3d_partial_bytes(const Shape& s, const Plan3d& pl, int T) {
 size_t soft3d_workspace_bytes(const Shape& s, int T) {
   if (!soft3d_supported(s, T)) return 0;
   const Plan3d pl = plan3d<float>(s);
-  return (size_t)256 + soft3d_partial_bytes(s, pl, T) + soft_reduce_mid_bytes(s.batch, T);
+  return (size_t)256 + soft3d_partial_bytes(s, pl, T) + soft_reduce_mid_bytes((int)pl.grid.x * 4, s.batch, T);
 }
 
 void launch_soft3d_fwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
@@ -557,11 +391,12 @@ void launch_soft3d_bwd_saved(const float* grid, const Shape& s, const float* u, 
   const StateView sv = state_view(const_cast<void*>(state), s.batch, (size_t)expect.units);
   launch_clear_f32(grad_X, s.N * s.batch, st);  // zero away from the critical vertices
   const dim3 g((unsigned)expect.units, (unsigned)s.batch);
+  const size_t lds = (size_t)T * 2 * sizeof(float);
   if (tiltc)
-    hipLaunchKernelGGL(soft3d_bwd_saved_kernel<true>, g, dim3(256), 0, st, grid, (int)s.D, (int)s.H, (int)s.W, s.N, u,
+    hipLaunchKernelGGL(soft3d_bwd_saved_kernel<true>, g, dim3(256), lds, st, grid, (int)s.D, (int)s.H, (int)s.W, s.N, u,
                        alpha, tau, T, kneg3d(lambda), lambda, gup, grad_X, sv, expect);
   else
-    hipLaunchKernelGGL(soft3d_bwd_saved_kernel<false>, g, dim3(256), 0, st, grid, (int)s.D, (int)s.H, (int)s.W, s.N, u,
+    hipLaunchKernelGGL(soft3d_bwd_saved_kernel<false>, g, dim3(256), lds, st, grid, (int)s.D, (int)s.H, (int)s.W, s.N, u,
                        alpha, tau, T, kneg3d(lambda), lambda, gup, grad_X, sv, expect);
 }
 

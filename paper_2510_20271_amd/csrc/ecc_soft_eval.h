@@ -1,0 +1,163 @@
+// Soft ECC: evaluation of a drained batch of critical vertices against the thresholds, shared by the sinks of
+// the strip (2D) and the tube (3D) sweep.
+//
+// A wave calls it with up to 64 entries, threshold-major: lane l takes the thresholds l, l + 64, ... one or two
+// at a time and runs over the entries, so that the sums over p of Eq. 6 / Eq. 9 / Eq. 10 of the paper need no
+// cross-lane reduction; the contraction of Eq. 8 with the upstream gradient is a fixed-order sum over the lanes.
+//
+// The running sums live in the unit's own row of partial sums in the workspace and not in registers: a batch
+// starts from them and puts them back (the first one of a unit starts from zero; most units have one or two).
+// Registers held across the sweep were what limited it: sums, thresholds and upstream gradient of four
+// thresholds a lane took the 3D kernels from 124 to 162 .. 204 vector registers (three or two waves on a SIMD
+// instead of four) and tied the path to 256 thresholds.  256^3 with 64 thresholds: forward sweep 43 -> 37 us,
+// backward 55 -> 42 us.  Any number of thresholds runs here: 16 x 217 x 181 with 512, which took 37 + 56 + 56 us in
+// the tile kernels of ecc_soft.hip, takes 92 us forward (derivatives included) and 25 us backward.
+#pragma once
+#include "ecc_device.h"
+
+namespace ecc {
+
+// z = (tau_j - yh) - yl is the float64 difference tau_j - y to within an ulp of z
+struct StagedValue {
+  float yh, yl, c;
+};
+
+// NC: coordinates; CHI / DERIV: which sums a row holds, {chi} {A0, A_1 .. A_NC} in this order, STRIDE floats a
+// threshold; GRADX: the contraction with the upstream gradient
+template <int NC, bool CHI, bool DERIV, bool GRADX, int STRIDE>
+struct SoftEval {
+  static constexpr int kA = CHI ? 1 : 0, kSums = kA + (DERIV ? 1 + NC : 0);
+  const float* tau;
+  const float* gup;  // this item's upstream gradient, or null for all ones
+  float* row;        // this unit's sums, or null
+  int T;
+  float kneg;
+  bool started;      // the row holds sums
+
+  __device__ __forceinline__ void init(const float* tau_, int T_, float kneg_, const float* gup_, float* row_) {
+    tau = tau_;
+    T = T_;
+    kneg = kneg_;
+    gup = gup_;
+    row = row_;
+    started = false;
+  }
+  __device__ __forceinline__ void store(int j, const float (&a)[kSums > 0 ? kSums : 1]) const {
+    float* p = row + (int64_t)j * STRIDE;
+    if constexpr (STRIDE == 4) {
+      *reinterpret_cast<float4*>(p) = make_float4(a[0], kSums > 1 ? a[kSums > 1 ? 1 : 0] : 0.f,
+                                                  kSums > 2 ? a[kSums > 2 ? 2 : 0] : 0.f,
+                                                  kSums > 3 ? a[kSums > 3 ? 3 : 0] : 0.f);
+    } else {
+#pragma unroll
+      for (int k = 0; k < kSums; ++k) p[k] = a[k];
+      if constexpr (kSums < STRIDE) {
+#pragma unroll
+        for (int k = kSums; k < STRIDE; ++k) p[k] = 0.f;
+      }
+    }
+  }
+  // S slots of 64 thresholds from slot t0 on; get(e, v, r): value and coordinates (relative to the unit's origin)
+  // of entry e; returns the lanes' share: lane e < n holds its entry's contraction over these slots
+  template <int S, typename Get>
+  __device__ __forceinline__ float slots(int t0, int n, float csat, const Get& get) const {
+    const int lane = threadIdx.x & (kWave - 1);
+    float tj[S], gj[S], acc[S][kSums > 0 ? kSums : 1];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int j = lane + kWave * (t0 + s);
+      const bool ok = j < T;
+      tj[s] = ok ? tau[j] : 0.0f;
+      if (GRADX) gj[s] = ok ? (gup ? gup[j] : 1.0f) : 0.0f;
+#pragma unroll
+      for (int k = 0; k < kSums; ++k) acc[s][k] = (started && ok && row) ? row[(int64_t)j * STRIDE + k] : 0.0f;
+      if (CHI) acc[s][0] += csat;
+    }
+    float mine = 0.0f;
+    for (int e = 0; e < n; ++e) {
+      StagedValue v;
+      float r[NC];
+      get(e, v, r);
+      float gd = 0.0f;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const float ex = soft_exp_neg((tj[s] - v.yh) - v.yl, kneg);
+        const float sg = __builtin_amdgcn_rcpf(1.0f + ex);
+        if constexpr (CHI) acc[s][0] += v.c * sg;
+        if constexpr (DERIV || GRADX) {
+          const float d = ex * sg * sg;  // sigma (1 - sigma)
+          if constexpr (DERIV) {
+            const float cd = v.c * d;
+            acc[s][kA] += cd;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) acc[s][kA + 1 + k] += cd * r[k];
+          }
+          if constexpr (GRADX) gd += gj[s] * d;
+        }
+      }
+      if constexpr (GRADX) {
+        gd = wave_sum_lane63(gd);
+        gd = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, gd), kWave - 1));
+        mine += lane == e ? gd : 0.0f;
+      }
+    }
+    if (row) {  // wave-uniform
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const int j = lane + kWave * (t0 + s);
+        if (j < T) store(j, acc[s]);
+      }
+    }
+    return mine;
+  }
+  // SLOTS: slots taken together (two share the reads of an entry; one where registers are short)
+  template <int SLOTS, typename Get>
+  __device__ __forceinline__ float run(int n, float csat, const Get& get) {
+    const int nt = (T + kWave - 1) / kWave;
+    float mine = 0.0f;
+    int t = 0;
+    if constexpr (SLOTS == 2)
+      for (; t + 2 <= nt; t += 2) mine += slots<2>(t, n, csat, get);
+    for (; t < nt; ++t) mine += slots<1>(t, n, csat, get);
+    started = true;
+    return mine;
+  }
+  // a unit without entries leaves zeros
+  __device__ __forceinline__ void finish() const {
+    if (!row || started) return;  // wave-uniform
+    const float zero[kSums > 0 ? kSums : 1] = {};
+    for (int j = threadIdx.x & (kWave - 1); j < T; j += kWave) store(j, zero);
+  }
+};
+
+// least and greatest threshold, by the whole wave
+__device__ __forceinline__ void threshold_span(const float* tau, int T, float& lo, float& hi) {
+  lo = INFINITY;
+  hi = -INFINITY;
+  for (int j = threadIdx.x & (kWave - 1); j < T; j += kWave) {
+    const float t = tau[j];
+    lo = fminf(lo, t);
+    hi = fmaxf(hi, t);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = fminf(lo, __shfl_xor(lo, o));
+    hi = fmaxf(hi, __shfl_xor(hi, o));
+  }
+}
+
+// Lanes with `keep` get consecutive positions; *csat receives the sum of c over the lanes with `ones` (dropped
+// entries whose sigmoids are all 1).  Returns the number of kept entries, `pos` the lane's position.
+__device__ __forceinline__ int pack_entries(bool keep, bool ones, float c, int n, float& csat, int& pos) {
+  const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
+  const int kept = __builtin_popcountll(m);
+  csat = 0.0f;
+  if (kept != n) {  // wave-uniform
+    const float sum = wave_sum_lane63(ones ? c : 0.0f);
+    csat = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sum), kWave - 1));
+  }
+  pos = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+  return kept;
+}
+
+}  // namespace ecc

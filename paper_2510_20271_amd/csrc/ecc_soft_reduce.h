@@ -134,19 +134,25 @@ __global__ __launch_bounds__(kRedWaves * kWave) void soft_reduce_final_kernel(co
   }
 }
 
+// slices the units are split into (about 64 units per slice at least), and units per slice
+static inline int soft_reduce_slices(int units, int& per) {
+  int slices = units / (4 * kRedWaves);
+  slices = slices < 1 ? 1 : (slices > kRedSlices ? kRedSlices : slices);
+  per = (units + slices - 1) / slices;
+  return (units + per - 1) / per;
+}
 // bytes of `mid` for a batch and T thresholds (the most any of the reductions needs)
-static inline size_t soft_reduce_mid_bytes(int64_t batch, int T) {
-  return (size_t)batch * kRedSlices * (size_t)T * kRedMaxSums * sizeof(double);
+static inline size_t soft_reduce_mid_bytes(int units, int64_t batch, int T) {
+  int per;
+  const int slices = soft_reduce_slices(units, per);
+  return slices > 1 ? (size_t)batch * slices * (size_t)T * kRedMaxSums * sizeof(double) : 0;
 }
 
 template <int STRIDE, bool CHI, int NC, typename Origin>
 static void launch_soft_reduce(const float* partial, double* mid, int units, int64_t batch, int T, float alpha,
                                float lambda, const Origin& origin, const RedOut& out, hipStream_t st) {
-  // slices the units are split into (about 64 units per slice at least), and units per slice
-  int slices = units / (4 * kRedWaves);
-  slices = slices < 1 ? 1 : (slices > kRedSlices ? kRedSlices : slices);
-  const int per = (units + slices - 1) / slices;
-  slices = (units + per - 1) / per;
+  int per;
+  const int slices = soft_reduce_slices(units, per);
   const unsigned tg = (unsigned)((T + kWave - 1) / kWave);
   hipLaunchKernelGGL((soft_reduce_kernel<STRIDE, CHI, NC, Origin>), dim3(tg, (unsigned)batch, (unsigned)slices),
                      dim3(kRedWaves * kWave), 0, st, partial, units, per, T, alpha, lambda, origin, mid, out);

@@ -515,6 +515,7 @@ static Plan2d plan2d(const Shape& s, bool sigmoid_sinks = false) {
   const int64_t row_bytes = (int64_t)W * (int64_t)sizeof(T);
   const int64_t cap = ((((int64_t)1 << 31) / row_bytes - 16) / kChunkRows) * kChunkRows;
   if (rows > cap) rows = cap;
+  if (rows > (1 << 20)) rows = 1 << 20;  // (what the sigmoid sinks' queue entries hold)
   p.rows_per_seg = (int)rows;
   p.nseg = (int)((H + p.rows_per_seg - 1) / p.rows_per_seg);
   const int units = p.nstrip * p.nseg;

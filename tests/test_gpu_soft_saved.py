@@ -194,3 +194,24 @@ def test_saved_state_3d_is_deterministic_and_agrees_with_the_stateless_pass():
     got = api.ecc_soft_bwd_saved(g, 3, ud, 0.01, td, 20.0, a[3])
     for i in range(2):
         _close(host(got)[i], host(ref)[i], 1e-3, "grad_X")
+
+
+@pytest.mark.parametrize("T", [128, 129, 257, 512, 1100])
+@pytest.mark.parametrize("shape,field", [((40, 300), "smooth"), ((21, 33), "noise"), ((13, 20, 70), "smooth"),
+                                         ((9, 10, 12), "noise")])
+def test_threshold_counts_around_the_wave_and_rows_of_several_batches(shape, field, T):
+    # noise: several batches of 64 entries a unit, so that its row of sums is taken up again
+    nd = len(shape)
+    X = synth.grf(shape, 1.5, 77) if field == "smooth" else np.random.default_rng(8).standard_normal(shape)
+    Xb = np.stack([X]).astype(np.float32)
+    u = np.array([0.6, -0.8] if nd == 2 else [0.48, -0.6, 0.64], np.float32)
+    tau = np.linspace(Xb.min() - 0.1, Xb.max() + 0.3, T).astype(np.float32)
+    G = np.random.default_rng(T).standard_normal((1, T)).astype(np.float32)
+    for tilted in (False, True):
+        _case(Xb, u, np.float32(0.02), tau, np.float32(6.0), G, tilted=tilted)
+    g, ud, td = dev(Xb), dev(u), dev(tau)  # the stateless backward pass forms the same three derivatives
+    a = api.ecc_soft_bwd(g, nd, ud, 0.02, td, 6.0, grad_chi=dev(G))
+    rgx, rdt, rdu = O.soft_bwd_batch(Xb, u, np.float32(0.02), tau, np.float32(6.0), G)
+    _close(host(a[0])[0], rgx[0], 1e-3, "grad_X")
+    _close_sum(host(a[1])[0], rdt[0], 1e-3, "dchi_dtau")
+    _close_sum(host(a[2])[0], rdu[0], 1e-3, "dchi_du")
