@@ -72,8 +72,9 @@ struct SoftSink {
   __device__ __forceinline__ void zero_row(int row, int col, const bool (&ok)[kNC], bool out_lane) const {
     if (!gx || !out_lane) return;
     float* p = gx + (int64_t)row * W + col;
-    if (!EDGE && (reinterpret_cast<uintptr_t>(p) & 15) == 0) {
-      *reinterpret_cast<float4*>(p) = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (!EDGE) {
+      typedef float Four __attribute__((ext_vector_type(4), aligned(4)));  // (one store at any row alignment)
+      *reinterpret_cast<Four*>(p) = Four{0.f, 0.f, 0.f, 0.f};
     } else {
 #pragma unroll
       for (int e = 0; e < kNC; ++e)
