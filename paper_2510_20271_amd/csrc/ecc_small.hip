@@ -193,10 +193,15 @@ __global__ __launch_bounds__(BLOCK) void small_finish_kernel(const SmallHead* __
   __syncthreads();
   {
     unsigned kmin = 0xffffffffu, kmax = 0u;
-    for (unsigned b = tid; b < blocks; b += BLOCK) {
-      const SmallHead h = heads[b];
-      kmin = min(kmin, h.min_key);
-      kmax = max(kmax, h.max_key);
+    for (unsigned b0 = tid; b0 < blocks; b0 += 4 * BLOCK) {  // four heads requested together: one trip to memory
+      SmallHead h[4];
+#pragma unroll
+      for (unsigned q = 0; q < 4; ++q) h[q] = heads[min(b0 + q * BLOCK, blocks - 1u)];
+#pragma unroll
+      for (unsigned q = 0; q < 4; ++q) {
+        kmin = min(kmin, h[q].min_key);
+        kmax = max(kmax, h[q].max_key);
+      }
     }
     if (kmin <= kmax) {
       atomicMin(&s_min, kmin);
