@@ -170,8 +170,10 @@ __device__ __forceinline__ void soft2d_sweep(WaveQueue<Sink>& queue, const float
   s.col0 = (unit % nstrip) * kStripOut - kNC;
   s.row0 = (unit / nstrip) * rows_per_seg;
   const bool on = unit < units;
-  s.eval.init(tau, T, kneg, gup ? gup + (int64_t)blockIdx.y * T : nullptr,
-              on && partial ? partial + ((int64_t)blockIdx.y * units + unit) * (int64_t)T * STRIDE : nullptr);
+  int j0, nj;
+  soft_layer(T, j0, nj);
+  s.eval.init(tau + j0, nj, kneg, gup ? gup + (int64_t)blockIdx.y * T + j0 : nullptr,
+              on && partial ? partial + (((int64_t)blockIdx.y * units + unit) * (int64_t)T + j0) * STRIDE : nullptr);
   const float* g = grid + (int64_t)blockIdx.y * N;
   s.xsrc = TILTC ? g : nullptr;
   WaveRange range;
@@ -221,12 +223,12 @@ __global__ __launch_bounds__(256, 4) void soft2d_fwd_save_kernel(const float* __
                                                               float* __restrict__ partial, StateView sv, unsigned cap) {
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), units = nstrip * nseg;
   WaveQueue<SoftSink<true, DERIV, false, true, 4>> queue;
-  queue.sink.cap = cap;
+  queue.sink.cap = blockIdx.z == 0 ? cap : 0u;  // (the first layer keeps the list)
   queue.sink.saved = 0u;
   queue.sink.list = sv.lists + ((size_t)blockIdx.y * units + (unit < units ? unit : 0)) * cap;
   const unsigned next_gen = *sv.gen + 1u;  // (the reduction kernel that follows stores it)
   soft2d_sweep<TILTC, 4>(queue, grid, H, W, N, nstrip, nseg, rows_per_seg, u, alpha, tau, T, kneg, nullptr, partial);
-  if (unit < units && (threadIdx.x & (kWave - 1)) == 0) {
+  if (unit < units && blockIdx.z == 0 && (threadIdx.x & (kWave - 1)) == 0) {
     sv.counts[(size_t)blockIdx.y * units + unit] = queue.sink.saved;
     if (queue.sink.saved > cap) sv.overflow[blockIdx.y] = next_gen;
   }
@@ -365,16 +367,20 @@ size_t soft2d_workspace_bytes(const Shape& s, int T) {
   return (size_t)256 + soft2d_partial_bytes(s, pl, T) + soft_reduce_mid_bytes(pl.nstrip * pl.nseg, s.batch, T);
 }
 
+static dim3 layered(const Plan2d& pl, const Shape& s, int T) {
+  return dim3(pl.grid.x, pl.grid.y, soft_layers((int64_t)pl.nstrip * pl.nseg * s.batch, T));
+}
+
 void launch_soft2d_fwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau,
                        int T, float lambda, float* chi, void* ws, hipStream_t st, bool tiltc) {
   const Plan2d pl = plan2d<float>(s, true);
   float* partial = static_cast<float*>(ws);
   profile_mark(st, false);
   if (tiltc)
-    hipLaunchKernelGGL(soft2d_fwd_kernel<true>, pl.grid, dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, s.N,
+    hipLaunchKernelGGL(soft2d_fwd_kernel<true>, layered(pl, s, T), dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, s.N,
                        pl.nstrip, pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), partial);
   else
-    hipLaunchKernelGGL(soft2d_fwd_kernel<false>, pl.grid, dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, s.N,
+    hipLaunchKernelGGL(soft2d_fwd_kernel<false>, layered(pl, s, T), dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, s.N,
                        pl.nstrip, pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), partial);
   profile_mark(st, true);
   const RedOut out = {chi, nullptr, nullptr, nullptr, nullptr, {}};
@@ -430,7 +436,7 @@ void launch_soft2d_fwd_save(const float* grid, const Shape& s, const float* u, f
   const bool deriv = dtau || du;
   profile_mark(st, false);
 #define ECC_GO(TC, DV)                                                                                        \
-  hipLaunchKernelGGL((soft2d_fwd_save_kernel<TC, DV>), pl.grid, dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, \
+  hipLaunchKernelGGL((soft2d_fwd_save_kernel<TC, DV>), layered(pl, s, T), dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, \
                      s.N, pl.nstrip, pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), partial, sv, hdr.cap)
   if (tiltc) { if (deriv) ECC_GO(true, true); else ECC_GO(true, false); }
   else       { if (deriv) ECC_GO(false, true); else ECC_GO(false, false); }

@@ -128,8 +128,10 @@ __device__ __forceinline__ void soft3d_sweep(s3::TubeQueue<Sink>& queue, const f
   s.plane = (int64_t)H * W;
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wv), units = gridDim.x * 4;
   unit_origin3(unit, D, H, W, gridDim.y, planes_per_seg, kRows3d, s.ox, s.oy, s.oz);
-  s.eval.init(tau, T, kneg, gup ? gup + (int64_t)blockIdx.y * T : nullptr,
-              partial ? partial + ((int64_t)blockIdx.y * units + unit) * (int64_t)T * STRIDE : nullptr);
+  int j0, nj;
+  soft_layer(T, j0, nj);
+  s.eval.init(tau + j0, nj, kneg, gup ? gup + (int64_t)blockIdx.y * T + j0 : nullptr,
+              partial ? partial + (((int64_t)blockIdx.y * units + unit) * (int64_t)T + j0) * STRIDE : nullptr);
   WaveRange range;
   const float* g = grid + (int64_t)blockIdx.y * N;
   if constexpr (TILTC) {
@@ -181,13 +183,13 @@ __global__ __launch_bounds__(256, kSoft3Waves) void soft3d_fwd_save_kernel(
     float* __restrict__ partial, StateView sv, unsigned cap) {
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), units = gridDim.x * 4;
   s3::TubeQueue<Soft3Sink<true, DERIV, false, true, 5>> queue;
-  queue.sink.cap = cap;
+  queue.sink.cap = blockIdx.z == 0 ? cap : 0u;  // (the first layer keeps the list)
   queue.sink.saved = 0u;
   queue.sink.list = sv.lists + ((size_t)blockIdx.y * units + unit) * cap;
   const unsigned next_gen = *sv.gen + 1u;  // (the reduction kernel that follows stores it)
   soft3d_sweep<TILTC, 5>(queue, grid, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, u, alpha, tau, T, kneg, nullptr,
                          partial);
-  if ((threadIdx.x & (kWave - 1)) == 0) {
+  if (blockIdx.z == 0 && (threadIdx.x & (kWave - 1)) == 0) {
     sv.counts[(size_t)blockIdx.y * units + unit] = queue.sink.saved;
     if (queue.sink.saved > cap) sv.overflow[blockIdx.y] = next_gen;
   }
@@ -297,12 +299,16 @@ size_t soft3d_workspace_bytes(const Shape& s, int T) {
   return (size_t)256 + soft3d_partial_bytes(s, pl, T) + soft_reduce_mid_bytes((int)pl.grid.x * 4, s.batch, T);
 }
 
+static dim3 layered(const Plan3d& pl, const Shape& s, int T) {
+  return dim3(pl.grid.x, pl.grid.y, soft_layers((int64_t)pl.grid.x * 4 * s.batch, T));
+}
+
 void launch_soft3d_fwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                        float lambda, float* chi, void* ws, hipStream_t st, bool tiltc) {
   const Plan3d pl = plan3d<float>(s);
   float* partial = static_cast<float*>(ws);
 #define ECC_GO(TC)                                                                                          \
-  hipLaunchKernelGGL(soft3d_fwd_kernel<TC>, pl.grid, dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
+  hipLaunchKernelGGL(soft3d_fwd_kernel<TC>, layered(pl, s, T), dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
                      (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,       \
                      kneg3d(lambda), partial)
   if (tiltc) ECC_GO(true);
@@ -373,7 +379,7 @@ void launch_soft3d_fwd_save(const float* grid, const Shape& s, const float* u, f
   double* mid = reinterpret_cast<double*>(static_cast<char*>(ws) + soft3d_partial_bytes(s, pl, T));
   const bool deriv = dtau || du;
 #define ECC_GO(TC, DV)                                                                                        \
-  hipLaunchKernelGGL((soft3d_fwd_save_kernel<TC, DV>), pl.grid, dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H, \
+  hipLaunchKernelGGL((soft3d_fwd_save_kernel<TC, DV>), layered(pl, s, T), dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H, \
                      (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,         \
                      kneg3d(lambda), partial, sv, hdr.cap)
   if (tiltc) { if (deriv) ECC_GO(true, true); else ECC_GO(true, false); }

@@ -5,8 +5,8 @@
 // at a time and runs over the entries, so that the sums over p of Eq. 6 / Eq. 9 / Eq. 10 of the paper need no
 // cross-lane reduction; the contraction of Eq. 8 with the upstream gradient is a fixed-order sum over the lanes.
 //
-// The running sums live in the unit's own row of partial sums in the workspace and not in registers: a batch
-// starts from them and puts them back (the first one of a unit starts from zero; most units have one or two).
+// The running sums live in the unit's own row of partial sums in the workspace and not in registers: a batch's sums
+// (formed from zero: shorter chains of float32 additions) are added to them (the first one of a unit starts from zero; most units have one or two).
 // Registers held across the sweep were what limited it: sums, thresholds and upstream gradient of four
 // thresholds a lane took the 3D kernels from 124 to 162 .. 204 vector registers (three or two waves on a SIMD
 // instead of four) and tied the path to 256 thresholds.  256^3 with 64 thresholds: forward sweep 43 -> 37 us,
@@ -62,7 +62,7 @@ struct SoftEval {
   template <int S, typename Get>
   __device__ __forceinline__ float slots(int t0, int n, float csat, const Get& get) const {
     const int lane = threadIdx.x & (kWave - 1);
-    float tj[S], gj[S], acc[S][kSums > 0 ? kSums : 1];
+    float tj[S], gj[S], acc[S][kSums > 0 ? kSums : 1], old[S][kSums > 0 ? kSums : 1];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const int j = lane + kWave * (t0 + s);
@@ -70,8 +70,11 @@ struct SoftEval {
       tj[s] = ok ? tau[j] : 0.0f;
       if (GRADX) gj[s] = ok ? (gup ? gup[j] : 1.0f) : 0.0f;
 #pragma unroll
-      for (int k = 0; k < kSums; ++k) acc[s][k] = (started && ok && row) ? row[(int64_t)j * STRIDE + k] : 0.0f;
-      if (CHI) acc[s][0] += csat;
+      for (int k = 0; k < kSums; ++k) {
+        old[s][k] = (started && ok && row) ? row[(int64_t)j * STRIDE + k] : 0.0f;
+        acc[s][k] = 0.0f;
+      }
+      if (CHI) old[s][0] += csat;
     }
     float mine = 0.0f;
     for (int e = 0; e < n; ++e) {
@@ -105,6 +108,8 @@ struct SoftEval {
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         const int j = lane + kWave * (t0 + s);
+#pragma unroll
+        for (int k = 0; k < kSums; ++k) acc[s][k] += old[s][k];
         if (j < T) store(j, acc[s]);
       }
     }
@@ -129,6 +134,26 @@ struct SoftEval {
     for (int j = threadIdx.x & (kWave - 1); j < T; j += kWave) store(j, zero);
   }
 };
+
+// A launch with few wave units (small batches, small grids) and many thresholds is as long as one wave's walk over
+// its thresholds while most of the chip idles.  Such a launch runs in `parts` layers of blocks (gridDim.z): every
+// layer sweeps the grid again, which is cheap then, and evaluates its own share of the thresholds, a multiple of 64.
+// Up to about three waves for each of the 1024 SIMDs.  No layers where a contraction over all thresholds is formed.
+// Forward pass with derivatives on 16 x 217 x 181 with 512 thresholds: 91 us in one layer of 224 waves, 21 us in four
+// layers of 448 (8 rows a wave instead of 16).
+static inline unsigned soft_layers(int64_t waves, int T) {
+  const int64_t slots = (T + kWave - 1) / kWave;
+  int64_t n = 3072 / (waves < 1 ? 1 : waves);
+  n = n < 1 ? 1 : (n > slots ? slots : n);
+  const int64_t per = (slots + n - 1) / n;
+  return (unsigned)((slots + per - 1) / per);
+}
+// first threshold and number of thresholds of a layer
+__device__ __forceinline__ void soft_layer(int T, int& j0, int& n) {
+  const int slots = (T + kWave - 1) / kWave, per = (slots + (int)gridDim.z - 1) / (int)gridDim.z * kWave;
+  j0 = min((int)blockIdx.z * per, T);
+  n = min(per, T - j0);
+}
 
 // least and greatest threshold, by the whole wave
 __device__ __forceinline__ void threshold_span(const float* tau, int T, float& lo, float& hi) {
