@@ -358,7 +358,7 @@ hipError_t launch_hard_small(const float* grid, const Shape& s, int bins, int64_
 // smoother fields of the 16 x 4096^2 benchmark batch 254 -> 257 us (8 of them 153 -> 152, 4 of them
 // 95 -> 81); volumes 2 x 256^3 82 -> 73 us, 4 x 256^3 118 -> 121 us, 512^3 205 -> 216 us (the lists of
 // the blocks lie far apart in a workspace of 8 bytes per vertex): hence the limits.
-constexpr int64_t kMidTotal2d = (int64_t)1 << 27, kMidTotal3d = (int64_t)1 << 25;  // vertices in the whole batch
+constexpr int64_t kMidTotal3d = (int64_t)1 << 25;  // vertices in the whole batch (2D: kMidTotal2d)
 constexpr int64_t kMidBatch = 4096;
 constexpr int64_t kMidFinishBlocks = 512;          // finishing blocks in all, about (8 to 128 per item)
 constexpr unsigned kMidHeads = 4096;             // more heads than this: a launch of its own reduces the range

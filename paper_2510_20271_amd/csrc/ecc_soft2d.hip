@@ -130,13 +130,12 @@ struct SoftSink {
 };
 
 static unsigned state_cap(const Plan2d& pl) {
-  // room for one vertex in eight of a unit's rows x 248 columns (64 entries at least)
-  const unsigned v = (unsigned)pl.rows_per_seg * (unsigned)kStripOut / 8u;
-  return (v < 64u ? 64u : v);
+  // room for one vertex in eight of a unit's rows x 248 columns and 64 more (a small unit's share varies)
+  return (unsigned)pl.rows_per_seg * (unsigned)kStripOut / 8u + 64u;
 }
 size_t soft2d_state_bytes(const Shape& s) {
   if (!soft2d_supported(s, 1)) return 256;
-  const Plan2d pl = plan2d<float>(s, true);
+  const Plan2d pl = plan2d<float>(s, Feed2d::kSigmoid);
   return state_bytes(s.batch, (size_t)pl.nstrip * pl.nseg, state_cap(pl));
 }
 
@@ -363,7 +362,7 @@ static double* soft2d_mid(void* ws, const Shape& s, const Plan2d& pl, int T) {
 
 size_t soft2d_workspace_bytes(const Shape& s, int T) {
   if (!soft2d_supported(s, T)) return 0;
-  const Plan2d pl = plan2d<float>(s, true);
+  const Plan2d pl = plan2d<float>(s, Feed2d::kSigmoid);
   return (size_t)256 + soft2d_partial_bytes(s, pl, T) + soft_reduce_mid_bytes(pl.nstrip * pl.nseg, s.batch, T);
 }
 
@@ -373,7 +372,7 @@ static dim3 layered(const Plan2d& pl, const Shape& s, int T) {
 
 void launch_soft2d_fwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau,
                        int T, float lambda, float* chi, void* ws, hipStream_t st, bool tiltc) {
-  const Plan2d pl = plan2d<float>(s, true);
+  const Plan2d pl = plan2d<float>(s, Feed2d::kSigmoid);
   float* partial = static_cast<float*>(ws);
   profile_mark(st, false);
   if (tiltc)
@@ -391,7 +390,7 @@ void launch_soft2d_fwd(const float* grid, const Shape& s, const float* u, float 
 void launch_soft2d_bwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau,
                        int T, float lambda, const float* gup, float* grad_X, float* dtau, float* du,
                        void* ws, hipStream_t st, bool tiltc) {
-  const Plan2d pl = plan2d<float>(s, true);
+  const Plan2d pl = plan2d<float>(s, Feed2d::kSigmoid);
   float* partial = (dtau || du) ? static_cast<float*>(ws) : nullptr;
   profile_mark(st, false);
   if (tiltc)
@@ -429,7 +428,7 @@ static SoftStateHeader state_header(const Shape& s, const Plan2d& pl, bool tiltc
 void launch_soft2d_fwd_save(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                             float lambda, float* chi, float* dtau, float* du, void* state, void* ws, hipStream_t st,
                             bool tiltc) {
-  const Plan2d pl = plan2d<float>(s, true);
+  const Plan2d pl = plan2d<float>(s, Feed2d::kSigmoid);
   const StateView sv = state_view(state, s.batch, (size_t)pl.nstrip * pl.nseg);
   const SoftStateHeader hdr = state_header(s, pl, tiltc);
   float* partial = static_cast<float*>(ws);
@@ -450,7 +449,7 @@ void launch_soft2d_fwd_save(const float* grid, const Shape& s, const float* u, f
 void launch_soft2d_bwd_saved(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                              float lambda, const float* gup, float* grad_X, const void* state, hipStream_t st,
                              bool tiltc) {
-  const Plan2d pl = plan2d<float>(s, true);
+  const Plan2d pl = plan2d<float>(s, Feed2d::kSigmoid);
   const StateView sv = state_view(const_cast<void*>(state), s.batch, (size_t)pl.nstrip * pl.nseg);
   const SoftStateHeader expect = state_header(s, pl, tiltc);
   const dim3 g((unsigned)(pl.nstrip * pl.nseg), (unsigned)s.batch);

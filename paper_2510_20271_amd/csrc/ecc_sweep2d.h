@@ -477,40 +477,60 @@ struct Plan2d {
   int nstrip, nseg, rows_per_seg;
   dim3 grid;
 };
-// sigmoid_sinks: the plan of the soft path, whose sinks do their work wave by wave and want
-// many short segments; the hard path's sweeps are measured best as below.
+// What the sweep feeds: it decides how many rows a wave takes.  A wave's march is a chain of dependent steps (about
+// 0.4 us a row when it has a SIMD for itself), so a launch that does not fill the chip wants short segments; every
+// segment reads five rows more than it puts out, and a block has costs of its own at its end.
+enum class Feed2d { kHist, kList, kSigmoid };
+
+// rows a wave takes; tubes: strips of all items; bins: of a kHist sweep
+static inline int64_t rows2d(const Shape& s, int64_t nstrip, int64_t tubes, Feed2d feed, int bins) {
+  const int64_t H = s.H, total = s.N * s.batch;
+  if (feed == Feed2d::kSigmoid) {
+    // 8 rows while that gives up to three waves for each of the 1024 SIMDs (ecc_soft_fwd + ecc_soft_bwd on
+    // 4 x 1024^2, T = 64: 46 -> 36 us; one 2048^2, T = 256: 69 -> 50 us); else 24 when that still leaves two rounds
+    // of waves, else 16
+    if (tubes * ((H + 7) / 8) <= 3072) return 8;
+    return tubes * ((H + 23) / 24) >= 8192 ? 24 : 16;
+  }
+  if (feed == Feed2d::kList && total <= kMidTotal2d) {
+    // A list per block: nothing is merged at a block's end.  Measured with 8 / 16 / 24 / 32 / 64 rows (us a call,
+    // float32): 1024 x 28^2 20.8 / 21.3 / 21.4 / 23.7, 1024^2 17.8 / 19.9 / 21.5 / 23.1 / 30.8, 64 directions of 256^2
+    // 23.9 / 21.9 / 25.2 / 25.8 / 35.7, 1024 x 128^2 43.7 / 39.2 / 47.2 / 53.2 / 57.8, 32 x 512^2 30.2 / 27.2 / 29.4 / 30.3 /
+    // 39.4, 4096^2 37.5 / 39.4 / 34.0 / 34.8 / 44.9, 8 x 4096^2 149 / 137 / 134 / 138 / 153: by the total first, then
+    // by the height (24 rows leave a low image's last segment and block half empty).
+    int64_t rows = total < ((int64_t)1 << 22) ? 8 : (H <= 1024 ? 16 : 24);
+    while (rows < 64 && tubes * ((H + rows - 1) / rows) > 131072) rows *= 2;  // (tall, narrow grids: the blocks' heads)
+    return rows;
+  }
+  // A histogram per block, cleared first and merged into the item's with one atomic per bin at the end: few bins and
+  // not too many blocks that meet in one item's histogram want short segments (us a call with 8 / 16 / 32 / 64 rows:
+  // 64 x 256^2 uint8 14.3 / 14.4 / 16.4 / 25.2, 2048^2 uint8 noise 25.6 / 26.0 / 36.9 / 64, 16 x 1024^2 uint8 24.0 / 21.3 /
+  // 23.4 / 30.7, 1024 x 224^2 uint8 42.9 / 42.2 / 41.6 / 39.0; but a 4677 x 3307 page 52.6 / 32.1 / 24.6 / 26.1, 16 x 1024^2
+  // with 4096 bins 54 / 40.9 / 34.2 / 39.5).
+  if (feed == Feed2d::kHist && nstrip * ((H + 15) / 16) <= 1280 && bins <= 1024)
+    return total <= ((int64_t)1 << 25) ? 16 : 32;
+  if (tubes * ((H + 15) / 16) <= 1024) return 16;  // at most one wave per SIMD even with short segments
+  // One large image gains 30 % from 24 -> 64 rows at 4096^2, 20 % from 16 -> 32 at 2048^2: about 1536 waves, within
+  // 32 .. 64 rows per segment.  Shared lists, 16 x 4096^2: 241 / 251 / 237 / 246 / 259 us with 24 / 32 / 48 / 64 / 96 rows.
+  const int64_t want = std::max<int64_t>(1, 1536 / tubes);
+  int64_t rows = ((H + want - 1) / want + kChunkRows - 1) / kChunkRows * kChunkRows;
+  // plenty of tubes (a large batch of small images): up to 128 rows, but two segments per image at least
+  // (2048 x 128^2 loses 17 % with one segment of 128)
+  int64_t longest = feed == Feed2d::kList ? 48 : 64;
+  if (tubes >= 1024)
+    longest = std::max<int64_t>(64, std::min<int64_t>(128, ((H + 1) / 2 + kChunkRows - 1) / kChunkRows * kChunkRows));
+  return rows < 32 ? 32 : (rows > longest ? longest : rows);
+}
+
 template <typename T>
-static Plan2d plan2d(const Shape& s, bool sigmoid_sinks = false) {
+static Plan2d plan2d(const Shape& s, Feed2d feed, int bins = 1) {
   Plan2d p;
   const int H = (int)s.H, W = (int)s.W;
   p.nstrip = (W + kStripOut - 1) / kStripOut;
   const int64_t tubes = (int64_t)p.nstrip * s.batch;
-  int64_t nseg;
-  if (sigmoid_sinks) {
-    // enough wave units to fill 256 CUs several times over, segments of >= 16 rows (24 when
-    // that still leaves two rounds of waves: a segment reads five rows more than it puts out)
-    nseg = (32768 + tubes - 1) / tubes;
-    const int64_t max_seg = tubes * ((H + 23) / 24) >= 8192 ? (H + 23) / 24 : (H + 15) / 16;
-    if (nseg > max_seg) nseg = max_seg;
-  } else if (tubes * ((H + 15) / 16) <= 1024) {
-    // at most one wave per SIMD even with the shortest segments: the call is as long as one
-    // wave's march, so the segments are as short as they come
-    nseg = (H + 15) / 16;
-  } else {
-    // Measured (rows per segment against time): a batch of 16 x 4096^2 is flat from 24 to 64
-    // rows and loses beyond 96; one 4096^2 image gains 30 % from 24 -> 64, one 2048^2 image
-    // 20 % from 16 -> 32, batches of 256^2 ... 512^2 images 25-30 % from 16 -> 32 ... 64.  Aim
-    // at about 1536 waves, within 32 ... 64 rows per segment.
-    const int64_t want = std::max<int64_t>(1, 1536 / tubes);
-    int64_t rows = (H + want - 1) / want;
-    rows = (rows + kChunkRows - 1) / kChunkRows * kChunkRows;
-    // plenty of tubes (a large batch of small images): up to 128 rows, but two segments per image at least
-    // (1024 x 224^2: 0.112 -> 0.085 ms with 2 x 112 rows; 2048 x 128^2 loses 17 % with one segment of 128)
-    int64_t longest = 64;
-    if (tubes >= 1024) longest = std::max<int64_t>(64, std::min<int64_t>(128, ((H + 1) / 2 + kChunkRows - 1) / kChunkRows * kChunkRows));
-    rows = rows < 32 ? 32 : (rows > longest ? longest : rows);
-    nseg = (H + rows - 1) / rows;
-  }
+  const int64_t aim = rows2d(s, p.nstrip, tubes, feed, bins);
+  int64_t nseg = (H + aim - 1) / aim;
+  if (feed == Feed2d::kSigmoid) nseg = std::min(nseg, (32768 + tubes - 1) / tubes);
   if (nseg < 1) nseg = 1;
   // whole chunks per segment; segment + prefetch must stay below 2^31 bytes
   int64_t rows = (H + nseg - 1) / nseg;

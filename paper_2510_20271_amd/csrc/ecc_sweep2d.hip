@@ -98,7 +98,7 @@ template <typename T, bool LV = false>
 static void launch2d_t(const void* grid, const Shape& s, bool levels, int bins, const HardHeader* hdr,
                        const float* table, unsigned long long* hist, hipStream_t st,
                        const unsigned* run_if, const DirArgs* dir, int conv) {
-  const Plan2d pl = plan2d<T>(s);
+  const Plan2d pl = plan2d<T>(s, Feed2d::kHist, bins);
   const bool tlds = !levels && (size_t)bins * 8 + kRingBytes2d <= 64 * 1024;
   const size_t lds = kRingBytes2d + (size_t)bins * (tlds ? 8 : 4);
   const T* p = static_cast<const T*>(grid);
@@ -135,7 +135,7 @@ static void launch2d_t(const void* grid, const Shape& s, bool levels, int bins, 
 template <typename T>
 static void launch2d_list_t(const void* grid, const Shape& s, const ListArgs& la, hipStream_t st, const DirArgs* dir,
                             int conv) {
-  const Plan2d pl = plan2d<T>(s);
+  const Plan2d pl = plan2d<T>(s, Feed2d::kList);
   const DirArgs none = {nullptr, 0.f, 1, 2};
   const T* p = static_cast<const T*>(grid);
 #define ECC_LIST(M, DIR)                                                                                 \
@@ -167,12 +167,12 @@ void launch_sweep2d_list(const void* grid, int dtype, const Shape& s, const List
 }
 
 unsigned sweep2d_block_vertices(const Shape& s, int dtype) {
-  const Plan2d pl = dtype == 2 ? plan2d<float>(s) : plan2d<F16>(s);
+  const Plan2d pl = dtype == 2 ? plan2d<float>(s, Feed2d::kList) : plan2d<F16>(s, Feed2d::kList);
   return 4u * (unsigned)kStripOut * (unsigned)pl.rows_per_seg;  // four wave units of 248 columns x the segment's rows
 }
 
 unsigned sweep2d_list_blocks(const Shape& s, int dtype) {
-  return dtype == 2 ? plan2d<float>(s).grid.x : plan2d<F16>(s).grid.x;
+  return dtype == 2 ? plan2d<float>(s, Feed2d::kList).grid.x : plan2d<F16>(s, Feed2d::kList).grid.x;
 }
 
 bool sweep2d_supported(const Shape& s, int bins) {
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(256) void coeff2d_kernel(const T* __restrict__ grid
 
 template <typename T>
 static void launch_coeff2d_t(const void* grid, const Shape& s, int8_t* out, hipStream_t st) {
-  const Plan2d pl = plan2d<T>(s);
+  const Plan2d pl = plan2d<T>(s, Feed2d::kList);
   hipLaunchKernelGGL((coeff2d_kernel<T>), pl.grid, dim3(256), ring_bytes2d<int4>(), st, static_cast<const T*>(grid),
                      (int)s.H, (int)s.W, s.N, pl.nstrip, pl.nseg, pl.rows_per_seg, out);
 }
