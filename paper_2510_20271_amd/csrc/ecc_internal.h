@@ -63,9 +63,8 @@ hipError_t launch_hard_mid(const void* grid, const Shape& s, int dtype, int bins
 hipError_t launch_hard_small(const float* grid, const Shape& s, int bins, int64_t* curve, HardHeader* hdr, float* table,
                              void* small, hipStream_t st, int conv);
 // single-pass mode: per-item lists of critical vertices (value, c) in the workspace
-// what a block that keeps a list of its own leaves behind (nothing has to be cleared for it)
 constexpr int64_t kMidTotal2d = (int64_t)1 << 27;  // 2D: vertices in the whole batch that still get a list per block
-
+// what a block that keeps a list of its own leaves behind (nothing has to be cleared for it)
 struct ListHead {
   unsigned count;             // critical vertices the block found
   unsigned min_key, max_key;  // float_key of the least / greatest value the block saw

@@ -8,8 +8,8 @@
 // parks the entry in a small LDS stage -- unless y lies so far outside [min tau, max tau]
 // that every sigmoid is 0 or 1 to 2^-64: such an entry adds c or nothing to every
 // threshold and is not evaluated.  Then every lane runs over the staged entries for the
-// thresholds it owns (tau_l, tau_{l+64}, ...; see ecc_soft_eval.h).  grad_X is
-// cleared by a fill kernel first and written at the critical vertices only.
+// thresholds it owns (tau_l, tau_{l+64}, ...; see ecc_soft_eval.h).  The sweep
+// clears grad_X plane by plane; it is written at the critical vertices only.
 // Each wave keeps its partial sums in a row of the workspace; a second kernel adds them
 // in a fixed order in float64, so results are run-to-run identical.
 #include "ecc_sweep3d.h"
@@ -36,6 +36,7 @@ struct Soft3Staged {
 template <bool CHI, bool DERIV, bool GRADX, bool SAVE, int STRIDE>
 struct Soft3Sink {
   static constexpr bool kTrackRange = false;
+  static constexpr bool kZeroFill = GRADX;
   double ux, uy, uz, alpha;
   float sat_lo, sat_hi;  // y <= sat_lo: every sigma is 1;  y >= sat_hi: every sigma is 0 (to 2^-64)
   int W;
@@ -324,7 +325,6 @@ void launch_soft3d_bwd(const float* grid, const Shape& s, const float* u, float 
                        hipStream_t st, bool tiltc) {
   const Plan3d pl = plan3d<float>(s);
   float* partial = (dtau || du) ? static_cast<float*>(ws) : nullptr;
-  if (grad_X) launch_clear_f32(grad_X, s.N * s.batch, st);  // zero away from the critical vertices
 #define ECC_GO(TC)                                                                                          \
   hipLaunchKernelGGL(soft3d_bwd_kernel<TC>, pl.grid, dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
                      (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,       \

@@ -401,7 +401,21 @@ __device__ __forceinline__ void sweep_tube(const T* __restrict__ g, int64_t item
         }
       }
     };
+    // The sink's per-vertex output is 0 except at critical vertices: a plane's share of it is cleared here, before any
+    // entry of the chunk is drained.  The stores hide behind the stencil's arithmetic (256^3: a fill kernel in front
+    // of the sweep took 12.7 us, the sweep is 7 us longer).
+    auto clear = [&](int zp) {
+      if constexpr (Sink::kZeroFill) {
+        if (queue.sink.gx == nullptr) return;  // wave-uniform
+        float* const base = queue.sink.gx + (int64_t)zp * plane;
+#pragma unroll
+        for (int j = 1; j <= R; ++j)
+          if (out_lane && (!SAFE || okj[j])) base[(int64_t)(j - 1) * W + (unsigned)(yb * W + x)] = 0.0f;
+      }
+    };
     for (; k + 2 <= n; k += 2) {
+      clear(z + k);
+      clear(z + k + 1);
       fix(pb, rawx);  // plane above pa
       load_plane(rawx);
       track(pa);
@@ -414,6 +428,7 @@ __device__ __forceinline__ void sweep_tube(const T* __restrict__ g, int64_t item
       push_up<R>(w, pb, pa, skip_top, skip_bottom);
     }
     if (k < n) {  // odd tail: only in the last chunk of the segment
+      clear(z + k);
       fix(pb, rawx);
       track(pa);
       push_plane<R>(w, pa, skip_top);

@@ -192,6 +192,7 @@ void launch_sweep3d(const void* grid, const Shape& s, int dtype, bool levels, in
 // tube-sweep kernel, made visible vertex by vertex.
 struct CoeffSink3d {
   static constexpr bool kTrackRange = false;
+  static constexpr bool kZeroFill = false;
   int8_t* out;    // this item's map
   int64_t plane;  // H * W
   int oz;         // first plane of the wave's segment
