@@ -34,7 +34,8 @@ def _forward(ctx, grid, u, tau, alpha, lam, tilted_c, theta=None):
     # than the small contraction.
     want = [n for n, need in (("dchi_du", need_u), ("dchi_dtau", need_tau)) if need]
     chi, dtau, du, state = api.ecc_soft_fwd_save(grid_c, ndim, u, alpha, tau_c, lam, tilted_c=ctx.tilted_c, want=want)
-    ctx.save_for_backward(grid_c, u, tau_c, state if need_x else None, dtau, du, theta)
+    # (the angles only where their gradient is wanted: a frozen direction may be changed in place before backward())
+    ctx.save_for_backward(grid_c, u, tau_c, state if need_x else None, dtau, du, theta if need_u else None)
     return chi
 
 

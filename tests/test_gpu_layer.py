@@ -154,3 +154,25 @@ def test_direction_is_that_of_the_tensor_operations():
             with torch.no_grad():
                 m.theta.copy_(theta[[i, 399 - i]][:nd - 1])
             assert torch.equal(layer.api.ecc_soft_direction(m.theta.detach()), m.direction().detach())
+
+
+@pytest.mark.parametrize("shape", [(20, 33), (9, 12, 17)])
+def test_frozen_direction_changed_between_forward_and_backward(shape):
+    """One backward pass over the curves of several directions, the layer's angle(s) set in place in between."""
+    nd = len(shape)
+    X = dev(np.stack([synth.grf(shape, 2.0, 290 + i) for i in range(2)])).requires_grad_()
+    m = layer.SoftECCLayer(nd, 24, float(X.min()), float(X.max()) + 0.4, alpha=0.02, learn_theta=False).cuda()
+    angles = [torch.tensor([a, 0.5 + a][:nd - 1], device="cuda") for a in (0.2, 0.9, 2.5)]
+    alone = []
+    for a in angles:
+        with torch.no_grad():
+            m.theta.copy_(a)
+        alone.append(torch.autograd.grad(m(X).sum(), [X, m.tau]))
+    outs = []
+    for a in angles:
+        with torch.no_grad():
+            m.theta.copy_(a)
+        outs.append(m(X).sum())
+    for got, parts in zip(torch.autograd.grad(sum(outs), [X, m.tau]), zip(*alone)):
+        # the same kernels; autograd adds the three in an order of its own, in float32
+        torch.testing.assert_close(got, sum(parts), rtol=1e-5, atol=1e-6 * float(sum(p.abs().max() for p in parts)))
