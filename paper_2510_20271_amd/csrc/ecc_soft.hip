@@ -16,6 +16,7 @@
 //
 // The sigmoid argument z = tau_j - X(p) - alpha <u,p> is formed in float64 and
 // rounded once; exp2 and reciprocal run on the float32 transcendental unit.
+#include "../../include/ecc.h"
 #include "ecc_device.h"
 #include "ecc_internal.h"
 
@@ -314,19 +315,33 @@ void launch_clear_f32(float* p, int64_t total, hipStream_t st) {
 // ---------------------------------------------------------------------------
 static int64_t tiles_of(const Shape& s) { return (s.N + kTile - 1) / kTile; }
 
+// The fused kernels keep a row of 16 or 20 bytes a threshold for every wave unit of their sweep, the tile kernels 16 bytes
+// for every 2048 vertices.  The units of small items are mostly padding, so with many thresholds the rows of a large batch
+// of them grow far beyond the tiles' (65535 x 16^3 with 4096 thresholds: 21.5 GB against 8.6), and the number a hard
+// call's bins name sizes the same workspace.  Above 256 thresholds the fused kernels therefore run where their rows need
+// no more than the tiles' or at most 64 MiB.
+static size_t tile_bytes(const Shape& s, int T) {
+  return (size_t)256 + (size_t)s.batch * (size_t)tiles_of(s) * (size_t)T * 4 * sizeof(float);
+}
+constexpr size_t kFusedRoom = (size_t)64 << 20;
+static bool fused_fits(const Shape& s, int T) {
+  if (T <= 256) return true;
+  if (T > ECC_MAX_THRESHOLDS) return false;  // (a hard call's bins: no soft call takes so many)
+  return std::max(soft2d_workspace_bytes(s, T), soft3d_workspace_bytes(s, T)) <= std::max(tile_bytes(s, T), kFusedRoom);
+}
+
 size_t soft_workspace_bytes(const Shape& s, int T) {
-  const size_t a = (size_t)256 + (size_t)s.batch * (size_t)tiles_of(s) * (size_t)T * 4 * sizeof(float);
-  const size_t b = soft2d_workspace_bytes(s, T), c = soft3d_workspace_bytes(s, T);
-  return std::max(a, std::max(b, c));
+  const size_t fused = fused_fits(s, T) ? std::max(soft2d_workspace_bytes(s, T), soft3d_workspace_bytes(s, T)) : 0;
+  return std::max(tile_bytes(s, T), fused);
 }
 
 // test aid (ecc_debug_force): the tile kernels of this file for every shape
 static bool use_soft2d(const Shape& s, int T) {
-  return !(forced_paths() & kForceSoftTiles) && soft2d_supported(s, T);
+  return !(forced_paths() & kForceSoftTiles) && soft2d_supported(s, T) && fused_fits(s, T);
 }
 
 static bool use_soft3d(const Shape& s, int T) {
-  return !(forced_paths() & kForceSoftTiles) && soft3d_supported(s, T);
+  return !(forced_paths() & kForceSoftTiles) && soft3d_supported(s, T) && fused_fits(s, T);
 }
 
 static float kneg_of(float lambda) { return (float)(-(double)lambda * 1.4426950408889634); }

@@ -69,6 +69,21 @@ def test_workspace_bytes_of_the_hard_flows():
         assert n <= w <= 2 * n, (dims, batch, w / n)
 
 
+@pytest.mark.parametrize("dims,batch", [((16, 16, 16), 4096), ((16, 16, 16), 65535), ((8, 8, 8), 65535), ((2, 2, 386), 36692),
+                                        ((28, 28), 65535), ((2, 3000), 1000), ((300, 8), 2000), ((217, 181), 16),
+                                        ((512, 512), 32), ((256, 256, 256), 1), ((4096, 4096), 16)])
+def test_many_thresholds_need_no_more_room_than_tiles(dims, batch):
+    """The number that is a soft call's thresholds is a hard call's bins: rows per wave unit, which small items leave
+    almost empty, must not inflate it."""
+    lib = _lib.load()
+    nd, d = len(dims), _dims(*dims)
+    tiles = batch * -(-int(np.prod(dims)) // 2048)
+    for n in (257, 1000, 4096, 4097, 16384):  # (a soft call takes 4096 thresholds at most)
+        hard = lib.ecc_workspace_bytes_dir(nd, d, batch, 1, n)
+        room = 64 << 20 if n <= 4096 else 0
+        assert lib.ecc_workspace_bytes(nd, d, batch, n) <= max(hard, 256 + tiles * n * 16, room), n
+
+
 INVALID, UNSUPPORTED, WORKSPACE, RANGE = -1, -2, -3, -4
 
 
