@@ -130,8 +130,10 @@ struct SoftSink {
 };
 
 static unsigned state_cap(const Plan2d& pl) {
-  // room for one vertex in eight of a unit's rows x 248 columns and 64 more (a small unit's share varies)
-  return (unsigned)pl.rows_per_seg * (unsigned)kStripOut / 8u + 64u;
+  // room for one vertex in eight of a unit's rows x 248 columns; 64 more for the units of 8 rows that small launches
+  // take (a small unit's share varies; there are 3072 of them at most)
+  const unsigned v = (unsigned)pl.rows_per_seg * (unsigned)kStripOut / 8u;
+  return pl.rows_per_seg == 8 && pl.nseg > 1 ? v + 64u : v;
 }
 size_t soft2d_state_bytes(const Shape& s) {
   if (!soft2d_supported(s, 1)) return 256;

@@ -341,8 +341,8 @@ void launch_soft3d_bwd(const float* grid, const Shape& s, const float* u, float 
 
 // ---- forward that saves its critical vertices, backward from the saved lists ----------------
 static unsigned state_cap3(const Plan3d& pl) {
-  // room for one vertex in eight of a unit's planes x 4 rows x 62 columns and 64 more (a small unit's share varies)
-  return ((unsigned)pl.planes_per_seg * (unsigned)kRows3d * (unsigned)s3::kOut / 8u + 127u) / 64u * 64u;
+  // room for one vertex in eight of a unit's planes x 4 rows x 62 columns, rounded up to 64 entries
+  return ((unsigned)pl.planes_per_seg * (unsigned)kRows3d * (unsigned)s3::kOut / 8u + 63u) / 64u * 64u;
 }
 static bool soft3d_saves(const Shape& s) { return soft3d_supported(s, 1) && s.N < ((int64_t)1 << 31); }
 size_t soft3d_state_bytes(const Shape& s) {

@@ -168,7 +168,8 @@ void launch_sweep2d_list(const void* grid, int dtype, const Shape& s, const List
 
 unsigned sweep2d_block_vertices(const Shape& s, int dtype) {
   const Plan2d pl = dtype == 2 ? plan2d<float>(s, Feed2d::kList) : plan2d<F16>(s, Feed2d::kList);
-  return 4u * (unsigned)kStripOut * (unsigned)pl.rows_per_seg;  // four wave units of 248 columns x the segment's rows
+  // four wave units of 248 columns x the segment's rows
+  return 4u * (unsigned)std::min<int64_t>(kStripOut, s.W) * (unsigned)std::min<int64_t>(pl.rows_per_seg, s.H);
 }
 
 unsigned sweep2d_list_blocks(const Shape& s, int dtype) {

@@ -164,7 +164,8 @@ void launch_sweep3d_list(const void* grid, int dtype, const Shape& s, const List
 unsigned sweep3d_list_blocks(const Shape& s) { return plan3d<float>(s, false).grid.x; }
 unsigned sweep3d_block_vertices(const Shape& s) {
   // four wave units of at most 62 columns x 4 rows (a folded unit: several row groups of fewer columns) x the segment's planes
-  return 4u * (unsigned)s3::kOut * (unsigned)kRows3d * (unsigned)plan3d<float>(s, false).planes_per_seg;
+  const int64_t planes = std::min<int64_t>(s.D, plan3d<float>(s, false).planes_per_seg);
+  return 4u * (unsigned)s3::kOut * (unsigned)kRows3d * (unsigned)planes;
 }
 
 bool sweep3d_supported(const Shape& s, int bins) {

@@ -160,8 +160,9 @@ def test_direction_is_that_of_the_tensor_operations():
 def test_frozen_direction_changed_between_forward_and_backward(shape):
     """One backward pass over the curves of several directions, the layer's angle(s) set in place in between."""
     nd = len(shape)
-    X = dev(np.stack([synth.grf(shape, 2.0, 290 + i) for i in range(2)])).requires_grad_()
+    X = dev(np.stack([synth.grf(shape, 2.0, 290 + i) for i in range(2)]))
     m = layer.SoftECCLayer(nd, 24, float(X.min()), float(X.max()) + 0.4, alpha=0.02, learn_theta=False).cuda()
+    X.requires_grad_()
     angles = [torch.tensor([a, 0.5 + a][:nd - 1], device="cuda") for a in (0.2, 0.9, 2.5)]
     alone = []
     for a in angles:
