@@ -304,13 +304,12 @@ __device__ __forceinline__ float soft_exp_neg(float z, float kneg) {
   return __builtin_amdgcn_exp2f(fminf(kneg * z, 126.0f));
 }
 
-constexpr float kSatLog2 = 64.0f;  // |lambda z| log2(e) beyond which sigma is 0 or 1 and sigma' is 0
-
-// Saturation bounds for thresholds in [lo, hi]: with k = lambda log2(e) = -kneg, sigma(tau - y) differs from
+// Saturation bounds for T thresholds in [lo, hi]: with k = lambda log2(e) = -kneg, sigma(tau - y) differs from
 // 1 by less than 2^-64 for y <= lo - 64/k and from 0 for y >= hi + 64/k (a little margin covers
-// the rounding of yh); sigma' is below 2^-64 lambda in both cases.
-__device__ __forceinline__ void soft_sat_bounds(float lo, float hi, float kneg, float& sat_lo, float& sat_hi) {
-  const float w = (kSatLog2 + 2.0f) / -kneg;
+// the rounding of y to float32); sigma' is below 2^-64 lambda in both cases.  With more than 256 thresholds nothing is
+// dropped that float32 can hold: there the bounds lie at 2^-126.
+__device__ __forceinline__ void soft_sat_bounds(float lo, float hi, float kneg, int T, float& sat_lo, float& sat_hi) {
+  const float w = (T > 256 ? 128.0f : 66.0f) / -kneg;
   sat_lo = lo - w - 1e-6f * fabsf(lo);
   sat_hi = hi + w + 1e-6f * fabsf(hi);
 }

@@ -18,10 +18,10 @@
 // Each wave keeps its partial sums in a row of the workspace; a second kernel adds the
 // rows in a fixed order in float64, so results are run-to-run identical.
 //
-// y = X(p) + alpha <u,p> is formed in float64 and carried as two floats (yh + yl), so that
-// z = (tau_j - yh) - yl is the float64 difference to within an ulp of z; exp2 and the
+// y = X(p) + alpha <u,p> and z = tau_j - y are formed in float64 and z is rounded once (two float32 subtractions of y
+// carried as two floats round twice; a float64 one and its conversion cost 1 to 2 % of these kernels); exp2 and the
 // reciprocal run on the float32 transcendental unit.  An entry whose y lies so far outside
-// [min tau, max tau] that every sigmoid is 0 or 1 to 2^-64 is not evaluated at all: it adds
+// [min tau, max tau] that every sigmoid is 0 or 1 (see soft_sat_bounds) is not evaluated at all: it adds
 // c to every threshold (sigma = 1) or nothing, and nothing to the derivatives.
 #include "ecc_sweep2d.h"
 #include "ecc_soft_eval.h"
@@ -37,7 +37,8 @@ struct SoftEntry {
   unsigned rel;  // row - row0 << 12 | column - col0 << 4 | c & 15
 };
 struct SoftStaged {
-  float yh, yl, c;  // X(p) + alpha <u,p> = yh + yl
+  double y;  // X(p) + alpha <u,p>
+  float c;
   unsigned rel;
 };
 
@@ -49,7 +50,7 @@ struct SoftSink {
   static constexpr bool kTrackRange = false;
   static constexpr bool kZeroFill = GRADX;
   double ux, uy, alpha;
-  float sat_lo, sat_hi;  // y <= sat_lo: every sigma is 1;  y >= sat_hi: every sigma is 0 (to 2^-64)
+  float sat_lo, sat_hi;  // y <= sat_lo: every sigma is 1;  y >= sat_hi: every sigma is 0 (soft_sat_bounds)
   // The sweep ran on the tilted field (c of the tilted field): the value it hands over
   // is the tilted one in float32; X is read again so that y is formed as always.
   const float* xsrc;  // this item's grid, or null when the sweep ran on X itself
@@ -91,8 +92,7 @@ struct SoftSink {
     if (xsrc) v = xsrc[(int64_t)row * W + col];  // wave-uniform condition
     const double y = (double)v + alpha * (ux * (double)col + uy * (double)row);
     SoftStaged e;
-    e.yh = (float)y;
-    e.yl = (float)(y - (double)e.yh);
+    e.y = y;
     e.c = (float)ci;
     e.rel = q.rel;
     if constexpr (SAVE) {
@@ -107,15 +107,16 @@ struct SoftSink {
     }
     float csat;
     int pos;
-    n = pack_entries(in && e.yh > sat_lo && e.yh < sat_hi, in && e.yh <= sat_lo, e.c, n, csat, pos);
-    if (in && e.yh > sat_lo && e.yh < sat_hi) stage[pos] = e;
-    if (!CHI) csat = 0.0f;  // (sigma' < 2^-64 lambda at every threshold; grad_X stays 0 there)
+    const float yf = (float)y;
+    const bool keep = in && yf > sat_lo && yf < sat_hi;
+    n = pack_entries(keep, in && yf <= sat_lo, e.c, n, csat, pos);
+    if (keep) stage[pos] = e;
+    if (!CHI) csat = 0.0f;  // (grad_X stays 0 at a saturated vertex)
     if (n == 0 && csat == 0.0f) return;
     const SoftStaged* st = stage;
     const float g = eval.template run<2>(n, csat, [st](int i, StagedValue& o, float (&r)[2]) {
       const SoftStaged s = st[i];
-      o.yh = s.yh;
-      o.yl = s.yl;
+      o.y = s.y;
       o.c = s.c;
       r[0] = (float)((s.rel >> 4) & 255u);
       r[1] = (float)(s.rel >> 12);
@@ -166,7 +167,7 @@ __device__ __forceinline__ void soft2d_sweep(WaveQueue<Sink>& queue, const float
   s.alpha = (double)alpha;
   float lo, hi;
   threshold_span(tau, T, lo, hi);
-  soft_sat_bounds(lo, hi, kneg, s.sat_lo, s.sat_hi);
+  soft_sat_bounds(lo, hi, kneg, T, s.sat_lo, s.sat_hi);
   s.W = W;
   s.col0 = (unit % nstrip) * kStripOut - kNC;
   s.row0 = (unit / nstrip) * rows_per_seg;
@@ -265,8 +266,8 @@ __global__ __launch_bounds__(256) void soft2d_bwd_saved_kernel(const float* __re
                                                                SoftStateHeader expect) {
   const int item = blockIdx.y, unit = blockIdx.x, units = nstrip * nseg;
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
-  extern __shared__ float stau[];  // [T] thresholds, [T] upstream gradient
-  float* const sg = stau + T;
+  extern __shared__ double stau[];  // [T] thresholds, [T] upstream gradient (float)
+  float* const sg = reinterpret_cast<float*>(stau + T);
   __shared__ StagedEntry stage[256];
   __shared__ float sred[2][4];
   __shared__ int skept[4];
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(256) void soft2d_bwd_saved_kernel(const float* __re
   float lo = INFINITY, hi = -INFINITY;
   for (int j = threadIdx.x; j < T; j += 256) {
     const float t = tau[j];
-    stau[j] = t;
+    stau[j] = (double)t;
     sg[j] = gup ? gup[(int64_t)item * T + j] : 1.0f;
     lo = fminf(lo, t);
     hi = fmaxf(hi, t);
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(256) void soft2d_bwd_saved_kernel(const float* __re
   lo = fminf(fminf(sred[0][0], sred[0][1]), fminf(sred[0][2], sred[0][3]));
   hi = fmaxf(fmaxf(sred[1][0], sred[1][1]), fmaxf(sred[1][2], sred[1][3]));
   float sat_lo, sat_hi;
-  soft_sat_bounds(lo, hi, kneg, sat_lo, sat_hi);
+  soft_sat_bounds(lo, hi, kneg, T, sat_lo, sat_hi);
 
   if (!usable) {
     const float* g = grid + (int64_t)item * N;
@@ -330,10 +331,9 @@ __global__ __launch_bounds__(256) void soft2d_bwd_saved_kernel(const float* __re
         float out = 0.0f;
         if (c != 0) {
           const double yv = (double)g[(int64_t)y * W + x] + (double)alpha * (ux * (double)x + uy * (double)y);
-          const float yh = (float)yv, yl = (float)(yv - (double)yh);
-          if (yh > sat_lo && yh < sat_hi) {
+          if ((float)yv > sat_lo && (float)yv < sat_hi) {
             float gd = 0.0f;
-            for (int j = 0; j < T; ++j) gd += sg[j] * soft_dsig(stau[j], yh, yl, kneg);
+            for (int j = 0; j < T; ++j) gd += sg[j] * soft_dsig(stau[j], yv, kneg);
             out = -lambda * (float)c * gd;
           }
         }
@@ -455,7 +455,7 @@ void launch_soft2d_bwd_saved(const float* grid, const Shape& s, const float* u, 
   const StateView sv = state_view(const_cast<void*>(state), s.batch, (size_t)pl.nstrip * pl.nseg);
   const SoftStateHeader expect = state_header(s, pl, tiltc);
   const dim3 g((unsigned)(pl.nstrip * pl.nseg), (unsigned)s.batch);
-  const size_t lds = (size_t)T * 2 * sizeof(float);
+  const size_t lds = (size_t)T * (sizeof(double) + sizeof(float));
   profile_mark(st, false);
   if (tiltc)
     hipLaunchKernelGGL(soft2d_bwd_saved_kernel<true>, g, dim3(256), lds, st, grid, (int)s.H, (int)s.W, s.N, pl.nstrip,

@@ -3,12 +3,12 @@
 //
 // As in 2D, only the critical vertices (c != 0) carry a term.  The tube sweep
 // finds them and queues (position, c); when 64 are drained together each lane
-// fetches one value, forms y = X(p) + alpha <u,p> in float64, carries it on as two
-// floats (yh + yl, so that (tau_j - yh) - yl is the float64 difference to an ulp) and
+// fetches one value, forms y = X(p) + alpha <u,p> in float64 and
 // parks the entry in a small LDS stage -- unless y lies so far outside [min tau, max tau]
-// that every sigmoid is 0 or 1 to 2^-64: such an entry adds c or nothing to every
+// that every sigmoid is 0 or 1 (see soft_sat_bounds): such an entry adds c or nothing to every
 // threshold and is not evaluated.  Then every lane runs over the staged entries for the
-// thresholds it owns (tau_l, tau_{l+64}, ...; see ecc_soft_eval.h).  The sweep
+// thresholds it owns (tau_l, tau_{l+64}, ...; see ecc_soft_eval.h), z = tau_j - y formed in
+// float64 and rounded once.  The sweep
 // clears grad_X plane by plane; it is written at the critical vertices only.
 // Each wave keeps its partial sums in a row of the workspace; a second kernel adds them
 // in a fixed order in float64, so results are run-to-run identical.
@@ -25,7 +25,8 @@ constexpr int kSoft3Slots = 1;  // slots of 64 thresholds taken together
 constexpr int kSoft3Waves = 4;  // waves on a SIMD that the registers are kept within
 
 struct Soft3Staged {
-  float yh, yl, c;  // X(p) + alpha <u,p> = yh + yl
+  double y;         // X(p) + alpha <u,p>
+  float c;
   unsigned inpl;    // element offset inside the plane
   float rx, ry, rz; // coordinates relative to the unit's origin
   unsigned zrel;    // plane of the segment
@@ -38,7 +39,7 @@ struct Soft3Sink {
   static constexpr bool kTrackRange = false;
   static constexpr bool kZeroFill = GRADX;
   double ux, uy, uz, alpha;
-  float sat_lo, sat_hi;  // y <= sat_lo: every sigma is 1;  y >= sat_hi: every sigma is 0 (to 2^-64)
+  float sat_lo, sat_hi;  // y <= sat_lo: every sigma is 1;  y >= sat_hi: every sigma is 0 (soft_sat_bounds)
   int W;
   int64_t plane;       // H * W
   int ox, oy, oz;      // origin of the wave's unit: coordinates are summed relative to it
@@ -56,8 +57,7 @@ struct Soft3Sink {
     const int yy = (int)(inpl / (unsigned)W), x = (int)(inpl - (unsigned)yy * (unsigned)W), z = oz + (int)zrel;
     const double y = (double)v + alpha * ((ux * (double)x + uy * (double)yy) + uz * (double)z);
     Soft3Staged e;
-    e.yh = (float)y;
-    e.yl = (float)(y - (double)e.yh);
+    e.y = y;
     e.c = (float)ci;
     e.inpl = inpl;
     e.rx = (float)(x - ox);
@@ -76,15 +76,16 @@ struct Soft3Sink {
     }
     float csat;
     int pos;
-    n = pack_entries(in && e.yh > sat_lo && e.yh < sat_hi, in && e.yh <= sat_lo, e.c, n, csat, pos);
-    if (in && e.yh > sat_lo && e.yh < sat_hi) stage[pos] = e;
+    const float yf = (float)y;
+    const bool keep = in && yf > sat_lo && yf < sat_hi;
+    n = pack_entries(keep, in && yf <= sat_lo, e.c, n, csat, pos);
+    if (keep) stage[pos] = e;
     if (!CHI) csat = 0.0f;  // (grad_X stays 0 at a saturated vertex)
     if (n == 0 && csat == 0.0f) return;
     const Soft3Staged* st = stage;
     const float g = eval.template run<kSoft3Slots>(n, csat, [st](int i, StagedValue& o, float (&r)[3]) {
       const Soft3Staged s = st[i];
-      o.yh = s.yh;
-      o.yl = s.yl;
+      o.y = s.y;
       o.c = s.c;
       r[0] = s.rx;
       r[1] = s.ry;
@@ -124,7 +125,7 @@ __device__ __forceinline__ void soft3d_sweep(s3::TubeQueue<Sink>& queue, const f
   s.alpha = (double)alpha;
   float lo, hi;
   threshold_span(tau, T, lo, hi);
-  soft_sat_bounds(lo, hi, kneg, s.sat_lo, s.sat_hi);
+  soft_sat_bounds(lo, hi, kneg, T, s.sat_lo, s.sat_hi);
   s.W = W;
   s.plane = (int64_t)H * W;
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wv), units = gridDim.x * 4;
@@ -209,8 +210,8 @@ __global__ __launch_bounds__(256) void soft3d_bwd_saved_kernel(const float* __re
                                                                SoftStateHeader expect) {
   const int item = blockIdx.y, unit = blockIdx.x, units = gridDim.x;
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
-  extern __shared__ float stau[];  // [T] thresholds, [T] upstream gradient
-  float* const sg = stau + T;
+  extern __shared__ double stau[];  // [T] thresholds, [T] upstream gradient (float)
+  float* const sg = reinterpret_cast<float*>(stau + T);
   __shared__ StagedEntry stage[256];
   __shared__ float sred[2][4];
   __shared__ int skept[4];
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(256) void soft3d_bwd_saved_kernel(const float* __re
   float lo = INFINITY, hi = -INFINITY;
   for (int j = threadIdx.x; j < T; j += 256) {
     const float t = tau[j];
-    stau[j] = t;
+    stau[j] = (double)t;
     sg[j] = gup ? gup[(int64_t)item * T + j] : 1.0f;
     lo = fminf(lo, t);
     hi = fmaxf(hi, t);
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(256) void soft3d_bwd_saved_kernel(const float* __re
   lo = fminf(fminf(sred[0][0], sred[0][1]), fminf(sred[0][2], sred[0][3]));
   hi = fmaxf(fmaxf(sred[1][0], sred[1][1]), fmaxf(sred[1][2], sred[1][3]));
   float sat_lo, sat_hi;
-  soft_sat_bounds(lo, hi, kneg, sat_lo, sat_hi);
+  soft_sat_bounds(lo, hi, kneg, T, sat_lo, sat_hi);
   float* gx = grad_X + (int64_t)item * N;
   if (!usable) {
     const float* g = grid + (int64_t)item * N;
@@ -258,10 +259,9 @@ __global__ __launch_bounds__(256) void soft3d_bwd_saved_kernel(const float* __re
       else c = coeff_at<float, 3>(g, D, H, W, z, y, x);
       if (c != 0) {
         const double yv = (double)g[i] + (double)alpha * ((ux * (double)x + uy * (double)y) + uz * (double)z);
-        const float yh = (float)yv, yl = (float)(yv - (double)yh);
-        if (yh > sat_lo && yh < sat_hi) {
+        if ((float)yv > sat_lo && (float)yv < sat_hi) {
           float gd = 0.0f;
-          for (int j = 0; j < T; ++j) gd += sg[j] * soft_dsig(stau[j], yh, yl, kneg);
+          for (int j = 0; j < T; ++j) gd += sg[j] * soft_dsig(stau[j], yv, kneg);
           gx[i] = -lambda * (float)c * gd;
         }
       }
@@ -396,7 +396,7 @@ void launch_soft3d_bwd_saved(const float* grid, const Shape& s, const float* u, 
   const StateView sv = state_view(const_cast<void*>(state), s.batch, (size_t)expect.units);
   launch_clear_f32(grad_X, s.N * s.batch, st);  // zero away from the critical vertices
   const dim3 g((unsigned)expect.units, (unsigned)s.batch);
-  const size_t lds = (size_t)T * 2 * sizeof(float);
+  const size_t lds = (size_t)T * (sizeof(double) + sizeof(float));
   if (tiltc)
     hipLaunchKernelGGL(soft3d_bwd_saved_kernel<true>, g, dim3(256), lds, st, grid, (int)s.D, (int)s.H, (int)s.W, s.N, u,
                        alpha, tau, T, kneg3d(lambda), lambda, gup, grad_X, sv, expect);

@@ -17,9 +17,10 @@
 
 namespace ecc {
 
-// z = (tau_j - yh) - yl is the float64 difference tau_j - y to within an ulp of z
+// z = tau_j - y is formed in float64 and rounded once
 struct StagedValue {
-  float yh, yl, c;
+  double y;
+  float c;
 };
 
 // NC: coordinates; CHI / DERIV: which sums a row holds, {chi} {A0, A_1 .. A_NC} in this order, STRIDE floats a
@@ -62,12 +63,13 @@ struct SoftEval {
   template <int S, typename Get>
   __device__ __forceinline__ float slots(int t0, int n, float csat, const Get& get) const {
     const int lane = threadIdx.x & (kWave - 1);
-    float tj[S], gj[S], acc[S][kSums > 0 ? kSums : 1], old[S][kSums > 0 ? kSums : 1];
+    double tj[S];
+    float gj[S], acc[S][kSums > 0 ? kSums : 1], old[S][kSums > 0 ? kSums : 1];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const int j = lane + kWave * (t0 + s);
       const bool ok = j < T;
-      tj[s] = ok ? tau[j] : 0.0f;
+      tj[s] = ok ? (double)tau[j] : 0.0;
       if (GRADX) gj[s] = ok ? (gup ? gup[j] : 1.0f) : 0.0f;
 #pragma unroll
       for (int k = 0; k < kSums; ++k) {
@@ -84,7 +86,7 @@ struct SoftEval {
       float gd = 0.0f;
 #pragma unroll
       for (int s = 0; s < S; ++s) {
-        const float ex = soft_exp_neg((tj[s] - v.yh) - v.yl, kneg);
+        const float ex = soft_exp_neg((float)(tj[s] - v.y), kneg);
         const float sg = __builtin_amdgcn_rcpf(1.0f + ex);
         if constexpr (CHI) acc[s][0] += v.c * sg;
         if constexpr (DERIV || GRADX) {

@@ -44,11 +44,12 @@ __device__ __forceinline__ bool state_usable(const StateView& v, const SoftState
 
 constexpr int kSavedLanes = 8;  // lanes per entry
 struct StagedEntry {
-  float yh, yl, c;
+  double y;
+  float c;
   int idx;
 };
-__device__ __forceinline__ float soft_dsig(float tau, float yh, float yl, float kneg) {  // sigma (1 - sigma)
-  const float ex = soft_exp_neg((tau - yh) - yl, kneg);
+__device__ __forceinline__ float soft_dsig(double tau, double y, float kneg) {  // sigma (1 - sigma)
+  const float ex = soft_exp_neg((float)(tau - y), kneg);
   const float s = __builtin_amdgcn_rcpf(1.0f + ex);
   return ex * s * s;
 }
@@ -60,7 +61,7 @@ __device__ __forceinline__ float soft_dsig(float tau, float yh, float yl, float 
 // first: entry number threadIdx.x of the list, requested by the caller ahead of time; stau / sg:
 // thresholds and upstream gradient in LDS; stage: 256 entries, skept: 4 ints of LDS.
 __device__ __forceinline__ void saved_lists_to_grad(const SavedEntry* __restrict__ list, unsigned cnt_raw, unsigned cap,
-                                                    const SavedEntry& first, const float* stau, const float* sg, int T,
+                                                    const SavedEntry& first, const double* stau, const float* sg, int T,
                                                     float kneg, float lambda, float sat_lo, float sat_hi,
                                                     float* __restrict__ gx, int64_t N, StagedEntry* stage, int* skept) {
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
@@ -73,11 +74,10 @@ __device__ __forceinline__ void saved_lists_to_grad(const SavedEntry* __restrict
     StagedEntry mine;
     if (e0 + threadIdx.x < cnt) {
       const SavedEntry en = e0 == 0 ? first : list[e0 + threadIdx.x];
-      mine.yh = (float)en.y;
-      mine.yl = (float)(en.y - (double)mine.yh);
+      mine.y = en.y;
       mine.c = (float)en.c;
       mine.idx = en.idx;
-      keep = mine.yh > sat_lo && mine.yh < sat_hi;
+      keep = (float)en.y > sat_lo && (float)en.y < sat_hi;
     }
     const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
     if (lane == 0) skept[wv] = __builtin_popcountll(m);
@@ -97,10 +97,10 @@ __device__ __forceinline__ void saved_lists_to_grad(const SavedEntry* __restrict
       float g0 = 0.0f, g1 = 0.0f;  // two independent chains
       int j = q;
       for (; j + kSavedLanes < T; j += 2 * kSavedLanes) {
-        g0 += sg[j] * soft_dsig(stau[j], en.yh, en.yl, kneg);
-        g1 += sg[j + kSavedLanes] * soft_dsig(stau[j + kSavedLanes], en.yh, en.yl, kneg);
+        g0 += sg[j] * soft_dsig(stau[j], en.y, kneg);
+        g1 += sg[j + kSavedLanes] * soft_dsig(stau[j + kSavedLanes], en.y, kneg);
       }
-      if (j < T) g0 += sg[j] * soft_dsig(stau[j], en.yh, en.yl, kneg);
+      if (j < T) g0 += sg[j] * soft_dsig(stau[j], en.y, kneg);
       float gd = g0 + g1;
       gd += dpp_move<0xB1, 0xf>(gd);   // quad_perm [1,0,3,2]
       gd += dpp_move<0x4E, 0xf>(gd);   // quad_perm [2,3,0,1]
