@@ -296,7 +296,7 @@ static size_t soft3d_partial_bytes(const Shape& s, const Plan3d& pl, int T) {
 
 size_t soft3d_workspace_bytes(const Shape& s, int T) {
   if (!soft3d_supported(s, T)) return 0;
-  const Plan3d pl = plan3d<float>(s, false);
+  const Plan3d pl = plan3d<float>(s);
   return (size_t)256 + soft3d_partial_bytes(s, pl, T) + soft_reduce_mid_bytes((int)pl.grid.x * 4, s.batch, T);
 }
 
@@ -306,7 +306,7 @@ static dim3 layered(const Plan3d& pl, const Shape& s, int T) {
 
 void launch_soft3d_fwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                        float lambda, float* chi, void* ws, hipStream_t st, bool tiltc) {
-  const Plan3d pl = plan3d<float>(s, false);
+  const Plan3d pl = plan3d<float>(s);
   float* partial = static_cast<float*>(ws);
 #define ECC_GO(TC)                                                                                          \
   hipLaunchKernelGGL(soft3d_fwd_kernel<TC>, layered(pl, s, T), dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
@@ -323,7 +323,7 @@ void launch_soft3d_fwd(const float* grid, const Shape& s, const float* u, float 
 void launch_soft3d_bwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                        float lambda, const float* gup, float* grad_X, float* dtau, float* du, void* ws,
                        hipStream_t st, bool tiltc) {
-  const Plan3d pl = plan3d<float>(s, false);
+  const Plan3d pl = plan3d<float>(s);
   float* partial = (dtau || du) ? static_cast<float*>(ws) : nullptr;
 #define ECC_GO(TC)                                                                                          \
   hipLaunchKernelGGL(soft3d_bwd_kernel<TC>, pl.grid, dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
@@ -347,7 +347,7 @@ static unsigned state_cap3(const Plan3d& pl) {
 static bool soft3d_saves(const Shape& s) { return soft3d_supported(s, 1) && s.N < ((int64_t)1 << 31); }
 size_t soft3d_state_bytes(const Shape& s) {
   if (!soft3d_saves(s)) return 256;
-  const Plan3d pl = plan3d<float>(s, false);
+  const Plan3d pl = plan3d<float>(s);
   return state_bytes(s.batch, (size_t)pl.grid.x * 4, state_cap3(pl));
 }
 bool soft3d_state_supported(const Shape& s, int T) { return soft3d_supported(s, T) && soft3d_saves(s); }
@@ -371,7 +371,7 @@ static SoftStateHeader state_header3(const Shape& s, const Plan3d& pl, bool tilt
 void launch_soft3d_fwd_save(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                             float lambda, float* chi, float* dtau, float* du, void* state, void* ws, hipStream_t st,
                             bool tiltc) {
-  const Plan3d pl = plan3d<float>(s, false);
+  const Plan3d pl = plan3d<float>(s);
   const SoftStateHeader hdr = state_header3(s, pl, tiltc);
   const StateView sv = state_view(state, s.batch, (size_t)hdr.units);
   float* partial = static_cast<float*>(ws);
@@ -391,7 +391,7 @@ void launch_soft3d_fwd_save(const float* grid, const Shape& s, const float* u, f
 void launch_soft3d_bwd_saved(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                              float lambda, const float* gup, float* grad_X, const void* state, hipStream_t st,
                              bool tiltc) {
-  const Plan3d pl = plan3d<float>(s, false);
+  const Plan3d pl = plan3d<float>(s);
   const SoftStateHeader expect = state_header3(s, pl, tiltc);
   const StateView sv = state_view(const_cast<void*>(state), s.batch, (size_t)expect.units);
   launch_clear_f32(grad_X, s.N * s.batch, st);  // zero away from the critical vertices

@@ -655,9 +655,8 @@ struct Plan3d {
   int nstrip, ngroup, nseg, planes_per_seg;
   dim3 grid;
 };
-// histogram: the sweep bins into a histogram (see the shortest segments below)
 template <typename T>
-static Plan3d plan3d(const Shape& s, bool histogram) {
+static Plan3d plan3d(const Shape& s) {
   constexpr int R = kRows3d;
   Plan3d p;
   const int D = (int)s.D, H = (int)s.H, W = (int)s.W;
@@ -683,18 +682,18 @@ static Plan3d plan3d(const Shape& s, bool histogram) {
     int64_t pl = (D + want - 1) / want;
     pl = (pl + 1) & ~(int64_t)1;
     if (pl < 12) pl = 12;
-    // Two full waves a SIMD with 24 planes do better than more waves with shorter segments, which read three extra
-    // planes each (us a call at the planes the line above gives / at 24: 193 x 229 x 193 int16 36.3 (18) / 31.2, pair of
-    // soft calls on 256^3 97.3 (20) / 92.2, 256^3 float32 48.5 (20) / 47.2; but 256^3 of independent uint16 levels 66.6
-    // (20) / 72.4: where most vertices may be critical, a histogram, 20 planes stay).
-    if (pl < (histogram ? 20 : 24) && per_seg * ((D + 23) / 24) >= 2048) pl = 24;
     if (pl < planes) planes = pl;
   }
-  // one-chunk segments of equal length (64 x 64^3: 64.3 us with 30 + 30 + 4 planes, 59.2 with 22 + 22 + 20; 16 x 128^3 68.0
-  // -> 63.5)
-  if (planes == s3::kChunk) {
+  // Segments of equal length: the call lasts as long as its longest one (64 x 64^3 float32: 65.4 us with 30 + 30 + 4
+  // planes, 59.4 with 22 + 22 + 20; 16 x 128^3 68.4 -> 63.4).  Not where that takes less than an eighth off full chunks:
+  // launches of many rounds of waves then lose more from the missing short last segments, which fill the gaps at the
+  // end (8 directions of 193 x 229 x 193: 118.6 us with 30 planes, 128.0 with 28).  Longer segments for small launches
+  // were measured and not taken: 24 planes instead of 12 make 193 x 229 x 193 float32 5 us faster on smooth fields (39.2
+  // -> 34.2) and 36 us slower on white noise (85 -> 121), where a wave's march is the draining of its vertices.
+  if (planes <= s3::kChunk) {
     const int64_t n = (D + planes - 1) / planes;
-    planes = ((D + n - 1) / n + 1) & ~(int64_t)1;
+    const int64_t equal = ((D + n - 1) / n + 1) & ~(int64_t)1;
+    if (planes < s3::kChunk || equal <= 26) planes = equal;
   }
   int64_t fit = (((int64_t)1 << 32) - 1) / ((int64_t)H * W);
   if (fit > (1 << 24) - 1) fit = (1 << 24) - 1;

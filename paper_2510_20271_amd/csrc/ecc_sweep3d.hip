@@ -92,7 +92,7 @@ static void launch3d_t(const void* grid, const Shape& s, bool levels, int bins, 
                        const float* table, unsigned long long* hist, hipStream_t st,
                        const unsigned* run_if, const DirArgs* dir, int conv) {
   constexpr int R = kRows3d;
-  const Plan3d pl = plan3d<T>(s, true);
+  const Plan3d pl = plan3d<T>(s);
   const bool tlds = !levels && (size_t)bins * 8 + kFixedLds3d <= 60 * 1024;
   const size_t lds = kFixedLds3d + (size_t)bins * (tlds ? 8 : 4);
   const T* p = static_cast<const T*>(grid);
@@ -129,7 +129,7 @@ static void launch3d_t(const void* grid, const Shape& s, bool levels, int bins, 
 template <typename T>
 static void launch3d_list_t(const void* grid, const Shape& s, const ListArgs& la, hipStream_t st, const DirArgs* dir,
                             int conv) {
-  const Plan3d pl = plan3d<T>(s, false);
+  const Plan3d pl = plan3d<T>(s);
   const DirArgs none = {nullptr, 0.f, 1, 3};
   const T* p = static_cast<const T*>(grid);
 #define ECC_LIST(M, DIR)                                                                                  \
@@ -161,10 +161,10 @@ void launch_sweep3d_list(const void* grid, int dtype, const Shape& s, const List
   }
 }
 
-unsigned sweep3d_list_blocks(const Shape& s) { return plan3d<float>(s, false).grid.x; }
+unsigned sweep3d_list_blocks(const Shape& s) { return plan3d<float>(s).grid.x; }
 unsigned sweep3d_block_vertices(const Shape& s) {
   // four wave units of at most 62 columns x 4 rows (a folded unit: several row groups of fewer columns) x the segment's planes
-  const int64_t planes = std::min<int64_t>(s.D, plan3d<float>(s, false).planes_per_seg);
+  const int64_t planes = std::min<int64_t>(s.D, plan3d<float>(s).planes_per_seg);
   return 4u * (unsigned)s3::kOut * (unsigned)kRows3d * (unsigned)planes;
 }
 
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(256) void coeff3d_kernel(const T* __restrict__ grid
 
 template <typename T>
 static void launch_coeff3d_t(const void* grid, const Shape& s, int8_t* out, hipStream_t st) {
-  const Plan3d pl = plan3d<T>(s, false);
+  const Plan3d pl = plan3d<T>(s);
   hipLaunchKernelGGL((coeff3d_kernel<T, kRows3d>), pl.grid, dim3(256), kFixedLds3d, st, static_cast<const T*>(grid),
                      (int)s.D, (int)s.H, (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, out);
 }
