@@ -346,14 +346,23 @@ static bool use_soft3d(const Shape& s, int T) {
 
 static float kneg_of(float lambda) { return (float)(-(double)lambda * 1.4426950408889634); }
 
+// The forward pass alone over a large batch of small items with many thresholds: a tile block spreads its list over
+// 256 threads, a wave unit of the sweep holds a few hundred vertices and walks all thresholds by itself.  us fused / tiles:
+// 1024 x 28^2 30.5 / 24.8 at T = 512, 2000 x 20^2 43 / 27, 8192 x 16^2 139 / 66, 300 x 100^2 at T = 1024 124 / 109; but
+// 256 x 28^2 14.3 / 20.0, 512 x 64^2 46.0 / 47.1, 512 x 20^3 75 / 103 at T = 512.  With the derivatives the fused kernels win.
+static bool tiles_forward(const Shape& s, int T) {
+  return T > 256 && s.batch * tiles_of(s) >= 1024 && (s.N <= 1024 || (T > 512 && s.N <= 16384));
+}
+
 hipError_t launch_soft_fwd(const float* grid, const Shape& s, const float* u, float alpha,
                            const float* tau, int T, float lambda, float* chi, void* ws,
                            hipStream_t st, bool tiltc) {
-  if (use_soft2d(s, T)) {
+  const bool tiles = tiles_forward(s, T);
+  if (!tiles && use_soft2d(s, T)) {
     launch_soft2d_fwd(grid, s, u, alpha, tau, T, lambda, chi, ws, st, tiltc);
     return hipGetLastError();
   }
-  if (use_soft3d(s, T)) {
+  if (!tiles && use_soft3d(s, T)) {
     launch_soft3d_fwd(grid, s, u, alpha, tau, T, lambda, chi, ws, st, tiltc);
     return hipGetLastError();
   }

@@ -8,7 +8,7 @@
 // is split: block (x = group of 64 thresholds, y = item, z = slice) of 16 waves adds the units of
 // its slice -- wave w takes units begin + w, begin + w + 16, ... in order, then wave 0 adds the 16
 // sums in order -- and, when there is more than one slice, leaves the slice's sums in `mid`, which
-// a second kernel adds in slice order.
+// a second kernel adds in slice order.  Items of at most four units take blocks of one wave instead.
 #pragma once
 #include "ecc_device.h"
 #include "ecc_internal.h"
@@ -57,20 +57,20 @@ __device__ __forceinline__ void red_stamp(const RedOut& o) {
 }
 
 // Origin: unit -> origin of its coordinates, `void operator()(int unit, int (&o)[3]) const`
-template <int STRIDE, bool CHI, int NC, typename Origin>
-__global__ __launch_bounds__(kRedWaves * kWave) void soft_reduce_kernel(const float* __restrict__ partial, int units,
+template <int WAVES, int STRIDE, bool CHI, int NC, typename Origin>
+__global__ __launch_bounds__(WAVES * kWave) void soft_reduce_kernel(const float* __restrict__ partial, int units,
                                                                         int per_slice, int T, float alpha, float lambda,
                                                                         Origin origin, double* __restrict__ mid,
                                                                         RedOut out) {
   constexpr int NS = RedLayout<CHI, NC>::kSums, A = RedLayout<CHI, NC>::kA;
-  __shared__ double red[NS][kRedWaves][kWave];
+  __shared__ double red[NS][WAVES][kWave];
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
   const int j = blockIdx.x * kWave + lane;
   const int item = blockIdx.y, slice = blockIdx.z;
   const int begin = slice * per_slice, end = min(units, begin + per_slice);
   double s[kRedMaxSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
   if (j < T) {
-    for (int q = begin + wv; q < end; q += kRedWaves) {
+    for (int q = begin + wv; q < end; q += WAVES) {
       float e[STRIDE];
       const float* p = partial + (((int64_t)item * units + q) * T + j) * STRIDE;
       if constexpr (STRIDE == 4) {
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kRedWaves * kWave) void soft_reduce_kernel(const fl
     double r[kRedMaxSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
     for (int c = 0; c < NS; ++c) {
       r[c] = red[c][0][lane];
-      for (int w = 1; w < kRedWaves; ++w) r[c] += red[c][w][lane];
+      for (int w = 1; w < WAVES; ++w) r[c] += red[c][w][lane];
     }
     if (gridDim.z == 1) {
       red_finish<CHI, NC>(r, (int64_t)item * T + j, alpha, lambda, out);
@@ -154,8 +154,13 @@ static void launch_soft_reduce(const float* partial, double* mid, int units, int
   int per;
   const int slices = soft_reduce_slices(units, per);
   const unsigned tg = (unsigned)((T + kWave - 1) / kWave);
-  hipLaunchKernelGGL((soft_reduce_kernel<STRIDE, CHI, NC, Origin>), dim3(tg, (unsigned)batch, (unsigned)slices),
-                     dim3(kRedWaves * kWave), 0, st, partial, units, per, T, alpha, lambda, origin, mid, out);
+  const dim3 grid(tg, (unsigned)batch, (unsigned)slices);
+  if (units <= 4)  // small items: one wave adds them all (1024 x 28^2, T = 512, forward: 33 us with blocks of 16 waves, 25 now)
+    hipLaunchKernelGGL((soft_reduce_kernel<1, STRIDE, CHI, NC, Origin>), grid, dim3(kWave), 0, st, partial, units, per, T,
+                       alpha, lambda, origin, mid, out);
+  else
+    hipLaunchKernelGGL((soft_reduce_kernel<kRedWaves, STRIDE, CHI, NC, Origin>), grid, dim3(kRedWaves * kWave), 0, st, partial,
+                       units, per, T, alpha, lambda, origin, mid, out);
   if (slices > 1)
     hipLaunchKernelGGL((soft_reduce_final_kernel<CHI, NC>), dim3(tg, (unsigned)batch), dim3(kRedWaves * kWave), 0, st, mid,
                        slices, T, alpha, lambda, out);

@@ -40,3 +40,39 @@ def test_layers(T, shape):
     _near(host(a), gx, 1e-3)  # (every element written, by the sweep's own clearing where c = 0)
     _near(host(t), dt, 1e-3)
     _near(host(d), du, 1e-3)
+
+
+@pytest.mark.parametrize("shape,T", [((16, 217, 181), 449), ((16, 217, 181), 513), ((5, 300, 500), 300),
+                                     ((6, 40, 60, 70), 513), ((6, 40, 60, 70), 300)])
+def test_fewer_layers_than_slots(shape, T):
+    """Several hundred wave units: more than one layer and several groups of 64 thresholds in each, the last layer
+    shorter."""
+    nd = len(shape) - 1
+    X = synth.grf_batch(shape[0], shape[1:], 2.0, T)
+    u = np.array([0.6, 0.8] if nd == 2 else [0.48, 0.6, 0.64], dtype=np.float32)
+    tau = np.linspace(float(X.min()), float(X.max()), T).astype(np.float32)
+    alpha, lam = 0.01, 20.0
+    g, ud, td = dev(X), dev(u), dev(tau)
+    chi = O.soft_fwd_batch(X, u, alpha, tau, lam)
+    gx, dt, du = O.soft_bwd_batch(X, u, alpha, tau, lam)
+    _near(host(api.ecc_soft_fwd(g, nd, ud, alpha, td, lam)), chi, 1e-4)
+    c, t, d, state = api.ecc_soft_fwd_save(g, nd, ud, alpha, td, lam)
+    _near(host(c), chi, 1e-4)
+    _near(host(t), dt, 1e-3)
+    _near(host(d), du, 1e-3)
+    _near(host(api.ecc_soft_bwd_saved(g, nd, ud, alpha, td, lam, state)), gx, 1e-3)
+
+
+@pytest.mark.parametrize("shape,T", [((1100, 9, 13), 257), ((1024, 31, 33), 300), ((600, 70, 50), 513),
+                                     ((1024, 9, 10, 11), 290)])
+def test_forward_of_a_large_batch_of_small_items(shape, T):
+    """The forward pass alone (tile kernels there) against the one that saves (fused): float32 sums of a few hundred
+    terms of size <= 6, grouped differently."""
+    nd = len(shape) - 1
+    X = torch.randn(shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(T))
+    u = dev(np.array([0.6, 0.8] if nd == 2 else [0.48, 0.6, 0.64], dtype=np.float32))
+    tau = torch.linspace(-3.0, 3.0, T, device="cuda")
+    for tilted in (False, True):
+        a = api.ecc_soft_fwd(X, nd, u, 0.01, tau, 20.0, tilted_c=tilted)
+        b = api.ecc_soft_fwd_save(X, nd, u, 0.01, tau, 20.0, tilted_c=tilted, want=())[0]
+        assert float((a - b).abs().max()) <= 1e-4 * float(b.abs().max())
