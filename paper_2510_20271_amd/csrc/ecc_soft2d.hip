@@ -37,14 +37,14 @@ struct SoftEntry {
   unsigned rel;  // row - row0 << 12 | column - col0 << 4 | c & 15
 };
 struct SoftStaged {
-  double y;  // X(p) + alpha <u,p>
+  double y;  // X(p) + alpha <u,p>, packed (see SoftArg)
   float c;
   unsigned rel;
 };
 
 // CHI / DERIV / GRADX: what is formed (see ecc_soft_eval.h); SAVE: every entry is also appended to the unit's list
 // in the state buffer.  ZERO: the sweep clears grad_X row by row.
-template <bool CHI, bool DERIV, bool GRADX, bool SAVE, int STRIDE>
+template <bool CHI, bool DERIV, bool GRADX, bool SAVE, int STRIDE, bool WIDE>
 struct SoftSink {
   typedef SoftEntry Entry;
   static constexpr bool kTrackRange = false;
@@ -57,7 +57,7 @@ struct SoftSink {
   int W;
   int col0, row0;     // origin of the wave's unit: coordinates are summed relative to it
   SoftStaged* stage;  // wave-private LDS, 64 entries
-  SoftEval<2, CHI, DERIV, GRADX, STRIDE> eval;
+  SoftEval<2, CHI, DERIV, GRADX, STRIDE, WIDE> eval;
   float* gx;          // GRADX: grad_X of this item or null
   float lambda;
   SavedEntry* list;     // SAVE: this unit's list
@@ -92,7 +92,7 @@ struct SoftSink {
     if (xsrc) v = xsrc[(int64_t)row * W + col];  // wave-uniform condition
     const double y = (double)v + alpha * (ux * (double)col + uy * (double)row);
     SoftStaged e;
-    e.y = y;
+    e.y = SoftArg<WIDE>::pack(y);
     e.c = (float)ci;
     e.rel = q.rel;
     if constexpr (SAVE) {
@@ -189,18 +189,18 @@ __device__ __forceinline__ void soft2d_sweep(WaveQueue<Sink>& queue, const float
 }
 
 // partial[(item * units + unit) * T + j]
-template <bool TILTC>
+template <bool TILTC, bool WIDE>
 __global__ __launch_bounds__(256, 4) void soft2d_fwd_kernel(const float* __restrict__ grid, int H, int W,
                                                          int64_t N, int nstrip, int nseg, int rows_per_seg,
                                                          const float* __restrict__ u, float alpha,
                                                          const float* __restrict__ tau, int T, float kneg,
                                                          float* __restrict__ partial) {
-  WaveQueue<SoftSink<true, false, false, false, 1>> queue;
+  WaveQueue<SoftSink<true, false, false, false, 1, WIDE>> queue;
   soft2d_sweep<TILTC, 1>(queue, grid, H, W, N, nstrip, nseg, rows_per_seg, u, alpha, tau, T, kneg, nullptr, partial);
 }
 
 // partial[((item * units + unit) * T + j) * 4 + {0: A0, 1: Ax, 2: Ay}]
-template <bool TILTC>
+template <bool TILTC, bool WIDE>
 __global__ __launch_bounds__(256, 4) void soft2d_bwd_kernel(const float* __restrict__ grid, int H, int W,
                                                          int64_t N, int nstrip, int nseg, int rows_per_seg,
                                                          const float* __restrict__ u, float alpha,
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256, 4) void soft2d_bwd_kernel(const float* __restr
                                                          float lambda, const float* __restrict__ gup,
                                                          float* __restrict__ grad_X,
                                                          float* __restrict__ partial) {
-  WaveQueue<SoftSink<false, true, true, false, 4>> queue;
+  WaveQueue<SoftSink<false, true, true, false, 4, WIDE>> queue;
   queue.sink.gx = grad_X ? grad_X + (int64_t)blockIdx.y * N : nullptr;
   queue.sink.lambda = lambda;
   soft2d_sweep<TILTC, 4>(queue, grid, H, W, N, nstrip, nseg, rows_per_seg, u, alpha, tau, T, kneg, gup, partial);
@@ -217,14 +217,14 @@ __global__ __launch_bounds__(256, 4) void soft2d_bwd_kernel(const float* __restr
 // Forward pass that saves its critical vertices: chi as soft2d_fwd_kernel, with DERIV the sums of Eq. 9 / Eq. 10 in
 // the same pass (they share the sigmoid), and every entry appended to the unit's own list in the state buffer.
 // partial[((item * units + unit) * T + j) * 4 + {0: chi, 1: A0, 2: Ax, 3: Ay}]
-template <bool TILTC, bool DERIV>
+template <bool TILTC, bool DERIV, bool WIDE>
 __global__ __launch_bounds__(256, 4) void soft2d_fwd_save_kernel(const float* __restrict__ grid, int H, int W, int64_t N,
                                                               int nstrip, int nseg, int rows_per_seg,
                                                               const float* __restrict__ u, float alpha,
                                                               const float* __restrict__ tau, int T, float kneg,
                                                               float* __restrict__ partial, StateView sv, unsigned cap) {
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), units = nstrip * nseg;
-  WaveQueue<SoftSink<true, DERIV, false, true, 4>> queue;
+  WaveQueue<SoftSink<true, DERIV, false, true, 4, WIDE>> queue;
   queue.sink.cap = blockIdx.z == 0 ? cap : 0u;  // (the first layer keeps the list)
   queue.sink.saved = 0u;
   queue.sink.list = sv.lists + ((size_t)blockIdx.y * units + (unit < units ? unit : 0)) * cap;
@@ -256,7 +256,7 @@ struct Origin2 {
 // the call lasts as long as its busiest unit.
 // An item whose lists cannot be used (header of another shape, a unit ran out of room) is
 // computed from the grid instead, vertex by vertex with the plain stencil: slow, but rare.
-template <bool TILTC>
+template <bool TILTC, bool WIDE>
 __global__ __launch_bounds__(256) void soft2d_bwd_saved_kernel(const float* __restrict__ grid, int H, int W, int64_t N,
                                                                int nstrip, int nseg, int rows_per_seg,
                                                                const float* __restrict__ u, float alpha,
@@ -266,7 +266,9 @@ __global__ __launch_bounds__(256) void soft2d_bwd_saved_kernel(const float* __re
                                                                SoftStateHeader expect) {
   const int item = blockIdx.y, unit = blockIdx.x, units = nstrip * nseg;
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
-  extern __shared__ double stau[];  // [T] thresholds, [T] upstream gradient (float)
+  typedef typename SoftArg<WIDE>::Tau Tau;
+  extern __shared__ double lds[];  // [T] thresholds, [T] upstream gradient
+  Tau* const stau = reinterpret_cast<Tau*>(lds);
   float* const sg = reinterpret_cast<float*>(stau + T);
   __shared__ StagedEntry stage[256];
   __shared__ float sred[2][4];
@@ -281,7 +283,7 @@ __global__ __launch_bounds__(256) void soft2d_bwd_saved_kernel(const float* __re
   float lo = INFINITY, hi = -INFINITY;
   for (int j = threadIdx.x; j < T; j += 256) {
     const float t = tau[j];
-    stau[j] = (double)t;
+    stau[j] = t;
     sg[j] = gup ? gup[(int64_t)item * T + j] : 1.0f;
     lo = fminf(lo, t);
     hi = fmaxf(hi, t);
@@ -332,8 +334,9 @@ __global__ __launch_bounds__(256) void soft2d_bwd_saved_kernel(const float* __re
         if (c != 0) {
           const double yv = (double)g[(int64_t)y * W + x] + (double)alpha * (ux * (double)x + uy * (double)y);
           if ((float)yv > sat_lo && (float)yv < sat_hi) {
+            const double packed = SoftArg<WIDE>::pack(yv);
             float gd = 0.0f;
-            for (int j = 0; j < T; ++j) gd += sg[j] * soft_dsig(stau[j], yv, kneg);
+            for (int j = 0; j < T; ++j) gd += sg[j] * soft_dsig<WIDE>(stau[j], packed, kneg);
             out = -lambda * (float)c * gd;
           }
         }
@@ -343,7 +346,7 @@ __global__ __launch_bounds__(256) void soft2d_bwd_saved_kernel(const float* __re
     return;
   }
 
-  saved_lists_to_grad(list, cnt_raw, expect.cap, first, stau, sg, T, kneg, lambda, sat_lo, sat_hi, gx, N, stage, skept);
+  saved_lists_to_grad<WIDE>(list, cnt_raw, expect.cap, first, stau, sg, T, kneg, lambda, sat_lo, sat_hi, gx, N, stage, skept);
 }
 
 static float kneg2d(float lambda) { return (float)(-(double)lambda * 1.4426950408889634); }
@@ -377,12 +380,11 @@ void launch_soft2d_fwd(const float* grid, const Shape& s, const float* u, float 
   const Plan2d pl = plan2d<float>(s, Feed2d::kSigmoid);
   float* partial = static_cast<float*>(ws);
   profile_mark(st, false);
-  if (tiltc)
-    hipLaunchKernelGGL(soft2d_fwd_kernel<true>, layered(pl, s, T), dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, s.N,
-                       pl.nstrip, pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), partial);
-  else
-    hipLaunchKernelGGL(soft2d_fwd_kernel<false>, layered(pl, s, T), dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, s.N,
-                       pl.nstrip, pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), partial);
+#define ECC_GO(TC, WD)                                                                                                 \
+  hipLaunchKernelGGL((soft2d_fwd_kernel<TC, WD>), layered(pl, s, T), dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, \
+                     s.N, pl.nstrip, pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), partial)
+  ECC_SOFT_VARIANT(tiltc, soft_wide(T));
+#undef ECC_GO
   profile_mark(st, true);
   const RedOut out = {chi, nullptr, nullptr, nullptr, nullptr, {}};
   launch_soft_reduce<1, true, -1>(partial, soft2d_mid(ws, s, pl, T), pl.nstrip * pl.nseg, s.batch, T, alpha, lambda,
@@ -395,14 +397,12 @@ void launch_soft2d_bwd(const float* grid, const Shape& s, const float* u, float 
   const Plan2d pl = plan2d<float>(s, Feed2d::kSigmoid);
   float* partial = (dtau || du) ? static_cast<float*>(ws) : nullptr;
   profile_mark(st, false);
-  if (tiltc)
-    hipLaunchKernelGGL(soft2d_bwd_kernel<true>, pl.grid, dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, s.N,
-                       pl.nstrip, pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), lambda, gup,
-                       grad_X, partial);
-  else
-    hipLaunchKernelGGL(soft2d_bwd_kernel<false>, pl.grid, dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, s.N,
-                       pl.nstrip, pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), lambda, gup,
-                       grad_X, partial);
+#define ECC_GO(TC, WD)                                                                                          \
+  hipLaunchKernelGGL((soft2d_bwd_kernel<TC, WD>), pl.grid, dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, s.N, \
+                     pl.nstrip, pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), lambda, gup, grad_X,  \
+                     partial)
+  ECC_SOFT_VARIANT(tiltc, soft_wide(T));
+#undef ECC_GO
   profile_mark(st, true);
   if (partial) {
     const RedOut out = {nullptr, dtau, du, nullptr, nullptr, {}};
@@ -436,11 +436,13 @@ void launch_soft2d_fwd_save(const float* grid, const Shape& s, const float* u, f
   float* partial = static_cast<float*>(ws);
   const bool deriv = dtau || du;
   profile_mark(st, false);
-#define ECC_GO(TC, DV)                                                                                        \
-  hipLaunchKernelGGL((soft2d_fwd_save_kernel<TC, DV>), layered(pl, s, T), dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, \
-                     s.N, pl.nstrip, pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), partial, sv, hdr.cap)
-  if (tiltc) { if (deriv) ECC_GO(true, true); else ECC_GO(true, false); }
-  else       { if (deriv) ECC_GO(false, true); else ECC_GO(false, false); }
+#define ECC_GO3(TC, DV, WD)                                                                                   \
+  hipLaunchKernelGGL((soft2d_fwd_save_kernel<TC, DV, WD>), layered(pl, s, T), dim3(256), kSoftLds, st, grid, (int)s.H, \
+                     (int)s.W, s.N, pl.nstrip, pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), partial, sv, \
+                     hdr.cap)
+#define ECC_GO(TC, WD) do { if (deriv) ECC_GO3(TC, true, WD); else ECC_GO3(TC, false, WD); } while (0)
+  ECC_SOFT_VARIANT(tiltc, soft_wide(T));
+#undef ECC_GO3
 #undef ECC_GO
   profile_mark(st, true);
   const RedOut out = {chi, dtau, du, sv.hdr, sv.gen, hdr};
@@ -455,14 +457,13 @@ void launch_soft2d_bwd_saved(const float* grid, const Shape& s, const float* u, 
   const StateView sv = state_view(const_cast<void*>(state), s.batch, (size_t)pl.nstrip * pl.nseg);
   const SoftStateHeader expect = state_header(s, pl, tiltc);
   const dim3 g((unsigned)(pl.nstrip * pl.nseg), (unsigned)s.batch);
-  const size_t lds = (size_t)T * (sizeof(double) + sizeof(float));
+  const size_t lds = (size_t)T * (soft_wide(T) ? sizeof(double) + sizeof(float) : 2 * sizeof(float));
   profile_mark(st, false);
-  if (tiltc)
-    hipLaunchKernelGGL(soft2d_bwd_saved_kernel<true>, g, dim3(256), lds, st, grid, (int)s.H, (int)s.W, s.N, pl.nstrip,
-                       pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), lambda, gup, grad_X, sv, expect);
-  else
-    hipLaunchKernelGGL(soft2d_bwd_saved_kernel<false>, g, dim3(256), lds, st, grid, (int)s.H, (int)s.W, s.N, pl.nstrip,
-                       pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), lambda, gup, grad_X, sv, expect);
+#define ECC_GO(TC, WD)                                                                                              \
+  hipLaunchKernelGGL((soft2d_bwd_saved_kernel<TC, WD>), g, dim3(256), lds, st, grid, (int)s.H, (int)s.W, s.N, pl.nstrip, \
+                     pl.nseg, pl.rows_per_seg, u, alpha, tau, T, kneg2d(lambda), lambda, gup, grad_X, sv, expect)
+  ECC_SOFT_VARIANT(tiltc, soft_wide(T));
+#undef ECC_GO
   profile_mark(st, true);
 }
 

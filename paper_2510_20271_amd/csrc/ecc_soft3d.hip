@@ -21,11 +21,15 @@
 
 namespace ecc {
 
-constexpr int kSoft3Slots = 1;  // slots of 64 thresholds taken together
-constexpr int kSoft3Waves = 4;  // waves on a SIMD that the registers are kept within
+// MANY: see many_thresholds below.  Slots of 64 thresholds taken together, and waves on a SIMD that the registers are kept
+// within.  Four waves leave 128 registers: the kernels spill 5 to 22 of them around a drain (32 to 76 bytes of scratch a
+// lane) and are the faster all the same where the sweep is what takes the time; the tilted forward kernel is not (8 x 96^3,
+// T = 64: 27.6 us with four waves, 23.1 with three) and takes three.
+constexpr int soft3_slots(bool many) { return many ? 4 : 1; }
+constexpr int soft3_waves(bool many) { return many ? 3 : 4; }
 
 struct Soft3Staged {
-  double y;         // X(p) + alpha <u,p>
+  double y;         // X(p) + alpha <u,p>, packed (see SoftArg)
   float c;
   unsigned inpl;    // element offset inside the plane
   float rx, ry, rz; // coordinates relative to the unit's origin
@@ -34,7 +38,7 @@ struct Soft3Staged {
 
 // CHI / DERIV / GRADX: what is formed (see ecc_soft_eval.h); SAVE: every entry is also appended to the unit's list
 // in the state buffer (sweep order, no atomics: the same on every run).
-template <bool CHI, bool DERIV, bool GRADX, bool SAVE, int STRIDE>
+template <bool CHI, bool DERIV, bool GRADX, bool SAVE, int STRIDE, bool MANY>
 struct Soft3Sink {
   static constexpr bool kTrackRange = false;
   static constexpr bool kZeroFill = GRADX;
@@ -44,7 +48,7 @@ struct Soft3Sink {
   int64_t plane;       // H * W
   int ox, oy, oz;      // origin of the wave's unit: coordinates are summed relative to it
   Soft3Staged* stage;  // wave-private LDS, 64 entries
-  SoftEval<3, CHI, DERIV, GRADX, STRIDE> eval;
+  SoftEval<3, CHI, DERIV, GRADX, STRIDE, MANY> eval;
   float* gx;           // GRADX: grad_X of this item or null
   float lambda;
   SavedEntry* list;     // SAVE: this unit's list
@@ -57,7 +61,7 @@ struct Soft3Sink {
     const int yy = (int)(inpl / (unsigned)W), x = (int)(inpl - (unsigned)yy * (unsigned)W), z = oz + (int)zrel;
     const double y = (double)v + alpha * ((ux * (double)x + uy * (double)yy) + uz * (double)z);
     Soft3Staged e;
-    e.y = y;
+    e.y = SoftArg<MANY>::pack(y);
     e.c = (float)ci;
     e.inpl = inpl;
     e.rx = (float)(x - ox);
@@ -83,7 +87,7 @@ struct Soft3Sink {
     if (!CHI) csat = 0.0f;  // (grad_X stays 0 at a saturated vertex)
     if (n == 0 && csat == 0.0f) return;
     const Soft3Staged* st = stage;
-    const float g = eval.template run<kSoft3Slots>(n, csat, [st](int i, StagedValue& o, float (&r)[3]) {
+    const float g = eval.template run<soft3_slots(MANY)>(n, csat, [st](int i, StagedValue& o, float (&r)[3]) {
       const Soft3Staged s = st[i];
       o.y = s.y;
       o.c = s.c;
@@ -149,26 +153,26 @@ __device__ __forceinline__ void soft3d_sweep(s3::TubeQueue<Sink>& queue, const f
 }
 
 // partial[(item * units + unit) * T + j]
-template <bool TILTC>
-__global__ __launch_bounds__(256, kSoft3Waves) void soft3d_fwd_kernel(const float* __restrict__ grid, int D, int H, int W,
+template <bool TILTC, bool MANY>
+__global__ __launch_bounds__(256, soft3_waves(MANY || TILTC)) void soft3d_fwd_kernel(const float* __restrict__ grid, int D, int H, int W,
                                                             int64_t N, int nstrip, int ngroup, int nseg,
                                                             int planes_per_seg, const float* __restrict__ u,
                                                             float alpha, const float* __restrict__ tau, int T,
                                                             float kneg, float* __restrict__ partial) {
-  s3::TubeQueue<Soft3Sink<true, false, false, false, 1>> queue;
+  s3::TubeQueue<Soft3Sink<true, false, false, false, 1, MANY>> queue;
   soft3d_sweep<TILTC, 1>(queue, grid, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, u, alpha, tau, T, kneg, nullptr,
                          partial);
 }
 
 // partial[((item * units + unit) * T + j) * 4 + {0: A0, 1: Ax, 2: Ay, 3: Az}]
-template <bool TILTC>
-__global__ __launch_bounds__(256, kSoft3Waves) void soft3d_bwd_kernel(const float* __restrict__ grid, int D, int H, int W,
+template <bool TILTC, bool MANY>
+__global__ __launch_bounds__(256, soft3_waves(MANY)) void soft3d_bwd_kernel(const float* __restrict__ grid, int D, int H, int W,
                                                             int64_t N, int nstrip, int ngroup, int nseg,
                                                             int planes_per_seg, const float* __restrict__ u,
                                                             float alpha, const float* __restrict__ tau, int T,
                                                             float kneg, float lambda, const float* __restrict__ gup,
                                                             float* __restrict__ grad_X, float* __restrict__ partial) {
-  s3::TubeQueue<Soft3Sink<false, true, true, false, 4>> queue;
+  s3::TubeQueue<Soft3Sink<false, true, true, false, 4, MANY>> queue;
   queue.sink.gx = grad_X ? grad_X + (int64_t)blockIdx.y * N : nullptr;
   queue.sink.lambda = lambda;
   soft3d_sweep<TILTC, 4>(queue, grid, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, u, alpha, tau, T, kneg, gup,
@@ -178,13 +182,13 @@ __global__ __launch_bounds__(256, kSoft3Waves) void soft3d_bwd_kernel(const floa
 // Forward pass that saves its critical vertices: chi as soft3d_fwd_kernel, with DERIV the sums of Eq. 9 / Eq. 10 in
 // the same pass (they share the sigmoid), and the unit's list.
 // partial[((item * units + unit) * T + j) * 5 + {0: chi, 1: A0, 2: Ax, 3: Ay, 4: Az}]
-template <bool TILTC, bool DERIV>
-__global__ __launch_bounds__(256, kSoft3Waves) void soft3d_fwd_save_kernel(
+template <bool TILTC, bool DERIV, bool MANY>
+__global__ __launch_bounds__(256, soft3_waves(MANY)) void soft3d_fwd_save_kernel(
     const float* __restrict__ grid, int D, int H, int W, int64_t N, int nstrip, int ngroup, int nseg, int planes_per_seg,
     const float* __restrict__ u, float alpha, const float* __restrict__ tau, int T, float kneg,
     float* __restrict__ partial, StateView sv, unsigned cap) {
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), units = gridDim.x * 4;
-  s3::TubeQueue<Soft3Sink<true, DERIV, false, true, 5>> queue;
+  s3::TubeQueue<Soft3Sink<true, DERIV, false, true, 5, MANY>> queue;
   queue.sink.cap = blockIdx.z == 0 ? cap : 0u;  // (the first layer keeps the list)
   queue.sink.saved = 0u;
   queue.sink.list = sv.lists + ((size_t)blockIdx.y * units + unit) * cap;
@@ -201,7 +205,7 @@ __global__ __launch_bounds__(256, kSoft3Waves) void soft3d_fwd_save_kernel(
 // the forward sweep walks that unit's list; grad_X has been cleared by a fill kernel.  An item
 // whose lists cannot be used (header of another shape, a unit ran out of room) is computed from
 // the grid instead, vertex by vertex with the plain stencil: slow, but rare.
-template <bool TILTC>
+template <bool TILTC, bool WIDE>
 __global__ __launch_bounds__(256) void soft3d_bwd_saved_kernel(const float* __restrict__ grid, int D, int H, int W,
                                                                int64_t N, const float* __restrict__ u, float alpha,
                                                                const float* __restrict__ tau, int T, float kneg,
@@ -210,7 +214,9 @@ __global__ __launch_bounds__(256) void soft3d_bwd_saved_kernel(const float* __re
                                                                SoftStateHeader expect) {
   const int item = blockIdx.y, unit = blockIdx.x, units = gridDim.x;
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
-  extern __shared__ double stau[];  // [T] thresholds, [T] upstream gradient (float)
+  typedef typename SoftArg<WIDE>::Tau Tau;
+  extern __shared__ double lds[];  // [T] thresholds, [T] upstream gradient
+  Tau* const stau = reinterpret_cast<Tau*>(lds);
   float* const sg = reinterpret_cast<float*>(stau + T);
   __shared__ StagedEntry stage[256];
   __shared__ float sred[2][4];
@@ -224,7 +230,7 @@ __global__ __launch_bounds__(256) void soft3d_bwd_saved_kernel(const float* __re
   float lo = INFINITY, hi = -INFINITY;
   for (int j = threadIdx.x; j < T; j += 256) {
     const float t = tau[j];
-    stau[j] = (double)t;
+    stau[j] = t;
     sg[j] = gup ? gup[(int64_t)item * T + j] : 1.0f;
     lo = fminf(lo, t);
     hi = fmaxf(hi, t);
@@ -260,15 +266,16 @@ __global__ __launch_bounds__(256) void soft3d_bwd_saved_kernel(const float* __re
       if (c != 0) {
         const double yv = (double)g[i] + (double)alpha * ((ux * (double)x + uy * (double)y) + uz * (double)z);
         if ((float)yv > sat_lo && (float)yv < sat_hi) {
+          const double packed = SoftArg<WIDE>::pack(yv);
           float gd = 0.0f;
-          for (int j = 0; j < T; ++j) gd += sg[j] * soft_dsig(stau[j], yv, kneg);
+          for (int j = 0; j < T; ++j) gd += sg[j] * soft_dsig<WIDE>(stau[j], packed, kneg);
           gx[i] = -lambda * (float)c * gd;
         }
       }
     }
     return;
   }
-  saved_lists_to_grad(list, cnt_raw, expect.cap, first, stau, sg, T, kneg, lambda, sat_lo, sat_hi, gx, N, stage, skept);
+  saved_lists_to_grad<WIDE>(list, cnt_raw, expect.cap, first, stau, sg, T, kneg, lambda, sat_lo, sat_hi, gx, N, stage, skept);
 }
 
 // origin of a unit's coordinates, for the reduction of ecc_soft_reduce.h
@@ -300,20 +307,25 @@ size_t soft3d_workspace_bytes(const Shape& s, int T) {
   return (size_t)256 + soft3d_partial_bytes(s, pl, T) + soft_reduce_mid_bytes((int)pl.grid.x * 4, s.batch, T);
 }
 
+// Above 128 thresholds the evaluation weighs more than the sweep: four slots share the reads of an entry, three waves a
+// SIMD hold their registers (us with one slot and four waves / four slots and three, fields of width 2: backward pass of
+// 128^3 with 256 thresholds 66.7 / 47.6, saving forward pass of 8 x 96^3 with 192 57.8 / 51.7, backward pass of 4 x 128^3
+// with 192 72.1 / 77.3; forward passes up to 128 thresholds are 2 to 4 % slower with three waves).
+static bool many_thresholds(int T) { return T > 128; }
+
 static dim3 layered(const Plan3d& pl, const Shape& s, int T) {
-  return dim3(pl.grid.x, pl.grid.y, soft_layers((int64_t)pl.grid.x * 4 * s.batch, T));
+  return dim3(pl.grid.x, pl.grid.y, soft_layers((int64_t)pl.grid.x * 4 * s.batch, T, T <= 256 ? 1536 : 3072));
 }
 
 void launch_soft3d_fwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                        float lambda, float* chi, void* ws, hipStream_t st, bool tiltc) {
   const Plan3d pl = plan3d<float>(s);
   float* partial = static_cast<float*>(ws);
-#define ECC_GO(TC)                                                                                          \
-  hipLaunchKernelGGL(soft3d_fwd_kernel<TC>, layered(pl, s, T), dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
+#define ECC_GO(TC, MANY)                                                                                          \
+  hipLaunchKernelGGL((soft3d_fwd_kernel<TC, MANY>), layered(pl, s, T), dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
                      (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,       \
                      kneg3d(lambda), partial)
-  if (tiltc) ECC_GO(true);
-  else ECC_GO(false);
+  ECC_SOFT_VARIANT(tiltc, many_thresholds(T));
 #undef ECC_GO
   double* mid = reinterpret_cast<double*>(static_cast<char*>(ws) + soft3d_partial_bytes(s, pl, T));
   const RedOut out = {chi, nullptr, nullptr, nullptr, nullptr, {}};
@@ -325,12 +337,11 @@ void launch_soft3d_bwd(const float* grid, const Shape& s, const float* u, float 
                        hipStream_t st, bool tiltc) {
   const Plan3d pl = plan3d<float>(s);
   float* partial = (dtau || du) ? static_cast<float*>(ws) : nullptr;
-#define ECC_GO(TC)                                                                                          \
-  hipLaunchKernelGGL(soft3d_bwd_kernel<TC>, pl.grid, dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
+#define ECC_GO(TC, MANY)                                                                                          \
+  hipLaunchKernelGGL((soft3d_bwd_kernel<TC, MANY>), pl.grid, dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
                      (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,       \
                      kneg3d(lambda), lambda, gup, grad_X, partial)
-  if (tiltc) ECC_GO(true);
-  else ECC_GO(false);
+  ECC_SOFT_VARIANT(tiltc, many_thresholds(T));
 #undef ECC_GO
   if (partial) {
     double* mid = reinterpret_cast<double*>(static_cast<char*>(ws) + soft3d_partial_bytes(s, pl, T));
@@ -377,12 +388,13 @@ void launch_soft3d_fwd_save(const float* grid, const Shape& s, const float* u, f
   float* partial = static_cast<float*>(ws);
   double* mid = reinterpret_cast<double*>(static_cast<char*>(ws) + soft3d_partial_bytes(s, pl, T));
   const bool deriv = dtau || du;
-#define ECC_GO(TC, DV)                                                                                        \
-  hipLaunchKernelGGL((soft3d_fwd_save_kernel<TC, DV>), layered(pl, s, T), dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H, \
+#define ECC_GO3(TC, DV, MANY)                                                                                       \
+  hipLaunchKernelGGL((soft3d_fwd_save_kernel<TC, DV, MANY>), layered(pl, s, T), dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H, \
                      (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,         \
                      kneg3d(lambda), partial, sv, hdr.cap)
-  if (tiltc) { if (deriv) ECC_GO(true, true); else ECC_GO(true, false); }
-  else       { if (deriv) ECC_GO(false, true); else ECC_GO(false, false); }
+#define ECC_GO(TC, MANY) do { if (deriv) ECC_GO3(TC, true, MANY); else ECC_GO3(TC, false, MANY); } while (0)
+  ECC_SOFT_VARIANT(tiltc, many_thresholds(T));
+#undef ECC_GO3
 #undef ECC_GO
   const RedOut out = {chi, dtau, du, sv.hdr, sv.gen, hdr};
   launch_soft_reduce<5, true, 3>(partial, mid, (int)pl.grid.x * 4, s.batch, T, alpha, lambda, origin3(s, pl), out, st);
@@ -396,13 +408,12 @@ void launch_soft3d_bwd_saved(const float* grid, const Shape& s, const float* u, 
   const StateView sv = state_view(const_cast<void*>(state), s.batch, (size_t)expect.units);
   launch_clear_f32(grad_X, s.N * s.batch, st);  // zero away from the critical vertices
   const dim3 g((unsigned)expect.units, (unsigned)s.batch);
-  const size_t lds = (size_t)T * (sizeof(double) + sizeof(float));
-  if (tiltc)
-    hipLaunchKernelGGL(soft3d_bwd_saved_kernel<true>, g, dim3(256), lds, st, grid, (int)s.D, (int)s.H, (int)s.W, s.N, u,
-                       alpha, tau, T, kneg3d(lambda), lambda, gup, grad_X, sv, expect);
-  else
-    hipLaunchKernelGGL(soft3d_bwd_saved_kernel<false>, g, dim3(256), lds, st, grid, (int)s.D, (int)s.H, (int)s.W, s.N, u,
-                       alpha, tau, T, kneg3d(lambda), lambda, gup, grad_X, sv, expect);
+  const size_t lds = (size_t)T * (soft_wide(T) ? sizeof(double) + sizeof(float) : 2 * sizeof(float));
+#define ECC_GO(TC, WD)                                                                                            \
+  hipLaunchKernelGGL((soft3d_bwd_saved_kernel<TC, WD>), g, dim3(256), lds, st, grid, (int)s.D, (int)s.H, (int)s.W, s.N, \
+                     u, alpha, tau, T, kneg3d(lambda), lambda, gup, grad_X, sv, expect)
+  ECC_SOFT_VARIANT(tiltc, soft_wide(T));
+#undef ECC_GO
 }
 
 }  // namespace ecc

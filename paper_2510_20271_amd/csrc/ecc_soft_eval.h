@@ -1,32 +1,35 @@
 // Soft ECC: evaluation of a drained batch of critical vertices against the thresholds, shared by the sinks of
 // the strip (2D) and the tube (3D) sweep.
 //
-// A wave calls it with up to 64 entries, threshold-major: lane l takes the thresholds l, l + 64, ... one or two
-// at a time and runs over the entries, so that the sums over p of Eq. 6 / Eq. 9 / Eq. 10 of the paper need no
+// A wave calls it with up to 64 entries, threshold-major: lane l takes the thresholds l, l + 64, ..., some slots of 64 at
+// a time, and runs over the entries, so that the sums over p of Eq. 6 / Eq. 9 / Eq. 10 of the paper need no
 // cross-lane reduction; the contraction of Eq. 8 with the upstream gradient is a fixed-order sum over the lanes.
 //
 // The running sums live in the unit's own row of partial sums in the workspace and not in registers: a batch's sums
-// (formed from zero: shorter chains of float32 additions) are added to them (the first one of a unit starts from zero; most units have one or two).
-// Registers held across the sweep were what limited it: sums, thresholds and upstream gradient of four
-// thresholds a lane took the 3D kernels from 124 to 162 .. 204 vector registers (three or two waves on a SIMD
-// instead of four) and tied the path to 256 thresholds.  256^3 with 64 thresholds: forward sweep 43 -> 37 us,
-// backward 55 -> 42 us.  Any number of thresholds runs here: 16 x 217 x 181 with 512, which took 37 + 56 + 56 us in
-// the tile kernels of ecc_soft.hip, takes 92 us forward (derivatives included) and 25 us backward.
+// (formed from zero: shorter chains of float32 additions) are added to them (the first batch of a unit starts the row;
+// most units have one or two).  Registers held across the sweep were what limited it: sums, thresholds and upstream
+// gradient of four thresholds a lane took the 3D kernels from 124 to 162 .. 204 vector registers (three or two waves on a
+// SIMD instead of four) and tied the path to 256 thresholds.  256^3 with 64 thresholds: forward 42.6 -> 38.6 us, backward
+// 73.8 -> 50.3 us.
+//
+// Eq. 8's sum over the lanes takes four entries together: two exchange steps interleave them over the lanes of a quad, so
+// that the other four steps serve all four at once (12 additions instead of 24; backward pass of 32 x 512^2, T = 64:
+// 35.9 -> 31.0 us).
 #pragma once
 #include "ecc_device.h"
 
 namespace ecc {
 
-// z = tau_j - y is formed in float64 and rounded once
 struct StagedValue {
-  double y;
+  double y;  // packed, see SoftArg
   float c;
 };
 
 // NC: coordinates; CHI / DERIV: which sums a row holds, {chi} {A0, A_1 .. A_NC} in this order, STRIDE floats a
-// threshold; GRADX: the contraction with the upstream gradient
-template <int NC, bool CHI, bool DERIV, bool GRADX, int STRIDE>
+// threshold; GRADX: the contraction with the upstream gradient; WIDE: see SoftArg
+template <int NC, bool CHI, bool DERIV, bool GRADX, int STRIDE, bool WIDE>
 struct SoftEval {
+  typedef SoftArg<WIDE> Arg;
   static constexpr int kA = CHI ? 1 : 0, kSums = kA + (DERIV ? 1 + NC : 0);
   const float* tau;
   const float* gup;  // this item's upstream gradient, or null for all ones
@@ -63,30 +66,29 @@ struct SoftEval {
   template <int S, typename Get>
   __device__ __forceinline__ float slots(int t0, int n, float csat, const Get& get) const {
     const int lane = threadIdx.x & (kWave - 1);
-    double tj[S];
-    float gj[S], acc[S][kSums > 0 ? kSums : 1], old[S][kSums > 0 ? kSums : 1];
+    typename Arg::Tau tj[S];
+    float gj[S], acc[S][kSums > 0 ? kSums : 1];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const int j = lane + kWave * (t0 + s);
       const bool ok = j < T;
-      tj[s] = ok ? (double)tau[j] : 0.0;
+      tj[s] = ok ? tau[j] : 0.0f;
       if (GRADX) gj[s] = ok ? (gup ? gup[j] : 1.0f) : 0.0f;
 #pragma unroll
       for (int k = 0; k < kSums; ++k) {
-        old[s][k] = (started && ok && row) ? row[(int64_t)j * STRIDE + k] : 0.0f;
         acc[s][k] = 0.0f;
       }
-      if (CHI) old[s][0] += csat;
     }
     float mine = 0.0f;
-    for (int e = 0; e < n; ++e) {
+    auto entry = [&](int e, bool valid) -> float {
       StagedValue v;
       float r[NC];
       get(e, v, r);
+      if (GRADX && !valid) v.c = 0.0f;
       float gd = 0.0f;
 #pragma unroll
       for (int s = 0; s < S; ++s) {
-        const float ex = soft_exp_neg((float)(tj[s] - v.y), kneg);
+        const float ex = soft_exp_neg(Arg::z(tj[s], v.y), kneg);
         const float sg = __builtin_amdgcn_rcpf(1.0f + ex);
         if constexpr (CHI) acc[s][0] += v.c * sg;
         if constexpr (DERIV || GRADX) {
@@ -100,30 +102,51 @@ struct SoftEval {
           if constexpr (GRADX) gd += gj[s] * d;
         }
       }
-      if constexpr (GRADX) {
-        gd = wave_sum_lane63(gd);
-        gd = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, gd), kWave - 1));
-        mine += lane == e ? gd : 0.0f;
+      return gd;
+    };
+    if constexpr (GRADX) {
+      for (int e = 0; e < n; e += 4) {
+        float g[4];  // (beyond the last entry: that one again with c = 0, its sum not used)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g[q] = entry(min(e + q, n - 1), e + q < n);
+        // lane l ends with entry e + (l & 3) summed over all lanes
+        const bool b0 = (lane & 1) != 0, b1 = (lane & 2) != 0;
+        const float r01 = (b0 ? g[1] : g[0]) + dpp_move<0xB1, 0xf>(b0 ? g[0] : g[1]);
+        const float r23 = (b0 ? g[3] : g[2]) + dpp_move<0xB1, 0xf>(b0 ? g[2] : g[3]);
+        float r = (b1 ? r23 : r01) + dpp_move<0x4E, 0xf>(b1 ? r01 : r23);
+        r += dpp_move<0x124, 0xf>(r);  // row_ror:4
+        r += dpp_move<0x128, 0xf>(r);  // row_ror:8
+        r = swap_add16(r);
+        r = swap_add32(r);
+        if ((lane & ~3) == e) mine += r;
       }
+    } else {
+      for (int e = 0; e < n; ++e) entry(e, true);
     }
     if (row) {  // wave-uniform
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         const int j = lane + kWave * (t0 + s);
 #pragma unroll
-        for (int k = 0; k < kSums; ++k) acc[s][k] += old[s][k];
+        for (int k = 0; k < kSums; ++k) {
+          float old = (started && j < T) ? row[(int64_t)j * STRIDE + k] : 0.0f;
+          if (CHI && k == 0) old += csat;
+          acc[s][k] += old;
+        }
         if (j < T) store(j, acc[s]);
       }
     }
     return mine;
   }
-  // SLOTS: slots taken together (two share the reads of an entry; one where registers are short)
+  // SLOTS: slots taken together at most (they share the reads of an entry; one where registers are short)
   template <int SLOTS, typename Get>
   __device__ __forceinline__ float run(int n, float csat, const Get& get) {
     const int nt = (T + kWave - 1) / kWave;
     float mine = 0.0f;
     int t = 0;
-    if constexpr (SLOTS == 2)
+    if constexpr (SLOTS >= 4)
+      for (; t + 4 <= nt; t += 4) mine += slots<4>(t, n, csat, get);
+    if constexpr (SLOTS >= 2)
       for (; t + 2 <= nt; t += 2) mine += slots<2>(t, n, csat, get);
     for (; t < nt; ++t) mine += slots<1>(t, n, csat, get);
     started = true;
@@ -138,14 +161,16 @@ struct SoftEval {
 };
 
 // A launch with few wave units (small batches, small grids) and many thresholds is as long as one wave's walk over
-// its thresholds while most of the chip idles.  Such a launch runs in `parts` layers of blocks (gridDim.z): every
+// its thresholds while most of the chip idles.  Such a launch runs in layers of blocks (gridDim.z): every
 // layer sweeps the grid again, which is cheap then, and evaluates its own share of the thresholds, a multiple of 64.
-// Up to about three waves for each of the 1024 SIMDs.  No layers where a contraction over all thresholds is formed.
+// Up to about three waves for each of the 1024 SIMDs (most_waves); for volumes, whose sweep is the larger part of the
+// call, half of that up to 256 thresholds (256 x 12^3, T = 192: 22.5 us in three layers, 16.2 in one).  No layers where a
+// contraction over all thresholds is formed.
 // Forward pass with derivatives on 16 x 217 x 181 with 512 thresholds: 91 us in one layer of 224 waves, 21 us in four
 // layers of 448 (8 rows a wave instead of 16).
-static inline unsigned soft_layers(int64_t waves, int T) {
+static inline unsigned soft_layers(int64_t waves, int T, int64_t most_waves = 3072) {
   const int64_t slots = (T + kWave - 1) / kWave;
-  int64_t n = 3072 / (waves < 1 ? 1 : waves);
+  int64_t n = most_waves / (waves < 1 ? 1 : waves);
   n = n < 1 ? 1 : (n > slots ? slots : n);
   const int64_t per = (slots + n - 1) / n;
   return (unsigned)((slots + per - 1) / per);

@@ -44,12 +44,20 @@ __device__ __forceinline__ bool state_usable(const StateView& v, const SoftState
 
 constexpr int kSavedLanes = 8;  // lanes per entry
 struct StagedEntry {
-  double y;
+  double y;  // packed, see SoftArg
   float c;
   int idx;
 };
-__device__ __forceinline__ float soft_dsig(double tau, double y, float kneg) {  // sigma (1 - sigma)
-  const float ex = soft_exp_neg((float)(tau - y), kneg);
+static inline bool soft_wide(int T) { return T > 256; }  // see SoftArg
+// the kernel variants of a launch: ECC_GO(tilted, second)
+#define ECC_SOFT_VARIANT(TC, SECOND)                              \
+  do {                                                            \
+    if (TC) { if (SECOND) ECC_GO(true, true); else ECC_GO(true, false); } \
+    else    { if (SECOND) ECC_GO(false, true); else ECC_GO(false, false); } \
+  } while (0)
+template <bool WIDE>
+__device__ __forceinline__ float soft_dsig(typename SoftArg<WIDE>::Tau tau, double y, float kneg) {  // sigma (1 - sigma)
+  const float ex = soft_exp_neg(SoftArg<WIDE>::z(tau, y), kneg);
   const float s = __builtin_amdgcn_rcpf(1.0f + ex);
   return ex * s * s;
 }
@@ -60,8 +68,9 @@ __device__ __forceinline__ float soft_dsig(double tau, double y, float kneg) {  
 // thresholds, three lane swaps add the eight partial sums.
 // first: entry number threadIdx.x of the list, requested by the caller ahead of time; stau / sg:
 // thresholds and upstream gradient in LDS; stage: 256 entries, skept: 4 ints of LDS.
+template <bool WIDE>
 __device__ __forceinline__ void saved_lists_to_grad(const SavedEntry* __restrict__ list, unsigned cnt_raw, unsigned cap,
-                                                    const SavedEntry& first, const double* stau, const float* sg, int T,
+                                                    const SavedEntry& first, const typename SoftArg<WIDE>::Tau* stau, const float* sg, int T,
                                                     float kneg, float lambda, float sat_lo, float sat_hi,
                                                     float* __restrict__ gx, int64_t N, StagedEntry* stage, int* skept) {
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
@@ -74,7 +83,7 @@ __device__ __forceinline__ void saved_lists_to_grad(const SavedEntry* __restrict
     StagedEntry mine;
     if (e0 + threadIdx.x < cnt) {
       const SavedEntry en = e0 == 0 ? first : list[e0 + threadIdx.x];
-      mine.y = en.y;
+      mine.y = SoftArg<WIDE>::pack(en.y);
       mine.c = (float)en.c;
       mine.idx = en.idx;
       keep = (float)en.y > sat_lo && (float)en.y < sat_hi;
@@ -97,10 +106,10 @@ __device__ __forceinline__ void saved_lists_to_grad(const SavedEntry* __restrict
       float g0 = 0.0f, g1 = 0.0f;  // two independent chains
       int j = q;
       for (; j + kSavedLanes < T; j += 2 * kSavedLanes) {
-        g0 += sg[j] * soft_dsig(stau[j], en.y, kneg);
-        g1 += sg[j + kSavedLanes] * soft_dsig(stau[j + kSavedLanes], en.y, kneg);
+        g0 += sg[j] * soft_dsig<WIDE>(stau[j], en.y, kneg);
+        g1 += sg[j + kSavedLanes] * soft_dsig<WIDE>(stau[j + kSavedLanes], en.y, kneg);
       }
-      if (j < T) g0 += sg[j] * soft_dsig(stau[j], en.y, kneg);
+      if (j < T) g0 += sg[j] * soft_dsig<WIDE>(stau[j], en.y, kneg);
       float gd = g0 + g1;
       gd += dpp_move<0xB1, 0xf>(gd);   // quad_perm [1,0,3,2]
       gd += dpp_move<0x4E, 0xf>(gd);   // quad_perm [2,3,0,1]
