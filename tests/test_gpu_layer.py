@@ -97,7 +97,8 @@ def test_layer_learns_its_thresholds_back():
 
 
 @pytest.mark.parametrize("nd,B,T", [(2, 1, 1), (2, 3, 63), (3, 7, 65), (2, 32, 128), (3, 16, 512), (2, 2, 1500),
-                                    (2, 33, 1025), (3, 600, 130), (2, 512, 64)])
+                                    (2, 33, 1025), (3, 600, 130), (2, 512, 64), (2, 513, 64), (3, 9000, 5),
+                                    (2, 40000, 1), (2, 20011, 16), (3, 65535, 33), (2, 3001, 200), (2, 70, 4096)])
 def test_contraction_with_the_upstream_gradient(nd, B, T):
     gen = torch.Generator(device="cuda").manual_seed(B * T)
     g, dtau = (torch.randn(B, T, generator=gen, device="cuda") for _ in range(2))
