@@ -96,15 +96,22 @@ def test_saved_state_of_another_shape_is_noticed():
         _close(gx[i], ref[i], 1e-3, f"grad_X[{i}]")
 
 
-@pytest.mark.parametrize("shape,T", [((9, 30, 7), 5), ((60, 70), 300), ((9, 30, 70), 300)])
-def test_saved_state_entry_points_on_shapes_without_state(shape, T):
-    # volumes narrower than 8 and T > 256 keep no state: the same entry points run the stateless kernels
+@pytest.mark.parametrize("shape,T,tiles", [((9, 30, 7), 5, False), ((60, 7), 300, False), ((9, 30, 7), 300, False),
+                                           ((60, 70), 300, False), ((9, 30, 70), 300, False),
+                                           ((60, 70), 300, True), ((9, 30, 70), 300, True)])
+def test_saved_state_entry_points_on_shapes_without_state(shape, T, tiles):
+    # grids narrower than 8 keep no state, nor does any grid forced through the tile kernels: the same entry points run
+    # the stateless kernels; the wider ones with many thresholds keep theirs
     nd = len(shape)
     Xb = np.stack([synth.grf(shape, 1.5, 60 + i) for i in range(2)])
     u = np.array([0.6, 0.8] if nd == 2 else [0.48, -0.6, 0.64], np.float32)
     tau = np.linspace(Xb.min(), Xb.max() + 1.0, T).astype(np.float32)
     G = np.random.default_rng(3).standard_normal((2, T)).astype(np.float32)
-    _case(Xb, u, np.float32(0.02), tau, np.float32(8.0), G)
+    prev = api.ecc_debug_force(api.ECC_FORCE_SOFT_TILES if tiles else 0)
+    try:
+        _case(Xb, u, np.float32(0.02), tau, np.float32(8.0), G)
+    finally:
+        api.ecc_debug_force(prev)
 
 
 def test_saved_state_is_deterministic_and_config_c5():

@@ -49,14 +49,19 @@ def test_soft_tilted_2d_fused(shape):
     _run_tilted(Xb, u, alpha, tau, np.float32(20.0), G, expect_other_c=min(shape) > 1)
 
 
-def test_soft_tilted_2d_tile_path_many_thresholds():
-    B, T = 2, 300  # more thresholds than the fused path takes
+@pytest.mark.parametrize("tiles", [False, True])
+def test_soft_tilted_2d_tile_path_many_thresholds(tiles):
+    B, T = 2, 300  # several groups of thresholds: in the fused kernels, and forced through the tile kernels
     Xb = np.stack([synth.grf((70, 130), 2.0, 70 + i) for i in range(B)])
     u = np.array([-0.8, 0.6], np.float32)
     alpha = np.float32(0.04)
     tau = np.linspace(-3, 9, T).astype(np.float32)
     G = np.random.default_rng(3).standard_normal((B, T)).astype(np.float32)
-    _run_tilted(Xb, u, alpha, tau, np.float32(15.0), G)
+    prev = api.ecc_debug_force(api.ECC_FORCE_SOFT_TILES if tiles else 0)
+    try:
+        _run_tilted(Xb, u, alpha, tau, np.float32(15.0), G)
+    finally:
+        api.ecc_debug_force(prev)
 
 
 @pytest.mark.parametrize("shape", [(2, 2, 2), (5, 6, 7), (9, 30, 70), (3, 33, 129)])

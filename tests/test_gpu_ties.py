@@ -159,20 +159,15 @@ def test_soft_tile_kernels_on_quantised_fields(shape):
     nd, B = len(shape), 2
     Xb = np.stack([_quantised(shape, 80 + i) for i in range(B)])
     u = np.array([np.cos(0.3), np.sin(0.3)] if nd == 2 else [0.48, -0.6, 0.64], np.float32)
-    # more thresholds than the fused paths take: the tile kernels by themselves
-    T = 300
-    tau = np.linspace(Xb.min() - 0.1, Xb.max() + 0.3, T).astype(np.float32)
-    G = np.random.default_rng(2).standard_normal((B, T)).astype(np.float32)
-    _soft_case(Xb, u, np.float32(0.01), tau, np.float32(20.0), G)
-    # and forced, with few thresholds
-    T = 7
-    tau = np.linspace(Xb.min() - 0.1, Xb.max() + 0.3, T).astype(np.float32)
-    G = G[:, :T].copy()
-    prev = api.ecc_debug_force(api.ECC_FORCE_SOFT_TILES)
-    try:
-        _soft_case(Xb, u, np.float32(0.01), tau, np.float32(20.0), G)
-    finally:
-        api.ecc_debug_force(prev)
+    # several groups of 256 thresholds, and few of them; the many also as a caller gets them (the fused kernels)
+    G = np.random.default_rng(2).standard_normal((B, 300)).astype(np.float32)
+    for T, force in ((300, 0), (300, api.ECC_FORCE_SOFT_TILES), (7, api.ECC_FORCE_SOFT_TILES)):
+        tau = np.linspace(Xb.min() - 0.1, Xb.max() + 0.3, T).astype(np.float32)
+        prev = api.ecc_debug_force(force)
+        try:
+            _soft_case(Xb, u, np.float32(0.01), tau, np.float32(20.0), G[:, :T].copy())
+        finally:
+            api.ecc_debug_force(prev)
 
 
 @pytest.mark.parametrize("shape", [(100, 259), (9, 30, 70)])
