@@ -90,8 +90,8 @@ void launch_sweep2d(const void* grid, const Shape& s, int dtype, bool levels, in
                     hipStream_t st, const unsigned* run_if, const DirArgs* dir = nullptr, int conv = 0);
 void launch_sweep2d_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st,
                          const DirArgs* dir = nullptr, int conv = 0);
-unsigned sweep2d_list_blocks(const Shape& s, int dtype);  // blocks per item of that launch
-unsigned sweep2d_block_vertices(const Shape& s, int dtype);  // most vertices a block of that launch owns
+unsigned sweep2d_list_blocks(const Shape& s, int dtype, bool shared);  // blocks per item of that launch
+unsigned sweep2d_block_vertices(const Shape& s, int dtype);  // most vertices a block of a launch with lists per block owns
 
 bool sweep3d_supported(const Shape& s, int bins);
 void launch_sweep3d(const void* grid, const Shape& s, int dtype, bool levels, int bins,

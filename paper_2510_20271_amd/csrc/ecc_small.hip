@@ -366,7 +366,7 @@ constexpr unsigned kMidBlocks = 65536;           // sweep blocks in all
 
 static bool mid_plan(const Shape& s, int dtype, unsigned& per_item, unsigned& cap) {
   if (s.ndim == 2 && sweep2d_supported(s, 1)) {
-    per_item = sweep2d_list_blocks(s, dtype);
+    per_item = sweep2d_list_blocks(s, dtype, false);
     cap = sweep2d_block_vertices(s, dtype);
   } else if (sweep3d_supported(s, 1)) {
     if (dtype != 2) return false;  // (the tube sweep's list kernels take float32 here)

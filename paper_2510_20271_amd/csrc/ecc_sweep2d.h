@@ -480,43 +480,66 @@ struct Plan2d {
 // What the sweep feeds: it decides how many rows a wave takes.  A wave's march is a chain of dependent steps (about
 // 0.4 us a row when it has a SIMD for itself), so a launch that does not fill the chip wants short segments; every
 // segment reads five rows more than it puts out, and a block has costs of its own at its end.
-enum class Feed2d { kHist, kList, kSigmoid };
+enum class Feed2d { kHist, kBlockLists, kSharedLists, kSigmoid };
 
-// rows a wave takes; tubes: strips of all items; bins: of a kHist sweep
-static inline int64_t rows2d(const Shape& s, int64_t nstrip, int64_t tubes, Feed2d feed, int bins) {
+// rows a wave takes; tubes: strips of all items; bytes: of an element; bins: of a kHist sweep
+static inline int64_t rows2d(const Shape& s, int64_t nstrip, int64_t tubes, Feed2d feed, int bytes, int bins) {
   const int64_t H = s.H, total = s.N * s.batch;
+  auto waves = [&](int64_t rows) { return tubes * ((H + rows - 1) / rows); };
   if (feed == Feed2d::kSigmoid) {
     // 8 rows while that gives up to three waves for each of the 1024 SIMDs (ecc_soft_fwd + ecc_soft_bwd on
     // 4 x 1024^2, T = 64: 46 -> 36 us; one 2048^2, T = 256: 69 -> 50 us); else 24 when that still leaves two rounds
     // of waves, else 16
-    if (tubes * ((H + 7) / 8) <= 3072) return 8;
-    return tubes * ((H + 23) / 24) >= 8192 ? 24 : 16;
+    if (waves(8) <= 3072) return 8;
+    return waves(24) >= 8192 ? 24 : 16;
   }
-  if (feed == Feed2d::kList && total <= kMidTotal2d) {
+  if (feed == Feed2d::kBlockLists) {
     // A list per block: nothing is merged at a block's end.  Measured with 8 / 16 / 24 / 32 / 64 rows (us a call,
     // float32): 1024 x 28^2 20.8 / 21.3 / 21.4 / 23.7, 1024^2 17.8 / 19.9 / 21.5 / 23.1 / 30.8, 64 directions of 256^2
     // 23.9 / 21.9 / 25.2 / 25.8 / 35.7, 1024 x 128^2 43.7 / 39.2 / 47.2 / 53.2 / 57.8, 32 x 512^2 30.2 / 27.2 / 29.4 / 30.3 /
     // 39.4, 4096^2 37.5 / 39.4 / 34.0 / 34.8 / 44.9, 8 x 4096^2 149 / 137 / 134 / 138 / 153: by the total first, then
     // by the height (24 rows leave a low image's last segment and block half empty).
-    int64_t rows = total < ((int64_t)1 << 22) ? 8 : (H <= 1024 ? 16 : 24);
-    while (rows < 64 && tubes * ((H + rows - 1) / rows) > 131072) rows *= 2;  // (tall, narrow grids: the blocks' heads)
+    int64_t rows = H <= 1024 ? 16 : 24;
+    if (total < ((int64_t)1 << 22) && nstrip * ((H + 7) / 8) <= 2048) rows = 8;
+    // Many waves cost more in the blocks' heads than short segments gain (500000 x 8 101 / 81 / 76 / 78 / 78,
+    // 2000000 x 8 361 / 284 / 260 / 248 / 236)
+    while (rows < 64 && waves(rows) > 24576) rows *= 2;
     return rows;
   }
+  // rows with which an image (of at most four strips) is four units, a whole block
+  const int64_t segs = (4 + nstrip - 1) / nstrip;
+  const int64_t four_units = ((H + segs - 1) / segs + kChunkRows - 1) / kChunkRows * kChunkRows;
   // A histogram per block, cleared first and merged into the item's with one atomic per bin at the end: few bins and
-  // not too many blocks that meet in one item's histogram want short segments (us a call with 8 / 16 / 32 / 64 rows:
-  // 64 x 256^2 uint8 14.3 / 14.4 / 16.4 / 25.2, 2048^2 uint8 noise 25.6 / 26.0 / 36.9 / 64, 16 x 1024^2 uint8 24.0 / 21.3 /
-  // 23.4 / 30.7, 1024 x 224^2 uint8 42.9 / 42.2 / 41.6 / 39.0; but a 4677 x 3307 page 52.6 / 32.1 / 24.6 / 26.1, 16 x 1024^2
-  // with 4096 bins 54 / 40.9 / 34.2 / 39.5).
-  if (feed == Feed2d::kHist && nstrip * ((H + 15) / 16) <= 1280 && bins <= 1024)
-    return total <= ((int64_t)1 << 25) ? 16 : 32;
-  if (tubes * ((H + 15) / 16) <= 1024) return 16;  // at most one wave per SIMD even with short segments
+  // not too many blocks that meet in one item's histogram want short segments (us a call with 8 / 16 / 24 / 32 / 64 rows:
+  // 64 x 256^2 uint8 noise 19.6 / 22.5 / 29.9 / 34.0 / 61, 16 x 512^2 smooth float32 13.1 / 14.2 / 16.0 / 17.0 / 24.8, 2048^2
+  // uint8 noise 25.6 / 26.0 / 30.7 / 36.8 / 64 and smooth 21.4 / 17.0 / 15.6 / 17.0 / 22.9; but a 4677 x 3307 page 52.9 / 32.1 /
+  // 27.3 / 24.8 / 26.6, 16 x 1024^2 with 4096 bins 54 / 40.9 / - / 34.2 / 39.5).  24 rows from 1024 units on: 2048^2.
+  if (feed == Feed2d::kHist && nstrip * ((H + 15) / 16) <= 1280 && bins <= 1024) {
+    if (total <= ((int64_t)1 << 25) && total * bytes <= ((int64_t)1 << 26))
+      return nstrip * ((H + 15) / 16) <= 1024 ? 16 : 24;
+    // Rounds of waves enough at any length: one byte a vertex is bound by the march (16 x 2048^2 noise 109 / 133 with 32 / 64
+    // rows), wider ones by the rows read twice (64 x 1024^2 float32 61.6 / 58.0, 512 x 512^2 144 / 131, 125 with 128; 16 rows
+    // lose beyond 2^26 bytes, 32 x 1024^2 float32 42 / 37).  Many small images take four units, a whole block (16384 x 64^2
+    // uint8 noise 416 us with the two units of 32 rows, 280 with four; 2000 x 100 x 300 161 with the eight of 32 rows, 147 with
+    // four).
+    const int64_t aim = bytes == 1 ? 32 : (tubes >= 1024 ? 128 : 64);
+    return s.batch >= 1024 && nstrip <= 4 && nstrip * ((H + aim - 1) / aim) <= 8 ? four_units : aim;
+  }
+  if (waves(16) <= 1024) return 16;  // at most one wave per SIMD even with short segments
+  // Many small images with lists that blocks share (batches beyond the lists per block): four units each as well, rather
+  // than one wave of a block's four (8192 x 64^2 215 -> 149 us; 1024 of them, one wave a SIMD, 54 -> 61).
+  if (feed == Feed2d::kSharedLists && nstrip == 1 && H <= 64 && tubes > 4096) return four_units;
   // One large image gains 30 % from 24 -> 64 rows at 4096^2, 20 % from 16 -> 32 at 2048^2: about 1536 waves, within
-  // 32 .. 64 rows per segment.  Shared lists, 16 x 4096^2: 241 / 251 / 237 / 246 / 259 us with 24 / 32 / 48 / 64 / 96 rows.
+  // 32 .. 64 rows per segment.  Shared lists beyond 2^27 vertices: 48 rows where images are up to 34 strips (8432 columns)
+  // wide, 4 to 6 % less (16 x 4096^2: 241 / 251 / 237 / 246 / 259 us with 24 / 32 / 48 / 64 / 96 rows, 3 x 8192^2 202 -> 188,
+  // 40 x 2048^2 179 -> 169, 5 x 5000 x 7000 180 -> 172); wider ones gain on some fields and lose on others (3 x 7000 x 9000 165 ->
+  // 176, 12000^2 170 -> 158).  Up to 2^27 vertices shorter segments gain on smooth fields (16 x 1024^2 float64 79 -> 66 with
+  // 24 rows) and lose on white noise, where the blocks contend for the lists (256 x 256^2 float64 1692 -> 2017): not taken.
   const int64_t want = std::max<int64_t>(1, 1536 / tubes);
   int64_t rows = ((H + want - 1) / want + kChunkRows - 1) / kChunkRows * kChunkRows;
   // plenty of tubes (a large batch of small images): up to 128 rows, but two segments per image at least
   // (2048 x 128^2 loses 17 % with one segment of 128)
-  int64_t longest = feed == Feed2d::kList ? 48 : 64;
+  int64_t longest = feed == Feed2d::kSharedLists && total > kMidTotal2d && nstrip <= 34 ? 48 : 64;
   if (tubes >= 1024)
     longest = std::max<int64_t>(64, std::min<int64_t>(128, ((H + 1) / 2 + kChunkRows - 1) / kChunkRows * kChunkRows));
   return rows < 32 ? 32 : (rows > longest ? longest : rows);
@@ -528,7 +551,7 @@ static Plan2d plan2d(const Shape& s, Feed2d feed, int bins = 1) {
   const int H = (int)s.H, W = (int)s.W;
   p.nstrip = (W + kStripOut - 1) / kStripOut;
   const int64_t tubes = (int64_t)p.nstrip * s.batch;
-  const int64_t aim = rows2d(s, p.nstrip, tubes, feed, bins);
+  const int64_t aim = rows2d(s, p.nstrip, tubes, feed, (int)sizeof(T), bins);
   int64_t nseg = (H + aim - 1) / aim;
   if (feed == Feed2d::kSigmoid) nseg = std::min(nseg, (32768 + tubes - 1) / tubes);
   if (nseg < 1) nseg = 1;

@@ -135,7 +135,7 @@ static void launch2d_t(const void* grid, const Shape& s, bool levels, int bins, 
 template <typename T>
 static void launch2d_list_t(const void* grid, const Shape& s, const ListArgs& la, hipStream_t st, const DirArgs* dir,
                             int conv) {
-  const Plan2d pl = plan2d<T>(s, Feed2d::kList);
+  const Plan2d pl = plan2d<T>(s, la.heads ? Feed2d::kBlockLists : Feed2d::kSharedLists);
   const DirArgs none = {nullptr, 0.f, 1, 2};
   const T* p = static_cast<const T*>(grid);
 #define ECC_LIST(M, DIR)                                                                                 \
@@ -167,13 +167,14 @@ void launch_sweep2d_list(const void* grid, int dtype, const Shape& s, const List
 }
 
 unsigned sweep2d_block_vertices(const Shape& s, int dtype) {
-  const Plan2d pl = dtype == 2 ? plan2d<float>(s, Feed2d::kList) : plan2d<F16>(s, Feed2d::kList);
+  const Plan2d pl = dtype == 2 ? plan2d<float>(s, Feed2d::kBlockLists) : plan2d<F16>(s, Feed2d::kBlockLists);
   // four wave units of 248 columns x the segment's rows
   return 4u * (unsigned)std::min<int64_t>(kStripOut, s.W) * (unsigned)std::min<int64_t>(pl.rows_per_seg, s.H);
 }
 
-unsigned sweep2d_list_blocks(const Shape& s, int dtype) {
-  return dtype == 2 ? plan2d<float>(s, Feed2d::kList).grid.x : plan2d<F16>(s, Feed2d::kList).grid.x;
+unsigned sweep2d_list_blocks(const Shape& s, int dtype, bool shared) {
+  const Feed2d feed = shared ? Feed2d::kSharedLists : Feed2d::kBlockLists;
+  return dtype == 2 ? plan2d<float>(s, feed).grid.x : plan2d<F16>(s, feed).grid.x;
 }
 
 bool sweep2d_supported(const Shape& s, int bins) {
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(256) void coeff2d_kernel(const T* __restrict__ grid
 
 template <typename T>
 static void launch_coeff2d_t(const void* grid, const Shape& s, int8_t* out, hipStream_t st) {
-  const Plan2d pl = plan2d<T>(s, Feed2d::kList);
+  const Plan2d pl = plan2d<T>(s, Feed2d::kSharedLists);
   hipLaunchKernelGGL((coeff2d_kernel<T>), pl.grid, dim3(256), ring_bytes2d<int4>(), st, static_cast<const T*>(grid),
                      (int)s.H, (int)s.W, s.N, pl.nstrip, pl.nseg, pl.rows_per_seg, out);
 }
