@@ -181,7 +181,7 @@ __device__ __forceinline__ void sweep_strip(const T* __restrict__ g, int64_t ite
   const bool first_lane = open_left && lane == 0, last_lane = open_right && lane == kWave - 1;
 
   // The resource starts at the first streamed row (and at column c0 unless the strip is an EDGE one), rounded down
-  // to a dword; `o` is a row's byte offset from there.
+  // to a dword; `soff` is the byte offset of a row from there.
   const int ya = max(y0 - 1, 0);
   const int64_t first = (int64_t)ya * W + (EDGE ? 0 : c0);
   const unsigned skew = ANY ? (unsigned)(reinterpret_cast<uintptr_t>(g + first) & 3) : 0u;

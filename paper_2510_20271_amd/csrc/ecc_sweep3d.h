@@ -684,16 +684,17 @@ static Plan3d plan3d(const Shape& s) {
     if (pl < 12) pl = 12;
     if (pl < planes) planes = pl;
   }
-  // Segments of equal length: the call lasts as long as its longest one (64 x 64^3 float32: 65.4 us with 30 + 30 + 4
-  // planes, 59.4 with 22 + 22 + 20; 16 x 128^3 68.4 -> 63.4).  Not where that takes less than an eighth off full chunks:
+  // One-chunk segments of equal length: the call lasts as long as its longest one (64 x 64^3 float32: 65.4 us with 30 + 30 +
+  // 4 planes, 59.4 with 22 + 22 + 20; 16 x 128^3 68.4 -> 63.4).  Not where that takes less than an eighth off a chunk:
   // launches of many rounds of waves then lose more from the missing short last segments, which fill the gaps at the
-  // end (8 directions of 193 x 229 x 193: 118.6 us with 30 planes, 128.0 with 28).  Longer segments for small launches
-  // were measured and not taken: 24 planes instead of 12 make 193 x 229 x 193 float32 5 us faster on smooth fields (39.2
-  // -> 34.2) and 36 us slower on white noise (85 -> 121), where a wave's march is the draining of its vertices.
-  if (planes <= s3::kChunk) {
+  // end (8 directions of 193 x 229 x 193: 118.6 us with 30 planes, 128.0 with 28).  Longer segments for the small launches
+  // above were measured and not taken: 24 planes instead of 12 make 193 x 229 x 193 faster on smooth fields (float32 39.2 -> 34.2
+  // us, int16 over a known window 35 -> 31) and slower on noise, where a wave's march is the draining of its vertices
+  // (float32 85 -> 121, uint8 47 -> 51).
+  if (planes == s3::kChunk) {
     const int64_t n = (D + planes - 1) / planes;
     const int64_t equal = ((D + n - 1) / n + 1) & ~(int64_t)1;
-    if (planes < s3::kChunk || equal <= 26) planes = equal;
+    if (equal <= 26) planes = equal;
   }
   int64_t fit = (((int64_t)1 << 32) - 1) / ((int64_t)H * W);
   if (fit > (1 << 24) - 1) fit = (1 << 24) - 1;
