@@ -327,6 +327,11 @@ constexpr size_t kFusedRoom = (size_t)64 << 20;
 static bool fused_fits(const Shape& s, int T) {
   if (T <= 256) return true;
   if (T > ECC_MAX_THRESHOLDS) return false;  // (a hard call's bins: no soft call takes so many)
+  // Large batches of tiny items stay with the tiles, which spread an item's few critical vertices over 256 threads where a
+  // wave unit walks all thresholds by itself (forward pass, fused / tiles: 2000 x 20^2 39 / 28 us and 8192 x 16^2 103 / 66 at
+  // T = 512, 1000 x 9^2 13.0 / 9.2 and 4096 x 28^2 68 / 56 at T = 300; but 1024 x 28^2 24.4 / 24.8, 512 x 32^2 19.2 / 23.6, 20 x 8^2
+  // 6.1 / 7.7 at T = 512).
+  if (s.N <= 512 ? s.batch >= 512 : (s.N <= 1024 && s.batch >= 2048)) return false;
   return std::max(soft2d_workspace_bytes(s, T), soft3d_workspace_bytes(s, T)) <= std::max(tile_bytes(s, T), kFusedRoom);
 }
 
@@ -346,23 +351,14 @@ static bool use_soft3d(const Shape& s, int T) {
 
 static float kneg_of(float lambda) { return (float)(-(double)lambda * 1.4426950408889634); }
 
-// The forward pass alone over a large batch of small items with many thresholds: a tile block spreads its list over
-// 256 threads, a wave unit of the sweep holds a few hundred vertices and walks all thresholds by itself.  us fused / tiles:
-// 1024 x 28^2 30.5 / 24.8 at T = 512, 2000 x 20^2 43 / 27, 8192 x 16^2 139 / 66, 300 x 100^2 at T = 1024 124 / 109; but
-// 256 x 28^2 14.3 / 20.0, 512 x 64^2 46.0 / 47.1, 512 x 20^3 75 / 103 at T = 512.  With the derivatives the fused kernels win.
-static bool tiles_forward(const Shape& s, int T) {
-  return T > 256 && s.batch * tiles_of(s) >= 1024 && (s.N <= 1024 || (T > 512 && s.N <= 16384));
-}
-
 hipError_t launch_soft_fwd(const float* grid, const Shape& s, const float* u, float alpha,
                            const float* tau, int T, float lambda, float* chi, void* ws,
                            hipStream_t st, bool tiltc) {
-  const bool tiles = tiles_forward(s, T);
-  if (!tiles && use_soft2d(s, T)) {
+  if (use_soft2d(s, T)) {
     launch_soft2d_fwd(grid, s, u, alpha, tau, T, lambda, chi, ws, st, tiltc);
     return hipGetLastError();
   }
-  if (!tiles && use_soft3d(s, T)) {
+  if (use_soft3d(s, T)) {
     launch_soft3d_fwd(grid, s, u, alpha, tau, T, lambda, chi, ws, st, tiltc);
     return hipGetLastError();
   }
@@ -412,6 +408,10 @@ hipError_t launch_soft_bwd(const float* grid, const Shape& s, const float* u, fl
 // ---- forward pass that saves its critical vertices, backward pass that reuses them ---------------
 size_t soft_state_bytes(const Shape& s) { return s.ndim == 3 ? soft3d_state_bytes(s) : soft2d_state_bytes(s); }
 
+// A state that an earlier call left must not pass for this one's: the backward call may name fewer thresholds and look for
+// lists.
+__global__ void drop_state_kernel(SoftStateHeader* h) { h->magic = 0u; }
+
 hipError_t launch_soft_fwd_save(const float* grid, const Shape& s, const float* u, float alpha, const float* tau,
                                 int T, float lambda, float* chi, float* dtau, float* du, void* state, void* ws,
                                 hipStream_t st, bool tiltc) {
@@ -424,6 +424,7 @@ hipError_t launch_soft_fwd_save(const float* grid, const Shape& s, const float* 
     return hipGetLastError();
   }
   // other shapes keep no state: the forward pass, then the threshold / direction sums of the backward one
+  hipLaunchKernelGGL(drop_state_kernel, dim3(1), dim3(1), 0, st, static_cast<SoftStateHeader*>(state));
   hipError_t e = launch_soft_fwd(grid, s, u, alpha, tau, T, lambda, chi, ws, st, tiltc);
   if (e == hipSuccess && (dtau || du))
     e = launch_soft_bwd(grid, s, u, alpha, tau, T, lambda, nullptr, nullptr, dtau, du, ws, st, tiltc);

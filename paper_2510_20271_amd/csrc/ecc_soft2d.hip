@@ -378,7 +378,8 @@ static dim3 layered(const Plan2d& pl, const Shape& s, int T) {
 void launch_soft2d_fwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau,
                        int T, float lambda, float* chi, void* ws, hipStream_t st, bool tiltc) {
   const Plan2d pl = plan2d<float>(s, Feed2d::kSigmoid);
-  float* partial = static_cast<float*>(ws);
+  const bool alone = pl.nstrip * pl.nseg == 1;  // an item is one unit: its row is the result
+  float* partial = alone ? chi : static_cast<float*>(ws);
   profile_mark(st, false);
 #define ECC_GO(TC, WD)                                                                                                 \
   hipLaunchKernelGGL((soft2d_fwd_kernel<TC, WD>), layered(pl, s, T), dim3(256), kSoftLds, st, grid, (int)s.H, (int)s.W, \
@@ -386,6 +387,7 @@ void launch_soft2d_fwd(const float* grid, const Shape& s, const float* u, float 
   ECC_SOFT_VARIANT(tiltc, soft_wide(T));
 #undef ECC_GO
   profile_mark(st, true);
+  if (alone) return;
   const RedOut out = {chi, nullptr, nullptr, nullptr, nullptr, {}};
   launch_soft_reduce<1, true, -1>(partial, soft2d_mid(ws, s, pl, T), pl.nstrip * pl.nseg, s.batch, T, alpha, lambda,
                                   Origin2{pl.nstrip, pl.rows_per_seg}, out, st);

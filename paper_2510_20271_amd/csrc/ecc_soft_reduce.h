@@ -8,7 +8,7 @@
 // is split: block (x = group of 64 thresholds, y = item, z = slice) of 16 waves adds the units of
 // its slice -- wave w takes units begin + w, begin + w + 16, ... in order, then wave 0 adds the 16
 // sums in order -- and, when there is more than one slice, leaves the slice's sums in `mid`, which
-// a second kernel adds in slice order.  Items of at most four units take blocks of one wave instead.
+// a second kernel adds in slice order.  Items of at most four units are added by a thread per threshold instead.
 #pragma once
 #include "ecc_device.h"
 #include "ecc_internal.h"
@@ -56,41 +56,47 @@ __device__ __forceinline__ void red_stamp(const RedOut& o) {
   }
 }
 
-// Origin: unit -> origin of its coordinates, `void operator()(int unit, int (&o)[3]) const`
-template <int WAVES, int STRIDE, bool CHI, int NC, typename Origin>
-__global__ __launch_bounds__(WAVES * kWave) void soft_reduce_kernel(const float* __restrict__ partial, int units,
+// Adds the sums at `at` (unit and threshold) of unit q.  Origin: unit -> origin of its coordinates,
+// `void operator()(int unit, int (&o)[3]) const`
+template <int STRIDE, bool CHI, int NC, typename Origin>
+__device__ __forceinline__ void red_add(const float* __restrict__ partial, int64_t at, int q, const Origin& origin,
+                                        double (&s)[kRedMaxSums]) {
+  constexpr int A = RedLayout<CHI, NC>::kA;
+  float e[STRIDE];
+  const float* p = partial + at * STRIDE;
+  if constexpr (STRIDE == 4) {
+    const float4 f = *reinterpret_cast<const float4*>(p);
+    e[0] = f.x, e[1] = f.y, e[2] = f.z, e[3] = f.w;
+  } else {
+#pragma unroll
+    for (int c = 0; c < STRIDE; ++c) e[c] = p[c];
+  }
+  if constexpr (CHI) s[0] += (double)e[0];
+  if constexpr (NC >= 0) {
+    int o[3];
+    origin(q, o);
+    const double a0 = (double)e[A];
+    s[A] += a0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) s[A + 1 + c] += (double)o[c] * a0 + (double)e[A + 1 + c];
+  }
+}
+
+template <int STRIDE, bool CHI, int NC, typename Origin>
+__global__ __launch_bounds__(kRedWaves * kWave) void soft_reduce_kernel(const float* __restrict__ partial, int units,
                                                                         int per_slice, int T, float alpha, float lambda,
                                                                         Origin origin, double* __restrict__ mid,
                                                                         RedOut out) {
-  constexpr int NS = RedLayout<CHI, NC>::kSums, A = RedLayout<CHI, NC>::kA;
-  __shared__ double red[NS][WAVES][kWave];
+  constexpr int NS = RedLayout<CHI, NC>::kSums;
+  __shared__ double red[NS][kRedWaves][kWave];
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
   const int j = blockIdx.x * kWave + lane;
   const int item = blockIdx.y, slice = blockIdx.z;
   const int begin = slice * per_slice, end = min(units, begin + per_slice);
   double s[kRedMaxSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  if (j < T) {
-    for (int q = begin + wv; q < end; q += WAVES) {
-      float e[STRIDE];
-      const float* p = partial + (((int64_t)item * units + q) * T + j) * STRIDE;
-      if constexpr (STRIDE == 4) {
-        const float4 f = *reinterpret_cast<const float4*>(p);
-        e[0] = f.x, e[1] = f.y, e[2] = f.z, e[3] = f.w;
-      } else {
-#pragma unroll
-        for (int c = 0; c < STRIDE; ++c) e[c] = p[c];
-      }
-      if constexpr (CHI) s[0] += (double)e[0];
-      if constexpr (NC >= 0) {
-        int o[3];
-        origin(q, o);
-        const double a0 = (double)e[A];
-        s[A] += a0;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) s[A + 1 + c] += (double)o[c] * a0 + (double)e[A + 1 + c];
-      }
-    }
-  }
+  if (j < T)
+    for (int q = begin + wv; q < end; q += kRedWaves)
+      red_add<STRIDE, CHI, NC>(partial, ((int64_t)item * units + q) * T + j, q, origin, s);
   for (int c = 0; c < NS; ++c) red[c][wv][lane] = s[c];
   if (gridDim.z == 1) red_stamp(out);
   __syncthreads();
@@ -98,7 +104,7 @@ __global__ __launch_bounds__(WAVES * kWave) void soft_reduce_kernel(const float*
     double r[kRedMaxSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
     for (int c = 0; c < NS; ++c) {
       r[c] = red[c][0][lane];
-      for (int w = 1; w < WAVES; ++w) r[c] += red[c][w][lane];
+      for (int w = 1; w < kRedWaves; ++w) r[c] += red[c][w][lane];
     }
     if (gridDim.z == 1) {
       red_finish<CHI, NC>(r, (int64_t)item * T + j, alpha, lambda, out);
@@ -106,6 +112,20 @@ __global__ __launch_bounds__(WAVES * kWave) void soft_reduce_kernel(const float*
       for (int c = 0; c < NS; ++c) mid[(((int64_t)item * gridDim.z + slice) * T + j) * NS + c] = r[c];
     }
   }
+}
+
+// Items of at most four units: a thread per threshold adds them all (blocks of 16 waves for one or two units took longer
+// than the sweep: 1024 x 28^2, T = 512, forward, 33 us).
+constexpr int kRedFew = 4;
+template <int STRIDE, bool CHI, int NC, typename Origin>
+__global__ __launch_bounds__(256) void soft_reduce_few_kernel(const float* __restrict__ partial, int units, int T, float alpha,
+                                                              float lambda, Origin origin, RedOut out) {
+  const int j = blockIdx.x * 256 + threadIdx.x, item = blockIdx.y;
+  red_stamp(out);
+  if (j >= T) return;
+  double s[kRedMaxSums] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int q = 0; q < units; ++q) red_add<STRIDE, CHI, NC>(partial, ((int64_t)item * units + q) * T + j, q, origin, s);
+  red_finish<CHI, NC>(s, (int64_t)item * T + j, alpha, lambda, out);
 }
 
 // wave w adds slices w, w + 16, ... in order, wave 0 adds the 16 sums in order
@@ -154,13 +174,13 @@ static void launch_soft_reduce(const float* partial, double* mid, int units, int
   int per;
   const int slices = soft_reduce_slices(units, per);
   const unsigned tg = (unsigned)((T + kWave - 1) / kWave);
-  const dim3 grid(tg, (unsigned)batch, (unsigned)slices);
-  if (units <= 4)  // small items: one wave adds them all (1024 x 28^2, T = 512, forward: 33 us with blocks of 16 waves, 25 now)
-    hipLaunchKernelGGL((soft_reduce_kernel<1, STRIDE, CHI, NC, Origin>), grid, dim3(kWave), 0, st, partial, units, per, T,
-                       alpha, lambda, origin, mid, out);
-  else
-    hipLaunchKernelGGL((soft_reduce_kernel<kRedWaves, STRIDE, CHI, NC, Origin>), grid, dim3(kRedWaves * kWave), 0, st, partial,
-                       units, per, T, alpha, lambda, origin, mid, out);
+  if (units <= kRedFew) {
+    hipLaunchKernelGGL((soft_reduce_few_kernel<STRIDE, CHI, NC, Origin>), dim3((unsigned)((T + 255) / 256), (unsigned)batch),
+                       dim3(256), 0, st, partial, units, T, alpha, lambda, origin, out);
+    return;
+  }
+  hipLaunchKernelGGL((soft_reduce_kernel<STRIDE, CHI, NC, Origin>), dim3(tg, (unsigned)batch, (unsigned)slices),
+                     dim3(kRedWaves * kWave), 0, st, partial, units, per, T, alpha, lambda, origin, mid, out);
   if (slices > 1)
     hipLaunchKernelGGL((soft_reduce_final_kernel<CHI, NC>), dim3(tg, (unsigned)batch), dim3(kRedWaves * kWave), 0, st, mid,
                        slices, T, alpha, lambda, out);

@@ -63,16 +63,17 @@ def test_fewer_layers_than_slots(shape, T):
     _near(host(api.ecc_soft_bwd_saved(g, nd, ud, alpha, td, lam, state)), gx, 1e-3)
 
 
-@pytest.mark.parametrize("shape,T", [((1100, 9, 13), 257), ((1024, 31, 33), 300), ((600, 70, 50), 513),
+@pytest.mark.parametrize("shape,T", [((1100, 9, 13), 257), ((9000, 8, 9), 40), ((400, 9, 13), 300), ((1024, 31, 33), 300), ((600, 70, 50), 513),
                                      ((1024, 9, 10, 11), 290)])
 def test_forward_of_a_large_batch_of_small_items(shape, T):
-    """The forward pass alone (tile kernels there) against the one that saves (fused): float32 sums of a few hundred
-    terms of size <= 6, grouped differently."""
+    """The forward pass alone and the one that saves: the same to the bit; a few items against the oracle."""
     nd = len(shape) - 1
     X = torch.randn(shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(T))
-    u = dev(np.array([0.6, 0.8] if nd == 2 else [0.48, 0.6, 0.64], dtype=np.float32))
-    tau = torch.linspace(-3.0, 3.0, T, device="cuda")
+    un = np.array([0.6, 0.8] if nd == 2 else [0.48, 0.6, 0.64], dtype=np.float32)
+    u, tau = dev(un), torch.linspace(-3.0, 3.0, T, device="cuda")
     for tilted in (False, True):
         a = api.ecc_soft_fwd(X, nd, u, 0.01, tau, 20.0, tilted_c=tilted)
-        b = api.ecc_soft_fwd_save(X, nd, u, 0.01, tau, 20.0, tilted_c=tilted, want=())[0]
-        assert float((a - b).abs().max()) <= 1e-4 * float(b.abs().max())
+        assert torch.equal(a, api.ecc_soft_fwd_save(X, nd, u, 0.01, tau, 20.0, tilted_c=tilted, want=())[0])
+    a = api.ecc_soft_fwd(X, nd, u, 0.01, tau, 20.0)
+    for i in (0, shape[0] // 2, shape[0] - 1):
+        _near(host(a[i]), O.soft_fwd_batch(host(X[i:i + 1]), un, 0.01, host(tau), 20.0)[0], 1e-4)

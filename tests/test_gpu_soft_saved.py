@@ -222,3 +222,22 @@ def test_threshold_counts_around_the_wave_and_rows_of_several_batches(shape, fie
     _close(host(a[0])[0], rgx[0], 1e-3, "grad_X")
     _close_sum(host(a[1])[0], rdt[0], 1e-3, "dchi_dtau")
     _close_sum(host(a[2])[0], rdu[0], 1e-3, "dchi_du")
+
+
+@pytest.mark.parametrize("shape", [(40, 50), (9, 20, 30)])
+def test_a_call_that_keeps_no_state_leaves_none_of_an_earlier_one(shape):
+    """The thresholds may differ between the two calls, so the backward call may look for lists where the forward call
+    kept none (more thresholds than its rows have room for; here: forced)."""
+    nd = len(shape)
+    A, B = (dev(np.stack([synth.grf(shape, 1.5, s + i) for i in range(2)])) for s in (160, 170))
+    u = dev(np.array([0.6, 0.8] if nd == 2 else [0.48, -0.6, 0.64], np.float32))
+    tau = torch.linspace(-1.0, 1.5, 9, device="cuda")
+    state = api.ecc_soft_fwd_save(A, nd, u, 0.02, tau, 8.0)[3]
+    prev = api.ecc_debug_force(api.ECC_FORCE_SOFT_TILES)
+    try:
+        api.ecc_soft_fwd_save(B, nd, u, 0.02, tau, 8.0, state=state)
+    finally:
+        api.ecc_debug_force(prev)
+    got, want = api.ecc_soft_bwd_saved(B, nd, u, 0.02, tau, 8.0, state), api.ecc_soft_bwd(B, nd, u, 0.02, tau, 8.0)[0]
+    for i in range(2):
+        _close(host(got[i]), host(want[i]), 1e-4, f"grad_X[{i}]")
