@@ -174,7 +174,8 @@ int ecc_coeff(const void* grid, int ndim, const int64_t* dims, int64_t batch, ec
  *   tau   device float32 [T], 1 <= T <= ECC_MAX_THRESHOLDS, shared by the batch
  *   lambda > 0 and finite;  alpha finite
  *   chi   device out float32 [batch][T]
- * Sigmoids are evaluated in float32 on an argument formed in float64; partial
+ * Sigmoids are evaluated in float32 on an argument formed in float64 (with up to
+ * 256 thresholds to within an ulp of it, beyond that rounded once); partial
  * sums are combined in a fixed order, so results are run-to-run identical.
  */
 int ecc_soft_fwd(const float* grid, int ndim, const int64_t* dims, int64_t batch,
@@ -223,8 +224,9 @@ int ecc_soft_bwd(const float* grid, int ndim, const int64_t* dims, int64_t batch
  *          (more than one in eight of some unit of rows / planes) that its list
  *          overflowed, are noticed on the device: those items are evaluated from
  *          the grid again, so the result is right either way.
- * Shapes outside the fused kernels (grids narrower than 8, volumes of
- * 2^31 vertices or more) keep no state: the two calls then run ecc_soft_fwd +
+ * Calls outside the fused kernels (grids narrower than 8, volumes of
+ * 2^31 vertices or more; with more than 256 thresholds also batches of many
+ * small items) keep no state: the two calls then run ecc_soft_fwd +
  * ecc_soft_bwd's kernels.  workspace as ecc_soft_fwd.
  */
 size_t ecc_soft_state_bytes(int ndim, const int64_t* dims /* host */, int64_t batch);
