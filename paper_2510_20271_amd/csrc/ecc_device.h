@@ -360,6 +360,7 @@ struct HistSink {  // drain target: the block's LDS histogram
   typedef float2 Entry;
   static constexpr bool kTrackRange = false;
   static constexpr bool kZeroFill = false;
+  static constexpr bool kDense = LEVELS;  // takes dense chunks of integer levels vertex by vertex (add_level)
   int* lhist;
   const float* table;  // float[bins] thresholds (LDS or global), unused for LEVELS
   int bins;
@@ -386,6 +387,11 @@ struct HistSink {  // drain target: the block's LDS histogram
     else b = bin_table<SUPER>(v, table, bins, lo, scale);
     if (b < bins) atomicAdd(&lhist[b], c);
   }
+  // every lane's own vertex: level v (an element of an integer grid), coefficient c (0: nothing to add)
+  __device__ __forceinline__ void add_level(unsigned v, int c) {
+    if (SUPER) v = min(v, (unsigned)bins - 1u);
+    if (c != 0 && v < (unsigned)bins) atomicAdd(&lhist[v], c);
+  }
 };
 
 // Drain target of the single-pass mode: a list of critical vertices (value, c)
@@ -402,6 +408,7 @@ struct ListSink {
   typedef float2 Entry;
   static constexpr bool kTrackRange = true;
   static constexpr bool kZeroFill = false;
+  static constexpr bool kDense = false;
   float2* list;       // this block's sub-list
   unsigned* counter;  // its fill count
   unsigned cap;       // entries per sub-list

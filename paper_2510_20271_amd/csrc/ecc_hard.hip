@@ -523,7 +523,7 @@ hipError_t launch_hard(const void* grid, const Shape& s, int dtype, int bins, bo
     la.lists = reinterpret_cast<float2*>(wsb + kTableOffset + table_bytes(bins) + counter_bytes(s));
     // no more sub-lists than blocks that append to them (a block uses one sub-list);
     // the room of the unused ones goes to the others
-    const unsigned blocks = fast2d ? sweep2d_list_blocks(s, dtype, true) : sweep3d_list_blocks(s);
+    const unsigned blocks = fast2d ? sweep2d_list_blocks(s, dtype, true) : sweep3d_list_blocks(s, dtype, true);
     la.nsub = list_nsub(s);
     la.cap = list_cap(s);
     while (la.nsub > 1 && la.nsub > blocks) {

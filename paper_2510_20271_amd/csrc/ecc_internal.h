@@ -99,8 +99,15 @@ void launch_sweep3d(const void* grid, const Shape& s, int dtype, bool levels, in
                     hipStream_t st, const unsigned* run_if, const DirArgs* dir = nullptr, int conv = 0);
 void launch_sweep3d_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st,
                          const DirArgs* dir = nullptr, int conv = 0);
-unsigned sweep3d_list_blocks(const Shape& s);
-unsigned sweep3d_block_vertices(const Shape& s);
+unsigned sweep3d_list_blocks(const Shape& s, int dtype, bool shared);
+unsigned sweep3d_block_vertices(const Shape& s, int dtype);
+// the same for one- and two-byte element types, two vertices to a register (ecc_sweep3d_packed.h)
+void launch_sweep3dp(const void* grid, const Shape& s, int dtype, bool levels, int bins, const HardHeader* hdr,
+                     const float* table, unsigned long long* hist, hipStream_t st, const unsigned* run_if, int conv);
+void launch_sweep3dp_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st, int conv);
+void launch_coeff3dp(const void* grid, const Shape& s, int dtype, int8_t* c_out, hipStream_t st);
+unsigned sweep3dp_blocks(const Shape& s, bool shared);
+unsigned sweep3dp_block_vertices(const Shape& s);
 
 // ---- sweep-kernel timing (measurement aid) ----------------------------------
 hipError_t profile_begin(int max_launches);

@@ -369,9 +369,8 @@ static bool mid_plan(const Shape& s, int dtype, unsigned& per_item, unsigned& ca
     per_item = sweep2d_list_blocks(s, dtype, false);
     cap = sweep2d_block_vertices(s, dtype);
   } else if (sweep3d_supported(s, 1)) {
-    if (dtype != 2) return false;  // (the tube sweep's list kernels take float32 here)
-    per_item = sweep3d_list_blocks(s);
-    cap = sweep3d_block_vertices(s);
+    per_item = sweep3d_list_blocks(s, dtype, false);
+    cap = sweep3d_block_vertices(s, dtype);
   } else {
     return false;
   }
@@ -386,6 +385,11 @@ bool mid_supported(const Shape& s, int bins, int dtype) {
     return false;
   unsigned per_item, cap;
   if (!mid_plan(s, dtype, per_item, cap)) return false;
+  // (volumes of two-byte elements have a plan of their own; the workspace's size does not depend on the type, and must not
+  // grow for float32 calls)
+  if (dtype != 2 && s.ndim == 3 &&
+      (!mid_supported(s, bins, 2) || mid_workspace_bytes(s, dtype) > mid_workspace_bytes(s, 2)))
+    return false;
   return (int64_t)per_item * s.batch <= kMidBlocks && per_item <= 64u * kFinishBlock;
 }
 

@@ -1,5 +1,5 @@
 // 3D sweep for gfx950: coefficient c(p) (Eq. 3 of the paper), critical vertices handed to a sink
-// (LDS histogram, list, or the sigmoid sums of the soft path).
+// (LDS histogram, list, or the sigmoid sums of the soft path); float32 (narrower types: ecc_sweep3d_packed.h).
 //
 // Layout.  A wave owns a tube of 62 output columns (64 lanes: one halo column
 // each side) x R output rows (plus one halo row above and below) and marches
@@ -91,20 +91,6 @@ template <typename T> struct Load;
 template <> struct Load<float> {
   static __device__ __forceinline__ float get(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, v, s, 0));
-  }
-};
-template <typename T> struct Load16 {  // two-byte elements, kept as they are until they are converted
-  static __device__ __forceinline__ T get(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s) {
-    return __builtin_bit_cast(T, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, v, s, 0));
-  }
-};
-template <> struct Load<uint16_t> : Load16<uint16_t> {};
-template <> struct Load<int16_t> : Load16<int16_t> {};
-template <> struct Load<F16> : Load16<F16> {};
-template <> struct Load<Bf16> : Load16<Bf16> {};
-template <> struct Load<uint8_t> {
-  static __device__ __forceinline__ uint8_t get(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s) {
-    return (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, v, s, 0);
   }
 };
 
@@ -541,6 +527,20 @@ __device__ __forceinline__ void sweep_tube(const T* __restrict__ g, int64_t item
 
 }  // namespace s3
 
+// Sink of the coefficient map: c(p) of the critical vertices
+struct CoeffSink3d {
+  static constexpr bool kTrackRange = false;
+  static constexpr bool kZeroFill = false;
+  static constexpr bool kDense = false;
+  int8_t* out;    // this item's map
+  int64_t plane;  // H * W
+  int oz;         // first plane of the wave's segment
+  __device__ __forceinline__ void take(int n, float, int c, unsigned inpl, unsigned zrel) {
+    const int lane = threadIdx.x & (kWave - 1);
+    if (lane < n) out[(int64_t)(oz + (int)zrel) * plane + inpl] = (int8_t)c;
+  }
+};
+
 // How the tubes of one z segment are numbered.  The strips but the last are full (62
 // outputs) and have one unit per row group; the last strip is folded when it is
 // narrow (see sweep_tube): F row groups per unit.  Units are padded to multiples of
@@ -551,7 +551,8 @@ struct Tiling3 {
   int S, F;                     // lanes per fold and folds of a last-strip unit
   int ngroupT, full, units_seg; // units of the last strip, units of the full strips, units per segment
 };
-__host__ __device__ __forceinline__ Tiling3 make_tiling3(int D, int H, int W, long long batch, int R) {
+__host__ __device__ __forceinline__ Tiling3 make_tiling3(int D, int H, int W, long long batch, int R,
+                                                         bool always_fold = false) {
   Tiling3 t;
   t.nstrip = (W + s3::kOut - 1) / s3::kOut;
   t.ngroup = (H + R - 1) / R;
@@ -563,7 +564,7 @@ __host__ __device__ __forceinline__ Tiling3 make_tiling3(int D, int H, int W, lo
   // 512^3); when every wave is resident at once it only makes the last strip's waves the
   // slowest ones (7 % lost on a 256^3 volume of i.i.d. values), so small launches keep one
   // row group per wave.
-  const bool many_rounds = (long long)t.nstrip * t.ngroup * batch * D >= 160000;  // about 1.3 rounds of 30-plane units
+  const bool many_rounds = always_fold || (long long)t.nstrip * t.ngroup * batch * D >= 160000;  // about 1.3 rounds of 30-plane units
   if (many_rounds && wt + 2 <= kWave / 2) {
     t.S = wt + 2;
     t.F = kWave / t.S;
