@@ -132,8 +132,14 @@ __device__ __forceinline__ int bin_from_table(float x, const float* __restrict__
                                               float lo, float scale) {
   float f = (x - lo) * scale;
   int b = (f > 0.0f) ? (int)fminf(f, (float)(bins - 1)) : 0;
-  while (b > 0 && x <= t[b - 1]) --b;
-  while (b < bins && x > t[b]) ++b;
+  const float below = t[max(b - 1, 0)], here = t[b];  // (one trip to the table: the guess is right but for rounding)
+  if (b > 0 && x <= below) {
+    do --b;
+    while (b > 0 && x <= t[b - 1]);
+  } else if (x > here) {
+    do ++b;
+    while (b < bins && x > t[b]);
+  }
   return b;
 }
 
@@ -147,8 +153,14 @@ __device__ __forceinline__ int bin_super_from_table(float x, const float* __rest
                                                     float lo, float scale) {
   float f = (x - lo) * scale;
   int b = (f > 0.0f) ? (int)fminf(f, (float)(bins - 1)) : 0;
-  while (b < bins - 1 && x >= t[b + 1]) ++b;
-  while (b >= 0 && x < t[b]) --b;
+  const float here = t[b], above = t[min(b + 1, bins - 1)];
+  if (b < bins - 1 && x >= above) {
+    do ++b;
+    while (b < bins - 1 && x >= t[b + 1]);
+  } else if (x < here) {
+    do --b;
+    while (b >= 0 && x < t[b]);
+  }
   return b < 0 ? bins : b;
 }
 // integer grids without a range: thresholds t_b = b; X <= b (sublevel) or X >= b (superlevel)
@@ -295,6 +307,32 @@ __device__ __forceinline__ float wave_sum_lane63(float v) {
   v += dpp_move<0x140, 0xf>(v);  // row_mirror: every lane holds its row's sum
   v += dpp_move<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
   v += dpp_move<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3: lane 63 holds the total
+  return v;
+}
+
+// The same moves for whole numbers: least / greatest of the 64 lanes, delivered in lane 63, and inclusive prefix sums.  (A
+// shuffle is a trip through LDS, six of them a reduction; an atomic of a whole wave on one LDS word takes the lanes one
+// after the other.)
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ unsigned dpp_move_u(unsigned old, unsigned x) {  // `old` where the move has no source
+  return (unsigned)__builtin_amdgcn_update_dpp((int)old, (int)x, CTRL, ROW_MASK, 0xf, false);
+}
+__device__ __forceinline__ unsigned wave_min_lane63(unsigned v) {
+  v = min(v, dpp_move_u<0xB1, 0xf>(v, v));
+  v = min(v, dpp_move_u<0x4E, 0xf>(v, v));
+  v = min(v, dpp_move_u<0x141, 0xf>(v, v));
+  v = min(v, dpp_move_u<0x140, 0xf>(v, v));
+  v = min(v, dpp_move_u<0x142, 0xa>(v, v));
+  return min(v, dpp_move_u<0x143, 0xc>(v, v));
+}
+__device__ __forceinline__ unsigned wave_max_lane63(unsigned v) { return ~wave_min_lane63(~v); }
+__device__ __forceinline__ unsigned wave_scan_add(unsigned v) {
+  v += dpp_move_u<0x111, 0xf>(0u, v);  // row_shr:1, 2, 4, 8: prefix sums of each row of 16 lanes
+  v += dpp_move_u<0x112, 0xf>(0u, v);
+  v += dpp_move_u<0x114, 0xf>(0u, v);
+  v += dpp_move_u<0x118, 0xf>(0u, v);
+  v += dpp_move_u<0x142, 0xa>(0u, v);  // the rows' totals handed on
+  v += dpp_move_u<0x143, 0xc>(0u, v);
   return v;
 }
 
