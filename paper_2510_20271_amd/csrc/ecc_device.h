@@ -132,15 +132,12 @@ __device__ __forceinline__ int bin_from_table(float x, const float* __restrict__
                                               float lo, float scale) {
   float f = (x - lo) * scale;
   int b = (f > 0.0f) ? (int)fminf(f, (float)(bins - 1)) : 0;
-  const float below = t[max(b - 1, 0)], here = t[b];  // (one trip to the table: the guess is right but for rounding)
-  if (b > 0 && x <= below) {
-    do --b;
-    while (b > 0 && x <= t[b - 1]);
-  } else if (x > here) {
-    do ++b;
-    while (b < bins && x > t[b]);
+  for (;;) {  // (both neighbours of the guess in one trip to the table; it is right but for rounding)
+    const float below = t[max(b - 1, 0)], here = t[min(b, bins - 1)];
+    if (b > 0 && x <= below) --b;
+    else if (b < bins && x > here) ++b;
+    else return b;
   }
-  return b;
 }
 
 // Superlevel curves (X >= tau) are read at the LOWER edges of the same bins:
@@ -153,15 +150,12 @@ __device__ __forceinline__ int bin_super_from_table(float x, const float* __rest
                                                     float lo, float scale) {
   float f = (x - lo) * scale;
   int b = (f > 0.0f) ? (int)fminf(f, (float)(bins - 1)) : 0;
-  const float here = t[b], above = t[min(b + 1, bins - 1)];
-  if (b < bins - 1 && x >= above) {
-    do ++b;
-    while (b < bins - 1 && x >= t[b + 1]);
-  } else if (x < here) {
-    do --b;
-    while (b >= 0 && x < t[b]);
+  for (;;) {
+    const float here = t[max(b, 0)], above = t[min(b + 1, bins - 1)];
+    if (b < bins - 1 && x >= above) ++b;
+    else if (b >= 0 && x < here) --b;
+    else return b < 0 ? bins : b;
   }
-  return b < 0 ? bins : b;
 }
 // integer grids without a range: thresholds t_b = b; X <= b (sublevel) or X >= b (superlevel)
 template <bool SUPER>
@@ -431,6 +425,27 @@ struct HistSink {  // drain target: the block's LDS histogram
     if (c != 0 && v < (unsigned)bins) atomicAdd(&lhist[v], c);
   }
 };
+
+// The end of a histogram block: its counters to where `out` says (every thread calls, after a barrier).
+template <int BLOCK>
+__device__ __forceinline__ void leave_histogram(const int* lhist, int bins, const HistOut& out) {
+  if (out.n == 0u) {
+    unsigned long long* const h = out.curve + (int64_t)blockIdx.y * bins;
+    for (int b = threadIdx.x; b < bins; b += BLOCK) {
+      const int v = lhist[b];
+      if (v != 0) atomicAdd(&h[b], (unsigned long long)(long long)v);
+    }
+  } else if (out.shared) {
+    int* const h = out.rows + ((size_t)blockIdx.y * out.n + (blockIdx.x & (out.n - 1u))) * (size_t)bins;  // (n: a power of two)
+    for (int b = threadIdx.x; b < bins; b += BLOCK) {
+      const int v = lhist[b];
+      if (v != 0) atomicAdd(&h[b], v);
+    }
+  } else {
+    int* const h = out.rows + ((size_t)blockIdx.y * out.n + blockIdx.x) * (size_t)bins;
+    for (int b = threadIdx.x; b < bins; b += BLOCK) h[b] = lhist[b];
+  }
+}
 
 // Drain target of the single-pass mode: a list of critical vertices (value, c)
 // in the workspace.  A wave reserves n slots with one atomic; when the list is

@@ -86,10 +86,10 @@ __global__ __launch_bounds__(kBlock) void minmax_f32_kernel(const float* __restr
 // ---------------------------------------------------------------------------
 // t_b = float32(lo + (b+1)(hi-lo)/B) in float64 with every operation rounded
 // on its own (no contraction), t_{B-1} = float32(hi); lower != 0: the lower edges
-// of the same bins (superlevel curves).
+// of the same bins (superlevel curves).  clear: what the sweep's blocks add to.
 __global__ void prepare_kernel(HardHeader* h, float* __restrict__ table, int bins, int from_device,
-                               double lo_host, double hi_host, unsigned long long* hist,
-                               int64_t hist_len, int lower) {
+                               double lo_host, double hi_host, unsigned* clear,
+                               int64_t clear_words, int lower) {
   double lo, hi;
   if (from_device) {
     lo = (double)key_float(h->min_key);
@@ -102,7 +102,7 @@ __global__ void prepare_kernel(HardHeader* h, float* __restrict__ table, int bin
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t b = tid; b < bins; b += stride)
     table[b] = lower ? threshold_lower_at((int)b, bins, lo, hi) : threshold_at((int)b, bins, lo, hi);
-  for (int64_t i = tid; i < hist_len; i += stride) hist[i] = 0ull;
+  for (int64_t i = tid; i < clear_words; i += stride) clear[i] = 0u;
   if (tid == 0) {
     h->lo = __double2float_rn(lo);
     h->scale = bin_scale(bins, lo, hi);
@@ -118,8 +118,7 @@ __global__ void prepare_kernel(HardHeader* h, float* __restrict__ table, int bin
 template <typename T, int ND, bool LEVELS, int CONV, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void sweep_generic_kernel(
     const T* __restrict__ grid, int64_t D, int64_t H, int64_t W, int64_t N, int bins,
-    const HardHeader* __restrict__ hdr, const float* __restrict__ table,
-    unsigned long long* __restrict__ hist) {
+    const HardHeader* __restrict__ hdr, const float* __restrict__ table, HistOut hist) {
   extern __shared__ int lhist[];
   for (int b = threadIdx.x; b < bins; b += BLOCK) lhist[b] = 0;
   __syncthreads();
@@ -152,11 +151,7 @@ __global__ __launch_bounds__(BLOCK) void sweep_generic_kernel(
     }
   }
   __syncthreads();
-  unsigned long long* out = hist + (int64_t)blockIdx.y * bins;
-  for (int b = threadIdx.x; b < bins; b += BLOCK) {
-    const int v = lhist[b];
-    if (v != 0) atomicAdd(&out[b], (unsigned long long)(long long)v);
-  }
+  leave_histogram<BLOCK>(lhist, bins, hist);
 }
 
 // ---------------------------------------------------------------------------
@@ -297,6 +292,78 @@ __global__ __launch_bounds__(BLOCK) void scan_kernel(long long* __restrict__ cur
   }
 }
 
+// The same from the rows that the blocks of a histogram sweep left: a block per item adds the item's n rows, bin by bin,
+// then scans.  Its loads are in flight together, sixteen a thread: the kernel is one trip to memory and a few dependent
+// steps.  32 bits: rows are kept for items of up to 2^28 vertices, |c| <= 7.
+// kRowsBlock: 1024 threads, or 256 where they have no more than sixteen loads each (up to 256 bins).
+constexpr int kRowsBins = 8;  // bins of a thread at the most
+template <int kRowsBlock>
+__global__ __launch_bounds__(kRowsBlock) void scan_rows_kernel(const int* __restrict__ rows, unsigned n, int bins, int suffix,
+                                                               long long* __restrict__ curve) {
+  extern __shared__ int lsum[];  // up to 1024 bins: [groups - 1][bins] sums of the other groups; beyond: [bins]
+  __shared__ int wsum[kRowsBlock / kWave];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
+  const int* const r0 = rows + (size_t)blockIdx.x * n * (size_t)bins;
+  long long* const out = curve + (int64_t)blockIdx.x * bins;
+  auto bin = [&](int b) { return suffix ? bins - 1 - b : b; };
+  auto across_waves = [&](int s) {  // exclusive prefix sum of s over the block's threads
+    const int inc = (int)wave_scan_add((unsigned)s);
+    if (lane == kWave - 1) wsum[wv] = inc;
+    __syncthreads();
+    int run = inc - s;
+#pragma unroll
+    for (int w = 0; w < kRowsBlock / kWave; ++w) run += w < wv ? wsum[w] : 0;
+    return run;
+  };
+  if (bins <= kRowsBlock) {  // a thread per bin, further groups of threads on further rows
+    const int groups = kRowsBlock / bins, group = tid / bins, b = tid - group * bins;
+    int s = 0;
+    if (group < groups) {
+      const int* const col = r0 + bin(b);
+      for (unsigned r = group; r < n; r += 16u * groups) {
+        int v[16];
+#pragma unroll
+        for (unsigned q = 0; q < 16u; ++q) v[q] = r + q * groups < n ? col[(size_t)(r + q * groups) * bins] : 0;
+#pragma unroll
+        for (unsigned q = 0; q < 16u; ++q) s += v[q];
+      }
+    }
+    if (groups > 1 && n > 1u) {
+      if (group > 0 && group < groups) lsum[(group - 1) * bins + b] = s;
+      __syncthreads();
+      if (group == 0)
+        for (int q = 1; q < groups && q < (int)n; ++q) s += lsum[(q - 1) * bins + b];
+    }
+    if (group > 0) s = 0;
+    const int run = across_waves(s) + s;
+    if (group == 0) out[bin(b)] = (long long)run;
+    return;
+  }
+  {
+    int s[kRowsBins];
+#pragma unroll
+    for (int j = 0; j < kRowsBins; ++j) s[j] = 0;
+    for (unsigned r = 0; r < n; ++r) {
+#pragma unroll
+      for (int j = 0; j < kRowsBins; ++j)
+        if (tid + j * kRowsBlock < bins) s[j] += r0[(size_t)r * bins + tid + j * kRowsBlock];
+    }
+#pragma unroll
+    for (int j = 0; j < kRowsBins; ++j)
+      if (tid + j * kRowsBlock < bins) lsum[tid + j * kRowsBlock] = s[j];
+  }
+  __syncthreads();
+  const int per = (bins + kRowsBlock - 1) / kRowsBlock;
+  const int b0 = min(tid * per, bins), b1 = min(b0 + per, bins);
+  int s = 0;
+  for (int b = b0; b < b1; ++b) s += lsum[bin(b)];
+  int run = across_waves(s);
+  for (int b = b0; b < b1; ++b) {
+    run += lsum[bin(b)];
+    out[bin(b)] = (long long)run;
+  }
+}
+
 void launch_scan(int64_t* curve, const Shape& s, int bins, int suffix, hipStream_t st) {
   long long* c = reinterpret_cast<long long*>(curve);
   if (bins <= 4 * 256) hipLaunchKernelGGL(scan_kernel<256>, dim3((unsigned)s.batch), dim3(256), 0, st, c, bins, suffix);
@@ -427,15 +494,43 @@ static int blocks_for(int64_t N) {
   return (int)(nb < 1 ? 1 : (nb > 4096 ? 4096 : nb));
 }
 
+static int generic_block(const Shape& s) { return s.N >= 8192 ? 1024 : kBlock; }
+static unsigned generic_blocks(const Shape& s) {
+  return (unsigned)std::min<int64_t>((s.N + generic_block(s) - 1) / generic_block(s), 4096);
+}
+
+// Rows of the histogram sweep's blocks in the workspace (room: bytes behind the table), or none.
+static HistOut hist_out(const Shape& s, int bins, bool levels, unsigned blocks, unsigned long long* curve, void* room, size_t bytes) {
+  HistOut h = {curve, nullptr, 0u, 0};
+  if (s.N > ((int64_t)1 << 28) || bins > 8192) return h;  // (sums and LDS of scan_rows_kernel)
+  const size_t row = (size_t)s.batch * bins * sizeof(int);
+  // A row for each block where that saves the launch that clears (one bin per level: there is no table to make either); 256^2
+  // uint8 noise 10.5 -> 8.1 us.  Otherwise rows where many blocks would meet in one item's histogram, up to 16, a power of
+  // two, and few enough that the scan reads them in one trip (4677 x 3307 uint8 page with 1 / 2 / 4 / 8 rows 29.4 / 20.2 / 17.1
+  // / 17.0 us; 256^3 uint16 noise, 4096 bins 40.1 / 37.8 / 38.3 / 42.4).  With fewer blocks the additions queue for less than
+  // the rows cost (64 x 256^2, 1024 bins, 8 blocks an item: 14.0 without, 15.4 with; 8 x 2048^2, 72 blocks 36.0 / 37.3;
+  // 100 x 120 x 90, 144 blocks 16.3 / 17.2; but 1024^2, 160 blocks 12.6 / 11.7).
+  unsigned n = blocks;
+  if (!levels || (int64_t)n * bins > 16384 || n > 64 || row * n > bytes) {
+    if (blocks < 160 || row > bytes) return h;
+    const unsigned most = (unsigned)std::max(2, std::min(16, 8192 / bins));
+    n = 1;
+    while (2 * n <= most && row * 2 * n <= bytes) n *= 2;
+    h.shared = 1;
+  }
+  h.rows = static_cast<int*>(room);
+  h.n = n;
+  return h;
+}
+
 template <typename T>
 static void launch_sweep_generic(const void* grid, const Shape& s, bool levels, int bins,
                                  const HardHeader* hdr, const float* table,
-                                 unsigned long long* hist, hipStream_t st, int conv) {
+                                 const HistOut& hist, hipStream_t st, int conv) {
   // Blocks of 1024 threads where there are enough vertices for them: a block ends with an atomic for every bin it met,
   // and blocks of 256 meet most of an 8-bit image's levels (256^2 uint8 noise, whole call: 15.0 us, now 13.1).
-  const bool large = s.N >= 8192;
-  const int block = large ? 1024 : kBlock;
-  dim3 g((unsigned)std::min<int64_t>((s.N + block - 1) / block, 4096), (unsigned)s.batch);
+  const bool large = generic_block(s) == 1024;
+  dim3 g(generic_blocks(s), (unsigned)s.batch);
   size_t lds = (size_t)bins * sizeof(int);
   const T* p = static_cast<const T*>(grid);
 #define ECC_BLOCK(ND, LV, CV, BL)                                                                         \
@@ -509,8 +604,6 @@ hipError_t launch_hard(const void* grid, const Shape& s, int dtype, int bins, bo
     }
   }
   const int64_t hist_len = s.batch * bins;
-  int prep_blocks = (int)((hist_len + kBlock - 1) / kBlock);
-  prep_blocks = prep_blocks > 1024 ? 1024 : prep_blocks;
 
   if (device_range && (fast2d || fast3d) && (!two_pass || dir)) {
     // Single pass over the grid: the sweep finds the critical vertices and the
@@ -545,8 +638,9 @@ hipError_t launch_hard(const void* grid, const Shape& s, int dtype, int bins, bo
     nblk = nblk > most ? most : (nblk < 1 ? 1 : nblk);
     hipLaunchKernelGGL(binlist_kernel, dim3((unsigned)nblk, (unsigned)s.batch), dim3(kBinBlock),
                        (size_t)bins * 2 * sizeof(int), st, la, table, bins, hist, super);
-    if (fast2d) launch_sweep2d(grid, s, dtype, false, bins, hdr, table, hist, st, &hdr->overflow, dir, conv);
-    else launch_sweep3d(grid, s, dtype, false, bins, hdr, table, hist, st, &hdr->overflow, dir, conv);
+    const HistOut out = {hist, nullptr, 0u, 0};
+    if (fast2d) launch_sweep2d(grid, s, dtype, false, bins, hdr, table, out, st, &hdr->overflow, dir, conv);
+    else launch_sweep3d(grid, s, dtype, false, bins, hdr, table, out, st, &hdr->overflow, dir, conv);
     launch_scan(curve, s, bins, super, st);
     return hipGetLastError();
   }
@@ -559,21 +653,42 @@ hipError_t launch_hard(const void* grid, const Shape& s, int dtype, int bins, bo
     hipLaunchKernelGGL(minmax_f32_kernel, dim3(nb), dim3(kBlock), 0, st,
                        static_cast<const float*>(grid), total, hdr);
   }
-  hipLaunchKernelGGL(prepare_kernel, dim3(prep_blocks), dim3(kBlock), 0, st, hdr, table, bins,
-                     device_range ? 1 : 0, lo, hi, hist, hist_len, super);
+  const unsigned blocks = fast2d ? sweep2d_hist_blocks(s, dtype, bins)
+                        : fast3d ? sweep3d_hist_blocks(s, dtype, bins) : generic_blocks(s);
+  const size_t before_rows = kTableOffset + table_bytes(bins);
+  const HistOut out = hist_out(s, bins, levels, blocks, hist, wsb + before_rows, hard_workspace_min_bytes(s, bins) - before_rows);
+  // (nothing to do for one bin per level with a row for each block)
+  const int64_t clear_words = out.n == 0u ? 2 * hist_len : out.shared ? hist_len * out.n : 0;
+  if (!levels || clear_words) {
+    const int64_t work = std::max<int64_t>(clear_words, bins);
+    hipLaunchKernelGGL(prepare_kernel, dim3((unsigned)std::min<int64_t>((work + kBlock - 1) / kBlock, 1024)), dim3(kBlock), 0,
+                       st, hdr, table, bins, device_range ? 1 : 0, lo, hi,
+                       out.n == 0u ? reinterpret_cast<unsigned*>(hist) : reinterpret_cast<unsigned*>(out.rows), clear_words,
+                       super);
+  }
   profile_mark(st, false);
   if (fast2d) {
-    launch_sweep2d(grid, s, dtype, levels, bins, hdr, table, hist, st, nullptr, dir, conv);
+    launch_sweep2d(grid, s, dtype, levels, bins, hdr, table, out, st, nullptr, dir, conv);
   } else if (fast3d) {
-    launch_sweep3d(grid, s, dtype, levels, bins, hdr, table, hist, st, nullptr, dir, conv);
+    launch_sweep3d(grid, s, dtype, levels, bins, hdr, table, out, st, nullptr, dir, conv);
   } else
   switch (dtype) {
-    case 0: launch_sweep_generic<uint8_t>(grid, s, levels, bins, hdr, table, hist, st, conv); break;
-    case 1: launch_sweep_generic<uint16_t>(grid, s, levels, bins, hdr, table, hist, st, conv); break;
-    default: launch_sweep_generic<float>(grid, s, levels, bins, hdr, table, hist, st, conv); break;
+    case 0: launch_sweep_generic<uint8_t>(grid, s, levels, bins, hdr, table, out, st, conv); break;
+    case 1: launch_sweep_generic<uint16_t>(grid, s, levels, bins, hdr, table, out, st, conv); break;
+    default: launch_sweep_generic<float>(grid, s, levels, bins, hdr, table, out, st, conv); break;
   }
   profile_mark(st, true);
-  launch_scan(curve, s, bins, super, st);
+  if (out.n) {
+    long long* const c = reinterpret_cast<long long*>(curve);
+    if (bins <= 256 && (int64_t)out.n * bins <= 4096)
+      hipLaunchKernelGGL(scan_rows_kernel<256>, dim3((unsigned)s.batch), dim3(256), 256 * sizeof(int), st, out.rows, out.n,
+                         bins, super, c);
+    else
+      hipLaunchKernelGGL(scan_rows_kernel<1024>, dim3((unsigned)s.batch), dim3(1024),
+                         (size_t)std::max(bins, 1024) * sizeof(int), st, out.rows, out.n, bins, super, c);
+  } else {
+    launch_scan(curve, s, bins, super, st);
+  }
   return hipGetLastError();
 }
 

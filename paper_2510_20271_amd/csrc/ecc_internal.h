@@ -45,6 +45,16 @@ void launch_coeff3d(const void* grid, const Shape& s, int dtype, int8_t* c_out, 
 constexpr unsigned kForceGeneric = 1u, kForceTwoPass = 2u, kForceSoftTiles = 4u, kForceNoSmall = 8u;
 unsigned forced_paths();
 
+// Where the blocks of a histogram sweep leave their counters.  `curve` (when n = 0): added to the item's 64-bit histogram,
+// cleared beforehand.  Otherwise n rows of int32 per item, [batch][n][bins]: a row for each block, written whole and not
+// cleared (n = blocks), or rows that blocks share, cleared beforehand; the scan adds them up.
+struct HistOut {
+  unsigned long long* curve;
+  int* rows;
+  unsigned n;
+  int shared;
+};
+
 // fast sweeps (one wave per column strip / tube, bit-sliced stencil)
 struct HardHeader;
 // small float32 inputs without a range: the whole call in two launches (ecc_small.hip);
@@ -86,8 +96,9 @@ struct ListArgs {
 };
 bool sweep2d_supported(const Shape& s, int bins);
 void launch_sweep2d(const void* grid, const Shape& s, int dtype, bool levels, int bins,
-                    const HardHeader* hdr, const float* table, unsigned long long* hist,
+                    const HardHeader* hdr, const float* table, const HistOut& hist,
                     hipStream_t st, const unsigned* run_if, const DirArgs* dir = nullptr, int conv = 0);
+unsigned sweep2d_hist_blocks(const Shape& s, int dtype, int bins);  // blocks per item of that launch
 void launch_sweep2d_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st,
                          const DirArgs* dir = nullptr, int conv = 0);
 unsigned sweep2d_list_blocks(const Shape& s, int dtype, bool shared);  // blocks per item of that launch
@@ -95,15 +106,17 @@ unsigned sweep2d_block_vertices(const Shape& s, int dtype);  // most vertices a 
 
 bool sweep3d_supported(const Shape& s, int bins);
 void launch_sweep3d(const void* grid, const Shape& s, int dtype, bool levels, int bins,
-                    const HardHeader* hdr, const float* table, unsigned long long* hist,
+                    const HardHeader* hdr, const float* table, const HistOut& hist,
                     hipStream_t st, const unsigned* run_if, const DirArgs* dir = nullptr, int conv = 0);
+unsigned sweep3d_hist_blocks(const Shape& s, int dtype, int bins);
 void launch_sweep3d_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st,
                          const DirArgs* dir = nullptr, int conv = 0);
 unsigned sweep3d_list_blocks(const Shape& s, int dtype, bool shared);
 unsigned sweep3d_block_vertices(const Shape& s, int dtype);
 // the same for one- and two-byte element types, two vertices to a register (ecc_sweep3d_packed.h)
 void launch_sweep3dp(const void* grid, const Shape& s, int dtype, bool levels, int bins, const HardHeader* hdr,
-                     const float* table, unsigned long long* hist, hipStream_t st, const unsigned* run_if, int conv);
+                     const float* table, const HistOut& hist, hipStream_t st, const unsigned* run_if, int conv);
+unsigned sweep3dp_hist_blocks(const Shape& s, int bins);
 void launch_sweep3dp_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st, int conv);
 void launch_coeff3dp(const void* grid, const Shape& s, int dtype, int8_t* c_out, hipStream_t st);
 unsigned sweep3dp_blocks(const Shape& s, bool shared);

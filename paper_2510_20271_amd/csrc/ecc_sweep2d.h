@@ -509,21 +509,25 @@ static inline int64_t rows2d(const Shape& s, int64_t nstrip, int64_t tubes, Feed
   // rows with which an image (of at most four strips) is four units, a whole block
   const int64_t segs = (4 + nstrip - 1) / nstrip;
   const int64_t four_units = ((H + segs - 1) / segs + kChunkRows - 1) / kChunkRows * kChunkRows;
-  // A histogram per block, cleared first and merged into the item's with one atomic per bin at the end: few bins and
-  // not too many blocks that meet in one item's histogram want short segments (us a call with 8 / 16 / 24 / 32 / 64 rows:
-  // 64 x 256^2 uint8 noise 19.6 / 22.5 / 29.9 / 34.0 / 61, 16 x 512^2 smooth float32 13.1 / 14.2 / 16.0 / 17.0 / 24.8, 2048^2
-  // uint8 noise 25.6 / 26.0 / 30.7 / 36.8 / 64 and smooth 21.4 / 17.0 / 15.6 / 17.0 / 22.9; but a 4677 x 3307 page 52.9 / 32.1 /
-  // 27.3 / 24.8 / 26.6, 16 x 1024^2 with 4096 bins 54 / 40.9 / - / 34.2 / 39.5).  24 rows from 1024 units on: 2048^2.
-  if (feed == Feed2d::kHist && nstrip * ((H + 15) / 16) <= 1280 && bins <= 1024) {
-    if (total <= ((int64_t)1 << 25) && total * bytes <= ((int64_t)1 << 26))
-      return nstrip * ((H + 15) / 16) <= 1024 ? 16 : 24;
-    // Rounds of waves enough at any length: one byte a vertex is bound by the march (16 x 2048^2 noise 109 / 133 with 32 / 64
-    // rows), wider ones by the rows read twice (64 x 1024^2 float32 61.6 / 58.0, 512 x 512^2 144 / 131, 125 with 128; 16 rows
-    // lose beyond 2^26 bytes, 32 x 1024^2 float32 42 / 37).  Many small images take four units, a whole block (16384 x 64^2
-    // uint8 noise 416 us with the two units of 32 rows, 280 with four; 2000 x 100 x 300 161 with the eight of 32 rows, 147 with
-    // four).
-    const int64_t aim = bytes == 1 ? 32 : (tubes >= 1024 ? 128 : 64);
-    return s.batch >= 1024 && nstrip <= 4 && nstrip * ((H + aim - 1) / aim) <= 8 ? four_units : aim;
+  if (feed == Feed2d::kHist) {
+    // A histogram per block, merged at its end, through rows of their own where many blocks would meet in one item's
+    // (hist_out): short segments, as a wave's march is what lasts, until there are waves enough for every SIMD three times
+    // over.  us a call with 8 / 16 / 24 / 32 rows: 512^2 uint8 noise 13.3 / 19.9 / 26.7 / 32.8, 2048^2 smooth float32 13.7 / 15.2 /
+    // 16.1 / 18.5, 16 x 512^2 float16 12.2 / 13.6 / 15.7 / 16.3.
+    // (many items and bins: the histograms weigh more; 200 x 100 x 140 float32, 1000 bins 15.9 with 8 rows, 14.7 with 16)
+    if (waves(8) <= 3072) return s.batch >= 64 && bins > 512 ? 16 : 8;
+    // Small images: a block (four units) each.  2000 x 28^2 uint8 24.1 / 33.5 / 33.4 / 43.7, 1000 x 100^2 42.7 / 42.5 / 58.4 / 38.6.
+    if (nstrip <= 2 && four_units <= 32) return four_units;
+    // One byte a vertex is bound by the march at any size (a 4677 x 3307 page 18.2 / 17.6 / 19.0 / 18.9, of noise 31.2 / 31.0 / 36.0 /
+    // 39.2; 8192^2 noise 98.8 / 95.8 / 101.5 / 105.1); wider elements by the rows read twice, sooner (64 x 256^2 float32 17.0 / 15.5 /
+    // 17.1 / 18.2, 8 x 2048^2 float32 44.4 / 38.6 / 38.0 / 37.3, float16 33.2 / 29.9 / 31.3 / 32.9, 16 x 2048^2 float16 56 / 50 / 50 / 47),
+    // and with many bins by the blocks' histograms (8192^2 uint16, 4096 bins 82 / 66 / 62 / 61; 48 rows 59, 64 63).
+    if (bytes == 1 || waves(16) <= 3072) return 16;
+    if (bins <= 1024 && waves(16) <= (bytes == 2 ? 20480 : 4608)) return 16;
+    // Rounds of waves enough at any length (512 x 512^2 float32 146 with 32 rows, 128 with 64, 125 with 128; float16 105 / 103 / 109)
+    if (tubes >= 1024) return bytes == 2 && bins <= 1024 ? 64 : 128;
+    if (bins > 1024) return total > ((int64_t)1 << 26) ? 48 : 32;
+    return bytes == 2 ? 32 : 64;
   }
   if (waves(16) <= 1024) return 16;  // at most one wave per SIMD even with short segments
   // Many small images with lists that blocks share (batches beyond the lists per block): four units each as well, rather

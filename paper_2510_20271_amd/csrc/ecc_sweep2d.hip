@@ -15,7 +15,7 @@ template <typename T, bool LEVELS, bool TLDS, int MODE>
 __global__ __launch_bounds__(256) void sweep2d_kernel(
     const T* __restrict__ grid, int H, int W, int64_t N, int bins, int nstrip, int nseg, int rows_per_seg,
     const HardHeader* __restrict__ hdr, const float* __restrict__ table,
-    unsigned long long* __restrict__ hist, const unsigned* __restrict__ run_if, DirArgs dir) {
+    HistOut hist, const unsigned* __restrict__ run_if, DirArgs dir) {
   if (run_if && *run_if == 0) return;
   extern __shared__ int smem[];
   // [4 waves][kChunkRows][64][kNC] floats of value ring, [4 waves] queues, histogram, table
@@ -47,11 +47,7 @@ __global__ __launch_bounds__(256) void sweep2d_kernel(
                     typename ModeTransform<MODE>::type());
   }
   __syncthreads();
-  unsigned long long* out = hist + (int64_t)blockIdx.y * bins;
-  for (int b = threadIdx.x; b < bins; b += 256) {
-    const int v = lhist[b];
-    if (v != 0) atomicAdd(&out[b], (unsigned long long)(long long)v);
-  }
+  leave_histogram<256>(lhist, bins, hist);
 }
 
 // Single-pass mode: critical vertices (value, c) go to the item's list in the
@@ -96,7 +92,7 @@ constexpr size_t kRingBytes2d = ring_bytes2d<float2>();
 // LV: the type also comes with one bin per level (uint8 / uint16 grids without a range)
 template <typename T, bool LV = false>
 static void launch2d_t(const void* grid, const Shape& s, bool levels, int bins, const HardHeader* hdr,
-                       const float* table, unsigned long long* hist, hipStream_t st,
+                       const float* table, const HistOut& hist, hipStream_t st,
                        const unsigned* run_if, const DirArgs* dir, int conv) {
   const Plan2d pl = plan2d<T>(s, Feed2d::kHist, bins);
   const bool tlds = !levels && (size_t)bins * 8 + kRingBytes2d <= 64 * 1024;
@@ -166,6 +162,12 @@ void launch_sweep2d_list(const void* grid, int dtype, const Shape& s, const List
   }
 }
 
+unsigned sweep2d_hist_blocks(const Shape& s, int dtype, int bins) {
+  const size_t size = dtype == 0 ? 1 : dtype == 2 ? 4 : 2;
+  return size == 1 ? plan2d<uint8_t>(s, Feed2d::kHist, bins).grid.x
+       : size == 2 ? plan2d<uint16_t>(s, Feed2d::kHist, bins).grid.x : plan2d<float>(s, Feed2d::kHist, bins).grid.x;
+}
+
 unsigned sweep2d_block_vertices(const Shape& s, int dtype) {
   const Plan2d pl = dtype == 2 ? plan2d<float>(s, Feed2d::kBlockLists) : plan2d<F16>(s, Feed2d::kBlockLists);
   // four wave units of 248 columns x the segment's rows
@@ -183,7 +185,7 @@ bool sweep2d_supported(const Shape& s, int bins) {
 }
 
 void launch_sweep2d(const void* grid, const Shape& s, int dtype, bool levels, int bins,
-                    const HardHeader* hdr, const float* table, unsigned long long* hist,
+                    const HardHeader* hdr, const float* table, const HistOut& hist,
                     hipStream_t st, const unsigned* run_if, const DirArgs* dir, int conv) {
   switch (dtype) {
     case 0: launch2d_t<uint8_t, true>(grid, s, levels, bins, hdr, table, hist, st, run_if, nullptr, conv); break;

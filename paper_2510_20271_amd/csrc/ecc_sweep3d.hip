@@ -8,7 +8,7 @@ template <int R, bool TLDS, int MODE>
 __global__ __launch_bounds__(256) void sweep3d_kernel(
     const float* __restrict__ grid, int D, int H, int W, int64_t N, int bins, int nstrip, int ngroup,
     int nseg, int planes_per_seg, const HardHeader* __restrict__ hdr,
-    const float* __restrict__ table, unsigned long long* __restrict__ hist,
+    const float* __restrict__ table, HistOut hist,
     const unsigned* __restrict__ run_if, DirArgs dir) {
   if (run_if && *run_if == 0) return;
   extern __shared__ int smem[];
@@ -42,11 +42,7 @@ __global__ __launch_bounds__(256) void sweep3d_kernel(
                        queue, xch, range, typename ModeTransform<MODE>::type());
   }
   __syncthreads();
-  unsigned long long* out = hist + (int64_t)blockIdx.y * bins;
-  for (int b = threadIdx.x; b < bins; b += 256) {
-    const int v = lhist[b];
-    if (v != 0) atomicAdd(&out[b], (unsigned long long)(long long)v);
-  }
+  leave_histogram<256>(lhist, bins, hist);
 }
 
 // Single-pass mode: critical vertices to the item's list, min / max to the header.
@@ -85,7 +81,7 @@ __global__ __launch_bounds__(256) void sweep3d_list_kernel(const float* __restri
 }
 
 static void launch3d(const float* p, const Shape& s, int bins, const HardHeader* hdr, const float* table,
-                     unsigned long long* hist, hipStream_t st, const unsigned* run_if, const DirArgs* dir, int conv) {
+                     const HistOut& hist, hipStream_t st, const unsigned* run_if, const DirArgs* dir, int conv) {
   constexpr int R = kRows3d;
   const Plan3d pl = plan3d<float>(s);
   const bool tlds = (size_t)bins * 8 + kFixedLds3d <= 60 * 1024;
@@ -145,6 +141,9 @@ void launch_sweep3d_list(const void* grid, int dtype, const Shape& s, const List
 unsigned sweep3d_list_blocks(const Shape& s, int dtype, bool shared) {
   return dtype == 2 ? plan3d<float>(s).grid.x : sweep3dp_blocks(s, shared);
 }
+unsigned sweep3d_hist_blocks(const Shape& s, int dtype, int bins) {
+  return dtype == 2 ? plan3d<float>(s).grid.x : sweep3dp_hist_blocks(s, bins);
+}
 unsigned sweep3d_block_vertices(const Shape& s, int dtype) {
   if (dtype != 2) return sweep3dp_block_vertices(s);
   // four wave units of at most 62 columns x 4 rows (a folded unit: several row groups of fewer columns) x the segment's planes
@@ -160,7 +159,7 @@ bool sweep3d_supported(const Shape& s, int bins) {
 }
 
 void launch_sweep3d(const void* grid, const Shape& s, int dtype, bool levels, int bins,
-                    const HardHeader* hdr, const float* table, unsigned long long* hist,
+                    const HardHeader* hdr, const float* table, const HistOut& hist,
                     hipStream_t st, const unsigned* run_if, const DirArgs* dir, int conv) {
   if (dtype != 2) launch_sweep3dp(grid, s, dtype, levels, bins, hdr, table, hist, st, run_if, conv);
   else launch3d(static_cast<const float*>(grid), s, bins, hdr, table, hist, st, run_if, dir, conv);

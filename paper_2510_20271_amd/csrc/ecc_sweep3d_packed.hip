@@ -13,7 +13,7 @@ __global__ __launch_bounds__(256, 4) void sweep3dp_kernel(const T* __restrict__ 
                                                        int bins, int nseg, int planes_per_seg,
                                                        const HardHeader* __restrict__ hdr,
                                                        const float* __restrict__ table,
-                                                       unsigned long long* __restrict__ hist,
+                                                       HistOut hist,
                                                        const unsigned* __restrict__ run_if) {
   if (run_if && *run_if == 0) return;
   extern __shared__ int smem[];
@@ -38,11 +38,7 @@ __global__ __launch_bounds__(256, 4) void sweep3dp_kernel(const T* __restrict__ 
   sweep3dp_wave<T, HistSink<LEVELS, mode_is_super(MODE)>, typename ModeTransform<MODE>::type>(
       grid + (int64_t)blockIdx.y * N, D, H, W, nseg, planes_per_seg, queue, range);
   __syncthreads();
-  unsigned long long* out = hist + (int64_t)blockIdx.y * bins;
-  for (int b = threadIdx.x; b < bins; b += 256) {
-    const int v = lhist[b];
-    if (v != 0) atomicAdd(&out[b], (unsigned long long)(long long)v);
-  }
+  leave_histogram<256>(lhist, bins, hist);
 }
 
 // Single-pass mode: critical vertices to the item's list, min / max to the header.
@@ -132,6 +128,7 @@ static Plan3dp plan3dp(const Shape& s, Feed3dp feed, int bins = 0) {
 unsigned sweep3dp_blocks(const Shape& s, bool shared) {
   return plan3dp(s, shared ? Feed3dp::kSharedLists : Feed3dp::kAlone).grid.x;
 }
+unsigned sweep3dp_hist_blocks(const Shape& s, int bins) { return plan3dp(s, Feed3dp::kHist, bins).grid.x; }
 unsigned sweep3dp_block_vertices(const Shape& s) {  // of a launch with a list per block
   const int64_t planes = std::min<int64_t>(s.D, plan3dp(s, Feed3dp::kAlone).planes_per_seg);
   return 4u * (unsigned)s3::kOut * (unsigned)s3p::kR * (unsigned)planes;
@@ -140,7 +137,7 @@ unsigned sweep3dp_block_vertices(const Shape& s) {  // of a launch with a list p
 // LV: the type also comes with one bin per level (uint8 / uint16 grids without a range)
 template <typename T, bool LV = false>
 static void launch3dp_t(const void* grid, const Shape& s, bool levels, int bins, const HardHeader* hdr,
-                        const float* table, unsigned long long* hist, hipStream_t st, const unsigned* run_if, int conv) {
+                        const float* table, const HistOut& hist, hipStream_t st, const unsigned* run_if, int conv) {
   const Plan3dp pl = plan3dp(s, Feed3dp::kHist, bins);
   const bool tlds = !levels && (size_t)bins * 8 + kQueueBytes3dp <= 60 * 1024;
   const size_t lds = kQueueBytes3dp + (size_t)bins * (tlds ? 8 : 4);
@@ -166,7 +163,7 @@ static void launch3dp_t(const void* grid, const Shape& s, bool levels, int bins,
 }
 
 void launch_sweep3dp(const void* grid, const Shape& s, int dtype, bool levels, int bins, const HardHeader* hdr,
-                     const float* table, unsigned long long* hist, hipStream_t st, const unsigned* run_if, int conv) {
+                     const float* table, const HistOut& hist, hipStream_t st, const unsigned* run_if, int conv) {
   switch (dtype) {
     case 0: launch3dp_t<uint8_t, true>(grid, s, levels, bins, hdr, table, hist, st, run_if, conv); break;
     case 1: launch3dp_t<uint16_t, true>(grid, s, levels, bins, hdr, table, hist, st, run_if, conv); break;
