@@ -112,7 +112,7 @@ constexpr size_t kSoft3Lds = kFixedLds3d + (size_t)4 * kWave * sizeof(Soft3Stage
 // field's coefficient.
 template <bool TILTC, int STRIDE, typename Sink>
 __device__ __forceinline__ void soft3d_sweep(s3::TubeQueue<Sink>& queue, const float* __restrict__ grid, int D, int H,
-                                             int W, int64_t N, int nstrip, int ngroup, int nseg, int planes_per_seg,
+                                             int W, int64_t N, const Tiling3& tl, int nseg, int planes_per_seg,
                                              const float* u, float alpha, const float* tau, int T, float kneg,
                                              const float* gup, float* partial) {
   extern __shared__ int smem[];
@@ -133,7 +133,7 @@ __device__ __forceinline__ void soft3d_sweep(s3::TubeQueue<Sink>& queue, const f
   s.W = W;
   s.plane = (int64_t)H * W;
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(wv), units = gridDim.x * 4;
-  unit_origin3(unit, D, H, W, gridDim.y, planes_per_seg, kRows3d, s.ox, s.oy, s.oz);
+  unit_origin3(unit, tl, planes_per_seg, kRows3d, s.ox, s.oy, s.oz);
   int j0, nj;
   soft_layer(T, j0, nj);
   s.eval.init(tau + j0, nj, kneg, gup ? gup + (int64_t)blockIdx.y * T + j0 : nullptr,
@@ -145,9 +145,9 @@ __device__ __forceinline__ void soft3d_sweep(s3::TubeQueue<Sink>& queue, const f
     const Tilt t = load_tilt(da, 0);
     TiltRaw tr;
     tr.ax = t.ax, tr.ay = t.ay, tr.az = t.az;
-    sweep3d_wave<float, kRows3d>(g, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, queue, xch, range, tr);
+    sweep3d_wave<float, kRows3d>(g, D, H, W, N, tl, nseg, planes_per_seg, queue, xch, range, tr);
   } else {
-    sweep3d_wave<float, kRows3d>(g, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, queue, xch, range, NoTilt());
+    sweep3d_wave<float, kRows3d>(g, D, H, W, N, tl, nseg, planes_per_seg, queue, xch, range, NoTilt());
   }
   s.eval.finish();
 }
@@ -155,19 +155,19 @@ __device__ __forceinline__ void soft3d_sweep(s3::TubeQueue<Sink>& queue, const f
 // partial[(item * units + unit) * T + j]
 template <bool TILTC, bool MANY>
 __global__ __launch_bounds__(256, soft3_waves(MANY || TILTC)) void soft3d_fwd_kernel(const float* __restrict__ grid, int D, int H, int W,
-                                                            int64_t N, int nstrip, int ngroup, int nseg,
+                                                            int64_t N, Tiling3 tl, int nseg,
                                                             int planes_per_seg, const float* __restrict__ u,
                                                             float alpha, const float* __restrict__ tau, int T,
                                                             float kneg, float* __restrict__ partial) {
   s3::TubeQueue<Soft3Sink<true, false, false, false, 1, MANY>> queue;
-  soft3d_sweep<TILTC, 1>(queue, grid, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, u, alpha, tau, T, kneg, nullptr,
+  soft3d_sweep<TILTC, 1>(queue, grid, D, H, W, N, tl, nseg, planes_per_seg, u, alpha, tau, T, kneg, nullptr,
                          partial);
 }
 
 // partial[((item * units + unit) * T + j) * 4 + {0: A0, 1: Ax, 2: Ay, 3: Az}]
 template <bool TILTC, bool MANY>
 __global__ __launch_bounds__(256, soft3_waves(MANY)) void soft3d_bwd_kernel(const float* __restrict__ grid, int D, int H, int W,
-                                                            int64_t N, int nstrip, int ngroup, int nseg,
+                                                            int64_t N, Tiling3 tl, int nseg,
                                                             int planes_per_seg, const float* __restrict__ u,
                                                             float alpha, const float* __restrict__ tau, int T,
                                                             float kneg, float lambda, const float* __restrict__ gup,
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256, soft3_waves(MANY)) void soft3d_bwd_kernel(cons
   s3::TubeQueue<Soft3Sink<false, true, true, false, 4, MANY>> queue;
   queue.sink.gx = grad_X ? grad_X + (int64_t)blockIdx.y * N : nullptr;
   queue.sink.lambda = lambda;
-  soft3d_sweep<TILTC, 4>(queue, grid, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, u, alpha, tau, T, kneg, gup,
+  soft3d_sweep<TILTC, 4>(queue, grid, D, H, W, N, tl, nseg, planes_per_seg, u, alpha, tau, T, kneg, gup,
                          partial);
 }
 
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(256, soft3_waves(MANY)) void soft3d_bwd_kernel(cons
 // partial[((item * units + unit) * T + j) * 5 + {0: chi, 1: A0, 2: Ax, 3: Ay, 4: Az}]
 template <bool TILTC, bool DERIV, bool MANY>
 __global__ __launch_bounds__(256, soft3_waves(MANY)) void soft3d_fwd_save_kernel(
-    const float* __restrict__ grid, int D, int H, int W, int64_t N, int nstrip, int ngroup, int nseg, int planes_per_seg,
+    const float* __restrict__ grid, int D, int H, int W, int64_t N, Tiling3 tl, int nseg, int planes_per_seg,
     const float* __restrict__ u, float alpha, const float* __restrict__ tau, int T, float kneg,
     float* __restrict__ partial, StateView sv, unsigned cap) {
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), units = gridDim.x * 4;
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256, soft3_waves(MANY)) void soft3d_fwd_save_kernel
   queue.sink.saved = 0u;
   queue.sink.list = sv.lists + ((size_t)blockIdx.y * units + unit) * cap;
   const unsigned next_gen = *sv.gen + 1u;  // (the reduction kernel that follows stores it)
-  soft3d_sweep<TILTC, 5>(queue, grid, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, u, alpha, tau, T, kneg, nullptr,
+  soft3d_sweep<TILTC, 5>(queue, grid, D, H, W, N, tl, nseg, planes_per_seg, u, alpha, tau, T, kneg, nullptr,
                          partial);
   if (blockIdx.z == 0 && (threadIdx.x & (kWave - 1)) == 0) {
     sv.counts[(size_t)blockIdx.y * units + unit] = queue.sink.saved;
@@ -280,14 +280,12 @@ __global__ __launch_bounds__(256) void soft3d_bwd_saved_kernel(const float* __re
 
 // origin of a unit's coordinates, for the reduction of ecc_soft_reduce.h
 struct Origin3 {
-  int D, H, W, nitems, planes_per_seg;
+  Tiling3 tl;
+  int planes_per_seg;
   __device__ __forceinline__ void operator()(int unit, int (&o)[3]) const {
-    unit_origin3(unit, D, H, W, nitems, planes_per_seg, kRows3d, o[0], o[1], o[2]);
+    unit_origin3(unit, tl, planes_per_seg, kRows3d, o[0], o[1], o[2]);
   }
 };
-static Origin3 origin3(const Shape& s, const Plan3d& pl) {
-  return Origin3{(int)s.D, (int)s.H, (int)s.W, (int)s.batch, pl.planes_per_seg};
-}
 
 static float kneg3d(float lambda) { return (float)(-(double)lambda * 1.4426950408889634); }
 
@@ -323,13 +321,13 @@ void launch_soft3d_fwd(const float* grid, const Shape& s, const float* u, float 
   float* partial = static_cast<float*>(ws);
 #define ECC_GO(TC, MANY)                                                                                          \
   hipLaunchKernelGGL((soft3d_fwd_kernel<TC, MANY>), layered(pl, s, T), dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
-                     (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,       \
+                     (int)s.W, s.N, pl.tl, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,       \
                      kneg3d(lambda), partial)
   ECC_SOFT_VARIANT(tiltc, many_thresholds(T));
 #undef ECC_GO
   double* mid = reinterpret_cast<double*>(static_cast<char*>(ws) + soft3d_partial_bytes(s, pl, T));
   const RedOut out = {chi, nullptr, nullptr, nullptr, nullptr, {}};
-  launch_soft_reduce<1, true, -1>(partial, mid, (int)pl.grid.x * 4, s.batch, T, alpha, lambda, origin3(s, pl), out, st);
+  launch_soft_reduce<1, true, -1>(partial, mid, (int)pl.grid.x * 4, s.batch, T, alpha, lambda, Origin3{pl.tl, pl.planes_per_seg}, out, st);
 }
 
 void launch_soft3d_bwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
@@ -339,14 +337,14 @@ void launch_soft3d_bwd(const float* grid, const Shape& s, const float* u, float 
   float* partial = (dtau || du) ? static_cast<float*>(ws) : nullptr;
 #define ECC_GO(TC, MANY)                                                                                          \
   hipLaunchKernelGGL((soft3d_bwd_kernel<TC, MANY>), pl.grid, dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
-                     (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,       \
+                     (int)s.W, s.N, pl.tl, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,       \
                      kneg3d(lambda), lambda, gup, grad_X, partial)
   ECC_SOFT_VARIANT(tiltc, many_thresholds(T));
 #undef ECC_GO
   if (partial) {
     double* mid = reinterpret_cast<double*>(static_cast<char*>(ws) + soft3d_partial_bytes(s, pl, T));
     const RedOut out = {nullptr, dtau, du, nullptr, nullptr, {}};
-    launch_soft_reduce<4, false, 3>(partial, mid, (int)pl.grid.x * 4, s.batch, T, alpha, lambda, origin3(s, pl), out, st);
+    launch_soft_reduce<4, false, 3>(partial, mid, (int)pl.grid.x * 4, s.batch, T, alpha, lambda, Origin3{pl.tl, pl.planes_per_seg}, out, st);
   }
 }
 
@@ -370,7 +368,7 @@ static SoftStateHeader state_header3(const Shape& s, const Plan3d& pl, bool tilt
   h.H = (int)s.H;
   h.W = (int)s.W;
   h.batch = (int)s.batch;
-  h.nstrip = pl.nstrip;
+  h.nstrip = pl.tl.nstrip;
   h.nseg = pl.nseg;
   h.rows_per_seg = pl.planes_per_seg;
   h.units = (int)pl.grid.x * 4;
@@ -390,14 +388,14 @@ void launch_soft3d_fwd_save(const float* grid, const Shape& s, const float* u, f
   const bool deriv = dtau || du;
 #define ECC_GO3(TC, DV, MANY)                                                                                       \
   hipLaunchKernelGGL((soft3d_fwd_save_kernel<TC, DV, MANY>), layered(pl, s, T), dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H, \
-                     (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,         \
+                     (int)s.W, s.N, pl.tl, pl.nseg, pl.planes_per_seg, u, alpha, tau, T,         \
                      kneg3d(lambda), partial, sv, hdr.cap)
 #define ECC_GO(TC, MANY) do { if (deriv) ECC_GO3(TC, true, MANY); else ECC_GO3(TC, false, MANY); } while (0)
   ECC_SOFT_VARIANT(tiltc, many_thresholds(T));
 #undef ECC_GO3
 #undef ECC_GO
   const RedOut out = {chi, dtau, du, sv.hdr, sv.gen, hdr};
-  launch_soft_reduce<5, true, 3>(partial, mid, (int)pl.grid.x * 4, s.batch, T, alpha, lambda, origin3(s, pl), out, st);
+  launch_soft_reduce<5, true, 3>(partial, mid, (int)pl.grid.x * 4, s.batch, T, alpha, lambda, Origin3{pl.tl, pl.planes_per_seg}, out, st);
 }
 
 void launch_soft3d_bwd_saved(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,

@@ -39,6 +39,7 @@
 #include "ecc_device.h"
 #include "ecc_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace ecc {
@@ -551,8 +552,8 @@ struct Tiling3 {
   int S, F;                     // lanes per fold and folds of a last-strip unit
   int ngroupT, full, units_seg; // units of the last strip, units of the full strips, units per segment
 };
-__host__ __device__ __forceinline__ Tiling3 make_tiling3(int D, int H, int W, long long batch, int R,
-                                                         bool always_fold = false) {
+// (on the host; kernels are handed the result)
+static inline Tiling3 make_tiling3(int D, int H, int W, long long batch, int R, bool always_fold = false) {
   Tiling3 t;
   t.nstrip = (W + s3::kOut - 1) / s3::kOut;
   t.ngroup = (H + R - 1) / R;
@@ -560,17 +561,22 @@ __host__ __device__ __forceinline__ Tiling3 make_tiling3(int D, int H, int W, lo
   const int wt = W - s3::kOut * (t.nstrip - 1);  // outputs of the last strip, 1..62
   t.S = kWave;
   t.F = 1;
-  // Folding pays when the launch runs many rounds of waves over the chip (fewer waves, 6 % on
-  // 512^3); when every wave is resident at once it only makes the last strip's waves the
-  // slowest ones (7 % lost on a 256^3 volume of i.i.d. values), so small launches keep one
-  // row group per wave.
-  const bool many_rounds = always_fold || (long long)t.nstrip * t.ngroup * batch * D >= 160000;  // about 1.3 rounds of 30-plane units
-  if (many_rounds && wt + 2 <= kWave / 2) {
-    t.S = wt + 2;
-    t.F = kWave / t.S;
-    if (t.F > 8) t.F = 8;
-    if (t.F > t.ngroup) t.F = t.ngroup;
-    if (t.F == 1) t.S = kWave;
+  // Folding pays where it takes waves off SIMDs that have more than two (or two, and one is left): the sweep is bound by
+  // the instructions a SIMD issues.  512^3 6 %; 193 x 229 x 193 39.0 -> 34.6 us, 8 x 64^3 26.6 -> 22.9, 256 x 24^3 35.3 ->
+  // 25.2, 20 x 50 x 60 x 70 35.0 -> 25.8 (whole calls, smooth fields; noise 3 to 20 % as well, 8 x 64^3 3 % slower).  With
+  // one wave on a SIMD, or two that stay two, it only makes the folded waves the slowest: 128^3 with 300 thresholds 24.0 ->
+  // 27.3, noise of 160 x 190 x 130 39.4 -> 41.8.  Counted in 12-plane segments, 1024 SIMDs and a sixteenth.
+  if (wt + 2 <= kWave / 2) {
+    int F = kWave / (wt + 2);
+    if (F > 8) F = 8;
+    if (F > t.ngroup) F = t.ngroup;
+    const long long segs = batch * ((D + 11) / 12);
+    const long long whole = segs * t.nstrip * t.ngroup4;
+    const long long folded = segs * ((t.nstrip - 1) * t.ngroup4 + (((t.ngroup + F - 1) / F + 3) & ~3));
+    if (F > 1 && (always_fold || whole > 2112 || (whole > 1088 && folded <= 1088))) {
+      t.S = wt + 2;
+      t.F = F;
+    }
   }
   t.ngroupT = (t.ngroup + t.F - 1) / t.F;
   t.full = (t.nstrip - 1) * t.ngroup4;
@@ -578,7 +584,7 @@ __host__ __device__ __forceinline__ Tiling3 make_tiling3(int D, int H, int W, lo
   return t;
 }
 // unit -> (segment, strip, first row group, is it a last-strip unit, has it any row)
-__host__ __device__ __forceinline__ void decode_unit3(const Tiling3& t, int unit, int& seg, int& strip, int& group,
+__device__ __forceinline__ void decode_unit3(const Tiling3& t, int unit, int& seg, int& strip, int& group,
                                                       bool& tail, bool& active) {
   seg = unit / t.units_seg;
   const int r = unit - seg * t.units_seg;
@@ -596,9 +602,8 @@ __host__ __device__ __forceinline__ void decode_unit3(const Tiling3& t, int unit
 }
 
 // origin of a wave's unit: first column of the tube (its halo column), first output row, first plane
-__host__ __device__ __forceinline__ void unit_origin3(int unit, int D, int H, int W, long long batch,
-                                                      int planes_per_seg, int R, int& ox, int& oy, int& oz) {
-  const Tiling3 tl = make_tiling3(D, H, W, batch, R);
+__device__ __forceinline__ void unit_origin3(int unit, const Tiling3& tl, int planes_per_seg, int R, int& ox, int& oy,
+                                             int& oz) {
   int seg, strip, group;
   bool tail, active;
   decode_unit3(tl, unit, seg, strip, group, tail, active);
@@ -613,10 +618,9 @@ __host__ __device__ __forceinline__ void unit_origin3(int unit, int D, int H, in
 // words are swapped through LDS.
 template <typename T, int R, typename Sink, typename TiltT>
 __device__ __forceinline__ void sweep3d_wave(const T* __restrict__ g, int D, int H, int W, int64_t N,
-                                             int nstrip, int ngroup, int nseg, int planes_per_seg,
+                                             const Tiling3& tl, int nseg, int planes_per_seg,
                                              s3::TubeQueue<Sink>& queue, unsigned* xch, WaveRange& range,
                                              const TiltT& tilt) {
-  const Tiling3 tl = make_tiling3(D, H, W, gridDim.y, R);
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   int seg, strip, group;
   bool tail, active;
@@ -628,7 +632,7 @@ __device__ __forceinline__ void sweep3d_wave(const T* __restrict__ g, int D, int
     const int yb = group * R;
     // the four waves of a block are four consecutive row groups of one strip and segment
     const bool skip_top = (unit & 3) != 0;
-    const bool skip_bottom = (unit & 3) != 3 && group + 1 < ngroup;
+    const bool skip_bottom = (unit & 3) != 3 && group + 1 < tl.ngroup;
     const bool safe = tail || (xs < 0) || (xs + kWave > W) || (yb == 0) || (yb + R + 1 > H);
     // tubes touching the grid boundary compute their own halo words (one variant fewer)
     if (safe)
@@ -653,7 +657,8 @@ constexpr int kXchInts = 2 * 4 * s3::kXchWords * kWave;  // exchange words of a 
 constexpr int kRows3d = 4;
 
 struct Plan3d {
-  int nstrip, ngroup, nseg, planes_per_seg;
+  Tiling3 tl;
+  int nseg, planes_per_seg;
   dim3 grid;
 };
 template <typename T>
@@ -662,8 +667,7 @@ static Plan3d plan3d(const Shape& s) {
   Plan3d p;
   const int D = (int)s.D, H = (int)s.H, W = (int)s.W;
   const Tiling3 tl = make_tiling3(D, H, W, s.batch, R);
-  p.nstrip = tl.nstrip;
-  p.ngroup = tl.ngroup;
+  p.tl = tl;
   const int64_t per_seg = (int64_t)tl.units_seg * s.batch;
   // about 2.5 rounds of waves over the chip on 512^3 (60-plane segments); measured best
   // between the ragged last round of fewer, longer segments and the three extra planes
@@ -675,23 +679,25 @@ static Plan3d plan3d(const Shape& s) {
   // whole chunks per segment; a segment's element offsets stay below 2^32 and its plane
   // count below 2^24 (what the critical-vertex queue stores)
   int64_t planes = ((D + nseg - 1) / nseg + s3::kChunk - 1) / s3::kChunk * s3::kChunk;
-  // A small launch, whose one-chunk segments leave wave slots empty (256 CUs x 4 SIMDs x 4 waves),
-  // takes shorter segments, down to 12 planes, until the slots are filled: each wave's march is
-  // the critical path of the call (256^3 uint16: 73 -> 66 us with 20-plane segments).
+  // A small launch, whose one-chunk segments leave wave slots empty (256 CUs x 4 SIMDs x 4 waves), takes shorter segments of
+  // equal length, down to 12 planes.  The waves on a SIMD take turns (the oldest first) and together issue almost without a
+  // gap, so what counts is that none waits for a second round and that a segment's three extra planes stay few: as many
+  // segments as the slots hold.  (One more, as before, cost a second round of a few blocks: 256^3 float32, folded, list sweep
+  // with 16 / 18 / 20 / 22 / 24 planes 47.2 / 44.6 / 45.2 / 42.5 / 42.0 us a call, 16 being the second round; noise, whose vertices a
+  // wave drains as it goes, 123 / 113 / 121 / 123 / 131.)  Whole calls, before and now, with the folding above: 256^3 list 49.5 ->
+  // 44.7 us, soft forward 41.5 -> 36.6, backward 53.9 -> 50.5; 2 x 182 x 218 x 182 over a known range 39.8 -> 33.6.
   if (per_seg * max_seg < 4096) {
-    int64_t want = (4096 + per_seg - 1) / per_seg;
-    int64_t pl = (D + want - 1) / want;
-    pl = (pl + 1) & ~(int64_t)1;
-    if (pl < 12) pl = 12;
-    if (pl < planes) planes = pl;
+    int64_t n = std::max<int64_t>(max_seg, 4096 / per_seg);
+    n = (D + std::max<int64_t>(12, (D + n - 1) / n) - 1) / std::max<int64_t>(12, (D + n - 1) / n);
+    planes = std::min(planes, (D + n - 1) / n);
   }
   // One-chunk segments of equal length: the call lasts as long as its longest one (64 x 64^3 float32: 65.4 us with 30 + 30 +
   // 4 planes, 59.4 with 22 + 22 + 20; 16 x 128^3 68.4 -> 63.4).  Not where that takes less than an eighth off a chunk:
   // launches of many rounds of waves then lose more from the missing short last segments, which fill the gaps at the
   // end (8 directions of 193 x 229 x 193: 118.6 us with 30 planes, 128.0 with 28).  Longer segments for the small launches
   // above were measured and not taken: 24 planes instead of 12 make 193 x 229 x 193 faster on smooth fields (float32 39.2 -> 34.2
-  // us, int16 over a known window 35 -> 31) and slower on noise, where a wave's march is the draining of its vertices
-  // (float32 85 -> 121, uint8 47 -> 51).
+  // us) and slower on noise, where a wave's march is the draining of its vertices
+  // (85 -> 121).
   if (planes == s3::kChunk) {
     const int64_t n = (D + planes - 1) / planes;
     const int64_t equal = ((D + n - 1) / n + 1) & ~(int64_t)1;

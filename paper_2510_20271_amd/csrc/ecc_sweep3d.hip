@@ -6,7 +6,7 @@ namespace ecc {
 // Histogram mode; run_if (may be null): do nothing unless *run_if != 0.
 template <int R, bool TLDS, int MODE>
 __global__ __launch_bounds__(256) void sweep3d_kernel(
-    const float* __restrict__ grid, int D, int H, int W, int64_t N, int bins, int nstrip, int ngroup,
+    const float* __restrict__ grid, int D, int H, int W, int64_t N, int bins, Tiling3 tl,
     int nseg, int planes_per_seg, const HardHeader* __restrict__ hdr,
     const float* __restrict__ table, HistOut hist,
     const unsigned* __restrict__ run_if, DirArgs dir) {
@@ -35,10 +35,10 @@ __global__ __launch_bounds__(256) void sweep3d_kernel(
   WaveRange range;
   if constexpr (MODE == kTilted) {
     const int d = blockIdx.y / dir.batch, item = blockIdx.y - d * dir.batch;
-    sweep3d_wave<float, R>(grid + (int64_t)item * N, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, queue, xch,
+    sweep3d_wave<float, R>(grid + (int64_t)item * N, D, H, W, N, tl, nseg, planes_per_seg, queue, xch,
                        range, load_tilt(dir, d));
   } else {
-    sweep3d_wave<float, R>(grid + (int64_t)blockIdx.y * N, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg,
+    sweep3d_wave<float, R>(grid + (int64_t)blockIdx.y * N, D, H, W, N, tl, nseg, planes_per_seg,
                        queue, xch, range, typename ModeTransform<MODE>::type());
   }
   __syncthreads();
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(256) void sweep3d_kernel(
 // Single-pass mode: critical vertices to the item's list, min / max to the header.
 template <int R, int MODE>
 __global__ __launch_bounds__(256) void sweep3d_list_kernel(const float* __restrict__ grid, int D, int H, int W,
-                                                           int64_t N, int nstrip, int ngroup, int nseg,
+                                                           int64_t N, Tiling3 tl, int nseg,
                                                            int planes_per_seg, ListArgs la, DirArgs dir) {
   extern __shared__ int smem[];
   unsigned* xch = reinterpret_cast<unsigned*>(smem);
@@ -70,10 +70,10 @@ __global__ __launch_bounds__(256) void sweep3d_list_kernel(const float* __restri
   WaveRange range;
   if constexpr (MODE == kTilted) {
     const int d = blockIdx.y / dir.batch, item = blockIdx.y - d * dir.batch;
-    sweep3d_wave<float, R>(grid + (int64_t)item * N, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, queue, xch,
+    sweep3d_wave<float, R>(grid + (int64_t)item * N, D, H, W, N, tl, nseg, planes_per_seg, queue, xch,
                        range, load_tilt(dir, d));
   } else {
-    sweep3d_wave<float, R>(grid + (int64_t)blockIdx.y * N, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg,
+    sweep3d_wave<float, R>(grid + (int64_t)blockIdx.y * N, D, H, W, N, tl, nseg, planes_per_seg,
                        queue, xch, range, typename ModeTransform<MODE>::type());
   }
   if (la.heads) block_list_end(la, range, own);
@@ -89,7 +89,7 @@ static void launch3d(const float* p, const Shape& s, int bins, const HardHeader*
   const DirArgs none = {nullptr, 0.f, 1, 3};
 #define ECC_GO(TL, TI)                                                                                    \
   hipLaunchKernelGGL((sweep3d_kernel<R, TL, TI>), pl.grid, dim3(256), lds, st, p, (int)s.D, (int)s.H,     \
-                     (int)s.W, s.N, bins, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, hdr, table,   \
+                     (int)s.W, s.N, bins, pl.tl, pl.nseg, pl.planes_per_seg, hdr, table,   \
                      hist, run_if, dir ? *dir : none)
 #define ECC_MODE(M)          \
   do {                       \
@@ -116,7 +116,7 @@ static void launch3d_list(const float* p, const Shape& s, const ListArgs& la, hi
   const DirArgs none = {nullptr, 0.f, 1, 3};
 #define ECC_LIST(M, DIR)                                                                                  \
   hipLaunchKernelGGL((sweep3d_list_kernel<kRows3d, M>), pl.grid, dim3(256), kFixedLds3d, st, p,           \
-                     (int)s.D, (int)s.H, (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, la, \
+                     (int)s.D, (int)s.H, (int)s.W, s.N, pl.tl, pl.nseg, pl.planes_per_seg, la, \
                      DIR)
   if (dir) {
     ECC_LIST(kTilted, *dir);
@@ -170,7 +170,7 @@ void launch_sweep3d(const void* grid, const Shape& s, int dtype, bool levels, in
 // tube-sweep kernel, made visible vertex by vertex.
 template <int R>
 __global__ __launch_bounds__(256) void coeff3d_kernel(const float* __restrict__ grid, int D, int H, int W, int64_t N,
-                                                      int nstrip, int ngroup, int nseg, int planes_per_seg,
+                                                      Tiling3 tl, int nseg, int planes_per_seg,
                                                       int8_t* __restrict__ out) {
   extern __shared__ int smem[];
   unsigned* xch = reinterpret_cast<unsigned*>(smem);
@@ -182,9 +182,9 @@ __global__ __launch_bounds__(256) void coeff3d_kernel(const float* __restrict__ 
   queue.sink.plane = (int64_t)H * W;
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int ox, oy;
-  unit_origin3(unit, D, H, W, gridDim.y, planes_per_seg, R, ox, oy, queue.sink.oz);
+  unit_origin3(unit, tl, planes_per_seg, R, ox, oy, queue.sink.oz);
   WaveRange range;
-  sweep3d_wave<float, R>(grid + (int64_t)blockIdx.y * N, D, H, W, N, nstrip, ngroup, nseg, planes_per_seg, queue, xch,
+  sweep3d_wave<float, R>(grid + (int64_t)blockIdx.y * N, D, H, W, N, tl, nseg, planes_per_seg, queue, xch,
                          range, NoTilt());
 }
 
@@ -195,7 +195,7 @@ void launch_coeff3d(const void* grid, const Shape& s, int dtype, int8_t* out, hi
   }
   const Plan3d pl = plan3d<float>(s);
   hipLaunchKernelGGL((coeff3d_kernel<kRows3d>), pl.grid, dim3(256), kFixedLds3d, st, static_cast<const float*>(grid),
-                     (int)s.D, (int)s.H, (int)s.W, s.N, pl.nstrip, pl.ngroup, pl.nseg, pl.planes_per_seg, out);
+                     (int)s.D, (int)s.H, (int)s.W, s.N, pl.tl, pl.nseg, pl.planes_per_seg, out);
 }
 
 }  // namespace ecc

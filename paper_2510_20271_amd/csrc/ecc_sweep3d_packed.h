@@ -419,9 +419,8 @@ __device__ __forceinline__ void sweep_tube(const T* __restrict__ g, int D, int H
 
 // Work unit of a wave: as in sweep3d_wave (row groups of four, strips of 62 columns, a narrow last strip folded).
 template <typename T, typename Sink, typename TiltT>
-__device__ __forceinline__ void sweep3dp_wave(const T* __restrict__ g, int D, int H, int W, int nseg,
-                                              int planes_per_seg, s3::TubeQueue<Sink>& queue, WaveRange& range) {
-  const Tiling3 tl = make_tiling3(D, H, W, gridDim.y, s3p::kR, true);
+__device__ __forceinline__ void sweep3dp_wave(const T* __restrict__ g, int D, int H, int W,
+                                              const Tiling3& tl, int nseg, int planes_per_seg, s3::TubeQueue<Sink>& queue, WaveRange& range) {
   const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   int seg, strip, group;
   bool tail, active;

@@ -10,7 +10,7 @@ namespace ecc {
 // Histogram mode; run_if (may be null): do nothing unless *run_if != 0.
 template <typename T, bool LEVELS, bool TLDS, int MODE>
 __global__ __launch_bounds__(256, 4) void sweep3dp_kernel(const T* __restrict__ grid, int D, int H, int W, int64_t N,
-                                                       int bins, int nseg, int planes_per_seg,
+                                                       int bins, Tiling3 tl, int nseg, int planes_per_seg,
                                                        const HardHeader* __restrict__ hdr,
                                                        const float* __restrict__ table,
                                                        HistOut hist,
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256, 4) void sweep3dp_kernel(const T* __restrict__ 
   queue.sink.scale = LEVELS ? 0.f : hdr->scale;
   WaveRange range;
   sweep3dp_wave<T, HistSink<LEVELS, mode_is_super(MODE)>, typename ModeTransform<MODE>::type>(
-      grid + (int64_t)blockIdx.y * N, D, H, W, nseg, planes_per_seg, queue, range);
+      grid + (int64_t)blockIdx.y * N, D, H, W, tl, nseg, planes_per_seg, queue, range);
   __syncthreads();
   leave_histogram<256>(lhist, bins, hist);
 }
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256, 4) void sweep3dp_kernel(const T* __restrict__ 
 // Single-pass mode: critical vertices to the item's list, min / max to the header.
 template <typename T, int MODE>
 __global__ __launch_bounds__(256, 4) void sweep3dp_list_kernel(const T* __restrict__ grid, int D, int H, int W, int64_t N,
-                                                            int nseg, int planes_per_seg, ListArgs la) {
+                                                            Tiling3 tl, int nseg, int planes_per_seg, ListArgs la) {
   extern __shared__ int smem[];
   s3::TubeQueue<ListSink> queue;
   queue.buf = reinterpret_cast<uint2*>(smem) + (threadIdx.x >> 6) * kQueueCap;
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256, 4) void sweep3dp_list_kernel(const T* __restri
   }
   queue.sink.cap = la.cap;
   WaveRange range;
-  sweep3dp_wave<T, ListSink, typename ModeTransform<MODE>::type>(grid + (int64_t)blockIdx.y * N, D, H, W, nseg,
+  sweep3dp_wave<T, ListSink, typename ModeTransform<MODE>::type>(grid + (int64_t)blockIdx.y * N, D, H, W, tl, nseg,
                                                                  planes_per_seg, queue, range);
   if (la.heads) block_list_end(la, range, own);
   else range.commit(la.hdr);
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256, 4) void sweep3dp_list_kernel(const T* __restri
 
 template <typename T>
 __global__ __launch_bounds__(256, 4) void coeff3dp_kernel(const T* __restrict__ grid, int D, int H, int W, int64_t N,
-                                                       int nseg, int planes_per_seg, int8_t* __restrict__ out) {
+                                                       Tiling3 tl, int nseg, int planes_per_seg, int8_t* __restrict__ out) {
   extern __shared__ int smem[];
   s3::TubeQueue<CoeffSink3d> queue;
   queue.buf = reinterpret_cast<uint2*>(smem) + (threadIdx.x >> 6) * kQueueCap;
@@ -77,15 +77,15 @@ __global__ __launch_bounds__(256, 4) void coeff3dp_kernel(const T* __restrict__ 
   queue.count = 0;
   queue.sink.out = out + (int64_t)blockIdx.y * N;
   queue.sink.plane = (int64_t)H * W;
-  const Tiling3 tl = make_tiling3(D, H, W, gridDim.y, s3p::kR, true);
   queue.sink.oz = (int)(blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) / tl.units_seg * planes_per_seg;
   WaveRange range;
-  sweep3dp_wave<T, CoeffSink3d, NoTilt>(grid + (int64_t)blockIdx.y * N, D, H, W, nseg, planes_per_seg, queue, range);
+  sweep3dp_wave<T, CoeffSink3d, NoTilt>(grid + (int64_t)blockIdx.y * N, D, H, W, tl, nseg, planes_per_seg, queue, range);
 }
 
 constexpr size_t kQueueBytes3dp = (size_t)4 * kQueueCap * sizeof(uint2);
 
 struct Plan3dp {
+  Tiling3 tl;
   int nseg, planes_per_seg;
   dim3 grid;
 };
@@ -95,6 +95,7 @@ static Plan3dp plan3dp(const Shape& s, Feed3dp feed, int bins = 0) {
   Plan3dp p;
   const int D = (int)s.D, H = (int)s.H, W = (int)s.W;
   const Tiling3 tl = make_tiling3(D, H, W, s.batch, s3p::kR, true);
+  p.tl = tl;
   const int64_t per_seg = (int64_t)tl.units_seg / 4 * s.batch;  // blocks
   // a segment's element offsets stay below 2^32 and its plane count below 2^24 (what the critical-vertex queue stores)
   int64_t fit = (((int64_t)1 << 32) - 1) / ((int64_t)H * W);
@@ -143,7 +144,7 @@ static void launch3dp_t(const void* grid, const Shape& s, bool levels, int bins,
   const size_t lds = kQueueBytes3dp + (size_t)bins * (tlds ? 8 : 4);
 #define ECC_GO(LV, TL, M)                                                                                     \
   hipLaunchKernelGGL((sweep3dp_kernel<T, LV, TL, M>), pl.grid, dim3(256), lds, st, static_cast<const T*>(grid), \
-                     (int)s.D, (int)s.H, (int)s.W, s.N, bins, pl.nseg, pl.planes_per_seg, hdr, table, hist, run_if)
+                     (int)s.D, (int)s.H, (int)s.W, s.N, bins, pl.tl, pl.nseg, pl.planes_per_seg, hdr, table, hist, run_if)
 #define ECC_MODE(M)                                  \
   do {                                               \
     if constexpr (LV) {                              \
@@ -178,7 +179,7 @@ static void launch3dp_list_t(const void* grid, const Shape& s, const ListArgs& l
   const Plan3dp pl = plan3dp(s, la.heads ? Feed3dp::kAlone : Feed3dp::kSharedLists);
 #define ECC_LIST(M)                                                                                             \
   hipLaunchKernelGGL((sweep3dp_list_kernel<T, M>), pl.grid, dim3(256), kQueueBytes3dp, st,                      \
-                     static_cast<const T*>(grid), (int)s.D, (int)s.H, (int)s.W, s.N, pl.nseg, pl.planes_per_seg, la)
+                     static_cast<const T*>(grid), (int)s.D, (int)s.H, (int)s.W, s.N, pl.tl, pl.nseg, pl.planes_per_seg, la)
   switch (mode_of_conv(conv)) {
     case kTopCells: ECC_LIST(kTopCells); break;
     case kSuper: ECC_LIST(kSuper); break;
@@ -196,7 +197,7 @@ template <typename T>
 static void launch_coeff3dp_t(const void* grid, const Shape& s, int8_t* out, hipStream_t st) {
   const Plan3dp pl = plan3dp(s, Feed3dp::kAlone);
   hipLaunchKernelGGL((coeff3dp_kernel<T>), pl.grid, dim3(256), kQueueBytes3dp, st, static_cast<const T*>(grid),
-                     (int)s.D, (int)s.H, (int)s.W, s.N, pl.nseg, pl.planes_per_seg, out);
+                     (int)s.D, (int)s.H, (int)s.W, s.N, pl.tl, pl.nseg, pl.planes_per_seg, out);
 }
 void launch_coeff3dp(const void* grid, const Shape& s, int dtype, int8_t* out, hipStream_t st) {
   if (dtype == 0) launch_coeff3dp_t<uint8_t>(grid, s, out, st);
