@@ -331,6 +331,12 @@ def ecc_soft_contract(grad_chi, dchi_dtau=None, dchi_du=None, theta=None, ndim=2
     return grad_tau, grad_dir
 
 
+def soft_step_workspace(item_shape, batch: int, T: int, device) -> torch.Tensor:
+    """The current stream's kept workspace, with room for every soft call of a step."""
+    return _cached_workspace(max(_kept_bytes(ecc_workspace_bytes, item_shape, batch, T),
+                                 _kept_bytes(ecc_soft_contract_bytes, batch, T)), device)
+
+
 def ecc_count_nonfinite(grid: torch.Tensor, count=None):
     """Number of NaN / Inf elements of a device tensor, as a device int64 scalar tensor (no sync)."""
     _need_device(grid, count)

@@ -6,7 +6,9 @@ sums of Eq. 9-10, which share its sigmoids, and the saved list of critical verti
 return d chi / d tau and d chi / d u uncontracted ([batch, T] and [batch, T, ndim]); the two
 small contractions with the upstream gradient that autograd needs are ``ecc_soft_contract`` (tensor
 operations only where a graph of the backward pass is asked for).  ``SoftECCLayer`` holds the learnable thresholds and a direction kept on the unit
-sphere by reparametrisation (an angle in 2D, two angles in 3D), as the main text suggests.
+sphere by reparametrisation (an angle in 2D, two angles in 3D), as the main text suggests.  For plain tensors
+it runs the same calls through the C++ twin of ``_SoftECCAngles`` (``csrc/layer_torch.cpp``), which spares a step most
+of its host work.
 
 Inputs must live on the GPU; there is no CPU path.
 """
@@ -100,6 +102,37 @@ class _SoftECCAngles(torch.autograd.Function):
         return *_backward(ctx, grad_chi), None, None, None
 
 
+_PLAIN = (torch.Tensor, torch.nn.Parameter)
+
+
+def _native_takes(grid, theta, tau, ndim: int) -> bool:
+    """What the C++ function is for: plain contiguous float32 tensors of the layer's shapes on one GPU, outside function
+    transforms, dispatch modes, tracing, compilation and forward-mode differentiation."""
+    return (type(grid) in _PLAIN and type(tau) in _PLAIN and grid.is_cuda and tau.is_cuda
+            and grid.dtype is torch.float32 and tau.dtype is torch.float32
+            and grid.dim() == ndim + 1 and tau.dim() == 1 and theta.dim() == 1
+            and grid.get_device() == tau.get_device() == theta.get_device()
+            and grid.is_contiguous() and tau.is_contiguous()
+            and not torch._C._are_functorch_transforms_active() and torch._C._len_torch_dispatch_stack() == 0
+            and torch._C._get_tracing_state() is None and not torch.compiler.is_compiling()
+            and torch.autograd.forward_ad._current_level < 0)
+
+
+_soft_angles = None
+
+
+def _native():
+    global _soft_angles
+    if _soft_angles is None:
+        api._lib.load()
+        try:
+            from . import _layer_native
+        except ImportError as e:
+            raise RuntimeError("_layer_native.so is missing: build it with `python -m paper_2510_20271_amd.build`") from e
+        _soft_angles = _layer_native.soft_angles
+    return _soft_angles
+
+
 def soft_ecc(grid, u, tau, alpha: float, lam: float, tilted_c: bool = False):
     """Functional form: grid [batch, (D,) H, W] float32 on the GPU, u [ndim], tau [T].
     tilted_c: take c(p) from the tilted field X + alpha <u, p> (so that a sharp sigmoid gives
@@ -145,5 +178,13 @@ class SoftECCLayer(torch.nn.Module):
         own = type(self).direction is SoftECCLayer.direction and "direction" not in self.__dict__
         if (own and type(theta) in (torch.nn.Parameter, torch.Tensor) and theta.is_cuda and theta.is_contiguous()
                 and theta.dtype == torch.float32 and theta.numel() == self.ndim - 1):
+            tau = self.tau
+            if _native_takes(grid, theta, tau, self.ndim) and grid.numel() and tau.numel():
+                run = _native()
+                try:
+                    ws = api.soft_step_workspace(tuple(grid.shape[1:]), grid.shape[0], tau.numel(), grid.device)
+                    return run(grid, theta, tau, self.alpha, self.lam, self.tilted_c, ws)
+                except RuntimeError:
+                    pass  # (refused: the Python function raises the library's own error)
             return _SoftECCAngles.apply(grid, theta, self.tau, self.alpha, self.lam, self.tilted_c)
         return soft_ecc(grid, self.direction(), self.tau, self.alpha, self.lam, self.tilted_c)

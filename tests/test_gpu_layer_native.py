@@ -1,0 +1,102 @@
+"""The layer's C++ autograd function against its Python twin: the same bits for every choice of what is learned, in steps,
+without gradients, with a graph of the backward pass and over batches of upstream gradients; what one of them refuses the
+other refuses as well."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2510_20271_amd import api, layer, synth
+from paper_2510_20271_amd.layer import SoftECCLayer
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(ndim, T, tilted=False, learn_tau=True, learn_theta=True, lam=20.0):
+    angles = [0.3] if ndim == 2 else [0.3, 1.1]
+    return SoftECCLayer(ndim, T, -1.0, 1.0, lam=lam, theta=angles, learn_tau=learn_tau, learn_theta=learn_theta,
+                        tilted_c=tilted).cuda()
+
+
+def _grid(shape):
+    return torch.from_numpy(synth.grf_batch(shape[0], shape[1:], 2.0, 17)).cuda()
+
+
+def _both(monkeypatch, fn):
+    calls = []
+    real = layer._native()
+    monkeypatch.setattr(layer, "_native", lambda: lambda *a: (calls.append(1), real(*a))[1])
+    a = fn()
+    assert calls, "the C++ function was not taken"
+    monkeypatch.setattr(layer, "_native_takes", lambda *args: False)
+    return a, fn()
+
+
+@pytest.mark.parametrize("shape", [(1, 30, 40), (3, 61, 67), (2, 12, 20, 33)])
+@pytest.mark.parametrize("T", [1, 37, 300])
+@pytest.mark.parametrize("learn", [(True, True, True), (False, True, False), (False, False, True), (True, False, False)])
+def test_same_bits(monkeypatch, shape, T, learn):
+    need_x, need_tau, need_theta = learn
+
+    def step():
+        m = _layer(len(shape) - 1, T, tilted=T == 37, learn_tau=need_tau, learn_theta=need_theta)
+        x = _grid(shape).requires_grad_(need_x)
+        chi = m(x)
+        g = torch.linspace(-1.0, 2.0, chi.numel(), device="cuda").view_as(chi)
+        chi.backward(g)
+        with torch.no_grad():
+            plain = m(x)
+        assert not plain.requires_grad
+        return chi.detach(), plain, x.grad, m.tau.grad, m.theta.grad
+
+    a, b = _both(monkeypatch, step)
+    for p, q, wanted in zip(a, b, (True, True, need_x, need_tau, need_theta)):
+        assert (p is None) == (q is None) == (not wanted)
+        assert p is None or torch.equal(p, q)
+
+
+def test_graph_of_the_backward_pass_and_batched_gradients(monkeypatch):
+    def run():
+        m = _layer(3, 20)
+        chi = m(_grid((2, 12, 20, 33)))
+        g = torch.ones_like(chi).requires_grad_()
+        gt, ga = torch.autograd.grad(chi, [m.tau, m.theta], g, create_graph=True)
+        second = torch.autograd.grad(gt.sum() + ga.sum(), g, retain_graph=True)[0]
+        m = _layer(3, 20, learn_theta=False)  # (a batch of upstream gradients: the thresholds alone)
+        chi = m(_grid((2, 12, 20, 33)))
+        many = torch.autograd.grad(chi, [m.tau], torch.stack([g.detach(), 2 * g.detach()]), is_grads_batched=True)[0]
+        return gt.detach(), ga.detach(), second, many
+
+    for p, q in zip(*_both(monkeypatch, run)):
+        torch.testing.assert_close(p, q, rtol=1e-6, atol=1e-6)
+
+
+def test_saved_tensors(monkeypatch):
+    m, x = _layer(2, 9), _grid((2, 20, 30)).requires_grad_()
+    packed = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: (packed.append(t.shape), t.clone())[1], lambda t: t):
+        chi = m(x)
+    assert packed
+    chi.sum().backward()
+    with pytest.raises(RuntimeError):  # a second time through a freed graph
+        chi.sum().backward()
+    chi = m(x)
+    with torch.no_grad():
+        x.add_(1.0)
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        chi.sum().backward()
+
+
+def test_refusals_stay(monkeypatch):
+    with pytest.raises(api.EccError):
+        _layer(2, 5, lam=-1.0)(_grid((1, 20, 30)))
+    m, x = _layer(2, 5), _grid((1, 20, 30))
+    with pytest.raises(RuntimeError):
+        torch.func.grad(lambda t: m(t).sum())(x)
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(m)(x[None])
+    with pytest.raises(ValueError):
+        m(x[0])
+    # other layouts and types go the Python way, with the same result
+    want = m(x)
+    assert torch.equal(m(x.transpose(1, 2).contiguous().transpose(1, 2)), want)
+    assert torch.equal(m(x.double()), want)
