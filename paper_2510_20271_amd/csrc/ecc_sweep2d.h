@@ -494,13 +494,15 @@ static inline int64_t rows2d(const Shape& s, int64_t nstrip, int64_t tubes, Feed
     return waves(24) >= 8192 ? 24 : 16;
   }
   if (feed == Feed2d::kBlockLists) {
-    // A list per block: nothing is merged at a block's end.  Measured with 8 / 16 / 24 / 32 / 64 rows (us a call,
-    // float32): 1024 x 28^2 20.8 / 21.3 / 21.4 / 23.7, 1024^2 17.8 / 19.9 / 21.5 / 23.1 / 30.8, 64 directions of 256^2
-    // 23.9 / 21.9 / 25.2 / 25.8 / 35.7, 1024 x 128^2 43.7 / 39.2 / 47.2 / 53.2 / 57.8, 32 x 512^2 30.2 / 27.2 / 29.4 / 30.3 /
-    // 39.4, 4096^2 37.5 / 39.4 / 34.0 / 34.8 / 44.9, 8 x 4096^2 149 / 137 / 134 / 138 / 153: by the total first, then
-    // by the height (24 rows leave a low image's last segment and block half empty).
+    // A list per block: nothing is merged at a block's end.  Measured with 8 / 16 / 24 / 32 rows (us a call, float32): 1024 x
+    // 28^2 13.4 / 13.8 / 13.7 / 15.6, 1024^2 13.5 / 15.7 / 17.9 / 20.3, 2048^2 16.9 / 18.1 / 19.8 / 22.0 (white noise 42.5 / 62.7 / 83.6 /
+    // 106), 16 x 512^2 16.5 / 18.0 / 20.2 / 21.4, 64 x 256^2 15.1 / 15.4 / 17.9 / 19.3, 64 directions of 256^2 15.3 / 15.3 / 17.8 / 18.1;
+    // 32 x 512^2 23.6 / 21.6 / 24.6 / 25.3, 1024 x 128^2 40.3 / 35.7 / 43.9 / 32.9, 4096^2 30.7 / 32.7 / 28.8 / 30.3, 8 x 4096^2 149 /
+    // 137 / 135 / 138: eight rows up to four waves a SIMD (or few vertices), then by the height (24 rows leave a low image's
+    // last segment and block half empty).
     int64_t rows = H <= 1024 ? 16 : 24;
-    if (total < ((int64_t)1 << 22) && nstrip * ((H + 7) / 8) <= 2048) rows = 8;
+    // (below 32 rows the lists' room, rounded up to segments, would grow)
+    if ((H >= 32 && waves(8) <= 4608) || (total < ((int64_t)1 << 22) && nstrip * ((H + 7) / 8) <= 2048)) rows = 8;
     // Many waves cost more in the blocks' heads than short segments gain (500000 x 8 101 / 81 / 76 / 78 / 78,
     // 2000000 x 8 361 / 284 / 260 / 248 / 236)
     while (rows < 64 && waves(rows) > 24576) rows *= 2;

@@ -1,10 +1,10 @@
 // The layer's autograd function in C++: the C ABI's calls of a training step with their tensors made, saved and handed
 // on by torch's C++ interface.
 //
-// A step of the layer is bound by the host: five kernels of 55 us in all (32 x 512^2, 128 thresholds), and 150 us of Python
-// around them on a slow one -- marshalling for four calls, and a backward pass whose Python half waits for the
-// interpreter on the engine's thread.  With this file a step takes 80 us there (16 x 217 x 181 with 512 thresholds 157 -> 81),
-// Python functions on a box with a quick host (16 x 217 x 181 with 512 thresholds 55.0 against 73.9).
+// A step of the layer was bound by the host: five kernels of 55 us in all (32 x 512^2, 128 thresholds), and up to 150 us of
+// Python around them -- marshalling for four calls, and a backward pass whose Python half waits for the interpreter on the
+// engine's thread.  With this file a step takes 80 us where it took 154 (16 x 217 x 181 with 512 thresholds: 157 -> 81), and
+// on a quicker host as long as its kernels, 52 where it took 73.
 //
 // layer.py takes this path for plain contiguous float32 tensors outside function transforms and tracing; everything else
 // goes through its Python functions, whose results are the same.
