@@ -342,24 +342,24 @@ def main():
                 api.ecc_hard(copies[it[0]], nd, bins, curve=cvi, workspace=wsi)
             ncold = max(args.steps, 2 * len(copies)) if name == "c3" else 512
             swc, msc, _ = kernel_ms(api, cold, ncold, len(copies) if name == "c3" else 64)
-            extra[name] = {"workload": {"c1": "C1: 2D 256^2 uint8 i.i.d., 256 levels (launch-latency bound, 3 launches)",
+            extra[name] = {"workload": {"c1": "C1: 2D 256^2 uint8 i.i.d., 256 levels (launch-latency bound, 2 launches)",
                                         "c3": "C3: 3D 256^3 uint16 i.i.d., 4096 levels"}[name],
                            "us_per_step": round(msi * 1e3, 2), "sweep_kernel_us": round(swi * 1e3, 2),
                            "gvoxel_per_s": round(X.size / msi / 1e6, 2),
                            "cold_us_per_step": round(msc * 1e3, 2), "cold_sweep_kernel_us": round(swc * 1e3, 2),
                            "cold_copies": len(copies)}
             if name == "c3":
-                rooflines["c3"] = roofline_alu(swi, "sweep3d_kernel<uint16> (levels, LDS histogram)", counters.get("c3"),
+                rooflines["c3"] = roofline_alu(swi, "sweep3dp_kernel<uint16> (levels, LDS histogram)", counters.get("c3"),
                                                X.nbytes, "2 bytes per vertex: HBM is idle by construction; the kernel is "
-                                               "bound by vector instruction issue (stencil, then a walk over the 60 % of "
-                                               "the vertices that are critical, each with one LDS histogram update)")
+                                               "bound by vector instruction issue (stencil, then the 60 % of "
+                                               "the vertices that are critical, binned from registers, one LDS update each)")
                 rooflines["c3"]["cold_kernel_ms"] = round(swc, 4)
             else:
                 rooflines["c1"] = roofline_hbm(float(X.nbytes), swi, "sweep_generic_kernel<uint8> (one thread per vertex)",
-                                               counters.get("c1"), note="64 KiB input: the call is three dependent "
+                                               counters.get("c1"), note="64 KiB input: the call is two dependent "
                                                "launches of a few microseconds each; a fraction of HBM peak says nothing here")
                 rooflines["c1"]["cold_kernel_ms"] = round(swc, 4)
-                rooflines["c1"]["launches_per_call"] = 3
+                rooflines["c1"]["launches_per_call"] = 2
             log(f"[bench] {name}: {msi * 1e3:.1f} us/step, sweep {swi * 1e3:.1f} us; cold {msc * 1e3:.1f} us/step, "
                 f"sweep {swc * 1e3:.1f} us ({len(copies)} copies)")
             del gi, copies

@@ -32,7 +32,7 @@ WORKLOADS = {
     "c4r": ("hard ECC, workload C4 with the range supplied (histogram-mode sweep)", "hard_c4_range.md",
             [("c4r", "sweep3d_kernel", 512 ** 3, 62)]),
     "c3": ("hard ECC, workload C3 (256^3 uint16 i.i.d., 4096 levels)", "hard_c3.md",
-           [("c3", "sweep3d_kernel<unsigned short", 256 ** 3, 62)]),
+           [("c3", "sweep3dp_kernel<unsigned short", 256 ** 3, 62)]),
     "c1": ("hard ECC, workload C1 (256^2 uint8 i.i.d., 256 levels)", "hard_c1.md",
            [("c1", "sweep_generic_kernel", 256 * 256, 64)]),
     "c5": ("soft ECC forward + backward, workload C5 (32 x 512^2 float32, T = 128)", "soft_c5.md",
