@@ -28,6 +28,14 @@ void check(int status) {
 }
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 float* f32(const Tensor& t) { return t.defined() ? t.data_ptr<float>() : nullptr; }
+// Saved tensors come back from saved-tensor hooks, upstream gradients from anywhere: what the kernels are handed is as the
+// forward pass made it, or nothing (numel < 0: any number of elements).
+void check_device(const Tensor& t, at::ScalarType type, int64_t numel, const at::Device& device) {
+  TORCH_CHECK_VALUE(t.defined() && t.layout() == at::kStrided && t.has_storage() && t.is_contiguous() && t.device() == device,
+                    "tensors must be contiguous device tensors");
+  TORCH_CHECK_VALUE(t.scalar_type() == type && (numel < 0 || t.numel() == numel),
+                    "a saved tensor or gradient is not of the type or size that the forward pass left");
+}
 int64_t padded(int64_t n) { return (n + 63) / 64 * 64; }
 
 // One buffer of floats: the direction, then (where wanted) d chi / d tau and d chi / d u, each at a multiple of 256 bytes.
@@ -64,7 +72,7 @@ struct Angles : public torch::autograd::Function<Angles> {
     ctx->saved_data["lam"] = lam;
     ctx->saved_data["tilted"] = tilted;
     ctx->saved_data["workspace"] = workspace;  // (of the forward pass's stream, on which the backward pass runs too)
-    ctx->saved_data["need"] = (int64_t)need_u * 2 + (int64_t)need_tau;
+    ctx->saved_data["need"] = (int64_t)ndim * 4 + (int64_t)need_u * 2 + (int64_t)need_tau;
     return chi;
   }
 
@@ -72,17 +80,24 @@ struct Angles : public torch::autograd::Function<Angles> {
     const variable_list saved = ctx->get_saved_variables();
     const Tensor &grid = saved[0], &kept = saved[1], &tau = saved[2], &state = saved[3], &theta = saved[4];
     const Tensor g = grads[0].contiguous().to(at::kFloat);
-    const int ndim = (int)grid.dim() - 1;
-    const int64_t batch = grid.size(0), T = tau.numel(), BT = batch * T;
-    const int64_t* dims = grid.sizes().data() + 1;
     const int64_t made = ctx->saved_data["need"].toInt();
     const bool made_u = (made & 2) != 0, made_tau = (made & 1) != 0;
+    const int ndim = (int)(made >> 2);
+    check_device(grid, at::kFloat, -1, grid.device());
+    TORCH_CHECK_VALUE(grid.is_cuda() && grid.dim() == ndim + 1, "grid must be a device tensor [batch, *item_shape]");
+    const int64_t batch = grid.size(0), T = tau.numel(), BT = batch * T;
+    const int64_t* dims = grid.sizes().data() + 1;
+    check_device(tau, at::kFloat, -1, grid.device());
+    check_device(kept, at::kFloat, Kept::size(BT, ndim, made_tau, made_u), grid.device());
+    if (made_u) check_device(theta, at::kFloat, ndim - 1, grid.device());
+    if (g.has_storage()) check_device(g, at::kFloat, BT, grid.device());
     const bool need_x = ctx->needs_input_grad(0), need_u = ctx->needs_input_grad(1) && made_u,
                need_tau = ctx->needs_input_grad(2) && made_tau;
     const Kept k(kept, BT, made_tau, made_u);
     Tensor grad_x, grad_theta, grad_tau;
     if (need_x) {
       TORCH_CHECK(g.has_storage(), "the gradient of the input needs an upstream gradient with memory of its own");
+      check_device(state, at::kByte, -1, grid.device());  // (its size is the library's to check)
       const Tensor ws = ctx->saved_data["workspace"].toTensor();
       grad_x = at::empty(grid.sizes(), grid.options());
       check(ecc_soft_bwd_saved(f32(grid), ndim, dims, batch, k.u, (float)ctx->saved_data["alpha"].toDouble(), f32(tau),

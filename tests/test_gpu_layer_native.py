@@ -100,3 +100,24 @@ def test_refusals_stay(monkeypatch):
     want = m(x)
     assert torch.equal(m(x.transpose(1, 2).contiguous().transpose(1, 2)), want)
     assert torch.equal(m(x.double()), want)
+
+
+@pytest.mark.parametrize("how", ["host", "strided", "short", "other type"])
+@pytest.mark.parametrize("which", range(5))  # the input, the derivatives, the thresholds, the state, the angles
+def test_what_a_hook_hands_back_is_checked(which, how):
+    """A saved-tensor hook that returns something else than was saved is refused before any kernel sees it."""
+    change = {"host": lambda t: t.cpu(), "strided": lambda t: torch.stack([t, t], -1)[..., 0],
+              "short": lambda t: t.reshape(-1)[: t.numel() // 2].clone(),
+              "other type": lambda t: t.double() if t.is_floating_point() else t.short()}[how]
+    m = SoftECCLayer(3, 9, -1.0, 1.0, theta=[0.3, 1.1]).cuda()
+    x, seen = _grid((2, 12, 20, 33)).requires_grad_(), []
+
+    def pack(t):
+        seen.append(t)
+        return len(seen) - 1, t
+
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda p: change(p[1]) if p[0] == which else p[1]):
+        chi = m(x)
+    assert len(seen) == 5
+    with pytest.raises(ValueError if how != "short" or which != 3 else RuntimeError):
+        chi.sum().backward()
