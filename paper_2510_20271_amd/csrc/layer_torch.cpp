@@ -12,7 +12,6 @@
 
 #include <c10/hip/HIPStream.h>
 
-#include <stdexcept>
 #include <string>
 
 #include "ecc.h"
@@ -23,8 +22,15 @@ using torch::Tensor;
 using torch::autograd::AutogradContext;
 using torch::autograd::variable_list;
 
+// What the library refuses is the Python binding's EccError, with its status, in the backward pass as well.
 void check(int status) {
-  if (status != ECC_OK) throw std::runtime_error(std::string("ecc status ") + std::to_string(status) + ": " + ecc_last_error());
+  if (status == ECC_OK) return;
+  const std::string message = ecc_last_error();  // (of this thread)
+  const py::gil_scoped_acquire gil;
+  const py::object type = py::module_::import("paper_2510_20271_amd.api").attr("EccError");
+  const py::object error = type(status, message);
+  PyErr_SetObject(type.ptr(), error.ptr());
+  throw py::error_already_set();
 }
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 float* f32(const Tensor& t) { return t.defined() ? t.data_ptr<float>() : nullptr; }

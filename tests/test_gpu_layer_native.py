@@ -121,3 +121,17 @@ def test_what_a_hook_hands_back_is_checked(which, how):
     assert len(seen) == 5
     with pytest.raises(ValueError if how != "short" or which != 3 else RuntimeError):
         chi.sum().backward()
+
+
+def test_a_refusal_in_the_backward_pass_has_its_status():
+    m, x, seen = _layer(2, 9), _grid((2, 20, 30)).requires_grad_(), []
+
+    def pack(t):
+        seen.append(t)
+        return len(seen) - 1, t
+
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda p: p[1][:256].clone() if p[0] == 3 else p[1]):
+        chi = m(x)  # (number 3 is the state)
+    with pytest.raises(api.EccError, match="state") as e:
+        chi.sum().backward()
+    assert e.value.status == -3
