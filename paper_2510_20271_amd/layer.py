@@ -180,11 +180,7 @@ class SoftECCLayer(torch.nn.Module):
                 and theta.dtype == torch.float32 and theta.numel() == self.ndim - 1):
             tau = self.tau
             if _native_takes(grid, theta, tau, self.ndim) and grid.numel() and tau.numel():
-                run = _native()
-                try:
-                    ws = api.soft_step_workspace(tuple(grid.shape[1:]), grid.shape[0], tau.numel(), grid.device)
-                    return run(grid, theta, tau, self.alpha, self.lam, self.tilted_c, ws)
-                except RuntimeError:
-                    pass  # (refused: the Python function raises the library's own error)
+                ws = api.soft_step_workspace(tuple(grid.shape[1:]), grid.shape[0], tau.numel(), grid.device)
+                return _native()(grid, theta, tau, self.alpha, self.lam, self.tilted_c, ws)
             return _SoftECCAngles.apply(grid, theta, self.tau, self.alpha, self.lam, self.tilted_c)
         return soft_ecc(grid, self.direction(), self.tau, self.alpha, self.lam, self.tilted_c)

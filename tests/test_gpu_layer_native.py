@@ -22,11 +22,24 @@ def _grid(shape):
 
 
 def _both(monkeypatch, fn):
-    calls = []
+    """fn through the C++ function, which has to return (the Python one is not there to step in), then through Python."""
+    returned = []
     real = layer._native()
-    monkeypatch.setattr(layer, "_native", lambda: lambda *a: (calls.append(1), real(*a))[1])
-    a = fn()
-    assert calls, "the C++ function was not taken"
+
+    def counted(*args):
+        chi = real(*args)
+        returned.append(chi)
+        assert chi.grad_fn is None or "SoftECCAngles" not in type(chi.grad_fn).__name__
+        return chi
+
+    def absent(*args):
+        raise AssertionError("the Python function was taken")
+
+    with monkeypatch.context() as m:
+        m.setattr(layer, "_native", lambda: counted)
+        m.setattr(layer._SoftECCAngles, "apply", absent)
+        a = fn()
+    assert returned
     monkeypatch.setattr(layer, "_native_takes", lambda *args: False)
     return a, fn()
 
@@ -135,3 +148,28 @@ def test_a_refusal_in_the_backward_pass_has_its_status():
     with pytest.raises(api.EccError, match="state") as e:
         chi.sum().backward()
     assert e.value.status == -3
+
+
+def test_errors_of_the_native_function_are_the_callers(monkeypatch):
+    """No second run through Python: memory that has run out, a hook's own error, a fault of the function itself."""
+    m, x, calls = _layer(2, 9), _grid((2, 20, 30)), []
+
+    def pack(t):
+        calls.append(1)
+        raise RuntimeError("of the hook")
+
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t):
+        with pytest.raises(RuntimeError, match="of the hook"):
+            m(x)
+    assert len(calls) == 1
+    for error in (torch.OutOfMemoryError("no memory"), RuntimeError("fault"), api.EccError(-1, "refused")):
+        calls.clear()
+
+        def fails(*args):
+            calls.append(1)
+            raise error
+
+        monkeypatch.setattr(layer, "_native", lambda: fails)
+        with pytest.raises(type(error)) as e:
+            m(x)
+        assert e.value is error and len(calls) == 1
