@@ -55,6 +55,22 @@ struct Kept {
   }
 };
 
+// The workspace of the forward pass for the backward pass, which runs on the same stream: not owned, so that a workspace that
+// was replaced by a larger one is not kept by the graphs of steps before.  Where it is gone, or the node is run on another
+// stream (whose calls it would not be safe with), room is allocated.
+struct Workspace : public torch::CustomClassHolder {
+  c10::weak_intrusive_ptr<at::TensorImpl, at::UndefinedTensorImpl> kept;
+  at::TensorOptions options;
+  int64_t bytes;
+  void* on;
+  explicit Workspace(const Tensor& t) : kept(t.getIntrusivePtr()), options(t.options()), bytes(t.numel()), on(stream()) {}
+  Tensor get() const {
+    if (on == stream())
+      if (auto impl = kept.lock()) return Tensor(std::move(impl));
+    return at::empty({bytes}, options);
+  }
+};
+
 struct Angles : public torch::autograd::Function<Angles> {
   static Tensor forward(AutogradContext* ctx, const Tensor& grid, const Tensor& theta, const Tensor& tau, double alpha,
                         double lam, bool tilted, const Tensor& workspace, bool need_x, bool need_u, bool need_tau) {
@@ -77,7 +93,7 @@ struct Angles : public torch::autograd::Function<Angles> {
     ctx->saved_data["alpha"] = alpha;
     ctx->saved_data["lam"] = lam;
     ctx->saved_data["tilted"] = tilted;
-    ctx->saved_data["workspace"] = workspace;  // (of the forward pass's stream, on which the backward pass runs too)
+    ctx->saved_data["workspace"] = at::IValue::make_capsule(c10::make_intrusive<Workspace>(workspace));
     ctx->saved_data["need"] = (int64_t)ndim * 4 + (int64_t)need_u * 2 + (int64_t)need_tau;
     return chi;
   }
@@ -101,10 +117,10 @@ struct Angles : public torch::autograd::Function<Angles> {
                need_tau = ctx->needs_input_grad(2) && made_tau;
     const Kept k(kept, BT, made_tau, made_u);
     Tensor grad_x, grad_theta, grad_tau;
+    const Tensor ws = c10::static_intrusive_pointer_cast<Workspace>(ctx->saved_data["workspace"].toCapsule())->get();
     if (need_x) {
       TORCH_CHECK(g.has_storage(), "the gradient of the input needs an upstream gradient with memory of its own");
       check_device(state, at::kByte, -1, grid.device());  // (its size is the library's to check)
-      const Tensor ws = ctx->saved_data["workspace"].toTensor();
       grad_x = at::empty(grid.sizes(), grid.options());
       check(ecc_soft_bwd_saved(f32(grid), ndim, dims, batch, k.u, (float)ctx->saved_data["alpha"].toDouble(), f32(tau),
                                (int)T, (float)ctx->saved_data["lam"].toDouble(), ctx->saved_data["tilted"].toBool() ? 1 : 0,
@@ -113,8 +129,7 @@ struct Angles : public torch::autograd::Function<Angles> {
     }
     if (need_u || need_tau) {
       if (!at::GradMode::is_enabled() && g.has_storage()) {
-        const Tensor ws = ctx->saved_data["workspace"].toTensor();
-        if (need_tau) grad_tau = at::empty({T}, grid.options());
+          if (need_tau) grad_tau = at::empty({T}, grid.options());
         if (need_u) grad_theta = at::empty({ndim - 1}, grid.options());
         check(ecc_soft_contract(f32(g), need_tau ? k.dtau : nullptr, need_u ? k.du : nullptr, need_u ? f32(theta) : nullptr,
                                 batch, (int)T, ndim, f32(grad_tau), f32(grad_theta), ws.data_ptr(), (size_t)ws.numel(),

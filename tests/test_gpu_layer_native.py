@@ -1,6 +1,8 @@
 """The layer's C++ autograd function against its Python twin: the same bits for every choice of what is learned, in steps,
 without gradients, with a graph of the backward pass and over batches of upstream gradients; what one of them refuses the
 other refuses as well."""
+import weakref
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -173,3 +175,35 @@ def test_errors_of_the_native_function_are_the_callers(monkeypatch):
         with pytest.raises(type(error)) as e:
             m(x)
         assert e.value is error and len(calls) == 1
+
+
+def test_a_graph_keeps_no_workspace():
+    """A step's workspace is the stream's: one that was replaced by a larger one goes, though a graph that used it is alive."""
+    torch.cuda.synchronize()
+    api._WS_CACHE.clear()
+    m, x = _layer(2, 9), _grid((2, 20, 30)).requires_grad_()
+    m(x).sum().backward()
+    want, x.grad = x.grad, None
+    chi = m(x)
+    (kept,) = [weakref.ref(ws) for ws in api._WS_CACHE.values()]
+    api.soft_step_workspace((300, 300), 4, 64, x.device)
+    assert kept() is None
+    chi.sum().backward()
+    assert torch.equal(x.grad, want)
+
+
+def test_a_node_run_on_another_stream_has_a_workspace_of_its_own():
+    torch.cuda.synchronize()
+    api._WS_CACHE.clear()
+    m, x = _layer(2, 1000), _grid((40, 30, 40)).requires_grad_()
+    g = torch.ones(40, 1000, device="cuda")  # (the contraction takes several blocks, whose sums go through the workspace)
+    m(x).backward(g)
+    chi = m(x)
+    (ws,) = api._WS_CACHE.values()
+    ws.fill_(0xAB)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()), torch.no_grad():
+        grad_x, grad_theta, grad_tau = chi.grad_fn(g)[:3]
+    torch.cuda.synchronize()
+    assert bool((ws == 0xAB).all())
+    assert torch.equal(grad_x, x.grad) and torch.equal(grad_tau, m.tau.grad) and torch.equal(grad_theta, m.theta.grad)
