@@ -181,6 +181,6 @@ class SoftECCLayer(torch.nn.Module):
             tau = self.tau
             if _native_takes(grid, theta, tau, self.ndim) and grid.numel() and tau.numel():
                 ws = api.soft_step_workspace(tuple(grid.shape[1:]), grid.shape[0], tau.numel(), grid.device)
-                return _native()(grid, theta, tau, self.alpha, self.lam, self.tilted_c, ws)
+                return _native()(grid, theta, tau, float(self.alpha), float(self.lam), bool(self.tilted_c), ws)
             return _SoftECCAngles.apply(grid, theta, self.tau, self.alpha, self.lam, self.tilted_c)
         return soft_ecc(grid, self.direction(), self.tau, self.alpha, self.lam, self.tilted_c)

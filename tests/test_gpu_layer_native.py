@@ -207,3 +207,11 @@ def test_a_node_run_on_another_stream_has_a_workspace_of_its_own():
     torch.cuda.synchronize()
     assert bool((ws == 0xAB).all())
     assert torch.equal(grad_x, x.grad) and torch.equal(grad_tau, m.tau.grad) and torch.equal(grad_theta, m.theta.grad)
+
+
+def test_parameters_of_other_types():
+    """alpha, lam and tilted_c may be whatever float() and bool() take, as through the Python function."""
+    m, x = _layer(2, 9), _grid((2, 20, 30))
+    want = m(x)
+    m.alpha, m.lam, m.tilted_c = torch.tensor(m.alpha), "20.0", ""
+    assert torch.equal(m(x), want)
