@@ -176,5 +176,7 @@ Tensor soft_angles(const Tensor& grid, const Tensor& theta, const Tensor& tau, d
 }  // namespace
 
 PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
-  m.def("soft_angles", &soft_angles, "Soft curves with the direction given by its angles, differentiable");
+  // (without the interpreter's lock, as the Python function's library calls: a launch waits when the device's queue is full)
+  m.def("soft_angles", &soft_angles, "Soft curves with the direction given by its angles, differentiable",
+        py::call_guard<py::gil_scoped_release>());
 }
