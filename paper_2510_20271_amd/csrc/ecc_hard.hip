@@ -210,8 +210,8 @@ __global__ __launch_bounds__(kBinBlock) void binlist_kernel(ListArgs la, float* 
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       if (i0 + q * kWave + lane < n) {
-        const int b = lower ? bin_super_from_table(e[q].x, ltable, bins, lo, scale)
-                            : bin_from_table(e[q].x, ltable, bins, lo, scale);
+        const int b = lower ? bin_super_from_table<true>(e[q].x, ltable, bins, lo, scale)
+                            : bin_from_table<true>(e[q].x, ltable, bins, lo, scale);
         if (b < bins) atomicAdd(&lhist[b], __float_as_int(e[q].y));
       }
     }

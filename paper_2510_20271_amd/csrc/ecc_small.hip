@@ -272,8 +272,8 @@ __global__ __launch_bounds__(BLOCK) void small_finish_kernel(const SmallHead* __
     for (unsigned q = 0; q < kDeep; ++q) {
       if (ok[q]) {
         const float v = __uint_as_float(e[q].x);
-        const int b = super ? bin_super_from_table(v, ltable, bins, lo, scale)
-                            : bin_from_table(v, ltable, bins, lo, scale);
+        const int b = super ? bin_super_from_table<true>(v, ltable, bins, lo, scale)
+                            : bin_from_table<true>(v, ltable, bins, lo, scale);
         if (b < bins) atomicAdd(&lhist[b], (int)e[q].y);
       }
     }
