@@ -17,6 +17,7 @@
 #include "ecc_soft_saved.h"
 #include "ecc_soft_reduce.h"
 
+#include <algorithm>
 #include <cstdlib>
 
 namespace ecc {
@@ -301,7 +302,7 @@ static size_t soft3d_partial_bytes(const Shape& s, const Plan3d& pl, int T) {
 
 size_t soft3d_workspace_bytes(const Shape& s, int T) {
   if (!soft3d_supported(s, T)) return 0;
-  const Plan3d pl = plan3d<float>(s);
+  const Plan3d pl = plan3d<float>(s, Fold3::kSoft);
   return (size_t)256 + soft3d_partial_bytes(s, pl, T) + soft_reduce_mid_bytes((int)pl.grid.x * 4, s.batch, T);
 }
 
@@ -317,7 +318,7 @@ static dim3 layered(const Plan3d& pl, const Shape& s, int T) {
 
 void launch_soft3d_fwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                        float lambda, float* chi, void* ws, hipStream_t st, bool tiltc) {
-  const Plan3d pl = plan3d<float>(s);
+  const Plan3d pl = plan3d<float>(s, Fold3::kSoft);
   float* partial = static_cast<float*>(ws);
 #define ECC_GO(TC, MANY)                                                                                          \
   hipLaunchKernelGGL((soft3d_fwd_kernel<TC, MANY>), layered(pl, s, T), dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
@@ -333,7 +334,7 @@ void launch_soft3d_fwd(const float* grid, const Shape& s, const float* u, float 
 void launch_soft3d_bwd(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                        float lambda, const float* gup, float* grad_X, float* dtau, float* du, void* ws,
                        hipStream_t st, bool tiltc) {
-  const Plan3d pl = plan3d<float>(s);
+  const Plan3d pl = plan3d<float>(s, Fold3::kSoft);
   float* partial = (dtau || du) ? static_cast<float*>(ws) : nullptr;
 #define ECC_GO(TC, MANY)                                                                                          \
   hipLaunchKernelGGL((soft3d_bwd_kernel<TC, MANY>), pl.grid, dim3(256), kSoft3Lds, st, grid, (int)s.D, (int)s.H,      \
@@ -349,15 +350,25 @@ void launch_soft3d_bwd(const float* grid, const Shape& s, const float* u, float 
 }
 
 // ---- forward that saves its critical vertices, backward from the saved lists ----------------
-static unsigned state_cap3(const Plan3d& pl) {
-  // room for one vertex in eight of a unit's planes x 4 rows x 62 columns, rounded up to 64 entries
-  return ((unsigned)pl.planes_per_seg * (unsigned)kRows3d * (unsigned)s3::kOut / 8u + 63u) / 64u * 64u;
+static unsigned state_cap3(const Shape& s, const Plan3d& pl) {
+  // room for one vertex in eight of a unit's planes x 4 rows x 62 columns, rounded up to 64 entries; of twelve planes at least
+  // in small launches, since the share of critical vertices varies the more the fewer there are (16 x 48 x 64 in segments of
+  // eight planes ran over: backward pass from the grid, 41 us instead of 14).
+  const Tiling3& tl = pl.tl;
+  const bool small = (int64_t)pl.nseg * tl.nstrip * tl.ngroup4 * s.batch <= 4096;
+  const unsigned planes = std::max(small ? 12u : 1u, (unsigned)pl.planes_per_seg);
+  const unsigned cap = (planes * (unsigned)kRows3d * (unsigned)s3::kOut / 8u + 63u) / 64u * 64u;
+  // The folded units of a narrow volume, whose unfolded ones had room for most of their few vertices, have room for one in
+  // four, unless the launch is many rounds long (739 x 8 x 8 x 16, a ninth of whose vertices is critical: 19 us, 27 from the
+  // grid).
+  if (tl.nstrip > 1 || tl.F == 1 || tl.ngroup * s.batch * s.D >= 160000) return cap;
+  return std::max(cap, ((unsigned)tl.F * (unsigned)s.W * planes + 63u) / 64u * 64u);
 }
 static bool soft3d_saves(const Shape& s) { return soft3d_supported(s, 1) && s.N < ((int64_t)1 << 31); }
 size_t soft3d_state_bytes(const Shape& s) {
   if (!soft3d_saves(s)) return 256;
-  const Plan3d pl = plan3d<float>(s);
-  return state_bytes(s.batch, (size_t)pl.grid.x * 4, state_cap3(pl));
+  const Plan3d pl = plan3d<float>(s, Fold3::kSoft);
+  return state_bytes(s.batch, (size_t)pl.grid.x * 4, state_cap3(s, pl));
 }
 bool soft3d_state_supported(const Shape& s, int T) { return soft3d_supported(s, T) && soft3d_saves(s); }
 
@@ -373,14 +384,14 @@ static SoftStateHeader state_header3(const Shape& s, const Plan3d& pl, bool tilt
   h.rows_per_seg = pl.planes_per_seg;
   h.units = (int)pl.grid.x * 4;
   h.tiltc = tiltc ? 1 : 0;
-  h.cap = state_cap3(pl);
+  h.cap = state_cap3(s, pl);
   return h;
 }
 
 void launch_soft3d_fwd_save(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                             float lambda, float* chi, float* dtau, float* du, void* state, void* ws, hipStream_t st,
                             bool tiltc) {
-  const Plan3d pl = plan3d<float>(s);
+  const Plan3d pl = plan3d<float>(s, Fold3::kSoft);
   const SoftStateHeader hdr = state_header3(s, pl, tiltc);
   const StateView sv = state_view(state, s.batch, (size_t)hdr.units);
   float* partial = static_cast<float*>(ws);
@@ -401,7 +412,7 @@ void launch_soft3d_fwd_save(const float* grid, const Shape& s, const float* u, f
 void launch_soft3d_bwd_saved(const float* grid, const Shape& s, const float* u, float alpha, const float* tau, int T,
                              float lambda, const float* gup, float* grad_X, const void* state, hipStream_t st,
                              bool tiltc) {
-  const Plan3d pl = plan3d<float>(s);
+  const Plan3d pl = plan3d<float>(s, Fold3::kSoft);
   const SoftStateHeader expect = state_header3(s, pl, tiltc);
   const StateView sv = state_view(const_cast<void*>(state), s.batch, (size_t)expect.units);
   launch_clear_f32(grad_X, s.N * s.batch, st);  // zero away from the critical vertices

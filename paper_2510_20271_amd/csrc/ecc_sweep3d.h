@@ -553,7 +553,8 @@ struct Tiling3 {
   int ngroupT, full, units_seg; // units of the last strip, units of the full strips, units per segment
 };
 // (on the host; kernels are handed the result)
-static inline Tiling3 make_tiling3(int D, int H, int W, long long batch, int R, bool always_fold = false) {
+enum class Fold3 { kByWaves, kSoft, kAlways };
+static inline Tiling3 make_tiling3(int D, int H, int W, long long batch, int R, Fold3 fold) {
   Tiling3 t;
   t.nstrip = (W + s3::kOut - 1) / s3::kOut;
   t.ngroup = (H + R - 1) / R;
@@ -566,14 +567,24 @@ static inline Tiling3 make_tiling3(int D, int H, int W, long long batch, int R, 
   // 25.2, 20 x 50 x 60 x 70 35.0 -> 25.8 (whole calls, smooth fields; noise 3 to 20 % as well, 8 x 64^3 3 % slower).  With
   // one wave on a SIMD, or two that stay two, it only makes the folded waves the slowest: 128^3 with 300 thresholds 24.0 ->
   // 27.3, noise of 160 x 190 x 130 39.4 -> 41.8.  Counted in 12-plane segments, 1024 SIMDs and a sixteenth.
+  // kSoft: a wave that has to evaluate its vertices' sigmoids takes as long as it has vertices.  With two strips and more a
+  // folded wave has no more of them than a full strip's (0.92 of the time over 300 calls); in volumes of one strip every wave
+  // is a folded one, with up to eight times the vertices of an unfolded, narrow one.  Those fold where one and a half waves
+  // a SIMD are left (276 x 27 x 24 x 23 backward 134 -> 89 us, 1280 x 9 x 18 x 14 forward 0.60 of the time; but 739 x 8 x 8 x 16,
+  // which leaves 739 waves, 1.23, 137 x 7 x 26 x 19 with 411 1.09).
   if (wt + 2 <= kWave / 2) {
     int F = kWave / (wt + 2);
     if (F > 8) F = 8;
     if (F > t.ngroup) F = t.ngroup;
+    // (as few folds as need that many waves: the waves of a strip then have even shares)
+    const int waves = (t.ngroup + F - 1) / F;
+    F = (t.ngroup + waves - 1) / waves;
     const long long segs = batch * ((D + 11) / 12);
     const long long whole = segs * t.nstrip * t.ngroup4;
     const long long folded = segs * ((t.nstrip - 1) * t.ngroup4 + (((t.ngroup + F - 1) / F + 3) & ~3));
-    if (F > 1 && (always_fold || whole > 2112 || (whole > 1088 && folded <= 1088))) {
+    bool pays = whole > 2112 || (whole > 1088 && folded <= 1088);
+    if (fold == Fold3::kSoft && t.nstrip == 1) pays = pays && segs * waves >= 1536;
+    if (F > 1 && (pays || fold == Fold3::kAlways)) {
       t.S = wt + 2;
       t.F = F;
     }
@@ -662,11 +673,11 @@ struct Plan3d {
   dim3 grid;
 };
 template <typename T>
-static Plan3d plan3d(const Shape& s) {
+static Plan3d plan3d(const Shape& s, Fold3 fold = Fold3::kByWaves) {
   constexpr int R = kRows3d;
   Plan3d p;
   const int D = (int)s.D, H = (int)s.H, W = (int)s.W;
-  const Tiling3 tl = make_tiling3(D, H, W, s.batch, R);
+  const Tiling3 tl = make_tiling3(D, H, W, s.batch, R, fold);
   p.tl = tl;
   const int64_t per_seg = (int64_t)tl.units_seg * s.batch;
   // about 2.5 rounds of waves over the chip on 512^3 (60-plane segments); measured best
@@ -680,7 +691,7 @@ static Plan3d plan3d(const Shape& s) {
   // count below 2^24 (what the critical-vertex queue stores)
   int64_t planes = ((D + nseg - 1) / nseg + s3::kChunk - 1) / s3::kChunk * s3::kChunk;
   // A small launch, whose one-chunk segments leave wave slots empty (256 CUs x 4 SIMDs x 4 waves), takes shorter segments of
-  // equal length, down to 12 planes.  The waves on a SIMD take turns (the oldest first) and together issue almost without a
+  // equal length, no more of them than 12 planes each would make (D = 13: two, of 7).  The waves on a SIMD take turns (the oldest first) and together issue almost without a
   // gap, so what counts is that none waits for a second round and that a segment's three extra planes stay few: as many
   // segments as the slots hold.  (One more, as before, cost a second round of a few blocks: 256^3 float32, folded, list sweep
   // with 16 / 18 / 20 / 22 / 24 planes 47.2 / 44.6 / 45.2 / 42.5 / 42.0 us a call, 16 being the second round; noise, whose vertices a

@@ -94,7 +94,7 @@ enum class Feed3dp { kHist, kSharedLists, kAlone };  // kAlone: nothing that blo
 static Plan3dp plan3dp(const Shape& s, Feed3dp feed, int bins = 0) {
   Plan3dp p;
   const int D = (int)s.D, H = (int)s.H, W = (int)s.W;
-  const Tiling3 tl = make_tiling3(D, H, W, s.batch, s3p::kR, true);
+  const Tiling3 tl = make_tiling3(D, H, W, s.batch, s3p::kR, Fold3::kAlways);
   p.tl = tl;
   const int64_t per_seg = (int64_t)tl.units_seg / 4 * s.batch;  // blocks
   // a segment's element offsets stay below 2^32 and its plane count below 2^24 (what the critical-vertex queue stores)

@@ -8,7 +8,7 @@ import re
 import numpy as np
 import pytest
 
-from paper_2510_20271_amd import _lib
+from paper_2510_20271_amd import _lib, api
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FAKE = ctypes.c_void_p(0x1000)  # non-NULL, 256-aligned, never dereferenced: validation fails first
@@ -277,3 +277,23 @@ def test_product_package_never_imports_the_oracle():
             if f.endswith((".py", ".hip", ".h")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in text.replace("CPU oracle", ""), f
+
+
+def _align(n):
+    return -(-n // 256) * 256
+
+
+@pytest.mark.parametrize("item,batch,units,planes,columns", [
+    ((8, 16, 16), 1, 4, 12, 31),       # a segment of eight planes: room as for twelve
+    ((16, 48, 64), 1, 2 * 24, 12, 31),  # two of them
+    ((23, 17, 12), 271, 8, 23, 31),    # one narrow strip, few waves: a row group each
+    ((8, 8, 8), 1913, 4, 8, 31),       # many: two row groups of eight columns a wave
+    ((8, 16, 20), 2593, 4, 8, 40),     # (four row groups: two waves of two)
+])
+def test_saved_lists_of_small_volumes(item, batch, units, planes, columns):
+    """The state of a saving forward pass: a list for each wave of its plan, entries of 16 bytes for every eighth vertex of
+    the wave's planes x 4 rows x 62 columns (of twelve planes at least in small launches), or for every fourth of its own
+    columns where a wave of a narrow volume takes several row groups."""
+    cap = -(-(planes * columns) // 64) * 64
+    want = 256 + _align(4 * batch) + _align(4 * batch * units) + batch * units * cap * 16
+    assert api.ecc_soft_state_bytes(item, batch) == want
