@@ -55,16 +55,6 @@ struct HistOut {
   int shared;
 };
 
-// Rows that the blocks of one item share where many of them would meet in its histogram: a power of two, few enough that the
-// scan reads them in one trip; 1: its one histogram.  us with 1 / 2 / 4 / 8 rows: 4677 x 3307 uint8 page 29.4 / 20.2 / 17.1 / 17.0;
-// 256^3 uint16 noise, 4096 bins 40.1 / 37.8 / 38.3 / 42.4.  With fewer blocks the additions queue for less than the rows cost
-// (64 x 256^2, 1024 bins, 8 blocks an item: 14.0 without, 15.4 with; 8 x 2048^2, 72 blocks 36.0 / 37.3; 100 x 120 x 90, 144
-// blocks 16.3 / 17.2; but 1024^2, 160 blocks 12.6 / 11.7).
-static inline unsigned shared_rows(int64_t blocks, int bins) {
-  if (blocks < 160) return 1u;
-  return bins <= 512 ? 16u : bins <= 1024 ? 8u : bins <= 2048 ? 4u : 2u;
-}
-
 // fast sweeps (one wave per column strip / tube, bit-sliced stencil)
 struct HardHeader;
 // small float32 inputs without a range: the whole call in two launches (ecc_small.hip);
@@ -90,10 +80,6 @@ struct ListHead {
   unsigned min_key, max_key;  // float_key of the least / greatest value the block saw
   unsigned pad;
 };
-// bytes of the heads and lists of so many blocks, each with room for so many vertices
-static inline size_t list_room(int64_t blocks, int64_t vertices) {
-  return ((size_t)blocks * sizeof(ListHead) + 255) / 256 * 256 + (size_t)blocks * (size_t)((vertices + 63) / 64 * 64) * sizeof(float2);
-}
 struct ListArgs {
   float2* lists;       // [batch][nsub][cap]
   unsigned* counters;  // [batch][nsub]
@@ -112,7 +98,7 @@ bool sweep2d_supported(const Shape& s, int bins);
 void launch_sweep2d(const void* grid, const Shape& s, int dtype, bool levels, int bins,
                     const HardHeader* hdr, const float* table, const HistOut& hist,
                     hipStream_t st, const unsigned* run_if, const DirArgs* dir = nullptr, int conv = 0);
-unsigned sweep2d_hist_blocks(const Shape& s, int dtype, int bins, bool levels);  // blocks per item of that launch
+unsigned sweep2d_hist_blocks(const Shape& s, int dtype, int bins);  // blocks per item of that launch
 void launch_sweep2d_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st,
                          const DirArgs* dir = nullptr, int conv = 0);
 unsigned sweep2d_list_blocks(const Shape& s, int dtype, bool shared);  // blocks per item of that launch
@@ -125,16 +111,16 @@ void launch_sweep3d(const void* grid, const Shape& s, int dtype, bool levels, in
 unsigned sweep3d_hist_blocks(const Shape& s, int dtype, int bins);
 void launch_sweep3d_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st,
                          const DirArgs* dir = nullptr, int conv = 0);
-unsigned sweep3d_shared_list_blocks(const Shape& s, int dtype);                              // blocks per item
-void sweep3d_list_plan(const Shape& s, int dtype, unsigned& per_item, unsigned& vertices);  // a list per block
+unsigned sweep3d_list_blocks(const Shape& s, int dtype, bool shared);
+unsigned sweep3d_block_vertices(const Shape& s, int dtype);
 // the same for one- and two-byte element types, two vertices to a register (ecc_sweep3d_packed.h)
 void launch_sweep3dp(const void* grid, const Shape& s, int dtype, bool levels, int bins, const HardHeader* hdr,
                      const float* table, const HistOut& hist, hipStream_t st, const unsigned* run_if, int conv);
 unsigned sweep3dp_hist_blocks(const Shape& s, int bins);
 void launch_sweep3dp_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st, int conv);
 void launch_coeff3dp(const void* grid, const Shape& s, int dtype, int8_t* c_out, hipStream_t st);
-unsigned sweep3dp_shared_list_blocks(const Shape& s);
-void sweep3dp_list_plan(const Shape& s, unsigned& per_item, unsigned& vertices);
+unsigned sweep3dp_blocks(const Shape& s, bool shared);
+unsigned sweep3dp_block_vertices(const Shape& s);
 
 // ---- sweep-kernel timing (measurement aid) ----------------------------------
 hipError_t profile_begin(int max_launches);
