@@ -55,19 +55,24 @@ struct Kept {
   }
 };
 
-// The workspace of the forward pass for the backward pass, which runs on the same stream: not owned, so that a workspace that
-// was replaced by a larger one is not kept by the graphs of steps before.  Where it is gone, or the node is run on another
-// stream (whose calls it would not be safe with), room is allocated.
-struct Workspace : public torch::CustomClassHolder {
+// What the backward pass needs beside the saved tensors (in one entry of the context: each is a search by name).
+// The workspace is not owned, so that one that was replaced by a larger one is not kept by the graphs of steps before.  Where
+// it is gone, or the node is run on another stream than the forward pass (with whose calls it would not be safe), room is
+// allocated.
+struct Step : public torch::CustomClassHolder {
+  float alpha, lam;
+  bool tilted, u, tau;  // u, tau: derivatives that the forward pass has left
+  int ndim;
   c10::weak_intrusive_ptr<at::TensorImpl, at::UndefinedTensorImpl> kept;
-  at::TensorOptions options;
   int64_t bytes;
   void* on;
-  explicit Workspace(const Tensor& t) : kept(t.getIntrusivePtr()), options(t.options()), bytes(t.numel()), on(stream()) {}
-  Tensor get() const {
+  Step(double alpha, double lam, bool tilted, int ndim, bool u, bool tau, const Tensor& ws)
+      : alpha((float)alpha), lam((float)lam), tilted(tilted), u(u), tau(tau), ndim(ndim), kept(ws.getIntrusivePtr()),
+        bytes(ws.numel()), on(stream()) {}
+  Tensor workspace(const Tensor& like) const {
     if (on == stream())
       if (auto impl = kept.lock()) return Tensor(std::move(impl));
-    return at::empty({bytes}, options);
+    return at::empty({bytes}, like.options().dtype(at::kByte));
   }
 };
 
@@ -90,11 +95,8 @@ struct Angles : public torch::autograd::Function<Angles> {
     // (the state only for the input's gradient; the angles only where theirs is wanted: a frozen direction may be changed
     // in place before the backward pass)
     ctx->save_for_backward({grid.detach(), kept, tau.detach(), need_x ? state : Tensor(), need_u ? theta : Tensor()});
-    ctx->saved_data["alpha"] = alpha;
-    ctx->saved_data["lam"] = lam;
-    ctx->saved_data["tilted"] = tilted;
-    ctx->saved_data["workspace"] = at::IValue::make_capsule(c10::make_intrusive<Workspace>(workspace));
-    ctx->saved_data["need"] = (int64_t)ndim * 4 + (int64_t)need_u * 2 + (int64_t)need_tau;
+    ctx->saved_data["step"] =
+        at::IValue::make_capsule(c10::make_intrusive<Step>(alpha, lam, tilted, ndim, need_u, need_tau, workspace));
     return chi;
   }
 
@@ -102,9 +104,9 @@ struct Angles : public torch::autograd::Function<Angles> {
     const variable_list saved = ctx->get_saved_variables();
     const Tensor &grid = saved[0], &kept = saved[1], &tau = saved[2], &state = saved[3], &theta = saved[4];
     const Tensor g = grads[0].contiguous().to(at::kFloat);
-    const int64_t made = ctx->saved_data["need"].toInt();
-    const bool made_u = (made & 2) != 0, made_tau = (made & 1) != 0;
-    const int ndim = (int)(made >> 2);
+    const auto step = c10::static_intrusive_pointer_cast<Step>(ctx->saved_data["step"].toCapsule());
+    const bool made_u = step->u, made_tau = step->tau;
+    const int ndim = step->ndim;
     check_device(grid, at::kFloat, -1, grid.device());
     TORCH_CHECK_VALUE(grid.is_cuda() && grid.dim() == ndim + 1, "grid must be a device tensor [batch, *item_shape]");
     const int64_t batch = grid.size(0), T = tau.numel(), BT = batch * T;
@@ -117,14 +119,13 @@ struct Angles : public torch::autograd::Function<Angles> {
                need_tau = ctx->needs_input_grad(2) && made_tau;
     const Kept k(kept, BT, made_tau, made_u);
     Tensor grad_x, grad_theta, grad_tau;
-    const Tensor ws = c10::static_intrusive_pointer_cast<Workspace>(ctx->saved_data["workspace"].toCapsule())->get();
+    const Tensor ws = step->workspace(grid);
     if (need_x) {
       TORCH_CHECK(g.has_storage(), "the gradient of the input needs an upstream gradient with memory of its own");
       check_device(state, at::kByte, -1, grid.device());  // (its size is the library's to check)
       grad_x = at::empty(grid.sizes(), grid.options());
-      check(ecc_soft_bwd_saved(f32(grid), ndim, dims, batch, k.u, (float)ctx->saved_data["alpha"].toDouble(), f32(tau),
-                               (int)T, (float)ctx->saved_data["lam"].toDouble(), ctx->saved_data["tilted"].toBool() ? 1 : 0,
-                               f32(g), f32(grad_x), state.data_ptr(), (size_t)state.numel(), ws.data_ptr(),
+      check(ecc_soft_bwd_saved(f32(grid), ndim, dims, batch, k.u, step->alpha, f32(tau), (int)T, step->lam,
+                               step->tilted ? 1 : 0, f32(g), f32(grad_x), state.data_ptr(), (size_t)state.numel(), ws.data_ptr(),
                                (size_t)ws.numel(), stream()));
     }
     if (need_u || need_tau) {
