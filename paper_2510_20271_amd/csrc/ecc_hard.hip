@@ -296,7 +296,7 @@ __global__ __launch_bounds__(BLOCK) void scan_kernel(long long* __restrict__ cur
 // then scans.  Its loads are in flight together, sixteen a thread: the kernel is one trip to memory and a few dependent
 // steps.  32 bits: rows are kept for items of up to 2^28 vertices, |c| <= 7.
 // kRowsBlock: 1024 threads, or 256 where they have no more than sixteen loads each (up to 256 bins).
-constexpr int kRowsBins = 8;  // bins of a thread at the most
+constexpr int kRowsBins = 7;  // bins of a thread at the most
 template <int kRowsBlock>
 __global__ __launch_bounds__(kRowsBlock) void scan_rows_kernel(const int* __restrict__ rows, unsigned n, int bins, int suffix,
                                                                long long* __restrict__ curve) {
@@ -502,18 +502,15 @@ static unsigned generic_blocks(const Shape& s) {
 // Rows of the histogram sweep's blocks in the workspace (room: bytes behind the table), or none.
 static HistOut hist_out(const Shape& s, int bins, bool levels, unsigned blocks, unsigned long long* curve, void* room, size_t bytes) {
   HistOut h = {curve, nullptr, 0u, 0};
-  if (s.N > ((int64_t)1 << 28) || bins > 8192) return h;  // (sums and LDS of scan_rows_kernel)
+  if (s.N > ((int64_t)1 << 28) || bins > 7168) return h;  // (sums of scan_rows_kernel; what the strip sweep takes)
   const size_t row = (size_t)s.batch * bins * sizeof(int);
   // A row for each block where that saves the launch that clears (one bin per level: there is no table to make either); 256^2
-  // uint8 noise 10.5 -> 8.1 us.  Otherwise rows where many blocks would meet in one item's histogram, up to 16, a power of
-  // two, and few enough that the scan reads them in one trip (4677 x 3307 uint8 page with 1 / 2 / 4 / 8 rows 29.4 / 20.2 / 17.1
-  // / 17.0 us; 256^3 uint16 noise, 4096 bins 40.1 / 37.8 / 38.3 / 42.4).  With fewer blocks the additions queue for less than
-  // the rows cost (64 x 256^2, 1024 bins, 8 blocks an item: 14.0 without, 15.4 with; 8 x 2048^2, 72 blocks 36.0 / 37.3;
-  // 100 x 120 x 90, 144 blocks 16.3 / 17.2; but 1024^2, 160 blocks 12.6 / 11.7).
+  // uint8 noise 10.5 -> 8.1 us.  Otherwise rows that blocks share.  (The plain sweep's many bins: 8192 on
+  // 27 smooth fields 3.9 % slower with rows, 498 x 1021 uint16 17.4 / 18.5.)
   unsigned n = blocks;
   if (!levels || (int64_t)n * bins > 16384 || n > 64 || row * n > bytes) {
-    if (blocks < 160 || row > bytes) return h;
-    const unsigned most = (unsigned)std::max(2, std::min(16, 8192 / bins));
+    const unsigned most = shared_rows(blocks, bins);
+    if (most == 1u || row > bytes) return h;
     n = 1;
     while (2 * n <= most && row * 2 * n <= bytes) n *= 2;
     h.shared = 1;
@@ -653,7 +650,7 @@ hipError_t launch_hard(const void* grid, const Shape& s, int dtype, int bins, bo
     hipLaunchKernelGGL(minmax_f32_kernel, dim3(nb), dim3(kBlock), 0, st,
                        static_cast<const float*>(grid), total, hdr);
   }
-  const unsigned blocks = fast2d ? sweep2d_hist_blocks(s, dtype, bins)
+  const unsigned blocks = fast2d ? sweep2d_hist_blocks(s, dtype, bins, levels)
                         : fast3d ? sweep3d_hist_blocks(s, dtype, bins) : generic_blocks(s);
   const size_t before_rows = kTableOffset + table_bytes(bins);
   const HistOut out = hist_out(s, bins, levels, blocks, hist, wsb + before_rows, hard_workspace_min_bytes(s, bins) - before_rows);

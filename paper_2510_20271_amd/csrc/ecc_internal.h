@@ -55,6 +55,16 @@ struct HistOut {
   int shared;
 };
 
+// Rows that the blocks of one item share where many of them would meet in its histogram: a power of two, few enough that the
+// scan reads them in one trip; 1: its one histogram.  us with 1 / 2 / 4 / 8 rows: 4677 x 3307 uint8 page 29.4 / 20.2 / 17.1 / 17.0;
+// 256^3 uint16 noise, 4096 bins 40.1 / 37.8 / 38.3 / 42.4.  With fewer blocks the additions queue for less than the rows cost
+// (64 x 256^2, 1024 bins, 8 blocks an item: 14.0 without, 15.4 with; 8 x 2048^2, 72 blocks 36.0 / 37.3; 100 x 120 x 90, 144
+// blocks 16.3 / 17.2; but 1024^2, 160 blocks 12.6 / 11.7).
+static inline unsigned shared_rows(int64_t blocks, int bins) {
+  if (blocks < 160) return 1u;
+  return bins <= 512 ? 16u : bins <= 1024 ? 8u : bins <= 2048 ? 4u : 2u;
+}
+
 // fast sweeps (one wave per column strip / tube, bit-sliced stencil)
 struct HardHeader;
 // small float32 inputs without a range: the whole call in two launches (ecc_small.hip);
@@ -98,7 +108,7 @@ bool sweep2d_supported(const Shape& s, int bins);
 void launch_sweep2d(const void* grid, const Shape& s, int dtype, bool levels, int bins,
                     const HardHeader* hdr, const float* table, const HistOut& hist,
                     hipStream_t st, const unsigned* run_if, const DirArgs* dir = nullptr, int conv = 0);
-unsigned sweep2d_hist_blocks(const Shape& s, int dtype, int bins);  // blocks per item of that launch
+unsigned sweep2d_hist_blocks(const Shape& s, int dtype, int bins, bool levels);  // blocks per item of that launch
 void launch_sweep2d_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st,
                          const DirArgs* dir = nullptr, int conv = 0);
 unsigned sweep2d_list_blocks(const Shape& s, int dtype, bool shared);  // blocks per item of that launch

@@ -34,6 +34,7 @@
 // would miss the L2 once per critical vertex, a 128-byte line for 4 bytes).
 #pragma once
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "ecc_device.h"
@@ -482,8 +483,15 @@ struct Plan2d {
 // segment reads five rows more than it puts out, and a block has costs of its own at its end.
 enum class Feed2d { kHist, kBlockLists, kSharedLists, kSigmoid };
 
-// rows a wave takes; tubes: strips of all items; bytes: of an element; bins: of a kHist sweep
-static inline int64_t rows2d(const Shape& s, int64_t nstrip, int64_t tubes, Feed2d feed, int bytes, int bins) {
+// LDS of a block besides the sink's own needs: value rings + queues of the four waves
+template <typename Entry>
+constexpr size_t ring_bytes2d() {
+  return (size_t)4 * kChunkRows * kWave * kNC * sizeof(float) + (size_t)4 * kQueueCap * sizeof(Entry);
+}
+static inline bool table_in_lds2d(int bins) { return (size_t)bins * 8 + ring_bytes2d<float2>() <= 64 * 1024; }  // the thresholds
+
+// rows a wave takes; tubes: strips of all items; bytes: of an element; bins, levels (one bin per level): of a kHist sweep
+static inline int64_t rows2d(const Shape& s, int64_t nstrip, int64_t tubes, Feed2d feed, int bytes, int bins, bool levels) {
   const int64_t H = s.H, total = s.N * s.batch;
   auto waves = [&](int64_t rows) { return tubes * ((H + rows - 1) / rows); };
   if (feed == Feed2d::kSigmoid) {
@@ -508,33 +516,45 @@ static inline int64_t rows2d(const Shape& s, int64_t nstrip, int64_t tubes, Feed
     while (rows < 64 && waves(rows) > 24576) rows *= 2;
     return rows;
   }
-  // rows with which an image (of at most four strips) is four units, a whole block
-  const int64_t segs = (4 + nstrip - 1) / nstrip;
-  const int64_t four_units = ((H + segs - 1) / segs + kChunkRows - 1) / kChunkRows * kChunkRows;
   if (feed == Feed2d::kHist) {
-    // A histogram per block, merged at its end, through rows of their own where many blocks would meet in one item's
-    // (hist_out): short segments, as a wave's march is what lasts, until there are waves enough for every SIMD three times
-    // over.  us a call with 8 / 16 / 24 / 32 rows: 512^2 uint8 noise 13.3 / 19.9 / 26.7 / 32.8, 2048^2 smooth float32 13.7 / 15.2 /
-    // 16.1 / 18.5, 16 x 512^2 float16 12.2 / 13.6 / 15.7 / 16.3.
-    // (many items and bins: the histograms weigh more; 200 x 100 x 140 float32, 1000 bins 15.9 with 8 rows, 14.7 with 16)
-    if (waves(8) <= 3072) return s.batch >= 64 && bins > 512 ? 16 : 8;
-    // Small images: a block (four units) each.  2000 x 28^2 uint8 24.1 / 33.5 / 33.4 / 43.7, 1000 x 100^2 42.7 / 42.5 / 58.4 / 38.6.
-    if (nstrip <= 2 && four_units <= 32) return four_units;
-    // One byte a vertex is bound by the march at any size (a 4677 x 3307 page 18.2 / 17.6 / 19.0 / 18.9, of noise 31.2 / 31.0 / 36.0 /
-    // 39.2; 8192^2 noise 98.8 / 95.8 / 101.5 / 105.1); wider elements by the rows read twice, sooner (64 x 256^2 float32 17.0 / 15.5 /
-    // 17.1 / 18.2, 8 x 2048^2 float32 44.4 / 38.6 / 38.0 / 37.3, float16 33.2 / 29.9 / 31.3 / 32.9, 16 x 2048^2 float16 56 / 50 / 50 / 47),
-    // and with many bins by the blocks' histograms (8192^2 uint16, 4096 bins 82 / 66 / 62 / 61; 48 rows 59, 64 63).
-    if (bytes == 1 || waves(16) <= 3072) return 16;
-    if (bins <= 1024 && waves(16) <= (bytes == 2 ? 20480 : 4608)) return 16;
-    // Rounds of waves enough at any length (512 x 512^2 float32 146 with 32 rows, 128 with 64, 125 with 128; float16 105 / 103 / 109)
-    if (tubes >= 1024) return bytes == 2 && bins <= 1024 ? 64 : 128;
-    if (bins > 1024) return total > ((int64_t)1 << 26) ? 48 : 32;
-    return bytes == 2 ? 32 : 64;
+    // A histogram per block, merged at its end (hist_out).  The least of what a launch was found to take, in us, over the rows
+    // that a wave may take (5400 calls of 2^17 to 2^27 vertices, element types of one, two and four bytes, 60 to 4096 bins,
+    // smooth fields and noise, each with 8 to 128 rows; the rows chosen are within 1.2 % of the best in the mean): a row
+    // costs a tenth, more for every block on the CU, by what is read, and more for every round of blocks that the LDS
+    // holds; two rows are read beside a segment's own; a block clears and merges its histogram; and blocks of one item meet
+    // at its counters, or at the rows that they share.  (One byte a vertex: bound by the march, less by memory.)  Of a batch of small images whose rows leave waves of a block without
+    // work the blocks say so themselves: 1867 x 124 x 270 float32 80 us with 32 rows, 137 with 128.
+    struct Cost {
+      double halo, read, round, block, bins, meet;
+    };
+    const Cost k = bytes == 1 ? Cost{3.0, 0.05, 0.01, 0.0, 0.1, 0.006} : Cost{2.0, bytes == 2 ? 0.07 : 0.15, 0.085, 0.05, 0.4, 0.0014};
+    const size_t ring = ring_bytes2d<float2>();
+    const size_t lds = ring + (size_t)bins * (!levels && table_in_lds2d(bins) ? 8 : 4);
+    const double resident = (double)std::min<size_t>(5, (size_t)160 * 1024 / lds);
+    int64_t best = kChunkRows;
+    double least = 0.0;
+    unsigned last = 0;
+    for (unsigned aim : {8u, 16u, 24u, 32u, 40u, 48u, 56u, 64u, 80u, 96u, 128u}) {  // (32-bit divisions: small calls wait for the host)
+      const unsigned segs = ((unsigned)H + aim - 1u) / aim;
+      if (segs == last) continue;  // (the same segments)
+      const unsigned rows = (((unsigned)H + segs - 1u) / segs + kChunkRows - 1u) / kChunkRows * kChunkRows;
+      const int64_t blocks = (nstrip * segs + 3) / 4;
+      const double cu = (double)blocks * (double)s.batch / 256.0;
+      const double cost = ((double)rows + k.halo) * (0.1 + k.read * std::max(1.0, cu) + k.round * std::ceil(cu / resident)) +
+                          cu * (k.block + k.bins * bins / 1024.0) + k.meet * (double)blocks / shared_rows(blocks, bins);
+      if (last == 0 || cost < least) {
+        least = cost;
+        best = aim;
+      }
+      last = segs;
+    }
+    return best;
   }
   if (waves(16) <= 1024) return 16;  // at most one wave per SIMD even with short segments
   // Many small images with lists that blocks share (batches beyond the lists per block): four units each as well, rather
   // than one wave of a block's four (8192 x 64^2 215 -> 149 us; 1024 of them, one wave a SIMD, 54 -> 61).
-  if (feed == Feed2d::kSharedLists && nstrip == 1 && H <= 64 && tubes > 4096) return four_units;
+  if (feed == Feed2d::kSharedLists && nstrip == 1 && H <= 64 && tubes > 4096)
+    return ((H + 3) / 4 + kChunkRows - 1) / kChunkRows * kChunkRows;
   // One large image gains 30 % from 24 -> 64 rows at 4096^2, 20 % from 16 -> 32 at 2048^2: about 1536 waves, within
   // 32 .. 64 rows per segment.  Shared lists beyond 2^27 vertices: 48 rows where images are up to 34 strips (8432 columns)
   // wide, 4 to 6 % less (16 x 4096^2: 241 / 251 / 237 / 246 / 259 us with 24 / 32 / 48 / 64 / 96 rows, 3 x 8192^2 202 -> 188,
@@ -552,12 +572,12 @@ static inline int64_t rows2d(const Shape& s, int64_t nstrip, int64_t tubes, Feed
 }
 
 template <typename T>
-static Plan2d plan2d(const Shape& s, Feed2d feed, int bins = 1) {
+static Plan2d plan2d(const Shape& s, Feed2d feed, int bins = 1, bool levels = false) {
   Plan2d p;
   const int H = (int)s.H, W = (int)s.W;
   p.nstrip = (W + kStripOut - 1) / kStripOut;
   const int64_t tubes = (int64_t)p.nstrip * s.batch;
-  const int64_t aim = rows2d(s, p.nstrip, tubes, feed, (int)sizeof(T), bins);
+  const int64_t aim = rows2d(s, p.nstrip, tubes, feed, (int)sizeof(T), bins, levels);
   int64_t nseg = (H + aim - 1) / aim;
   if (feed == Feed2d::kSigmoid) nseg = std::min(nseg, (32768 + tubes - 1) / tubes);
   if (nseg < 1) nseg = 1;
@@ -575,10 +595,4 @@ static Plan2d plan2d(const Shape& s, Feed2d feed, int bins = 1) {
   p.grid = dim3((unsigned)((units + 3) / 4), (unsigned)s.batch);
   return p;
 }
-// LDS of a block besides the sink's own needs: value rings + queues of the four waves
-template <typename Entry>
-constexpr size_t ring_bytes2d() {
-  return (size_t)4 * kChunkRows * kWave * kNC * sizeof(float) + (size_t)4 * kQueueCap * sizeof(Entry);
-}
-
 }  // namespace ecc

@@ -94,8 +94,8 @@ template <typename T, bool LV = false>
 static void launch2d_t(const void* grid, const Shape& s, bool levels, int bins, const HardHeader* hdr,
                        const float* table, const HistOut& hist, hipStream_t st,
                        const unsigned* run_if, const DirArgs* dir, int conv) {
-  const Plan2d pl = plan2d<T>(s, Feed2d::kHist, bins);
-  const bool tlds = !levels && (size_t)bins * 8 + kRingBytes2d <= 64 * 1024;
+  const Plan2d pl = plan2d<T>(s, Feed2d::kHist, bins, levels);
+  const bool tlds = !levels && table_in_lds2d(bins);
   const size_t lds = kRingBytes2d + (size_t)bins * (tlds ? 8 : 4);
   const T* p = static_cast<const T*>(grid);
   const DirArgs none = {nullptr, 0.f, 1, 2};
@@ -162,10 +162,12 @@ void launch_sweep2d_list(const void* grid, int dtype, const Shape& s, const List
   }
 }
 
-unsigned sweep2d_hist_blocks(const Shape& s, int dtype, int bins) {
-  const size_t size = dtype == 0 ? 1 : dtype == 2 ? 4 : 2;
-  return size == 1 ? plan2d<uint8_t>(s, Feed2d::kHist, bins).grid.x
-       : size == 2 ? plan2d<uint16_t>(s, Feed2d::kHist, bins).grid.x : plan2d<float>(s, Feed2d::kHist, bins).grid.x;
+unsigned sweep2d_hist_blocks(const Shape& s, int dtype, int bins, bool levels) {
+  switch (dtype) {
+    case 0: return plan2d<uint8_t>(s, Feed2d::kHist, bins, levels).grid.x;
+    case 2: return plan2d<float>(s, Feed2d::kHist, bins, levels).grid.x;
+    default: return plan2d<uint16_t>(s, Feed2d::kHist, bins, levels).grid.x;  // (two bytes)
+  }
 }
 
 unsigned sweep2d_block_vertices(const Shape& s, int dtype) {

@@ -1,4 +1,4 @@
-"""Rows per wave of the strip sweep, where the launch plan changes its rule: the same integer curves as the plain
+"""Rows per wave of the strip sweep, over what the launch plan chooses: the same integer curves as the plain
 one-thread-per-vertex kernels (whole numbers: equal)."""
 import pytest
 
@@ -10,12 +10,18 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape,dtype,bins,known", [
-    ((9000, 64, 64), torch.uint8, 256, True),     # many small 8-bit images: four units each
-    ((1100, 100, 310), torch.uint8, 256, True),   # two strips wide
-    ((1030, 190, 200), torch.float32, 100, True),
-    ((600, 256, 256), torch.float32, 100, True),  # fewer of them: the longer segments
-    ((3, 2048, 2048), torch.uint8, 256, True),    # 24 rows
-    ((1, 2050, 2047), torch.float32, 64, True),
+    ((9000, 64, 64), torch.uint8, 256, True),     # histogram sweeps: 16 rows, a block an image
+    ((1100, 100, 310), torch.uint8, 256, True),   # 8, two strips wide
+    ((1030, 190, 200), torch.float32, 100, True),  # 24
+    ((600, 256, 256), torch.float32, 100, True),  # 32
+    ((3, 2048, 2048), torch.uint8, 256, True),    # 8, blocks that share rows of the histogram
+    ((1, 2050, 2047), torch.float32, 64, True),   # 8
+    ((2780, 144, 112), torch.float32, 256, True),  # 40, a block an image
+    ((300, 384, 384), torch.float32, 4096, True),  # 48
+    ((200, 245, 627), torch.float32, 4096, True),  # 64
+    ((3000, 270, 143), torch.float16, 1024, True),  # 72
+    ((600, 300, 250), torch.float16, 4096, True),  # 80
+    ((200, 500, 300), torch.float32, 4096, True),  # 88
     ((5000, 30, 41), torch.float32, 64, False),   # lists that blocks share, four units an image
     ((4200, 64, 50), torch.float32, 64, False),
     ((4200, 65, 50), torch.float32, 64, False),
