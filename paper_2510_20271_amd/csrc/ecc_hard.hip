@@ -480,11 +480,11 @@ size_t hard_workspace_min_bytes(const Shape& s, int bins) {
   const size_t small = small_supported(s, bins) ? small_workspace_bytes(s) : 0;
   return kTableOffset + table_bytes(bins) + std::max(lists, small);
 }
-// with room for a list per block of the sweep (mid-sized float grids; the launch plans of the
-// four-byte and the two-byte types differ)
+// with room for a list per block of the sweep (mid-sized float grids; in images the launch plans of the
+// four-byte and the two-byte types differ, in volumes those of the latter keep to the former's room)
 size_t hard_workspace_bytes(const Shape& s, int bins) {
   size_t mid = 0;
-  for (int dtype : {2, 3})
+  for (int dtype = 2; dtype <= (s.ndim == 2 ? 3 : 2); ++dtype)
     if (mid_supported(s, bins, dtype)) mid = std::max(mid, kTableOffset + table_bytes(bins) + mid_workspace_bytes(s, dtype));
   return std::max(hard_workspace_min_bytes(s, bins), mid);
 }
@@ -613,7 +613,7 @@ hipError_t launch_hard(const void* grid, const Shape& s, int dtype, int bins, bo
     la.lists = reinterpret_cast<float2*>(wsb + kTableOffset + table_bytes(bins) + counter_bytes(s));
     // no more sub-lists than blocks that append to them (a block uses one sub-list);
     // the room of the unused ones goes to the others
-    const unsigned blocks = fast2d ? sweep2d_list_blocks(s, dtype, true) : sweep3d_list_blocks(s, dtype, true);
+    const unsigned blocks = fast2d ? sweep2d_list_blocks(s, dtype, true) : sweep3d_shared_list_blocks(s, dtype);
     la.nsub = list_nsub(s);
     la.cap = list_cap(s);
     while (la.nsub > 1 && la.nsub > blocks) {

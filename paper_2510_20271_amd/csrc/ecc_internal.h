@@ -90,6 +90,10 @@ struct ListHead {
   unsigned min_key, max_key;  // float_key of the least / greatest value the block saw
   unsigned pad;
 };
+// bytes of the heads and lists of so many blocks, each with room for so many vertices
+static inline size_t list_room(int64_t blocks, int64_t vertices) {
+  return ((size_t)blocks * sizeof(ListHead) + 255) / 256 * 256 + (size_t)blocks * (size_t)((vertices + 63) / 64 * 64) * sizeof(float2);
+}
 struct ListArgs {
   float2* lists;       // [batch][nsub][cap]
   unsigned* counters;  // [batch][nsub]
@@ -121,16 +125,16 @@ void launch_sweep3d(const void* grid, const Shape& s, int dtype, bool levels, in
 unsigned sweep3d_hist_blocks(const Shape& s, int dtype, int bins);
 void launch_sweep3d_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st,
                          const DirArgs* dir = nullptr, int conv = 0);
-unsigned sweep3d_list_blocks(const Shape& s, int dtype, bool shared);
-unsigned sweep3d_block_vertices(const Shape& s, int dtype);
+unsigned sweep3d_shared_list_blocks(const Shape& s, int dtype);                              // blocks per item
+void sweep3d_list_plan(const Shape& s, int dtype, unsigned& per_item, unsigned& vertices);  // a list per block
 // the same for one- and two-byte element types, two vertices to a register (ecc_sweep3d_packed.h)
 void launch_sweep3dp(const void* grid, const Shape& s, int dtype, bool levels, int bins, const HardHeader* hdr,
                      const float* table, const HistOut& hist, hipStream_t st, const unsigned* run_if, int conv);
 unsigned sweep3dp_hist_blocks(const Shape& s, int bins);
 void launch_sweep3dp_list(const void* grid, int dtype, const Shape& s, const ListArgs& la, hipStream_t st, int conv);
 void launch_coeff3dp(const void* grid, const Shape& s, int dtype, int8_t* c_out, hipStream_t st);
-unsigned sweep3dp_blocks(const Shape& s, bool shared);
-unsigned sweep3dp_block_vertices(const Shape& s);
+unsigned sweep3dp_shared_list_blocks(const Shape& s);
+void sweep3dp_list_plan(const Shape& s, unsigned& per_item, unsigned& vertices);
 
 // ---- sweep-kernel timing (measurement aid) ----------------------------------
 hipError_t profile_begin(int max_launches);

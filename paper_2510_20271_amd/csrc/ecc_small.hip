@@ -368,8 +368,7 @@ static bool mid_plan(const Shape& s, int dtype, unsigned& per_item, unsigned& ca
     per_item = sweep2d_list_blocks(s, dtype, false);
     cap = sweep2d_block_vertices(s, dtype);
   } else if (sweep3d_supported(s, 1)) {
-    per_item = sweep3d_list_blocks(s, dtype, false);
-    cap = sweep3d_block_vertices(s, dtype);
+    sweep3d_list_plan(s, dtype, per_item, cap);
   } else {
     return false;
   }
@@ -384,10 +383,10 @@ bool mid_supported(const Shape& s, int bins, int dtype) {
     return false;
   unsigned per_item, cap;
   if (!mid_plan(s, dtype, per_item, cap)) return false;
-  // (volumes of two-byte elements have a plan of their own; the workspace's size does not depend on the type, and must not
-  // grow for float32 calls)
+  // (volumes of two-byte elements have a plan of their own; the workspace's size does not depend on the type, and is that of
+  // float32 calls)
   if (dtype != 2 && s.ndim == 3 &&
-      (!mid_supported(s, bins, 2) || mid_workspace_bytes(s, dtype) > mid_workspace_bytes(s, 2)))
+      (!mid_supported(s, bins, 2) || list_room((int64_t)per_item * s.batch, cap) > mid_workspace_bytes(s, 2)))
     return false;
   return (int64_t)per_item * s.batch <= kMidBlocks && per_item <= 64u * kFinishBlock;
 }
@@ -395,8 +394,7 @@ bool mid_supported(const Shape& s, int bins, int dtype) {
 size_t mid_workspace_bytes(const Shape& s, int dtype) {
   unsigned per_item, cap;
   if (!mid_plan(s, dtype, per_item, cap)) return 0;
-  const size_t blocks = (size_t)per_item * s.batch;
-  return (blocks * sizeof(ListHead) + 255) / 256 * 256 + blocks * cap * sizeof(float2);
+  return list_room((int64_t)per_item * s.batch, cap);
 }
 
 hipError_t launch_hard_mid(const void* grid, const Shape& s, int dtype, int bins, int64_t* curve, HardHeader* hdr,

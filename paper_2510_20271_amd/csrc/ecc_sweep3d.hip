@@ -138,17 +138,22 @@ void launch_sweep3d_list(const void* grid, int dtype, const Shape& s, const List
   else launch3d_list(static_cast<const float*>(grid), s, la, st, dir, conv);
 }
 
-unsigned sweep3d_list_blocks(const Shape& s, int dtype, bool shared) {
-  return dtype == 2 ? plan3d<float>(s).grid.x : sweep3dp_blocks(s, shared);
+unsigned sweep3d_shared_list_blocks(const Shape& s, int dtype) {
+  return dtype == 2 ? plan3d<float>(s).grid.x : sweep3dp_shared_list_blocks(s);
 }
 unsigned sweep3d_hist_blocks(const Shape& s, int dtype, int bins) {
   return dtype == 2 ? plan3d<float>(s).grid.x : sweep3dp_hist_blocks(s, bins);
 }
-unsigned sweep3d_block_vertices(const Shape& s, int dtype) {
-  if (dtype != 2) return sweep3dp_block_vertices(s);
+// blocks per item, and the most vertices of a block, of a launch with a list for each block
+void sweep3d_list_plan(const Shape& s, int dtype, unsigned& per_item, unsigned& vertices) {
+  if (dtype != 2) {
+    sweep3dp_list_plan(s, per_item, vertices);
+    return;
+  }
   // four wave units of at most 62 columns x 4 rows (a folded unit: several row groups of fewer columns) x the segment's planes
-  const int64_t planes = std::min<int64_t>(s.D, plan3d<float>(s).planes_per_seg);
-  return 4u * (unsigned)s3::kOut * (unsigned)kRows3d * (unsigned)planes;
+  const Plan3d pl = plan3d<float>(s);
+  per_item = pl.grid.x;
+  vertices = 4u * (unsigned)s3::kOut * (unsigned)kRows3d * (unsigned)std::min<int64_t>(s.D, pl.planes_per_seg);
 }
 
 bool sweep3d_supported(const Shape& s, int bins) {

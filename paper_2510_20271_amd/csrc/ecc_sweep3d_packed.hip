@@ -89,7 +89,11 @@ struct Plan3dp {
   int nseg, planes_per_seg;
   dim3 grid;
 };
-enum class Feed3dp { kHist, kSharedLists, kAlone };  // kAlone: nothing that blocks share (a list per block, the map)
+enum class Feed3dp { kHist, kSharedLists, kBlockLists, kMap };
+// entries of a block's list: its four wave units of 62 columns x 4 rows (a folded unit: several row groups of fewer columns)
+static int64_t block_vertices3dp(const Shape& s, int planes) {
+  return (int64_t)4 * s3::kOut * s3p::kR * std::min<int64_t>(s.D, planes);
+}
 // bins: of a histogram sweep
 static Plan3dp plan3dp(const Shape& s, Feed3dp feed, int bins = 0) {
   Plan3dp p;
@@ -100,39 +104,51 @@ static Plan3dp plan3dp(const Shape& s, Feed3dp feed, int bins = 0) {
   // a segment's element offsets stay below 2^32 and its plane count below 2^24 (what the critical-vertex queue stores)
   int64_t fit = (((int64_t)1 << 32) - 1) / ((int64_t)H * W);
   fit = std::min<int64_t>(fit, (1 << 24) - 1) / s3p::kChunk * s3p::kChunk;  // (a supported plane has fewer than 2^27 elements)
-  // Planes per segment, whole chunks: the least of what a launch was found to take (us).  A wave's plane costs 0.35 us, and
-  // 0.21 for every wave on its SIMD (a block is a wave on each SIMD of a CU; between the mean and the fullest CU); a segment has about five planes' worth of
-  // work besides its own; a block clears and merges its histogram (1.4 us a million counters), and the blocks of an item
-  // meet at its counters (10 ns a block, of those that end together), those of a list launch at the range and the lists' fill
-  // counts.  Against measurements with 8 / 16 / 24 / 32 / 40 / 48 planes (us a call): 256^3 uint16 noise, 4096 bins 65 / 47 /
-  // 42 / 44 / 41 / 46; 193 x 229 x 193 int16, 1024 bins 36 / 29 / 30 / 32 / 32 / 36; 128^3 uint8 noise 16 / 20 / 23 / 27 / 31 /
-  // 34; 8 x 128^3 int16 35 / 31 / 37 / 37 / 39 / 43; 4 x 100^3 uint16 noise, 4096 bins 35 / 27 / 28 / 26 / 27 / 30; 512^3
-  // uint16 162 / 141 / 130 / 131 / 130 / 131.
+  // Planes per segment, whole chunks (then segments of equal length): the least of what a launch was found to take (us).  A
+  // wave's plane costs 0.35 us, and 0.21 for every wave on its SIMD (a block is a wave on each SIMD of a CU; between the mean
+  // and the fullest CU); a segment has about five planes' worth of work besides its own; a block clears and merges its
+  // histogram (1.4 us a million counters), and the blocks of an item meet at its counters, or at the rows that they share
+  // (10 ns a block, of those that end together).  Over 500 histogram calls (2^17 to 2^26 vertices, 64 to 4096 bins, smooth
+  // fields and noise) within 1.5 % of the best of 8 / 16 / 24 / 32 / 40 / 48 planes in the mean: 256^3 uint16 noise, 4096 bins
+  // 58 / 44 / 37 / 41 / 38 / -; 193 x 229 x 193 int16, 1024 bins 23.8 / 24.6 / 26.1 / 28.5 / 30.4 / -.
+  // Lists that blocks share: 32 planes.  A list that is full still costs every batch its reservation, and the fewer blocks
+  // there are the fewer of them wait for one another: white noise of 220 x 376 x 465 bfloat16 5555 us with 8 planes, 4446 with
+  // 24, 4201 with 32, smooth fields 93 / 77 / 75.
+  // A list for each block: no more room than the float32 plan's lists have, which every type's workspace holds (shorter
+  // segments of a ragged volume need more, and the call would take the shared lists: 7 x 73 x 94 x 93 bfloat16 40 us, 21 with
+  // 16 planes).
+  const size_t room = feed == Feed3dp::kBlockLists ? mid_workspace_bytes(s, 2) : 0;
   double least = 0.0;
-  int64_t planes = s3p::kChunk;
-  for (int64_t pl = s3p::kChunk; pl <= 48 && pl <= fit && pl < D + s3p::kChunk; pl += s3p::kChunk) {
-    const double blocks = (double)((D + pl - 1) / pl * per_seg);
-    const double meet = feed == Feed3dp::kHist ? 0.01 * std::min(1024.0, blocks / (double)s.batch)
-                      : feed == Feed3dp::kSharedLists ? 0.03 * std::min(1024.0, blocks) : 0.0;
-    const double cu = std::max(1.0, blocks / 256.0);
-    const double cost = (double)(pl + 5) * (0.35 + 0.105 * (cu + std::ceil(cu))) + meet + 1.4e-6 * blocks * bins;
-    if (pl == s3p::kChunk || cost < least) {
+  int64_t planes = 0;
+  int last = 0;
+  for (int aim = s3p::kChunk; feed != Feed3dp::kSharedLists && aim <= 48 && aim <= fit && last != 1; aim += s3p::kChunk) {
+    const int segs = (D + aim - 1) / aim;
+    if (segs == last) continue;  // (the same segments)
+    last = segs;
+    const int pl = (D + segs - 1) / segs;
+    const int64_t blocks = segs * per_seg;
+    if (room && list_room(blocks, block_vertices3dp(s, pl)) > room) continue;
+    const int64_t of_item = (int64_t)segs * tl.units_seg / 4;
+    const double meet = feed == Feed3dp::kHist ? 0.01 * (double)std::min<int64_t>(1024, of_item) / shared_rows(of_item, bins) : 0.0;
+    const double cu = std::max(1.0, (double)blocks / 256.0);
+    const double cost = (double)(pl + 5) * (0.35 + 0.105 * (cu + std::ceil(cu))) + meet + 1.4e-6 * (double)blocks * bins;
+    if (planes == 0 || cost < least) {
       least = cost;
-      planes = pl;
+      planes = aim;
     }
   }
+  if (planes == 0) planes = std::min<int64_t>(32, fit);  // (shared lists, or no list for each block: mid_supported)
   p.nseg = (int)((D + planes - 1) / planes);
-  p.planes_per_seg = (D + p.nseg - 1) / p.nseg;  // segments of equal length
+  p.planes_per_seg = (D + p.nseg - 1) / p.nseg;
   p.grid = dim3((unsigned)(p.nseg * (int64_t)tl.units_seg / 4), (unsigned)s.batch);
   return p;
 }
-unsigned sweep3dp_blocks(const Shape& s, bool shared) {
-  return plan3dp(s, shared ? Feed3dp::kSharedLists : Feed3dp::kAlone).grid.x;
-}
+unsigned sweep3dp_shared_list_blocks(const Shape& s) { return plan3dp(s, Feed3dp::kSharedLists).grid.x; }
 unsigned sweep3dp_hist_blocks(const Shape& s, int bins) { return plan3dp(s, Feed3dp::kHist, bins).grid.x; }
-unsigned sweep3dp_block_vertices(const Shape& s) {  // of a launch with a list per block
-  const int64_t planes = std::min<int64_t>(s.D, plan3dp(s, Feed3dp::kAlone).planes_per_seg);
-  return 4u * (unsigned)s3::kOut * (unsigned)s3p::kR * (unsigned)planes;
+void sweep3dp_list_plan(const Shape& s, unsigned& per_item, unsigned& vertices) {
+  const Plan3dp pl = plan3dp(s, Feed3dp::kBlockLists);
+  per_item = pl.grid.x;
+  vertices = (unsigned)block_vertices3dp(s, pl.planes_per_seg);
 }
 
 // LV: the type also comes with one bin per level (uint8 / uint16 grids without a range)
@@ -176,7 +192,7 @@ void launch_sweep3dp(const void* grid, const Shape& s, int dtype, bool levels, i
 
 template <typename T>
 static void launch3dp_list_t(const void* grid, const Shape& s, const ListArgs& la, hipStream_t st, int conv) {
-  const Plan3dp pl = plan3dp(s, la.heads ? Feed3dp::kAlone : Feed3dp::kSharedLists);
+  const Plan3dp pl = plan3dp(s, la.heads ? Feed3dp::kBlockLists : Feed3dp::kSharedLists);
 #define ECC_LIST(M)                                                                                             \
   hipLaunchKernelGGL((sweep3dp_list_kernel<T, M>), pl.grid, dim3(256), kQueueBytes3dp, st,                      \
                      static_cast<const T*>(grid), (int)s.D, (int)s.H, (int)s.W, s.N, pl.tl, pl.nseg, pl.planes_per_seg, la)
@@ -195,7 +211,7 @@ void launch_sweep3dp_list(const void* grid, int dtype, const Shape& s, const Lis
 
 template <typename T>
 static void launch_coeff3dp_t(const void* grid, const Shape& s, int8_t* out, hipStream_t st) {
-  const Plan3dp pl = plan3dp(s, Feed3dp::kAlone);
+  const Plan3dp pl = plan3dp(s, Feed3dp::kMap);
   hipLaunchKernelGGL((coeff3dp_kernel<T>), pl.grid, dim3(256), kQueueBytes3dp, st, static_cast<const T*>(grid),
                      (int)s.D, (int)s.H, (int)s.W, s.N, pl.tl, pl.nseg, pl.planes_per_seg, out);
 }

@@ -16,7 +16,7 @@ from tests.test_gpu_soft import _close, _close_sum
 
 pytestmark = pytest.mark.gpu
 
-# (batch, D, H, W): strips * row groups * batch * D >= 160000 turns the folding on
+# (batch, D, H, W): far more waves than two a SIMD, where the folding is on
 BIG = [(6, 200, 202, 136), (8, 200, 202, 70), (9, 190, 199, 66), (16, 200, 203, 20)]
 
 
@@ -49,7 +49,7 @@ def test_folded_integer_levels(dtype, levels):
 def test_folded_conventions_and_directions():
     b, D, H, W = 2, 200, 202, 136
     X = _smooth(b, (D, H, W), 411)
-    # the folding depends on the whole launch: pad the batch so that it is on, check two items
+    # the folding depends on the whole launch: pad the batch, check two items
     Xb = np.concatenate([X, np.repeat(X[:1], 4, axis=0)])
     lo, hi = float(Xb.min()), float(Xb.max())
     t = O.thresholds_equal_width(lo, hi, 64)
@@ -84,3 +84,41 @@ def test_folded_soft_forward_backward():
         _close(gx[i], rgx, 1e-3, f"grad_X[{i}]")
         _close_sum(dt[i], rdt, 1e-3, f"dchi_dtau[{i}]")
         _close_sum(du[i], rdu, 1e-3, f"dchi_du[{i}]")
+
+
+# Two strips (8 columns left over, 6 folds) of 16 row groups and 12 planes: 32 waves an item, 20 with the last strip folded.
+# Folded from 1088 waves on if 1088 are left at most (35 to 54 items), and above 2112 (67).
+@pytest.mark.parametrize("b", [34, 35, 54, 55, 66, 67])
+def test_where_the_folding_starts(b):
+    X = _smooth(b, (12, 64, 70), 600 + b)
+    lo, hi = float(X.min()), float(X.max())
+    want = OC.ecc_hard_batch(X, O.thresholds_equal_width(lo, hi, 50))
+    g = dev(X)
+    np.testing.assert_array_equal(host(api.ecc_hard(g, 3, 50)), want)
+    np.testing.assert_array_equal(host(api.ecc_hard(g, 3, 50, range=(lo, hi))), want)
+
+
+@pytest.mark.parametrize("b", [1535, 1536])
+def test_where_the_folding_of_narrow_volumes_starts_in_the_soft_calls(b):
+    """One strip of two row groups: a wave each, or one wave an item where 1536 waves are left."""
+    D, H, W, T = 12, 8, 8, 7
+    X = np.random.default_rng(b).standard_normal((b, D, H, W)).astype(np.float32)
+    X[:, :, ::2, ::2] += 2.0
+    tau = np.linspace(-1.0, 3.0, T).astype(np.float32)
+    u = np.array([0.48, -0.6, 0.64], np.float32)
+    G = np.random.default_rng(3).standard_normal((b, T)).astype(np.float32)
+    g, ud, td, Gd = dev(X), dev(u), dev(tau), dev(G)
+    chi, dt, du, state = api.ecc_soft_fwd_save(g, 3, ud, 0.004, td, 9.0)
+    assert torch.equal(chi, api.ecc_soft_fwd(g, 3, ud, 0.004, td, 9.0))
+    gx = host(api.ecc_soft_bwd_saved(g, 3, ud, 0.004, td, 9.0, state, grad_chi=Gd))
+    bx, bt, bu = (host(a) for a in api.ecc_soft_bwd(g, 3, ud, 0.004, td, 9.0, grad_chi=Gd))
+    chi, dt, du = host(chi), host(dt), host(du)
+    for i in (0, 1, b // 2, b - 1):
+        _close_sum(chi[i], O.soft_fwd(X[i], u, 0.004, tau, 9.0), 1e-4, f"chi[{i}]")
+        rgx, rdt, rdu = O.soft_bwd(X[i], u, 0.004, tau, 9.0, G[i])
+        for a in (gx, bx):
+            _close(a[i], rgx, 1e-3, f"grad_X[{i}]")
+        for a in (dt, bt):
+            _close_sum(a[i], rdt, 1e-3, f"dchi_dtau[{i}]")
+        for a in (du, bu):
+            _close_sum(a[i], rdu, 1e-3, f"dchi_du[{i}]")

@@ -67,3 +67,24 @@ def test_packed_sweep_against_the_oracle(kind, shape, flow):
             c = host(api.ecc_coeff(g, 3))
             for i in range(min(shape[0], 4)):
                 np.testing.assert_array_equal(c[i], O.coeff(Y[i]))
+
+
+@pytest.mark.parametrize("kind", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", [(7, 73, 94, 93), (36, 75, 46, 42), (6, 51, 70, 63)])
+def test_lists_keep_to_the_room_of_float32(kind, shape, flow):
+    """A list for each block whose segments of eight planes would need more room than the workspace has: longer ones."""
+    x = np.stack([np.roll(synth.grf(shape[1:], 2.0, 5), 3 * i, axis=2) for i in range(shape[0])])
+    g = _tensor(kind, x)
+    Y = g.float().cpu().numpy()
+    t = O.thresholds_equal_width(float(Y.min()), float(Y.max()), 200)
+    np.testing.assert_array_equal(host(api.ecc_hard(g, 3, 200)), OC.ecc_hard_batch(Y, t))
+
+
+def test_shared_lists_of_a_large_volume():
+    """More vertices than a list for each block is kept for: lists that blocks share, and their sweep in reserve."""
+    x = synth.grf((330, 320, 322), 2.0, 9)  # (beyond 2^25)
+    for y in (x, np.random.default_rng(1).standard_normal(x.shape).astype(np.float32)):  # (noise: the lists run over)
+        g = _tensor("f16", y[None])
+        Y = g.float().cpu().numpy()
+        t = O.thresholds_equal_width(float(Y.min()), float(Y.max()), 200)
+        np.testing.assert_array_equal(host(api.ecc_hard(g, 3, 200)), OC.ecc_hard_batch(Y, t))
