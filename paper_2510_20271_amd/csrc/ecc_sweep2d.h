@@ -505,10 +505,16 @@ static inline int64_t rows2d(const Shape& s, int64_t nstrip, int64_t tubes, Feed
     // A list per block: nothing is merged at a block's end.  Measured with 8 / 16 / 24 / 32 rows (us a call, float32): 1024 x
     // 28^2 13.4 / 13.8 / 13.7 / 15.6, 1024^2 13.5 / 15.7 / 17.9 / 20.3, 2048^2 16.9 / 18.1 / 19.8 / 22.0 (white noise 42.5 / 62.7 / 83.6 /
     // 106), 16 x 512^2 16.5 / 18.0 / 20.2 / 21.4, 64 x 256^2 15.1 / 15.4 / 17.9 / 19.3, 64 directions of 256^2 15.3 / 15.3 / 17.8 / 18.1;
-    // 32 x 512^2 23.6 / 21.6 / 24.6 / 25.3, 1024 x 128^2 40.3 / 35.7 / 43.9 / 32.9, 4096^2 30.7 / 32.7 / 28.8 / 30.3, 8 x 4096^2 149 /
-    // 137 / 135 / 138: eight rows up to four waves a SIMD (or few vertices), then by the height (24 rows leave a low image's
-    // last segment and block half empty).
+    // 32 x 512^2 23.6 / 21.6 / 24.6 / 25.3, 4096^2 30.7 / 32.7 / 28.8 / 30.3, 8 x 4096^2 149 / 137 / 135 / 138: eight rows up to four
+    // waves a SIMD (or few vertices), then by the height (24 rows leave a low image's last segment and block half empty).  32
+    // rows take 5 to 9 % less on smooth images up to 1024 rows high (512 x 256^2 57.3 / 52.6 with 16 / 32, 128 x 512^2 52.9 / 48.7)
+    // and more on white noise (128 x 512^2 137 / 154): not taken.
     int64_t rows = H <= 1024 ? 16 : 24;
+    // But a block an image where its four waves have all but equal shares and every SIMD four waves: 1024 x 128^2 40.4 -> 35.7
+    // (noise 72.1 -> 69.9), 2000 x 96^2 63.3 -> 52.5, 1502 x 89 x 194 noise 112 -> 96, 4000 x 142 x 57 float16 noise 340 -> 231; with two
+    // waves a SIMD it costs (512 x 128^2 21.6 -> 23.3).
+    const int64_t quarter = ((H + 3) / 4 + kChunkRows - 1) / kChunkRows * kChunkRows;
+    if (nstrip == 1 && s.batch >= 1024 && quarter >= 24 && quarter <= 40) return quarter;
     // (below 32 rows the lists' room, rounded up to segments, would grow)
     if ((H >= 32 && waves(8) <= 4608) || (total < ((int64_t)1 << 22) && nstrip * ((H + 7) / 8) <= 2048)) rows = 8;
     // Many waves cost more in the blocks' heads than short segments gain (500000 x 8 101 / 81 / 76 / 78 / 78,

@@ -27,6 +27,9 @@ pytestmark = pytest.mark.gpu
     ((4200, 65, 50), torch.float32, 64, False),
     ((1, 30000, 30), torch.float32, 64, False),   # a list per block, narrow grids
     ((1, 500000, 9), torch.float32, 64, False),
+    ((1024, 128, 128), torch.float32, 64, False),  # a list per block, a block an image: 32, 24 and 40 rows a wave
+    ((1030, 69, 171), torch.float16, 64, False),
+    ((1100, 142, 57), torch.float32, 64, False),
     ((33, 1024, 1024), torch.float64, 64, False),
 ])
 def test_curves_equal_those_of_the_plain_kernels(shape, dtype, bins, known):
