@@ -12,7 +12,7 @@ the hard path with the range supplied; directional curves; the grid sizes of the
 Tables 1-2; and the CPU oracle on the host cores (a baseline, not the target).
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--quick]
-    python bench.py --only c1|c2|c2r|c3|c4|c4r|c5|dir|sizes|calib    one workload, no JSON (profiling runs)
+    python bench.py --only c1|c2|c2r|c3|c4|c4r|c5|dir|soft3d|scan|step|sizes|batches|calib    one workload, no JSON (profiling runs)
 
 Counter-based figures (HBM traffic, VALU / LDS instruction counts) cannot be taken inside this
 process; they come from rocprofv3 runs of `bench.py --only <workload>` summarised by
@@ -95,7 +95,7 @@ def roofline_hbm(alg_bytes, k_ms, kernel, counters, note=None):
 
 
 def roofline_alu(k_ms, kernel, counters, alg_bytes, note):
-    """A kernel bound by vector instruction issue: achieved = lane-operations issued (SQ_INSTS_VALU x 64, from
+    """A kernel nearer to the vector units' limit than to the memory's: achieved = lane-operations issued (SQ_INSTS_VALU x 64, from
     the rocprofv3 run) per second of the kernel's duration measured here."""
     c = counters or {}
     if "SQ_INSTS_VALU" not in c:
@@ -111,6 +111,39 @@ def roofline_alu(k_ms, kernel, counters, alg_bytes, note):
         if k in c:
             r[k] = int(c[k])
     return r
+
+
+def step_host_times(args, torch, synth):
+    """A training step of the layer (32 x 512^2, 128 thresholds; input, thresholds and angle learned): the step among others,
+    and how long the host takes to put a forward and a backward pass into an idle device's queue."""
+    from paper_2510_20271_amd.layer import SoftECCLayer
+    x = torch.from_numpy(synth.config_c5()).cuda()
+    m = SoftECCLayer(2, 128, float(x.min()), float(x.max()), alpha=0.01, lam=20.0, theta=[0.3]).cuda()
+    x.requires_grad_()
+    g = torch.ones(32, 128, device="cuda")
+    host = [0.0, 0.0]
+
+    def step():
+        t0 = time.perf_counter()
+        chi = m(x)
+        t1 = time.perf_counter()
+        torch.autograd.grad(chi, [x, m.tau, m.theta], g)
+        host[0], host[1] = host[0] + t1 - t0, host[1] + time.perf_counter() - t1
+
+    for _ in range(args.warmup):
+        step()
+    n = 10 * args.steps
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    for _ in range(n):
+        step()
+    torch.cuda.synchronize()
+    among = (time.perf_counter() - t0) / n * 1e6
+    host[:] = 0.0, 0.0
+    for _ in range(n):
+        step()
+        torch.cuda.synchronize()
+    log(f"[bench] step 32 x 512^2: {among:.1f} us; host alone: forward {host[0] / n * 1e6:.1f}, backward {host[1] / n * 1e6:.1f} us")
 
 
 # "New" kernel times of the paper's Tables 1 and 2 (ms, one RTX A6000; dtype, bins and timing
@@ -188,8 +221,9 @@ def main():
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=3)
     ap.add_argument("--quick", action="store_true", help="C2 only: skip the other workloads and the CPU baseline")
-    ap.add_argument("--only", default="", help="profiling aid: run one of c1, c2, c2r, c3, c4, c4r, c5, dir, sizes, batches, "
-                                               "calib (a plain 1 GiB copy); no JSON")
+    ap.add_argument("--only", default="", help="profiling aid: run one of c1, c2, c2r, c3, c4, c4r, c5, dir, soft3d, sizes, "
+                                               "batches, scan (an int16 volume over a known range), step (a training "
+                                               "step of the layer), calib (a plain 1 GiB copy); no JSON")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py: this build runs on ONE GPU; --gpus must be 1 (the path shards by batch item / "
@@ -350,9 +384,10 @@ def main():
                            "cold_copies": len(copies)}
             if name == "c3":
                 rooflines["c3"] = roofline_alu(swi, "sweep3dp_kernel<uint16> (levels, LDS histogram)", counters.get("c3"),
-                                               X.nbytes, "2 bytes per vertex: HBM is idle by construction; the kernel is "
-                                               "bound by vector instruction issue (stencil, then the 60 % of "
-                                               "the vertices that are critical, binned from registers, one LDS update each)")
+                                               X.nbytes, "2 bytes per vertex: HBM is idle by construction; half of the vector "
+                                               "units' issue slots (stencil, then the 60 % of the vertices that are "
+                                               "critical, binned from registers), the rest the march of three waves a "
+                                               "SIMD, LDS updates and the blocks' histograms")
                 rooflines["c3"]["cold_kernel_ms"] = round(swc, 4)
             else:
                 rooflines["c1"] = roofline_hbm(float(X.nbytes), swi, "sweep_generic_kernel<uint8> (one thread per vertex)",
@@ -480,7 +515,7 @@ def main():
         torch.cuda.empty_cache()
 
     # ---------------- soft forward + backward on a volume (fused 3D path) ---------
-    if full:
+    if want("soft3d"):
         V = synth.grf((256, 256, 256), 3.0, 5151)[None]
         T3 = 64
         gv = torch.from_numpy(V).cuda()
@@ -508,6 +543,17 @@ def main():
         log(f"[bench] soft 3D 256^3: fwd_save+bwd_saved {mss:.4f} ms, stateless fwd+bwd {msv:.4f} ms")
         del gv, gxv, wsv, stv
         torch.cuda.empty_cache()
+        if only == "soft3d":
+            return
+
+    if only == "scan":
+        gs = torch.from_numpy((synth.grf((193, 229, 193), 2.0, 6161) * 2000).astype(np.int16)[None]).cuda()
+        mss = time_steps(lambda: api.ecc_hard(gs, 3, BINS, range=(-4000.0, 4000.0), superlevel=True), args.steps, args.warmup)
+        log(f"[bench] scan 193x229x193 int16: {mss * 1e3:.1f} us/step")
+        return
+    if only == "step":
+        step_host_times(args, torch, synth)
+        return
 
     # ---------------- the grid sizes of the paper's Tables 1-2 -------------------
     if want("sizes"):

@@ -130,7 +130,7 @@ struct Angles : public torch::autograd::Function<Angles> {
     }
     if (need_u || need_tau) {
       if (!at::GradMode::is_enabled() && g.has_storage()) {
-          if (need_tau) grad_tau = at::empty({T}, grid.options());
+        if (need_tau) grad_tau = at::empty({T}, grid.options());
         if (need_u) grad_theta = at::empty({ndim - 1}, grid.options());
         check(ecc_soft_contract(f32(g), need_tau ? k.dtau : nullptr, need_u ? k.du : nullptr, need_u ? f32(theta) : nullptr,
                                 batch, (int)T, ndim, f32(grad_tau), f32(grad_theta), ws.data_ptr(), (size_t)ws.numel(),

@@ -39,7 +39,14 @@ WORKLOADS = {
            [("c5_fwd", "soft2d_fwd_kernel", 32 * 512 * 512, 248), ("c5_bwd", "soft2d_bwd_kernel", 32 * 512 * 512, 248),
             ("c5_fwd_save", "soft2d_fwd_save_kernel", 32 * 512 * 512, 248),
             ("c5_bwd_saved", "soft2d_bwd_saved_kernel", 32 * 512 * 512, 248)]),
-    # kernel trace only: the launches behind every row of the size table
+    "scan": ("hard ECC of a 193 x 229 x 193 int16 volume over a known range, 1024 bins, superlevel sets", "hard_scan.md",
+             [("scan", "sweep3dp_kernel<short", 193 * 229 * 193, 62)]),
+    "soft3d": ("soft ECC forward + backward, one 256^3 float32 volume, T = 64", "soft_3d.md",
+               [("soft3d_fwd", "soft3d_fwd_kernel", 256 ** 3, 62), ("soft3d_bwd", "soft3d_bwd_kernel", 256 ** 3, 62),
+                ("soft3d_fwd_save", "soft3d_fwd_save_kernel", 256 ** 3, 62),
+                ("soft3d_bwd_saved", "soft3d_bwd_saved_kernel", 256 ** 3, 62)]),
+    # kernel trace only: the launches of a training step; the launches behind every row of the size table
+    "step": ("a training step of the layer (32 x 512^2 float32, T = 128; input, thresholds and angle learned)", "soft_step.md", []),
     "sizes": ("hard ECC, the grid sizes of the paper's Tables 1-2 (one float32 field per size, 1024 bins, range found on "
               "the device): two launches up to 256^2, three up to 8192^2 / 256^3, five beyond", "hard_sizes.md", []),
 }
@@ -78,7 +85,7 @@ def read_stats(path):
         return rows
     for r in csv.DictReader(open(path)):
         n = short(r["Name"])
-        if n.startswith("at::") or "rocclr" in n or "elementwise" in n:
+        if not n or n.startswith("at::") or "rocclr" in n or "elementwise" in n:
             continue
         rows.append((n, int(r["Calls"]), float(r["AverageNs"]) / 1e3, float(r["MinNs"]) / 1e3, float(r["MaxNs"]) / 1e3,
                      float(r["Percentage"])))
@@ -169,7 +176,10 @@ def main():
                     per = vals["SQ_INSTS_VALU"] / (nvert / lanes)
                     entry["valu_per_wave_row"] = round(per, 1)
                     s += f"VALU instructions per {lanes}-vertex wave row: {per:.1f}.  "
-                s += (f"VALU issue utilisation, taking 4 cycles per wave instruction on each of the 1024 SIMDs: {util:.2f}.")
+                s += (f"VALU issue utilisation, taking 4 cycles per wave instruction on each of the 1024 SIMDs: {util:.2f}")
+                if avg:
+                    s += f"; of the slots that the undisturbed duration has at 2.4 GHz: {vals['SQ_INSTS_VALU'] * 4 / (1024 * 2400 * avg[0]):.2f}"
+                s += "."
                 if vals.get("SQ_INSTS_LDS"):
                     s += (f"  LDS: {vals['SQ_INSTS_LDS']:.0f} instructions, {vals.get('SQ_ACTIVE_INST_LDS') or 0:.0f} busy cycles, "
                           f"{vals.get('SQ_LDS_BANK_CONFLICT') or 0:.0f} of them bank conflicts (summed over 256 CUs).")
