@@ -359,8 +359,8 @@ static unsigned state_cap3(const Shape& s, const Plan3d& pl) {
   const unsigned planes = std::max(small ? 12u : 1u, (unsigned)pl.planes_per_seg);
   const unsigned cap = (planes * (unsigned)kRows3d * (unsigned)s3::kOut / 8u + 63u) / 64u * 64u;
   // The folded units of a narrow volume, whose unfolded ones had room for most of their few vertices, have room for one in
-  // four, unless the launch is many rounds long (739 x 8 x 8 x 16, a ninth of whose vertices is critical: 19 us, 27 from the
-  // grid).
+  // four, unless the launch is many rounds long (739 x 8 x 8 x 16 folded, a ninth of whose vertices is critical: 19 us, 27 from
+  // the grid).
   if (tl.nstrip > 1 || tl.F == 1 || tl.ngroup * s.batch * s.D >= 160000) return cap;
   return std::max(cap, ((unsigned)tl.F * (unsigned)s.W * planes + 63u) / 64u * 64u);
 }

@@ -569,9 +569,12 @@ static inline Tiling3 make_tiling3(int D, int H, int W, long long batch, int R, 
   // 27.3, noise of 160 x 190 x 130 39.4 -> 41.8.  Counted in 12-plane segments, 1024 SIMDs and a sixteenth.
   // kSoft: a wave that has to evaluate its vertices' sigmoids takes as long as it has vertices.  With two strips and more a
   // folded wave has no more of them than a full strip's (0.92 of the time over 300 calls); in volumes of one strip every wave
-  // is a folded one, with up to eight times the vertices of an unfolded, narrow one.  Those fold where one and a half waves
-  // a SIMD are left (276 x 27 x 24 x 23 backward 134 -> 89 us, 1280 x 9 x 18 x 14 forward 0.60 of the time; but 739 x 8 x 8 x 16,
-  // which leaves 739 waves, 1.23, 137 x 7 x 26 x 19 with 411 1.09).
+  // is a folded one, with up to eight times the vertices of an unfolded, narrow one.  Those fold where that saves blocks, which
+  // hold four row groups of a segment whether they have them or not, and one and a half waves a SIMD are left.  Time of forward +
+  // backward, and of the saving pair, folded against unfolded, over 46 shapes: 276 x 27 x 24 x 23, 6 row groups in 3 waves, 0.65 and
+  // 0.75, 1654 x 6 x 23 x 26 0.66 and 0.68, 808 x 27 x 21 x 10 0.81 and 0.94; but 700 x 50 x 12 x 20, 3 in 2, 1.32 and 1.39, 1600 x 20 x 8 x
+  // 17, 2 in 1, 0.99 and 1.10, 864 x 44 x 13 x 9, 4 in 1, 1.20 and 1.39; and 100 x 36 x 40 x 20, 1500 waves left, 1.13 and 1.14, 300 x 12 x
+  // 30 x 12, 600 left, 1.68 and 1.64 (rough fields; smooth ones gain there).
   if (wt + 2 <= kWave / 2) {
     int F = kWave / (wt + 2);
     if (F > 8) F = 8;
@@ -583,7 +586,12 @@ static inline Tiling3 make_tiling3(int D, int H, int W, long long batch, int R, 
     const long long whole = segs * t.nstrip * t.ngroup4;
     const long long folded = segs * ((t.nstrip - 1) * t.ngroup4 + (((t.ngroup + F - 1) / F + 3) & ~3));
     bool pays = whole > 2112 || (whole > 1088 && folded <= 1088);
-    if (fold == Fold3::kSoft && t.nstrip == 1) pays = pays && segs * waves >= 1536;
+    if (fold == Fold3::kSoft && t.nstrip == 1) {
+      // (in the segments that the launch will have: of up to 30 planes where the items fill the wave slots)
+      const long long per = batch * ((waves + 3) & ~3), chunks = (D + s3::kChunk - 1) / s3::kChunk;
+      const long long nseg = per * chunks >= 4096 ? chunks : std::max(chunks, std::min<long long>((D + 11) / 12, 4096 / per));
+      pays = pays && folded < whole && batch * nseg * waves >= 1536;
+    }
     if (F > 1 && (pays || fold == Fold3::kAlways)) {
       t.S = wt + 2;
       t.F = F;

@@ -287,8 +287,9 @@ def _align(n):
     ((8, 16, 16), 1, 4, 12, 31),       # a segment of eight planes: room as for twelve
     ((16, 48, 64), 1, 2 * 24, 12, 31),  # two of them
     ((23, 17, 12), 271, 8, 23, 31),    # one narrow strip, few waves: a row group each
-    ((8, 8, 8), 1913, 4, 8, 31),       # many: two row groups of eight columns a wave
-    ((8, 16, 20), 2593, 4, 8, 40),     # (four row groups: two waves of two)
+    ((8, 8, 8), 1913, 4, 8, 31),       # (many)
+    ((8, 16, 20), 2593, 4, 8, 31),     # a block of four row groups
+    ((8, 20, 20), 2593, 4, 8, 40),     # five: three waves of two
 ])
 def test_saved_lists_of_small_volumes(item, batch, units, planes, columns):
     """The state of a saving forward pass: a list for each wave of its plan, entries of 16 bytes for every eighth vertex of

@@ -98,10 +98,10 @@ def test_where_the_folding_starts(b):
     np.testing.assert_array_equal(host(api.ecc_hard(g, 3, 50, range=(lo, hi))), want)
 
 
-@pytest.mark.parametrize("b", [1535, 1536])
-def test_where_the_folding_of_narrow_volumes_starts_in_the_soft_calls(b):
-    """One strip of two row groups: a wave each, or one wave an item where 1536 waves are left."""
-    D, H, W, T = 12, 8, 8, 7
+@pytest.mark.parametrize("b,H", [(1535, 20), (1536, 20), (1600, 16)])
+def test_where_the_folding_of_narrow_volumes_starts_in_the_soft_calls(b, H):
+    """One strip of five row groups: two blocks of four waves, or one wave an item where 1536 waves are left; of four: unfolded."""
+    D, W, T = 12, 8, 7
     X = np.random.default_rng(b).standard_normal((b, D, H, W)).astype(np.float32)
     X[:, :, ::2, ::2] += 2.0
     tau = np.linspace(-1.0, 3.0, T).astype(np.float32)
