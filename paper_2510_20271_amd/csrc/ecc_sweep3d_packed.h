@@ -11,13 +11,15 @@
 // and below the tube are formed by the wave itself (16 instructions of 86 a plane); the waves of a block need no barrier.
 // Lane-shifted operands cost a move each, as packed subtractions take no DPP modifier: 12 a plane.
 //
-// A plane of a wave (four rows of 62 columns) takes 85 vector instructions and about 20 of the Boolean phase, against 117
-// and 15 of the float32 sweep, through which these types went before.  Dense chunks of levels are taken vertex by vertex
-// from the keys still in registers, the coefficients turned into nibbles (about 5 instructions a vertex where the queue
-// takes 40).  Whole calls, before and now: 256^3 uint16 noise over 4096 levels 67 -> 42 us (81 -> 40 vector instructions for
-// a row of 62 columns, by the counters), 128^3 uint8 noise 26.5 -> 18, 193 x 229 x 193 int16 over a known window 35.3 -> 29,
-// 256^3 float16 60 -> 45 (three launches instead of five), 512^3 uint16 142 -> 134.  Five waves on a SIMD instead of four
-// change nothing; the vector units issue nine cycles in ten on 512^3.
+// A plane of a wave (four rows of 62 columns) takes 86 vector instructions (uint16; three fewer where keys need no flip) and
+// about 20 of the Boolean phase, against 117 and 15 of the float32 sweep, through which these types went before.  Dense chunks
+// of levels are taken vertex by vertex from the keys still in registers, the coefficients turned into nibbles (about 5
+// instructions a vertex where the queue takes 40).  Whole calls, through the float32 sweep and now: 256^3 uint16 noise over 4096
+// levels 66.0 -> 37 us (81 -> 39 vector instructions for a row of 62 columns, by the counters), 128^3 uint8 noise 26.3 -> 14.3,
+// 193 x 229 x 193 int16 over a known range 35.0 -> 24.8, 256^3 float16 60 -> 37 (three launches instead of five), 512^3 uint16
+// smooth 143 -> 134, noise 326 -> 151.  Five waves on a SIMD instead of four change nothing.  By the counters the vector units of
+// these launches are at 0.56 (256^3 noise) and 0.42 (193 x 229 x 193) of their peak: segments of eight planes, which fill the chip,
+// have about five planes' worth of work besides their own, and a wave's march has few others to overlap with.
 #pragma once
 #include "ecc_sweep3d.h"
 
