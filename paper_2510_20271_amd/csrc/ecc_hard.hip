@@ -297,7 +297,8 @@ __global__ __launch_bounds__(BLOCK) void scan_kernel(long long* __restrict__ cur
 // steps.  32 bits: rows are kept for items of up to 2^28 vertices, |c| <= 7.
 // kRowsBlock: 1024 threads, or 256 where they have no more than sixteen loads each (up to 256 bins).
 constexpr int kRowsBins = 7;  // bins of a thread at the most
-template <int kRowsBlock>
+// RUNS: more bins than threads, a run of them each (compiled apart: in one kernel the others took 1.5 us more).
+template <int kRowsBlock, bool RUNS>
 __global__ __launch_bounds__(kRowsBlock) void scan_rows_kernel(const int* __restrict__ rows, unsigned n, int bins, int suffix,
                                                                long long* __restrict__ curve) {
   extern __shared__ int lsum[];  // up to 1024 bins: [groups - 1][bins] sums of the other groups
@@ -315,7 +316,7 @@ __global__ __launch_bounds__(kRowsBlock) void scan_rows_kernel(const int* __rest
     for (int w = 0; w < kRowsBlock / kWave; ++w) run += w < wv ? wsum[w] : 0;
     return run;
   };
-  if (bins <= kRowsBlock) {  // a thread per bin, further groups of threads on further rows
+  if constexpr (!RUNS) {  // a thread per bin, further groups of threads on further rows
     const int groups = kRowsBlock / bins, group = tid / bins, b = tid - group * bins;
     int s = 0;
     if (group < groups) {
@@ -337,32 +338,32 @@ __global__ __launch_bounds__(kRowsBlock) void scan_rows_kernel(const int* __rest
     if (group > 0) s = 0;
     const int run = across_waves(s) + s;
     if (group == 0) out[bin(b)] = (long long)run;
-    return;
-  }
-  // a run of up to seven bins a thread, two rows in flight together
-  const int per = (bins + kRowsBlock - 1) / kRowsBlock;
-  const int b0 = min(tid * per, bins), b1 = min(b0 + per, bins);
-  int v[kRowsBins];
+  } else {
+    // two rows in flight together
+    const int per = (bins + kRowsBlock - 1) / kRowsBlock;
+    const int b0 = min(tid * per, bins), b1 = min(b0 + per, bins);
+    int v[kRowsBins];
 #pragma unroll
-  for (int j = 0; j < kRowsBins; ++j) v[j] = 0;
-  for (unsigned r = 0; r < n; r += 2u) {
-    int p[kRowsBins], q[kRowsBins];
+    for (int j = 0; j < kRowsBins; ++j) v[j] = 0;
+    for (unsigned r = 0; r < n; r += 2u) {
+      int p[kRowsBins], q[kRowsBins];
+#pragma unroll
+      for (int j = 0; j < kRowsBins; ++j) {
+        p[j] = b0 + j < b1 ? r0[(size_t)r * bins + bin(b0 + j)] : 0;
+        q[j] = b0 + j < b1 && r + 1u < n ? r0[(size_t)(r + 1u) * bins + bin(b0 + j)] : 0;
+      }
+#pragma unroll
+      for (int j = 0; j < kRowsBins; ++j) v[j] += p[j] + q[j];
+    }
+    int s = 0;
+#pragma unroll
+    for (int j = 0; j < kRowsBins; ++j) s += v[j];
+    int run = across_waves(s);
 #pragma unroll
     for (int j = 0; j < kRowsBins; ++j) {
-      p[j] = b0 + j < b1 ? r0[(size_t)r * bins + bin(b0 + j)] : 0;
-      q[j] = b0 + j < b1 && r + 1u < n ? r0[(size_t)(r + 1u) * bins + bin(b0 + j)] : 0;
+      run += v[j];
+      if (b0 + j < b1) out[bin(b0 + j)] = (long long)run;
     }
-#pragma unroll
-    for (int j = 0; j < kRowsBins; ++j) v[j] += p[j] + q[j];
-  }
-  int s = 0;
-#pragma unroll
-  for (int j = 0; j < kRowsBins; ++j) s += v[j];
-  int run = across_waves(s);
-#pragma unroll
-  for (int j = 0; j < kRowsBins; ++j) {
-    run += v[j];
-    if (b0 + j < b1) out[bin(b0 + j)] = (long long)run;
   }
 }
 
@@ -685,11 +686,14 @@ hipError_t launch_hard(const void* grid, const Shape& s, int dtype, int bins, bo
   if (out.n) {
     long long* const c = reinterpret_cast<long long*>(curve);
     if (bins <= 256 && (int64_t)out.n * bins <= 4096)
-      hipLaunchKernelGGL(scan_rows_kernel<256>, dim3((unsigned)s.batch), dim3(256), 256 * sizeof(int), st, out.rows, out.n,
+      hipLaunchKernelGGL((scan_rows_kernel<256, false>), dim3((unsigned)s.batch), dim3(256), 256 * sizeof(int), st, out.rows, out.n,
                          bins, super, c);
+    else if (bins <= 1024)
+      hipLaunchKernelGGL((scan_rows_kernel<1024, false>), dim3((unsigned)s.batch), dim3(1024), 1024 * sizeof(int), st, out.rows,
+                         out.n, bins, super, c);
     else
-      hipLaunchKernelGGL(scan_rows_kernel<1024>, dim3((unsigned)s.batch), dim3(1024),
-                         1024 * sizeof(int), st, out.rows, out.n, bins, super, c);
+      hipLaunchKernelGGL((scan_rows_kernel<1024, true>), dim3((unsigned)s.batch), dim3(1024), 0, st, out.rows, out.n, bins, super,
+                         c);
   } else {
     launch_scan(curve, s, bins, super, st);
   }
